@@ -336,7 +336,7 @@ static int preprocess_model(int32_t n, int64_t m, const int32_t *row_ptr, const 
         skis::Arena arena;
         arena.stream = stream;
         skis::Prep prep;
-        skis::preprocess(arena, n, m, row_ptr, col, w, thr || alias, prep, stream, model);
+        skis::preprocess(arena, n, m, row_ptr, col, w, thr || alias, prep, stream, model, false);
         if (P && m > 0)
             SKIS_HIP_TRY(hipMemcpyAsync(P, prep.P.ptr, sizeof(double) * (size_t)m, hipMemcpyDeviceToDevice, stream));
         if (q) SKIS_HIP_TRY(hipMemcpyAsync(q, prep.q.ptr, sizeof(double) * (size_t)n, hipMemcpyDeviceToDevice, stream));

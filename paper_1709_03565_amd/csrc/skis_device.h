@@ -38,6 +38,55 @@ __device__ __forceinline__ void philox2x64(uint32_t c0, uint32_t c1, uint32_t c2
     Y = ((uint64_t)c3 << 32) | c2;
 }
 
+// The call with counter (c0, c1, c2, c3) in two parts, for callers that keep c1 and c2 over many
+// c0: the first gives the part of rounds 1 and 2 that does not depend on c0 (and c3), the second
+// the rest, 18 of the 20 multiplications.
+struct PhiloxHead {
+    uint32_t c1; // word 1 after round 1
+    uint32_t p_lo, p_hi; // round 2's product of word 0
+};
+
+__device__ __forceinline__ PhiloxHead philox_head(uint32_t c1, uint32_t c2, uint32_t k0)
+{
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
+    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
+    const uint64_t p0 = (uint64_t)0xD2511F53u * n0;
+    return {(uint32_t)p1, (uint32_t)p0, (uint32_t)(p0 >> 32)};
+}
+
+__device__ __forceinline__ void philox_tail(uint32_t c0, const PhiloxHead &h, uint32_t c3, uint32_t k0, uint32_t k1,
+                                            uint64_t &X, uint64_t &Y)
+{
+    // round 1
+    const uint64_t q0 = (uint64_t)0xD2511F53u * c0;
+    uint32_t c2 = __builtin_amdgcn_bitop3_b32((uint32_t)(q0 >> 32), c3, k1, 0x96);
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+    // round 2
+    const uint64_t q1 = (uint64_t)0xCD9E8D57u * c2;
+    c0 = __builtin_amdgcn_bitop3_b32((uint32_t)(q1 >> 32), h.c1, k0, 0x96);
+    c2 = __builtin_amdgcn_bitop3_b32(h.p_hi, (uint32_t)q0, k1, 0x96);
+    uint32_t c1 = (uint32_t)q1;
+    c3 = h.p_lo;
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+#pragma unroll
+    for (int r = 2; r < 10; ++r) {
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
+        const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
+        const uint32_t n0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c1, k0, 0x96);
+        const uint32_t n2 = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c3, k1, 0x96);
+        c1 = (uint32_t)p1;
+        c3 = (uint32_t)p0;
+        c0 = n0;
+        c2 = n2;
+        k0 += 0x9E3779B9u;
+        k1 += 0xBB67AE85u;
+    }
+    X = ((uint64_t)c1 << 32) | c0;
+    Y = ((uint64_t)c3 << 32) | c2;
+}
+
 // floor(w * 2^64) for a non-negative float w < 1 given by its bits, in integer arithmetic:
 // w = man * 2^(ex-150) for a normal number, so w * 2^64 = man * 2^(ex-86).
 __device__ __forceinline__ uint64_t coin_threshold(uint32_t wbits)
@@ -49,6 +98,9 @@ __device__ __forceinline__ uint64_t coin_threshold(uint32_t wbits)
     const uint32_t sh = 86u - ex;
     return sh >= 24u ? 0ull : (man >> sh);
 }
+
+// The bits of an edge's weight as the coins read them: -0 counts as +0.
+__device__ __forceinline__ uint32_t weight_bits(float w) { return __float_as_uint(w) & 0x7FFFFFFFu; }
 
 // An edge of probability w (bits of a float in [0,1], +0 for zero) is live for a 64-bit
 // uniform word x iff w >= 1 or x < floor(w * 2^64): probability exactly w for w >= 2^-40.
@@ -169,6 +221,32 @@ __device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane)
 __device__ __forceinline__ unsigned long long lane_value64(unsigned long long v, int lane)
 {
     const uint32_t lo = lane_value((uint32_t)v, lane), hi = lane_value((uint32_t)(v >> 32), lane);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+// The lanes whose x is below / equal to y, as a mask (one comparison into a scalar pair; a ballot of
+// a bool that is also used otherwise costs two VALU instructions more), and the lane's own bit of
+// a mask.  Every lane must be active.
+__device__ __forceinline__ unsigned long long lanes_lt(uint32_t x, uint32_t y)
+{
+    return __builtin_amdgcn_uicmp(x, y, 36);
+}
+__device__ __forceinline__ unsigned long long lanes_eq(uint32_t x, uint32_t y)
+{
+    return __builtin_amdgcn_uicmp(x, y, 32);
+}
+__device__ __forceinline__ bool in_mask(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// base plus the set bits of m below this lane.
+__device__ __forceinline__ uint32_t mask_rank(unsigned long long m, uint32_t base = 0u)
+{
+    return (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
+}
+
+// Value of lane s (uniform over the wave).
+__device__ __forceinline__ unsigned long long readlane64(unsigned long long v, int s)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, s);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), s);
     return ((unsigned long long)hi << 32) | lo;
 }
 

@@ -139,9 +139,14 @@ enum : int { MODEL_IC = 0, MODEL_LT = 1 };
 struct Prep {
     int model = MODEL_IC;
     DevBuf<int32_t> row_ptr;    // private copy [n+1]
-    DevBuf<uint2> edges;        // interleaved (col, coin_threshold_hi(w)) per edge, padded with
-                                // (0, 0) records to a multiple of four edges
-    DevBuf<uint32_t> wbits;     // [m] w bits per edge (+0 for -0): coin ties and the roots' fallback
+    const int32_t *col = nullptr; // the caller's arrays, borrowed for the call
+    const float *w = nullptr;
+    // independent cascade (the samplers' coins): the coin threshold of every edge, padded with 0
+    // to a multiple of four edges, and per row (row begin, coin threshold of its first edge), with
+    // (m, 0) at n; uniform: in every row all edges have that threshold
+    DevBuf<uint32_t> th;
+    DevBuf<uint2> rows;
+    bool uniform = false;
     DevBuf<double> P;           // [m] prefix products (IC) or running sums of w (LT)
     DevBuf<double> q;           // [n]
     DevBuf<uint64_t> W;         // [n]
@@ -150,10 +155,10 @@ struct Prep {
     double Gamma = 0.0;
 };
 
-// Validates the graph, copies row_ptr, interleaves (col, coin threshold), keeps the w bits,
-// computes P, q, W, C, Gamma and (if build_alias) the alias table.  Throws Error on failure.
+// Validates the graph, copies row_ptr, forms the coin thresholds (if coins, under IC), computes
+// P, q, W, C, Gamma and (if build_alias) the alias table.  Throws Error on failure.
 void preprocess(Arena &arena, int32_t n, int64_t m, const int32_t *row_ptr, const int32_t *col,
-                const float *w, bool build_alias, Prep &out, hipStream_t s, int model = MODEL_IC);
+                const float *w, bool build_alias, Prep &out, hipStream_t s, int model = MODEL_IC, bool coins = true);
 
 // ---------------------------------------------------------------------------------
 // Sampling (rows a4-a7, a11) and compaction.

@@ -51,8 +51,8 @@ struct LtArgs {
     const int32_t *row_ptr;
     const double *S;       // running sums of w along each row
     const double *q;       // 1 - gamma_v
-    const uint2 *edges;    // (col, .) per edge
-    const uint32_t *wbits; // w bits per edge
+    const int32_t *col;
+    const float *w;
     int32_t *staging;
     uint64_t stage_cap;
     uint32_t *out_size;
@@ -100,9 +100,9 @@ __device__ __forceinline__ bool lt_root(const LtArgs &a, uint32_t jl, uint32_t j
     int32_t e = lt_first_above(a.S, rb, re, theta);
     if (e >= re) { // theta rounded up to the row's sum: the last in-edge of positive weight
         e = re - 1;
-        while (e > rb && a.wbits[e] == 0u) --e;
+        while (e > rb && a.w[e] == 0.0f) --e;
     }
-    first = (int32_t)a.edges[e].x;
+    first = a.col[e];
     return true;
 }
 
@@ -115,7 +115,7 @@ __device__ __forceinline__ int32_t lt_pick(const LtArgs &a, uint32_t jl, uint32_
     const double V = (double)(X >> 11) * 0x1p-53;
     deg = (uint32_t)(re - rb);
     const int32_t f = lt_first_above(a.S, rb, re, V);
-    return f < re ? (int32_t)a.edges[f].x : -1;
+    return f < re ? a.col[f] : -1;
 }
 
 __global__ __launch_bounds__(LT_BLOCK) void k_lt_walk(LtArgs a)
@@ -334,7 +334,7 @@ __global__ void k_lt_zero(LtCounters *c, unsigned long long *n_medium)
 void sample_lt(Arena &arena, const Prep &prep, int32_t n, const LtIo &io, LtStats &st, hipStream_t s)
 {
     if (prep.model != MODEL_LT) throw Error{SKIS_EHIP, "internal error: the LT sampler needs LT preprocessing"};
-    if (!prep.alias.ptr || !prep.row_ptr.ptr || !prep.P.ptr || !prep.q.ptr || !prep.edges.ptr || !prep.wbits.ptr ||
+    if (!prep.alias.ptr || !prep.row_ptr.ptr || !prep.P.ptr || !prep.q.ptr || !prep.col || !prep.w ||
         !io.rec || !io.out_size || !io.out_off || !io.out_probed || !io.medium || !io.n_medium || !io.staging)
         throw Error{SKIS_EHIP, "internal error: null buffer for the LT sampler"};
     const uint32_t count = io.count;
@@ -377,8 +377,8 @@ void sample_lt(Arena &arena, const Prep &prep, int32_t n, const LtIo &io, LtStat
         A.row_ptr = prep.row_ptr.ptr;
         A.S = prep.P.ptr;
         A.q = prep.q.ptr;
-        A.edges = prep.edges.ptr;
-        A.wbits = prep.wbits.ptr;
+        A.col = prep.col;
+        A.w = prep.w;
         A.staging = io.staging->ptr;
         A.stage_cap = cap;
         A.out_size = io.out_size;

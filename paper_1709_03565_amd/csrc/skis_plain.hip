@@ -19,9 +19,10 @@ constexpr uint64_t PLAIN_MAX_PROBE = 4096;                // longest probe run b
 
 struct PlainCtx {
     const int32_t *row_ptr;
-    const uint4 *pairs;              // edge records two at a time, padded to whole quads
+    const int32_t *col;
+    const uint32_t *th;              // coin thresholds, padded to whole quads
     int64_t nquads;
-    const uint32_t *wbits;           // w bits per edge: coin ties
+    const float *w;                  // coin ties
     unsigned long long *hash;
     uint64_t hmask;
     uint32_t *sizes;                 // per sample of the chunk
@@ -154,8 +155,8 @@ __global__ __launch_bounds__(PLAIN_BLOCK) void k_plain_expand(uint64_t n_items, 
                 atomicOr(c.err, 8);
                 continue;
             }
-            const uint4 p0 = c.pairs[2 * qd], p1 = c.pairs[2 * qd + 1];
-            const uint32_t col[4] = {p0.x, p0.z, p1.x, p1.z}, th[4] = {p0.y, p0.w, p1.y, p1.w};
+            const uint4 t4 = reinterpret_cast<const uint4 *>(c.th)[qd];
+            const uint32_t th[4] = {t4.x, t4.y, t4.z, t4.w};
             const uint64_t j = j0 + (uint32_t)it.x;
             uint64_t X, Y;
             philox2x64((uint32_t)qd, (uint32_t)j, (uint32_t)(j >> 32), TAG_EDGE, seed_lo, seed_hi, X, Y);
@@ -165,8 +166,8 @@ __global__ __launch_bounds__(PLAIN_BLOCK) void k_plain_expand(uint64_t n_items, 
                 if (e < it.y || e >= it.z) continue;
                 const bool live = hw[h] != th[h]
                                       ? hw[h] < th[h]
-                                      : coin_live(c.wbits[e], coin_with_low_half(hw[h], (uint32_t)e, j, seed_lo, seed_hi));
-                if (live) plain_visit(c, (uint32_t)it.x, (int32_t)col[h]);
+                                      : coin_live(weight_bits(c.w[e]), coin_with_low_half(hw[h], (uint32_t)e, j, seed_lo, seed_hi));
+                if (live) plain_visit(c, (uint32_t)it.x, c.col[e]);
             }
         }
         __syncthreads();
@@ -273,9 +274,10 @@ void sample_plain(Arena &arena, const PlainInputs &in, PlainOutputs &out, hipStr
             hipLaunchKernelGGL(k_plain_fill<unsigned long long>, dim3(1), dim3(64), 0, s, (uint64_t)4, ctr.ptr, 0ull);
             PlainCtx c;
             c.row_ptr = in.row_ptr;
-            c.pairs = in.pairs;
+            c.col = in.col;
+            c.th = in.th;
             c.nquads = in.nquads;
-            c.wbits = in.wbits;
+            c.w = in.w;
             c.hash = hash.ptr;
             c.hmask = hcap - 1;
             c.sizes = sizes.ptr;

@@ -88,19 +88,30 @@ __global__ __launch_bounds__(256) void k_find_long(int32_t n, int64_t m, const i
     }
 }
 
-// One thread per row: validates the row, writes the interleaved (col, w) records, P and q.
-// Rows longer than LONG_ROW are k_prep_long's.  lt: running sums S in P (S[e] = S[e-1] + w[e],
-// 0 before the row's first edge) and q = 1 - the row's sum.
+// The coin threshold of an edge from its weight.
+__device__ __forceinline__ uint32_t edge_threshold(float w)
+{
+    return coin_threshold_hi(weight_bits(w));
+}
+
+// One thread per row: validates the row, writes its coin thresholds, P and q.  Rows longer than
+// LONG_ROW are k_prep_long's, but their row record is written here.  lt: running sums S in P
+// (S[e] = S[e-1] + w[e], 0 before the row's first edge) and q = 1 - the row's sum.  th is null
+// when no coin will be drawn (LT, the preprocessing alone).  *mixed: set when some row's edges
+// differ in their threshold.  The thresholds alone are kept (4 B an edge; the col values and the
+// w bits stay in the caller's arrays): a copy of (col, threshold) records and of the w bits had
+// cost 12 B an edge of writes, and every coin of the sampler 8 B of reads.
 __global__ __launch_bounds__(256) void k_prep_rows(int32_t n, int64_t m, const int32_t *__restrict__ row_ptr,
                                                    const int32_t *__restrict__ col, const float *__restrict__ w,
-                                                   int32_t *__restrict__ rp_copy, uint2 *__restrict__ edges,
-                                                   uint32_t *__restrict__ wbits, double *__restrict__ P,
-                                                   double *__restrict__ q, int *err, int lt)
+                                                   int32_t *__restrict__ rp_copy, uint2 *__restrict__ rows,
+                                                   uint32_t *__restrict__ th, double *__restrict__ P,
+                                                   double *__restrict__ q, int *err, int *mixed, int lt)
 {
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const int32_t a = row_ptr[v], b = row_ptr[v + 1];
         rp_copy[v] = a;
         if (v == n - 1) rp_copy[n] = b;
+        if (rows && v == n - 1) rows[n] = make_uint2((uint32_t)b, 0u);
         int bad = 0;
         if (v == 0 && a != 0) bad |= ERR_ROWPTR;
         if (v == n - 1 && (int64_t)b != m) bad |= ERR_ROWPTR;
@@ -111,11 +122,14 @@ __global__ __launch_bounds__(256) void k_prep_rows(int32_t n, int64_t m, const i
         }
         if (b - a > LONG_ROW) { // listed by k_find_long
             if (bad) atomicOr(err, bad);
+            if (rows) rows[v] = make_uint2((uint32_t)a, edge_threshold(w[a]));
             continue;
         }
         // ROW_BATCH edges at a time, the next batch's loads issued (clamped to the row's last
         // edge, so unconditionally) before this batch is used: one memory latency per batch
         double run = lt ? 0.0 : 1.0;
+        uint32_t th0 = 0u;
+        bool same = true;
         if (b > a) {
             int32_t uc[ROW_BATCH];
             float wc[ROW_BATCH];
@@ -125,6 +139,7 @@ __global__ __launch_bounds__(256) void k_prep_rows(int32_t n, int64_t m, const i
                 uc[k] = col[e];
                 wc[k] = w[e];
             }
+            th0 = edge_threshold(wc[0]);
             for (int32_t e0 = a; e0 < b; e0 += ROW_BATCH) {
                 int32_t un[ROW_BATCH];
                 float wn[ROW_BATCH];
@@ -139,11 +154,13 @@ __global__ __launch_bounds__(256) void k_prep_rows(int32_t n, int64_t m, const i
                     const int32_t e = e0 + k;
                     if (e >= b) break;
                     const int32_t u = uc[k];
-                    float wf = wc[k];
+                    const float wf = wc[k];
                     bad |= check_edge(u, wf, v, n);
-                    if (wf == 0.0f) wf = 0.0f; // -0 -> +0: the coin reads the bits
-                    edges[e] = make_uint2((uint32_t)u, coin_threshold_hi(__float_as_uint(wf)));
-                    wbits[e] = __float_as_uint(wf);
+                    if (th) {
+                        const uint32_t x = edge_threshold(wf);
+                        same = same && x == th0;
+                        th[e] = x;
+                    }
                     run = lt ? __dadd_rn(run, (double)wf) : __dmul_rn(run, __dsub_rn(1.0, (double)wf));
                     P[e] = run;
                 }
@@ -160,6 +177,8 @@ __global__ __launch_bounds__(256) void k_prep_rows(int32_t n, int64_t m, const i
         } else {
             q[v] = run;
         }
+        if (rows) rows[v] = make_uint2((uint32_t)a, th0);
+        if (!same && !*mixed) *mixed = 1; // every writer writes 1
         if (bad) atomicOr(err, bad);
     }
 }
@@ -174,7 +193,7 @@ __global__ __launch_bounds__(256) void k_prep_rows(int32_t n, int64_t m, const i
 // the 4-bit LDS counter forced a wait for the newest ones), and keeps, every LONG_BLK
 // products, the running product before the block (a checkpoint).  The other three waves, at
 // the same time, load chunk c + 1 (coalesced, every load of a thread issued before the first
-// is used), validate it, write its edge records and w bits and put its factors 1 - w into LDS
+// is used), validate it, write its coin thresholds and put its factors 1 - w into LDS
 // (1 past the row's end: a multiply by 1 leaves the chain as it is), and rebuild the products
 // of chunk c - 1: each thread takes a block, starts from its checkpoint and multiplies the
 // same factors in the same order, so every product is the chain's own, and writes them out.
@@ -270,9 +289,9 @@ __device__ __forceinline__ void rebuild_block(const double *F, int blk, int cnt,
 template <bool LT>
 __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__restrict__ row_ptr,
                                                    const int32_t *__restrict__ col, const float *__restrict__ w,
-                                                   uint2 *__restrict__ edges, uint32_t *__restrict__ wbits,
+                                                   uint32_t *__restrict__ th,
                                                    double *__restrict__ P, double *__restrict__ q, int *err,
-                                                   const int32_t *__restrict__ long_rows,
+                                                   int *mixed, const int32_t *__restrict__ long_rows,
                                                    const unsigned int *__restrict__ n_long,
                                                    const unsigned int *__restrict__ n_huge,
                                                    unsigned int *__restrict__ next_row)
@@ -290,6 +309,8 @@ __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__r
     // Every load and store is unconditional, at the edge clamped to the row's last one (a
     // clamped store writes the value that edge's own thread writes), so the compiler's wait
     // counts stay exact: with loads and stores under branches it waited for every store.
+    uint32_t th0 = 0u; // the row's first threshold
+    bool same = true;
     auto feed = [&](int32_t v, int32_t c0, int32_t b, int buf) -> int {
         int32_t u[LONG_PER];
         float wf[LONG_PER];
@@ -304,11 +325,13 @@ __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__r
         for (int k = 0; k < LONG_PER; ++k) {
             const int i = t - 64 + k * LONG_FEED;
             const int32_t e = c0 + i, ec = min(e, b - 1);
-            float x = wf[k];
+            const float x = wf[k];
             bad |= check_edge(u[k], x, v, n);
-            if (x == 0.0f) x = 0.0f; // -0 -> +0: the coin reads the bits
-            edges[ec] = make_uint2((uint32_t)u[k], coin_threshold_hi(__float_as_uint(x)));
-            wbits[ec] = __float_as_uint(x);
+            if (th) {
+                const uint32_t tx = edge_threshold(x);
+                same = same && tx == th0;
+                th[ec] = tx;
+            }
             const double f = e < b ? (LT ? (double)x : __dsub_rn(1.0, (double)x)) : ident;
             if (k + 1 < LONG_PER || i < LONG_EDGES) s_f[buf][i] = f;
         }
@@ -346,6 +369,7 @@ __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__r
         const int32_t a = row_ptr[v], b = row_ptr[v + 1];
         const int nchunks = (b - a + LONG_EDGES - 1) / LONG_EDGES;
         int bad = 0;
+        if (th) th0 = edge_threshold(w[a]);
         if (t >= 64) bad |= feed(v, a, b, 0);
         __syncthreads();
         double run = ident; // lane 0's chain
@@ -375,7 +399,21 @@ __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__r
             }
         }
         if (bad) atomicOr(err, bad);
+        if (!same && !*mixed) *mixed = 1;
+        same = true;
         __syncthreads();
+    }
+}
+
+// Sum of hi:lo over the wave, two 64-bit halves with carry (every lane gets it).
+__device__ __forceinline__ void wave_sum128(uint64_t &lo, uint64_t &hi)
+{
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const uint64_t olo = __shfl_xor(lo, d, 64), ohi = __shfl_xor(hi, d, 64);
+        const uint64_t nlo = lo + olo;
+        hi = hi + ohi + (nlo < lo ? 1ull : 0ull);
+        lo = nlo;
     }
 }
 
@@ -408,13 +446,7 @@ __global__ __launch_bounds__(256) void k_weights(int32_t n, int s_shift, const d
     // block reduction (4 waves)
     accW = wave_sum(accW);
     uint64_t lo = (uint64_t)accK, hi = (uint64_t)(accK >> 64);
-    // 128-bit wave sum via two 64-bit halves with carry
-    for (int d = 32; d > 0; d >>= 1) {
-        uint64_t olo = __shfl_xor(lo, d, 64), ohi = __shfl_xor(hi, d, 64);
-        uint64_t nlo = lo + olo;
-        hi = hi + ohi + (nlo < lo ? 1ull : 0ull);
-        lo = nlo;
-    }
+    wave_sum128(lo, hi);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     if (lane == 0) {
         shW[wid] = accW;
@@ -439,17 +471,24 @@ struct PrepScalars {
     double Gamma;
 };
 
-__global__ void k_weights_final(int nb, const uint64_t *partW, const u128 *partK, PrepScalars *out)
+// One wave adds the partial sums (integers: the order does not matter).  A single lane's loop over
+// the 4096 partials of a large graph, one memory latency each, had taken 0.4 ms.
+__global__ __launch_bounds__(64) void k_weights_final(int nb, const uint64_t *__restrict__ partW,
+                                                      const u128 *__restrict__ partK, PrepScalars *out)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
     uint64_t C = 0;
     u128 K = 0;
-    for (int i = 0; i < nb; ++i) {
+    for (int i = threadIdx.x; i < nb; i += 64) {
         C += partW[i];
         K += partK[i];
     }
-    out->C = C;
-    out->Gamma = ldexp(u128_to_double(K), -53);
+    C = wave_sum(C);
+    uint64_t lo = (uint64_t)K, hi = (uint64_t)(K >> 64);
+    wave_sum128(lo, hi);
+    if (threadIdx.x == 0) {
+        out->C = C;
+        out->Gamma = ldexp(u128_to_double(((u128)hi << 64) | lo), -53);
+    }
 }
 
 // ---- alias table: the sequential sweep expressed by prefix sums -------------------------
@@ -571,29 +610,35 @@ static int root_shift(int32_t n)
 }
 
 void preprocess(Arena &arena, int32_t n, int64_t m, const int32_t *row_ptr, const int32_t *col, const float *w,
-                bool build_alias, Prep &out, hipStream_t s, int model)
+                bool build_alias, Prep &out, hipStream_t s, int model, bool coins)
 {
     if (model != MODEL_IC && model != MODEL_LT) throw Error{SKIS_EINVAL, "model must be 0 (IC) or 1 (LT)"};
     out.model = model;
     const int lt = model == MODEL_LT ? 1 : 0;
     out.row_ptr.alloc(arena, (size_t)n + 1);
+    out.col = col;
+    out.w = w;
+    if (lt) coins = false;
     const size_t m_quad = (size_t)((m + 3) & ~(int64_t)3);
-    out.edges.alloc(arena, m_quad > 0 ? m_quad : 4);
-    out.wbits.alloc(arena, (size_t)(m > 0 ? m : 1));
+    if (coins) {
+        out.th.alloc(arena, m_quad > 0 ? m_quad : 4);
+        out.rows.alloc(arena, (size_t)n + 1);
+    }
     out.P.alloc(arena, (size_t)(m > 0 ? m : 1));
     out.q.alloc(arena, (size_t)n);
     out.W.alloc(arena, (size_t)n);
-    // every edge record below m is written by the row kernels; the quad padding past m is clear
-    if (out.edges.count > (size_t)m)
-        SKIS_HIP_TRY(hipMemsetAsync(out.edges.ptr + m, 0, (out.edges.count - (size_t)m) * sizeof(uint2), s));
+    // every threshold below m is written by the row kernels; the quad padding past m is clear
+    if (out.th.count > (size_t)m)
+        SKIS_HIP_TRY(hipMemsetAsync(out.th.ptr + m, 0, (out.th.count - (size_t)m) * sizeof(uint32_t), s));
     DevBuf<int> err;
-    err.alloc(arena, 4);
-    SKIS_HIP_TRY(hipMemsetAsync(err.ptr, 0, 4 * sizeof(int), s));
+    err.alloc(arena, 5);
+    SKIS_HIP_TRY(hipMemsetAsync(err.ptr, 0, 5 * sizeof(int), s));
+    int *const mixed = err.ptr + 1; // read with the flags
     DevBuf<int32_t> long_rows;
     long_rows.alloc(arena, (size_t)n);
-    unsigned int *n_long = reinterpret_cast<unsigned int *>(err.ptr + 1);
-    unsigned int *next_long = reinterpret_cast<unsigned int *>(err.ptr + 2);
-    unsigned int *n_huge = reinterpret_cast<unsigned int *>(err.ptr + 3);
+    unsigned int *n_long = reinterpret_cast<unsigned int *>(err.ptr + 2);
+    unsigned int *next_long = reinterpret_cast<unsigned int *>(err.ptr + 3);
+    unsigned int *n_huge = reinterpret_cast<unsigned int *>(err.ptr + 4);
     if (reinterpret_cast<uintptr_t>(out.P.ptr) & 15) throw Error{SKIS_EHIP, "internal error: P is not 16-byte aligned"};
     // The long rows' chains (bound by their length) run beside the short rows.  k_prep_long
     // follows k_find_long on the caller's stream and k_prep_rows goes to a second stream, which
@@ -616,14 +661,14 @@ void preprocess(Arena &arena, int32_t n, int64_t m, const int32_t *row_ptr, cons
     SKIS_HIP_TRY(hipEventCreateWithFlags(&join, hipEventDisableTiming));
     SKIS_HIP_TRY(hipEventRecord(fork, s));
     hipLaunchKernelGGL(lt ? k_prep_long<true> : k_prep_long<false>, dim3((unsigned)device_cu_count()), dim3(256), 0, s,
-                       n, row_ptr, col, w, out.edges.ptr, out.wbits.ptr, out.P.ptr, out.q.ptr, err.ptr, long_rows.ptr,
+                       n, row_ptr, col, w, out.th.ptr, out.P.ptr, out.q.ptr, err.ptr, mixed, long_rows.ptr,
                        n_long, n_huge, next_long);
     const hipError_t long_err = hipGetLastError();
     // from here on, s waits for s2 before anything else, whatever fails
     hipError_t side_err = hipStreamWaitEvent(s2, fork, 0);
     if (side_err == hipSuccess) {
         hipLaunchKernelGGL(k_prep_rows, dim3(prep_rows_grid(n)), dim3(256), 0, s2, n, m, row_ptr, col, w,
-                           out.row_ptr.ptr, out.edges.ptr, out.wbits.ptr, out.P.ptr, out.q.ptr, err.ptr, lt);
+                           out.row_ptr.ptr, out.rows.ptr, out.th.ptr, out.P.ptr, out.q.ptr, err.ptr, mixed, lt);
         side_err = hipGetLastError();
     }
     const hipError_t rec_err = hipEventRecord(join, s2);
@@ -632,9 +677,11 @@ void preprocess(Arena &arena, int32_t n, int64_t m, const int32_t *row_ptr, cons
     SKIS_HIP_TRY(hipStreamWaitEvent(s, join, 0));
     SKIS_HIP_TRY(long_err);
     SKIS_HIP_TRY(side_err);
-    int herr = 0;
-    SKIS_HIP_TRY(hipMemcpyAsync(&herr, err.ptr, sizeof(int), hipMemcpyDeviceToHost, s));
+    int hflags[2] = {0, 0};
+    SKIS_HIP_TRY(hipMemcpyAsync(hflags, err.ptr, sizeof(hflags), hipMemcpyDeviceToHost, s));
     SKIS_HIP_TRY(hipStreamSynchronize(s));
+    out.uniform = coins && !hflags[1];
+    const int herr = hflags[0];
     if (herr) {
         std::string msg = "invalid graph:";
         if (herr & ERR_ROWPTR) msg += " row_ptr must start at 0, end at m and be nondecreasing;";

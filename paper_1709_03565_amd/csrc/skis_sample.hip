@@ -28,6 +28,13 @@
 namespace skis {
 
 constexpr uint32_t DEFERRED = 0xFFFFFFFFu;
+constexpr uint32_t NO_ID = 0xFFFFFFFFu; // an unused place of a list of handed-on samples
+// Atomics on one address are serialised over the whole device, about 9.4 ns each (a launch that
+// took one per 16 ids and one per handed-on sample was bound by them: 4.5M in 42 ms), so the
+// counters of many workgroups are spread over buckets and ids and list places are taken in chunks.
+constexpr int STAT_BUCKETS = 32, STAT_ROW = 8;
+constexpr int HANDON_CHUNK = 16;  // list places a wave of the first tiers reserves at a time
+constexpr uint32_t ID_RANGE_MAX = 256; // sample ids a wave reserves at a time, at most
 constexpr int SMALL_SORT = 1024;   // sizes up to this are sorted in registers by k_gather_sort
 constexpr int SORT_LDS_MAX = 8192; // sizes up to this are sorted by k_gather_medium_regs and
                                    // k_gather_block, larger ones through a node bitmap by
@@ -53,8 +60,8 @@ __global__ __launch_bounds__(256) void k_roots(uint64_t j0, uint32_t count, cons
                                                uint32_t seed_lo, uint32_t seed_hi,
                                                int32_t n, uint64_t C, const AliasEntry *__restrict__ alias,
                                                const int32_t *__restrict__ row_ptr, const double *__restrict__ q,
-                                               const double *__restrict__ P, const uint2 *__restrict__ edges,
-                                               const uint32_t *__restrict__ wbits, int4 *__restrict__ rec, int32_t *__restrict__ u1, int *__restrict__ err,
+                                               const double *__restrict__ P, const int32_t *__restrict__ col,
+                                               const float *__restrict__ w, int4 *__restrict__ rec, int32_t *__restrict__ u1, int *__restrict__ err,
                                                int ris)
 {
     const uint32_t base = range ? (uint32_t)range[0] : 0u;
@@ -101,10 +108,10 @@ __global__ __launch_bounds__(256) void k_roots(uint64_t j0, uint32_t count, cons
         int32_t istar = lo;
         if (istar >= re) { // theta rounded up to gamma: last in-edge of positive probability
             istar = re - 1;
-            while (istar > rb && wbits[istar] == 0u) --istar;
+            while (istar > rb && w[istar] == 0.0f) --istar;
         }
         rec[i] = make_int4(root, istar, rb, re);
-        u1[i] = (int32_t)edges[istar].x;
+        u1[i] = col[istar];
     }
 }
 
@@ -125,11 +132,11 @@ constexpr unsigned long long ID_PERM_PRIME = 4294967291ull;
 
 struct SampleArgs {
     int32_t n;
-    const int32_t *row_ptr;
-    const uint4 *pairs;         // edge records two at a time: (col[2p], th[2p], col[2p+1], th[2p+1]),
-                                // th = coin_threshold_hi(w); padded to whole quads of edges
-    int64_t nquads;             // pairs holds 2 * nquads records
-    const uint32_t *wbits;      // w bits per edge, read when a coin's high half ties th
+    const uint2 *rows;          // per row (begin, coin threshold of its first edge), (m, 0) at n
+    const uint32_t *th;         // coin thresholds, padded to whole quads
+    int64_t nquads;             // th holds 4 * nquads of them
+    const int32_t *col;
+    const float *w;             // read when a coin's high half ties the threshold
     const int4 *rec;
     const int32_t *u1;
     uint64_t j0;
@@ -154,8 +161,9 @@ struct SampleArgs {
     uint32_t *medium;
     unsigned long long *n_medium;
     int *overflow;
-    unsigned long long *tier_stats; // [5]: samples finished by this launch, their entries, their edges
-                                    // probed; the edges and the nodes (items) this launch expanded
+    // [STAT_BUCKETS][STAT_ROW]: samples finished by this launch, their entries, their edges probed;
+    // the edges and the nodes (items) this launch expanded; the samples it handed on
+    unsigned long long *tier_stats;
     uint32_t *gbits;            // bitmap tier: [slots][words]
     int32_t *glist;             // bitmap tier: [slots][n]
     uint64_t words;
@@ -202,8 +210,557 @@ template <int S, int RCAP, int QPL, int TIER> constexpr int sample_min_waves()
     return TIER == 0 && S <= 4 && RCAP <= 192 && QPL == 1 ? 5 : TIER == 2 ? 6 : 1;
 }
 
-template <int BLOCK, int S, int RCAP, int HCAP, int ICAP, int QPL, int TIER>
-__global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) void k_sample(SampleArgs a)
+// ---------------------------------------------------------------------------------------
+// The LDS tiers of one-wave workgroups (64 items a pass).  Lane s owns slot s and keeps its
+// sample's state in registers; a pass is
+//   1. finished and handed-on samples: staging space by a prefix sum over the slots, then the
+//      wave writes each out and clears the hash slots its list names;
+//   2. admission into the empty slots;
+//   3. up to 64 items (the root's later edges, unexpanded nodes), one a lane: its row record is
+//      read (one 12-byte load: begin and threshold, next row's begin) and an LDS record
+//      (quad offset, first edge, length, threshold) describes it to the sweeps;
+//   4. sweeps of 64 edge quads: a lane's item is the prefix maximum over marks that the items
+//      leave at their first quad (marks carry the sweep's number, so they are never cleared),
+//      one Philox call gives the quad's four coins, the live lanes of each of the four edges
+//      are a ballot, and live edge ids go into a queue;
+//   5. whenever 64 ids are queued, their heads col[e] are loaded, and the nodes of the load
+//      before are inserted: the load's latency passes behind the sweeps in between.
+// What bounds it: VALU issue (the Philox multiplies at a quarter of the rate of other 32-bit
+// operations), so the pass keeps the instructions per swept edge low.  UNIFORM: every row's
+// edges share one threshold (prep.uniform: weighted cascade, constant probabilities), which the
+// row record holds: a sweep then reads no edge data at all, only the heads of live edges (about
+// one in 17 to 34 swept edges on the weighted-cascade workloads).  Otherwise a sweep reads the
+// quad's four thresholds (16 bytes).
+// ---------------------------------------------------------------------------------------
+constexpr int WQ_CAP = 192;                   // queued live edges: below 64 before a sweep, then 128 of it at most
+constexpr uint32_t CNT_BIG_ROW = 0x40000000u; // set in a slot's node count: hand it on
+
+template <int S, int RCAP, int HCAP, int TIER, bool UNIFORM>
+__device__ __forceinline__ void sample_wave(const SampleArgs &a)
+{
+    // least ids a wave reserves at a time (a sample of the one-slot tier is long: small ranges keep
+    // the launch's end short)
+    constexpr uint32_t ID_RANGE_MIN = S > 1 ? 16 : 4;
+    // the first tiers reserve places of the hand-on list in chunks (unused ones hold NO_ID)
+    constexpr bool CHUNKED = TIER == 0;
+    static_assert(!CHUNKED || S <= HANDON_CHUNK, "one chunk covers the hand-ons of a pass");
+    static_assert(HCAP > RCAP && HCAP <= 65535, "list entries are 8- or 16-bit hash slot indexes");
+    static_assert(S <= 64 && S <= (int)ID_RANGE_MIN, "slots are owned by lanes, and one range covers them");
+    static_assert(RCAP <= SMALL_SORT, "no sample of these tiers is listed for the larger sorts");
+    using LIdx = std::conditional_t<(HCAP <= 256), uint8_t, uint16_t>;
+    __shared__ int32_t sh_hash[S * HCAP];
+    __shared__ LIdx sh_lidx[S * RCAP]; // the hash slots of a sample's nodes in discovery order
+    __shared__ uint32_t s_cnt[S];      // nodes of each slot's sample (CNT_BIG_ROW: hand it on)
+    // (first item, list position - item, first edge of the root's item or -1, sample)
+    __shared__ int4 s_slot[S];
+    __shared__ uint4 it_rec[64];              // (first quad - position, first edge, edges, threshold)
+    __shared__ uint32_t it_jl[S > 1 ? 64 : 1]; // low half of the sample's id
+    __shared__ uint8_t it_slot[S > 1 ? 64 : 1];
+    __shared__ uint32_t s_qmap[64];           // sweep position -> item marks
+    __shared__ uint32_t wq_edge[WQ_CAP];      // queued live edges and the items they were swept for
+    __shared__ uint8_t wq_item[S > 1 ? WQ_CAP : 1];
+    // item -> slot marks, then prefix sums of the items' degrees: used while the queue is empty
+    uint32_t *const s_map = wq_edge;
+
+    const int lane = threadIdx.x;
+    const bool own = lane < S;
+    const uint32_t n = (uint32_t)a.n;
+    const uint32_t j0_lo = (uint32_t)a.j0, j0_hi = (uint32_t)(a.j0 >> 32);
+    const uint32_t seed_lo = a.seed_lo, seed_hi = a.seed_hi;
+    // list places and ids are below 2^32: sample counts are below 2^31, and a list's unused places
+    // and the ranges past its end come to at most a few hundred a workgroup
+    const uint32_t id_count = (uint32_t)(SKIS_KARG(id_count_dev) ? *SKIS_KARG(id_count_dev) : SKIS_KARG(id_count));
+    const uint32_t id_base = SKIS_KARG(id_base_dev) ? (uint32_t)*SKIS_KARG(id_base_dev) : 0u;
+    auto sync = [] { block_sync<64>(); };
+    auto hash_slot = [](int32_t u) -> uint32_t {
+        return (uint32_t)(((uint64_t)((uint32_t)u * 0x9E3779B1u) * (uint64_t)HCAP) >> 32);
+    };
+    // Adds u to slot s's sample if it is not there yet.
+    auto visit = [&](int s, int32_t u) {
+        if (s_cnt[s] > (uint32_t)RCAP) return; // handed on: it resumes from the pass's start
+        int32_t *H = sh_hash + s * HCAP;
+        uint32_t h = hash_slot(u);
+        int32_t old;
+        int left = HCAP;
+#pragma unroll 1
+        for (;;) { // one exit: several cost the wave a dozen mask operations a probe
+            old = atomicCAS(&H[h], -1, u);
+            if (old == -1 || old == u || --left == 0) break;
+            h = h + 1 == (uint32_t)HCAP ? 0u : h + 1;
+        }
+        if (old == -1) {
+            const uint32_t pos = atomicAdd(&s_cnt[s], 1u);
+            if (pos < (uint32_t)RCAP) sh_lidx[s * RCAP + pos] = (LIdx)h;
+        } else if (old != u) {
+            atomicOr(&s_cnt[s], CNT_BIG_ROW); // full: the sample has outgrown the slot
+        }
+    };
+
+    // the slot's sample (lane s)
+    int flags = 0;
+    uint32_t idx = 0, cursor = 0, probed = 0; // probed < 2^31: in-degrees of distinct nodes
+    int32_t rib = 0; // first edge of the root's item
+    uint32_t snap_cnt = 0, snap_probed = 0;   // as of the pass's start, for a handover
+    int32_t snap_cursor = 0;
+    // this launch's counts: samples finished, their entries and edges probed; edges and items set up
+    unsigned long long st_ent = 0, st_prb = 0, st_swp = 0;
+    uint32_t st_fin = 0, st_itm = 0, st_hnd = 0;
+    // staging space is reserved STAGE_CHUNK entries at a time; [st_base, st_end) is open
+    constexpr unsigned long long STAGE_CHUNK = 8ull * S * RCAP;
+    unsigned long long st_base = 0, st_end = 0;
+    // places of the id list (or ids): [rng_next, rng_end) is reserved; the ranges shrink as the
+    // places run out
+    const uint32_t nwg = gridDim.x;
+    // a quarter of an even share of rem ids; the least in the one-slot tier (with such ranges its
+    // launch at 40M nodes took 69 ms instead of 58: its samples are long and differ)
+    auto range_size = [&](uint32_t rem) -> uint32_t {
+        return min(max(rem / (nwg * 4u), ID_RANGE_MIN), S > 1 ? ID_RANGE_MAX : ID_RANGE_MIN);
+    };
+    // (the first is the workgroup's own; no longer than the least range, since a workgroup that finds
+    // no room at first starts it at the end: with a quarter of an even share these tails cost 20 %)
+    uint32_t rng_next = ID_RANGE_MIN * blockIdx.x, rng_end = rng_next + ID_RANGE_MIN;
+    // lane s's next sample, its record loaded while the slot's current one runs: place, sample,
+    // record; and the place and sample of the one after it
+    uint32_t nx_pos = 0, nx_id = NO_ID, nx2_pos = 0, nx2_id = NO_ID;
+    int4 nx_rec = make_int4(0, 0, 0, 0);
+    int32_t nx_u = 0;
+    unsigned long long hand_next = 0, hand_end = 0; // open chunk of the hand-on list
+    uint32_t qtag = 64;
+
+    for (int i = lane; i < S * HCAP; i += 64) sh_hash[i] = -1;
+    s_qmap[lane] = 0u;
+    if (own) s_cnt[lane] = 0u;
+    sync();
+
+    // the lanes in m (a bool per lane) move on to the sample after next, whose record starts to
+    // load, and take another place for the one after that
+    auto advance = [&](bool m) {
+        if (m) {
+            nx_pos = nx2_pos;
+            nx_id = nx2_id;
+            if (nx_id != NO_ID) {
+                nx_rec = SKIS_KARG(rec)[nx_id];
+                nx_u = SKIS_KARG(u1)[nx_id];
+            }
+        }
+        const unsigned long long mm = __ballot(m);
+        const uint32_t want = (uint32_t)__popcll(mm), rank = mask_rank(mm), left = rng_end - rng_next;
+        uint32_t pos = rng_next + rank;
+        if (left < want) {
+            uint32_t b = rng_end, z = 0;
+            if (rng_end < id_count) { // else the places are used up
+                z = range_size(id_count - rng_end);
+                if (lane == 0) b = (uint32_t)atomicAdd(SKIS_KARG(next), (unsigned long long)z) + ID_RANGE_MIN * nwg;
+                b = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+            }
+            if (rank >= left) pos = b + (rank - left);
+            rng_next = b + (want - left);
+            rng_end = b + max(z, want - left);
+        } else {
+            rng_next += want;
+        }
+        if (m) {
+            nx2_pos = pos;
+            nx2_id = NO_ID;
+            if (pos < id_count) nx2_id = SKIS_KARG(id_list) ? SKIS_KARG(id_list)[pos] : id_base + pos;
+            else nx2_pos = NO_ID;
+        }
+    };
+    advance(own);
+    advance(own);
+
+    for (;;) {
+        // ---- 1. finished and handed-on samples ---------------------------------------------
+        // (the next samples' records have arrived, or are waited for here, before this pass's
+        // stores, behind which the wait would take them in)
+        asm volatile("" : "+v"(nx_id), "+v"(nx_rec.x), "+v"(nx_rec.y), "+v"(nx_rec.z), "+v"(nx_rec.w), "+v"(nx_u));
+        uint32_t cnt = own ? s_cnt[lane] : 0u;
+        {
+            const bool act = (flags & F_ACTIVE) != 0;
+            const bool defer = act && ((flags & F_DEFER) || cnt > (uint32_t)RCAP);
+            const bool fin = act && !defer && !(flags & F_ROOTPEND) && cursor >= cnt;
+            const unsigned long long fm = __ballot(fin), dm = __ballot(defer);
+            if (fm) {
+                const uint32_t fcnt = fin ? cnt : 0u;
+                const uint32_t fincl = wave_incl_scan_n<S>(fcnt);
+                const unsigned long long ftot = lane_value(fincl, S - 1);
+                if (st_base + ftot > st_end) {
+                    const unsigned long long want = ftot > STAGE_CHUNK ? ftot : STAGE_CHUNK;
+                    unsigned long long b = 0;
+                    if (lane == 0) b = atomicAdd(SKIS_KARG(stage_used), want);
+                    st_base = first_lane_value64(b);
+                    st_end = st_base + want;
+                }
+                const unsigned long long off = st_base + (unsigned long long)(fincl - fcnt);
+                st_base += ftot;
+                bool room = true;
+                if (fin) {
+                    SKIS_KARG(out_size)[idx] = cnt;
+                    SKIS_KARG(out_off)[idx] = off;
+                    SKIS_KARG(out_probed)[idx] = (unsigned long long)probed;
+                    st_fin += 1;
+                    st_ent += cnt;
+                    st_prb += probed;
+                    room = off + cnt <= SKIS_KARG(stage_cap);
+                    if (!room) atomicOr(SKIS_KARG(overflow), 1);
+                }
+                const unsigned long long rm = __ballot(fin && room);
+                int32_t *const staging = SKIS_KARG(staging);
+                for (unsigned long long m = fm; m; m &= m - 1ull) {
+                    const int s = __ffsll(m) - 1;
+                    const int c = (int)__builtin_amdgcn_readlane((int)cnt, s);
+                    const bool wr = (rm >> s) & 1ull;
+                    int32_t *const dst = staging + readlane64(off, s);
+                    for (int t = lane; t < c; t += 64) {
+                        const int h = s * HCAP + sh_lidx[s * RCAP + t];
+                        const int32_t u = sh_hash[h];
+                        sh_hash[h] = -1;
+                        if (wr) dst[t] = u;
+                    }
+                }
+                if (fin) flags = 0;
+            }
+            if (dm) {
+                const unsigned long long nd = (unsigned long long)__popcll(dm), rank = mask_rank(dm);
+                unsigned long long k = hand_next + rank;
+                if (hand_end - hand_next < nd) {
+                    const unsigned long long left = hand_end - hand_next;
+                    const unsigned long long need = CHUNKED ? (unsigned long long)HANDON_CHUNK : nd;
+                    unsigned long long b = 0;
+                    if (lane == 0) b = atomicAdd(SKIS_KARG(n_deferred), need);
+                    b = first_lane_value64(b);
+                    if (rank >= left) k = b + (rank - left);
+                    hand_next = b + (nd - left);
+                    hand_end = b + need;
+                } else {
+                    hand_next += nd;
+                }
+                if (defer) st_hnd += 1;
+                bool ho = false;
+                if (defer) {
+                    SKIS_KARG(deferred)[k] = idx;
+                    SKIS_KARG(out_size)[idx] = DEFERRED;
+                    ho = SKIS_KARG(ho_state_out) && k < SKIS_KARG(ho_cap_out);
+                    if (ho) {
+                        Handover h;
+                        h.count = (int32_t)snap_cnt;
+                        h.cursor_rp = snap_cursor;
+                        h.probed = snap_probed;
+                        SKIS_KARG(ho_state_out)[k] = h;
+                    }
+                }
+                const unsigned long long hm = __ballot(ho);
+                for (unsigned long long m = dm; m; m &= m - 1ull) {
+                    const int s = __ffsll(m) - 1;
+                    if ((hm >> s) & 1ull) {
+                        const int c = (int)__builtin_amdgcn_readlane((int)snap_cnt, s);
+                        int32_t *const dst = SKIS_KARG(ho_nodes_out) + readlane64(k, s) * (size_t)SKIS_KARG(ho_stride_out);
+                        for (int t = lane; t < c; t += 64) dst[t] = sh_hash[s * HCAP + sh_lidx[s * RCAP + t]];
+                    }
+                    sync();
+                    for (int t = lane; t < HCAP; t += 64) sh_hash[s * HCAP + t] = -1; // keys past the list, too
+                }
+                if (defer) flags = 0;
+            }
+            sync();
+        }
+
+        // ---- 2. admission into every empty slot, those left above included -------------------
+        const bool want = own && flags == 0 && nx_pos != NO_ID; // NO_ID: no place left
+        bool resume = false;
+        uint32_t ho_rec = 0;
+        if (__ballot(want)) {
+            if (want && nx_id != NO_ID) { // an unused place: another one in the next pass
+                const uint32_t i = nx_id;
+                const int4 r = nx_rec;
+                const int32_t u = nx_u;
+                // a RIS record has no first live in-edge: u = -1 and i* = row begin - 1
+                const bool ris_rec = u == -1;
+                if (i >= id_base + (SKIS_KARG(id_list) ? 0x7FFFFFFFu : id_count) || (uint32_t)r.x >= n ||
+                    (ris_rec ? (r.y != r.z - 1 || r.w < r.z) : ((uint32_t)u >= n || r.y < r.z || r.w <= r.y)) ||
+                    (int64_t)r.w > 4 * a.nquads) {
+                    atomicOr(SKIS_KARG(overflow), 8); // bounds guard: the sample is left out
+                } else {
+                    idx = i;
+                    rib = r.y + 1;
+                    probed = (uint32_t)(r.w - r.z);
+                    cnt = ris_rec ? 1u : 2u;
+                    cursor = 1u;
+                    flags = F_ACTIVE | (r.y + 1 < r.w ? F_ROOTPEND : 0);
+                    if (SKIS_KARG(ho_state_in)) {
+                        const uint32_t *hs = SKIS_KARG(ho_slot_in);
+                        ho_rec = hs ? hs[nx_pos] : nx_pos;
+                        if (ho_rec < SKIS_KARG(ho_cap_in)) {
+                            const Handover h = SKIS_KARG(ho_state_in)[ho_rec];
+                            const int cur = h.cursor_rp >> 1;
+                            if (h.count >= 1 && h.count <= RCAP && cur >= 1 && cur <= h.count) {
+                                resume = true; // its nodes go back into hash and list below
+                                cnt = (uint32_t)h.count;
+                                cursor = (uint32_t)cur;
+                                probed = (uint32_t)h.probed;
+                                flags = F_ACTIVE | ((h.cursor_rp & 1) ? F_ROOTPEND : 0);
+                            }
+                        }
+                    }
+                    if ((uint32_t)(r.w - r.z) > a.big_row) flags |= F_DEFER;
+                    if (!resume) {
+                        // root and u1 differ (no self-loops), so they take two slots
+                        int32_t *H = sh_hash + lane * HCAP;
+                        const uint32_t h0 = hash_slot(r.x);
+                        H[h0] = r.x;
+                        sh_lidx[lane * RCAP] = (LIdx)h0;
+                        if (!ris_rec) {
+                            uint32_t h1 = hash_slot(u);
+                            if (h1 == h0) h1 = h1 + 1 == (uint32_t)HCAP ? 0u : h1 + 1;
+                            H[h1] = u;
+                            sh_lidx[lane * RCAP + 1] = (LIdx)h1;
+                        }
+                    }
+                    s_cnt[lane] = cnt;
+                }
+            }
+            advance(want);
+            const unsigned long long resm = __ballot(resume);
+            if (resm) {
+                sync();
+                for (unsigned long long m = resm; m; m &= m - 1ull) {
+                    const int s = __ffsll(m) - 1;
+                    const int c = (int)__builtin_amdgcn_readlane((int)cnt, s);
+                    const int32_t *src = SKIS_KARG(ho_nodes_in) +
+                                         (size_t)(uint32_t)__builtin_amdgcn_readlane((int)ho_rec, s) * (size_t)SKIS_KARG(ho_stride_in);
+                    int32_t *H = sh_hash + s * HCAP;
+                    for (int t = lane; t < c; t += 64) { // distinct nodes, fewer than HCAP
+                        const int32_t u = src[t];
+                        uint32_t h = hash_slot(u);
+#pragma unroll 1
+                        for (int k = 0; k < HCAP && atomicCAS(&H[h], -1, u) != -1; ++k)
+                            h = h + 1 == (uint32_t)HCAP ? 0u : h + 1;
+                        sh_lidx[s * RCAP + t] = (LIdx)h;
+                    }
+                }
+            }
+        }
+        // without an active slot either the places are used up or the ones offered were unused
+        if (__ballot(flags & F_ACTIVE) == 0ull) {
+            if (__ballot(own && nx_pos != NO_ID) == 0ull) break;
+            continue;
+        }
+
+        // ---- 3. the pass's items -----------------------------------------------------------
+        snap_cnt = cnt;
+        snap_probed = probed;
+        snap_cursor = (int32_t)(cursor * 2u) + ((flags & F_ROOTPEND) ? 1 : 0);
+        int pend = 0, rp = 0;
+        if ((flags & F_ACTIVE) && !(flags & F_DEFER)) {
+            rp = (flags & F_ROOTPEND) ? 1 : 0;
+            pend = rp + (int)(cnt - cursor);
+        }
+        int take, ibase;
+        if constexpr (S > 1) {
+            const int base = wave_incl_scan_n<S>(pend) - pend;
+            take = min(max(64 - base, 0), pend);
+            ibase = base; // taken slots are filled in order, so their items start where they pend
+        } else {
+            take = min(64, pend);
+            ibase = 0;
+        }
+        const int trp = take > 0 ? rp : 0;
+        const unsigned long long tm = __ballot(take > 0);
+        const int nitems = tm ? __builtin_amdgcn_readlane(ibase + take, 63 - __clzll((long long)tm)) : 0;
+        s_map[lane] = 0u;
+        sync();
+        if (take > 0) {
+            s_map[ibase] = (uint32_t)lane + 1u;
+            s_slot[lane] = make_int4(ibase, (int)cursor - trp - ibase, trp ? rib : -1, (int)idx);
+            cursor += (uint32_t)(take - trp);
+            if (trp) flags &= ~F_ROOTPEND;
+        }
+        sync();
+        const int sl = S > 1 ? max((int)wave_incl_max_dpp(s_map[lane]) - 1, 0) : 0;
+        const bool has = lane < nitems;
+        int32_t x = 0, rbeg = -1;
+        uint32_t sidx = 0;
+        if (has) {
+            const int4 si = s_slot[sl];
+            sidx = (uint32_t)si.w;
+            const bool root_item = si.z >= 0 && lane == si.x; // the root is the list's first node
+            if (root_item) rbeg = si.z;
+            x = sh_hash[sl * HCAP + sh_lidx[sl * RCAP + (root_item ? 0 : lane + si.y)]];
+            if ((uint32_t)x >= n) { // bounds guard: report, never index
+                atomicOr(SKIS_KARG(overflow), 4);
+                x = 0;
+                rbeg = INT32_MAX;
+            }
+        }
+        const uint2 row = a.rows[x];
+        const uint32_t row_end = a.rows[x + 1].x;
+        uint32_t beg = 0, len = 0, deg = 0;
+        bool big = false;
+        if (has) {
+            beg = rbeg >= 0 ? (uint32_t)rbeg : row.x;
+            len = beg < row_end ? row_end - beg : 0u;
+            if (rbeg < 0) {
+                deg = len;
+                if (len > a.big_row) {
+                    atomicOr(&s_cnt[sl], CNT_BIG_ROW);
+                    big = true;
+                    len = 0;
+                }
+            }
+            st_swp += len;
+            st_itm += 1;
+        }
+        const uint32_t nq = len ? ((beg + len - 1) >> 2) - (beg >> 2) + 1u : 0u;
+        const uint32_t qincl = wave_incl_scan_dpp(nq), pb = qincl - nq;
+        // the only sample meets a row that hands it on: nothing of this pass is needed
+        const uint32_t total = S == 1 && __ballot(big) ? 0u : lane_value(qincl, 63);
+        it_rec[lane] = make_uint4((beg >> 2) - pb, beg, len, row.y);
+        if constexpr (S > 1) {
+            it_jl[lane] = j0_lo + sidx;
+            it_slot[lane] = (uint8_t)sl;
+        }
+        if constexpr (S > 1) {
+            s_map[lane] = wave_incl_scan_dpp(deg); // every lane has read its mark
+            sync();
+            if (take > 0) probed += s_map[ibase + take - 1] - (ibase ? s_map[ibase - 1] : 0u);
+        } else {
+            const uint32_t d = lane_value(wave_incl_scan_dpp(deg), 63);
+            if (lane == 0) probed += d;
+            sync();
+        }
+
+        // ---- 4., 5. sweeps and visits ---------------------------------------------------------
+        uint32_t wq_n = 0, ld_n = 0; // queued edges; nodes loaded and not yet visited (uniform)
+        int32_t ld_u = 0;
+        int ld_s = 0;
+        auto insert = [&]() {
+            if (lane < (int)ld_n) visit(ld_s, ld_u);
+            ld_n = 0;
+        };
+        auto load = [&](uint32_t c) { // the last c (1 .. 64) queued edges
+            sync();
+            const uint32_t k = wq_n - c + ((uint32_t)lane < c ? (uint32_t)lane : 0u);
+            ld_s = S > 1 ? (int)it_slot[wq_item[k]] : 0;
+            ld_u = a.col[wq_edge[k]];
+            ld_n = c;
+            wq_n -= c;
+            sync();
+        };
+        auto push = [&](unsigned long long live, uint32_t e, uint32_t item) {
+            if (in_mask(live)) {
+                const uint32_t k = mask_rank(live, wq_n);
+                wq_edge[k] = e;
+                if constexpr (S > 1) wq_item[k] = (uint8_t)item;
+            }
+            wq_n += (uint32_t)__popcll(live);
+        };
+        PhiloxHead ph{};
+        if constexpr (S == 1) {
+            const uint32_t i = (uint32_t)__builtin_amdgcn_readfirstlane((int)idx);
+            const uint64_t j = a.j0 + i;
+            ph = philox_head((uint32_t)j, (uint32_t)(j >> 32), seed_lo);
+        }
+        for (uint32_t base = 0; base < total; base += 64) { // total < 2^31: base does not wrap
+            const uint32_t p = base + (uint32_t)lane;
+            if (nq && pb < base + 64 && qincl > base) s_qmap[max((int)(pb - base), 0)] = qtag | (uint32_t)lane;
+            sync();
+            const uint32_t it = wave_incl_max_dpp(s_qmap[lane]) & 63u;
+            qtag += 64;
+            const uint4 r = it_rec[it];
+            uint32_t jl = 0u;
+            if constexpr (S > 1) jl = it_jl[it];
+            uint32_t q = r.x + p;
+            uint32_t len_in = p < total ? r.z : 0u;
+            uint4 th = make_uint4(r.w, r.w, r.w, r.w);
+            if constexpr (!UNIFORM) {
+                if (q >= (uint32_t)a.nquads) { // past the pass's last quad, or a bounds guard
+                    if (len_in) atomicOr(SKIS_KARG(overflow), 2);
+                    q = 0;
+                    len_in = 0;
+                }
+                th = reinterpret_cast<const uint4 *>(a.th)[q];
+            }
+            // the round keys are formed here, by scalar adds: hoisted out of the loop they would
+            // take twenty scalar registers and push others into VGPR lanes
+            uint32_t k0 = seed_lo, k1 = seed_hi;
+            asm volatile("" : "+s"(k0), "+s"(k1));
+            uint64_t X, Y;
+            if constexpr (S > 1) {
+                philox2x64(q, jl, j0_hi + (jl < j0_lo ? 1u : 0u), TAG_EDGE, k0, k1, X, Y);
+            } else { // one sample: its part of the first two rounds is scalar
+                philox_tail(q, ph, TAG_EDGE, k0, k1, X, Y);
+            }
+            const uint32_t w0 = (uint32_t)X, w1 = (uint32_t)(X >> 32), w2 = (uint32_t)Y, w3 = (uint32_t)(Y >> 32);
+            // edge 4q + h is the item's when 4q + h - (its first edge) < (its edges), unsigned
+            const uint32_t e0 = 4u * q, d0 = e0 - r.y;
+            const unsigned long long in0 = lanes_lt(d0, len_in), in1 = lanes_lt(d0 + 1u, len_in),
+                                     in2 = lanes_lt(d0 + 2u, len_in), in3 = lanes_lt(d0 + 3u, len_in);
+            unsigned long long l0 = lanes_lt(w0, th.x) & in0, l1 = lanes_lt(w1, th.y) & in1,
+                               l2 = lanes_lt(w2, th.z) & in2, l3 = lanes_lt(w3, th.w) & in3;
+            const unsigned long long t0 = lanes_eq(w0, th.x) & in0, t1 = lanes_eq(w1, th.y) & in1,
+                                     t2 = lanes_eq(w2, th.z) & in2, t3 = lanes_eq(w3, th.w) & in3;
+            if (t0 | t1 | t2 | t3) { // a coin's high half equals the threshold's: almost never
+                const uint64_t j = S > 1 ? ((uint64_t)(j0_hi + (jl < j0_lo ? 1u : 0u)) << 32) | jl
+                                        : a.j0 + (uint32_t)s_slot[0].w;
+                auto whole = [&](unsigned long long t, uint32_t e, uint32_t hw) -> unsigned long long {
+                    bool live = false;
+                    if (in_mask(t))
+                        live = coin_live(weight_bits(SKIS_KARG(w)[e]), coin_with_low_half(hw, e, j, seed_lo, seed_hi));
+                    return __ballot(live);
+                };
+                l0 |= whole(t0, e0, w0);
+                l1 |= whole(t1, e0 + 1u, w1);
+                l2 |= whole(t2, e0 + 2u, w2);
+                l3 |= whole(t3, e0 + 3u, w3);
+            }
+            push(l0, e0, it);
+            push(l1, e0 + 1u, it);
+            for (;;) { // a second round when the sweep holds many live edges (rows of high probability)
+                const bool rest = (l2 | l3) != 0ull && wq_n <= (uint32_t)(WQ_CAP - 128);
+                if (rest) {
+                    push(l2, e0 + 2u, it);
+                    push(l3, e0 + 3u, it);
+                    l2 = l3 = 0ull;
+                }
+                if (wq_n < 64) break;
+                insert();
+                if (S == 1 && s_cnt[0] > (uint32_t)RCAP) { // the only sample outgrew its slot
+                    wq_n = 0;
+                    base = total; // the pass ends here
+                    break;
+                }
+                load(64);
+            }
+        }
+        insert();
+        while (wq_n) {
+            load(min(wq_n, 64u));
+            insert();
+        }
+        if (qtag > 0xF0000000u) { // marks must grow: start over from clear ones
+            s_qmap[lane] = 0u;
+            qtag = 64;
+        }
+        sync();
+    }
+    if constexpr (CHUNKED)
+        if ((unsigned long long)lane < hand_end - hand_next) SKIS_KARG(deferred)[hand_next + lane] = NO_ID;
+    if (SKIS_KARG(tier_stats)) {
+        unsigned long long *const ts = SKIS_KARG(tier_stats) + (blockIdx.x % STAT_BUCKETS) * STAT_ROW;
+        const unsigned long long v[6] = {wave_sum((unsigned long long)st_fin), wave_sum(st_ent), wave_sum(st_prb),
+                                         wave_sum(st_swp), wave_sum((unsigned long long)st_itm),
+                                         wave_sum((unsigned long long)st_hnd)};
+        unsigned long long mine = 0;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) mine = lane == k ? v[k] : mine;
+        if (lane < 6 && mine) atomicAdd(ts + lane, mine);
+    }
+}
+
+// The other shapes and the HBM tiers: several waves a workgroup, or more items a pass, or visited
+// sets in global memory.
+template <int BLOCK, int S, int RCAP, int HCAP, int ICAP, int QPL, int TIER, bool UNIFORM>
+__device__ __forceinline__ void sample_block(const SampleArgs &a)
 {
     constexpr bool GLOBAL = TIER == 3; // bitmap visited sets: a sample never outgrows them
     constexpr bool GHASH = TIER == 2;  // hash visited sets in global memory
@@ -225,7 +782,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
     using LIdx = std::conditional_t<(HCAP <= 256), uint8_t, uint16_t>;
     __shared__ LIdx sh_lidx[LSZ];
     __shared__ uint32_t s_idx[S];
-    __shared__ int32_t s_count[S], s_cursor[S], s_flags[S], s_rib[S], s_rie[S];
+    __shared__ int32_t s_count[S], s_cursor[S], s_flags[S], s_rib[S], s_rootn[S];
     __shared__ unsigned long long s_probed[S];
     // phase B1 work of a slot: s_wo_cnt >= 0 entries to write at s_wo_off, -1 a hand-on
     // without handover, -2 a hand-on whose nodes go to handover s_wo_off; a slot flagged
@@ -235,6 +792,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
     __shared__ Handover s_snap[HO_OUT ? S : 1]; // each slot's state at the start of the pass
     __shared__ int32_t s_ibase[S + 1], s_ifirst[S], s_irp[S];
     __shared__ int32_t it_beg[ICAP], it_end[ICAP], it_pb[ICAP + 1];
+    __shared__ uint32_t it_th[UNIFORM ? ICAP : 1];
     __shared__ uint8_t it_slot[ICAP];
     __shared__ int32_t s_nitems, s_alive;
     __shared__ unsigned long long s_idnext, s_idend;
@@ -256,8 +814,8 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
     constexpr bool WMAP_QUAD = BLOCK == 64 && ICAP <= 64 && QPL == 1;
     __shared__ uint32_t s_imap[WMAP_SLOT ? 64 : 1];
     __shared__ uint32_t s_qmap[WMAP_QUAD ? 64 : 1];
-    // per wave: the live edges of the pass's sweeps not yet visited (node, slot)
-    __shared__ int32_t s_vq_node[(BLOCK / 64) * VQ_CAP];
+    // per wave: the live edges of the pass's sweeps not yet visited (edge, slot)
+    __shared__ int32_t s_vq_edge[(BLOCK / 64) * VQ_CAP];
     __shared__ uint8_t s_vq_slot[(BLOCK / 64) * VQ_CAP];
 
     const int tid = threadIdx.x;
@@ -354,7 +912,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
     };
 
     // lane s of wave 0 counts what slot s finishes; summed once when the workgroup exits
-    unsigned long long st_fin = 0, st_ent = 0, st_prb = 0;
+    unsigned long long st_fin = 0, st_ent = 0, st_prb = 0, st_hnd = 0;
     // every lane counts the edges and items it sets up (the work of this launch)
     unsigned long long st_swp = 0, st_itm = 0;
     if constexpr (!GLOBAL)
@@ -410,6 +968,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
                 if (!GLOBAL && (f & F_DEFER)) {
                     const uint32_t i = s_idx[s];
                     const unsigned long long k = atomicAdd(SKIS_KARG(n_deferred), 1ull);
+                    st_hnd += 1;
                     SKIS_KARG(deferred)[k] = i;
                     SKIS_KARG(out_size)[i] = DEFERRED;
                     s_wo_cnt[s] = -1; // nothing to write; its hash may hold keys past the list
@@ -574,7 +1133,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
                     } else {
                     s_idx[s] = i;
                     s_rib[s] = r.y + 1;
-                    s_rie[s] = r.w;
+                    s_rootn[s] = r.x;
                     s_probed[s] = (unsigned long long)(r.w - r.z);
                     s_count[s] = ris_rec ? 1 : 2;
                     s_cursor[s] = 1;
@@ -754,6 +1313,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
                     ss[k] = sl;
                     if (s_irp[sl] && t == 0) {
                         rootit[k] = true;
+                        xs[k] = s_rootn[sl]; // in range (checked at admission)
                     } else {
                         const int32_t x = list_node(sl, s_ifirst[sl] + t - s_irp[sl]);
                         if ((uint32_t)x >= (uint32_t)n) { // bounds guard: report, never index
@@ -766,11 +1326,14 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
                 }
             }
             int rb[IPT], re[IPT];
+            uint32_t rth[IPT];
 #pragma unroll
             for (int k = 0; k < IPT; ++k) {
                 const int32_t xc = xs[k] >= 0 ? xs[k] : 0;
-                rb[k] = a.row_ptr[xc];
-                re[k] = a.row_ptr[xc + 1];
+                const uint2 row = a.rows[xc];
+                rb[k] = (int)row.x;
+                rth[k] = row.y;
+                re[k] = (int)a.rows[xc + 1].x;
             }
 #pragma unroll
             for (int k = 0; k < IPT; ++k) {
@@ -780,7 +1343,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
                 int beg, end;
                 if (rootit[k]) {
                     beg = s_rib[sl];
-                    end = s_rie[sl];
+                    end = re[k];
                 } else {
                     beg = xs[k] >= 0 ? rb[k] : 0;
                     end = xs[k] >= 0 ? re[k] : 0;
@@ -795,6 +1358,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
                 it_slot[it] = (uint8_t)sl;
                 it_beg[it] = beg;
                 it_end[it] = end;
+                if constexpr (UNIFORM) it_th[it] = rth[k];
                 it_pb[it] = end > beg ? ((end - 1) >> 2) - (beg >> 2) + 1 : 0;
             }
         }
@@ -847,7 +1411,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
         // lanes that hold a live edge in a sweep.  The nodes a pass adds are expanded in later
         // passes only, so when they are inserted within the pass does not matter.  Every lane
         // of a wave runs the same number of sweeps (the wave-level scan needs them all).
-        int32_t *const vq_node = s_vq_node + (tid >> 6) * VQ_CAP;
+        int32_t *const vq_edge = s_vq_edge + (tid >> 6) * VQ_CAP;
         uint8_t *const vq_slot = s_vq_slot + (tid >> 6) * VQ_CAP;
         uint32_t vq_n = 0; // entries in the wave's queue (the same in every lane)
         auto vq_flush = [&]() {
@@ -855,7 +1419,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            for (uint32_t i = (uint32_t)(tid & 63); i < vq_n; i += 64) visit((int)vq_slot[i], vq_node[i]);
+            for (uint32_t i = (uint32_t)(tid & 63); i < vq_n; i += 64) visit((int)vq_slot[i], a.col[vq_edge[i]]);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -885,6 +1449,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
                 }
             }
             int pq[QPL], ps[QPL];
+            uint32_t pth[QPL]; // UNIFORM: the row's threshold
             uint32_t pin[QPL]; // edges of the quad inside the item's range, one bit each
 #pragma unroll
             for (int g = 0; g < QPL; ++g) {
@@ -892,6 +1457,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
                 ps[g] = -1;
                 pq[g] = 0;
                 pin[g] = 0u;
+                pth[g] = 0u;
                 if (g >= qpl || idx >= total) continue;
                 while (it_pb[lo + 1] <= idx) ++lo; // it_pb[nitems] = total > idx
                 const int sl = it_slot[lo];
@@ -903,17 +1469,18 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
                 }
                 ps[g] = sl;
                 pq[g] = q;
+                if constexpr (UNIFORM) pth[g] = it_th[lo];
                 const int lead = max(it_beg[lo] - 4 * q, 0), tail = max(4 * q + 4 - it_end[lo], 0);
                 pin[g] = (0xFu << lead) & (0xFu >> tail);
             }
             // every load is issued, unconditionally (a lane without a quad reads quad 0, which
-            // exists whenever the pass has a quad at all), before any is used: a load under a
-            // branch would make the compiler wait for it before the next one
-            uint4 pr[2 * QPL];
+            // always exists), before any is used: a load under a branch would make the compiler
+            // wait for it before the next one
+            uint4 pr[QPL];
 #pragma unroll
             for (int g = 0; g < QPL; ++g) {
-                pr[2 * g] = a.pairs[2 * pq[g]];
-                pr[2 * g + 1] = a.pairs[2 * pq[g] + 1];
+                if constexpr (UNIFORM) pr[g] = make_uint4(pth[g], pth[g], pth[g], pth[g]);
+                else pr[g] = reinterpret_cast<const uint4 *>(a.th)[pq[g]];
             }
             // coins first; the live edges (bit 4g + h: edge h of quad g) are then visited
             // through one call site, so the hash probing is not inlined 4 * QPL times
@@ -926,7 +1493,7 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
                 uint64_t X, Y;
                 philox2x64((uint32_t)pq[g], (uint32_t)j, (uint32_t)(j >> 32), TAG_EDGE, a.seed_lo, a.seed_hi, X, Y);
                 const uint32_t hw[4] = {(uint32_t)X, (uint32_t)(X >> 32), (uint32_t)Y, (uint32_t)(Y >> 32)};
-                const uint32_t th[4] = {pr[2 * g].y, pr[2 * g].w, pr[2 * g + 1].y, pr[2 * g + 1].w};
+                const uint32_t th[4] = {pr[g].x, pr[g].y, pr[g].z, pr[g].w};
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
                     live |= (uint32_t)(hw[h] < th[h]) << (4 * g + h);
@@ -935,23 +1502,17 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
                 live &= ~(0xFu << (4 * g)) | (pin[g] << (4 * g));
                 tie &= ~(0xFu << (4 * g)) | (pin[g] << (4 * g));
             }
-            static_assert(QPL <= 2, "the live-edge switch covers up to 2 quads per lane");
+            static_assert(QPL <= 2, "the live-edge selection covers up to 2 quads per lane");
             while (tie) { // almost never taken
                 const int c = __ffs(tie) - 1;
                 tie &= tie - 1u;
-                uint4 q;
-                switch (c >> 1) {
-                case 0: q = pr[0]; break;
-                case 1: q = pr[1]; break;
-                case 2: q = pr[QPL > 1 ? 2 : 0]; break;
-                default: q = pr[QPL > 1 ? 3 : 0]; break;
-                }
                 const bool g1 = QPL > 1 && c >= 4;
                 const int e = 4 * (g1 ? pq[QPL - 1] : pq[0]) + (c & 3);
                 const uint64_t j = a.j0 + s_idx[g1 ? ps[QPL - 1] : ps[0]];
                 // the coin's high half equals the threshold's
-                const uint32_t hw = (c & 1) ? q.w : q.y;
-                if (coin_live(SKIS_KARG(wbits)[e], coin_with_low_half(hw, (uint32_t)e, j, a.seed_lo, a.seed_hi)))
+                const uint4 t = g1 ? pr[QPL - 1] : pr[0];
+                const uint32_t hw = (c & 2) ? ((c & 1) ? t.w : t.z) : ((c & 1) ? t.y : t.x);
+                if (coin_live(weight_bits(SKIS_KARG(w)[e]), coin_with_low_half(hw, (uint32_t)e, j, a.seed_lo, a.seed_hi)))
                     live |= 1u << c;
             }
             // the sweep's live edges into the queue (visited at once when a sweep alone holds
@@ -965,20 +1526,13 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
             while (live) {
                 const int c = __ffs(live) - 1;
                 live &= live - 1u;
-                uint4 q;
-                int sl;
-                // a switch, not an index into pr[]: the arrays stay in registers
-                switch (c >> 1) {
-                case 0: q = pr[0]; sl = ps[0]; break;
-                case 1: q = pr[1]; sl = ps[0]; break;
-                case 2: q = pr[QPL > 1 ? 2 : 0]; sl = ps[QPL > 1 ? 1 : 0]; break;
-                default: q = pr[QPL > 1 ? 3 : 0]; sl = ps[QPL > 1 ? 1 : 0]; break;
-                }
-                const int32_t u = (int32_t)((c & 1) ? q.z : q.x);
+                const bool g1 = QPL > 1 && c >= 4;
+                const int e = 4 * (g1 ? pq[QPL - 1] : pq[0]) + (c & 3);
+                const int sl = g1 ? ps[QPL - 1] : ps[0];
                 if (direct) {
-                    visit(sl, u);
+                    visit(sl, a.col[e]);
                 } else {
-                    vq_node[pos] = u;
+                    vq_edge[pos] = e;
                     vq_slot[pos] = (uint8_t)sl;
                     ++pos;
                 }
@@ -990,27 +1544,64 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
         if (!s_alive) break;
     }
     if (SKIS_KARG(tier_stats)) {
+        unsigned long long *const ts = SKIS_KARG(tier_stats) + (blockIdx.x % STAT_BUCKETS) * STAT_ROW;
         if (tid < 64) {
             st_fin = wave_sum(st_fin);
             st_ent = wave_sum(st_ent);
             st_prb = wave_sum(st_prb);
+            st_hnd = wave_sum(st_hnd);
             if (tid == 0 && st_fin) {
-                atomicAdd(SKIS_KARG(tier_stats) + 0, st_fin);
-                atomicAdd(SKIS_KARG(tier_stats) + 1, st_ent);
-                atomicAdd(SKIS_KARG(tier_stats) + 2, st_prb);
+                atomicAdd(ts + 0, st_fin);
+                atomicAdd(ts + 1, st_ent);
+                atomicAdd(ts + 2, st_prb);
             }
+            if (tid == 0 && st_hnd) atomicAdd(ts + 5, st_hnd);
         }
         st_swp = wave_sum(st_swp);
         st_itm = wave_sum(st_itm);
         if ((tid & 63) == 0 && st_itm) {
-            atomicAdd(SKIS_KARG(tier_stats) + 3, st_swp);
-            atomicAdd(SKIS_KARG(tier_stats) + 4, st_itm);
+            atomicAdd(ts + 3, st_swp);
+            atomicAdd(ts + 4, st_itm);
         }
     }
 }
 
-// ---------------------------------------------------------------------------------------
 #undef SKIS_KARG
+
+// k_sample draws coins against the threshold of every edge; k_sample_uniform serves graphs whose
+// rows have one threshold each (Prep::uniform) from the row records, for the shapes that the
+// default options run.
+template <int BLOCK, int S, int RCAP, int HCAP, int ICAP, int QPL, int TIER, bool UNIFORM>
+__device__ __forceinline__ void sample_body(const SampleArgs &a)
+{
+    if constexpr (BLOCK == 64 && TIER <= 1 && ICAP == 64) sample_wave<S, RCAP, HCAP, TIER, UNIFORM>(a);
+    else sample_block<BLOCK, S, RCAP, HCAP, ICAP, QPL, TIER, UNIFORM>(a);
+}
+
+template <int BLOCK, int S, int RCAP, int HCAP, int ICAP, int QPL, int TIER>
+__global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) void k_sample(SampleArgs a)
+{
+    sample_body<BLOCK, S, RCAP, HCAP, ICAP, QPL, TIER, false>(a);
+}
+
+template <int BLOCK, int S, int RCAP, int HCAP, int ICAP, int QPL, int TIER>
+__global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) void k_sample_uniform(SampleArgs a)
+{
+    sample_body<BLOCK, S, RCAP, HCAP, ICAP, QPL, TIER, true>(a);
+}
+
+// The front of the default first tier: many small slots, so that a pass of a wave has items for
+// most of its lanes although a small sample offers about three a pass.  Samples that outgrow a
+// slot go on to the four-slot kernel with their state.
+constexpr int FRONT_SLOTS = 16, FRONT_RCAP = 44, FRONT_HCAP = 64;
+
+template <bool UNIFORM>
+__global__ __launch_bounds__(64) void k_sample_front(SampleArgs a)
+{
+    sample_wave<FRONT_SLOTS, FRONT_RCAP, FRONT_HCAP, 0, UNIFORM>(a);
+}
+
+// ---------------------------------------------------------------------------------------
 
 // Compaction: sort each sample and write it at sample_ptr[i].
 // ---------------------------------------------------------------------------------------
@@ -1463,8 +2054,8 @@ struct ChainCtl {
     unsigned long long cursor;            // first sample id not yet handed to a chunk
     unsigned long long base, count;       // the current chunk: ids [base, base + count)
     unsigned long long next0, next1, next2, next3; // id counters of the four tiers
-    unsigned long long nd0, nd1, nd2;     // samples handed on by tiers 0, 1, 2 in this chunk
-    unsigned long long tot0, tot1, tot2;  // the same, summed over chunks
+    unsigned long long nextf, ndf;        // the front's id counter and hand-ons in this chunk
+    unsigned long long nd0, nd1, nd2;     // places of the lists tiers 0, 1, 2 hand on in this chunk
     unsigned long long replays;
 };
 
@@ -1480,6 +2071,8 @@ __global__ __launch_bounds__(64) void k_chain_begin(ChainCtl *c, uint64_t T, uin
     c->next1 = 0;
     c->next2 = 0;
     c->next3 = 0;
+    c->nextf = 0;
+    c->ndf = 0;
     c->nd0 = 0;
     c->nd1 = 0;
     c->nd2 = 0;
@@ -1488,9 +2081,6 @@ __global__ __launch_bounds__(64) void k_chain_begin(ChainCtl *c, uint64_t T, uin
 __global__ __launch_bounds__(64) void k_chain_end(ChainCtl *c)
 {
     if (threadIdx.x != 0) return;
-    c->tot0 += c->nd0;
-    c->tot1 += c->nd1;
-    c->tot2 += c->nd2;
     c->replays += 1;
 }
 
@@ -1523,11 +2113,20 @@ struct Counters {
     unsigned long long stage_used;
     unsigned long long n_deferred;
     unsigned long long n_medium;
+    unsigned long long next_front, n_front; // the front's id counter and its hand-ons
     int overflow;
     int pad;
-    unsigned long long tier[4][5]; // per tier: samples finished, their entries, their edges probed,
-                                   // edges and nodes the launch expanded
+    // per tier (SampleArgs::tier_stats); row 4: the front of the first tier
+    unsigned long long tier[5][STAT_BUCKETS][STAT_ROW];
+    // count k of tier t; the front's samples count for the first tier, its hand-ons go there
+    uint64_t tier_sum(int t, int k) const
+    {
+        uint64_t x = 0;
+        for (int b = 0; b < STAT_BUCKETS; ++b) x += tier[t][b][k] + (t == 0 && k < 5 ? tier[4][b][k] : 0ull);
+        return x;
+    }
 };
+static_assert(sizeof(Counters) % 8 == 0, "cleared in 8-byte words");
 
 typedef void (*SampleKernel)(SampleArgs);
 
@@ -1541,7 +2140,7 @@ struct Variant {
 // another wave; with 256 threads four waves share the slots and meet at barriers.
 static const Variant kTier0[] = {
     {64, 4, 192, 2, k_sample<64, 4, 192, 256, 128, 2, 0>},
-    {64, 4, 192, 1, k_sample<64, 4, 192, 256, 64, 1, 0>},
+    {64, 4, 192, 1, k_sample<64, 4, 192, 256, 64, 1, 0>}, // default (uniform rows: kTier0Uniform)
     {64, 4, 256, 2, k_sample<64, 4, 256, 320, 128, 2, 0>},
     {64, 4, 256, 1, k_sample<64, 4, 256, 320, 64, 1, 0>},
     {64, 2, 256, 1, k_sample<64, 2, 256, 320, 64, 1, 0>},
@@ -1559,13 +2158,15 @@ static const Variant kTier0[] = {
     {256, 32, 128, 2, k_sample<256, 32, 128, 172, 1024, 2, 0>},
     {256, 16, 256, 2, k_sample<256, 16, 256, 344, 1024, 2, 0>},
 };
+static SampleKernel const kTier0Uniform = k_sample_uniform<64, 4, 192, 256, 64, 1, 0>;
 // second tier: samples that outgrew the first, slots of 1024 nodes in LDS
 // (64 items a pass and two quads a lane: 341 ms at 1.4B edges against 350 with one quad,
 // 345 with 128 items, 399 and 469 with 128 and 256 items and one quad)
 static const Variant kTierMidV[] = {
-    {64, 1, 1024, 2, k_sample<64, 1, 1024, 1368, 64, 2, 1>},
+    {64, 1, 1024, 2, k_sample<64, 1, 1024, 1200, 64, 2, 1>},
     {256, 8, 1024, 2, k_sample<256, 8, 1024, 1368, 1024, 2, 1>},
 };
+static SampleKernel const kTierMidUniform = k_sample_uniform<64, 1, 1024, 1200, 64, 2, 1>;
 // Third tier: one sample per one-wave workgroup, its visited set a hash of TIERH_HCAP slots
 // and its node list TIERH_RCAP entries in HBM, so that every compute unit holds as many
 // samples as waves fit (the samples that outgrow 1024 nodes number about 1 % on the 1.4B-edge
@@ -1580,6 +2181,7 @@ constexpr int TIERH_HCAP = 8192;
 // bitmap tier's sixteen waves than by one
 constexpr uint32_t TIERH_BIG_ROW = 65536;
 static SampleKernel const kTierHash = k_sample<64, 1, TIERH_RCAP, TIERH_HCAP, 64, 1, 2>;
+static SampleKernel const kTierHashUniform = k_sample_uniform<64, 1, TIERH_RCAP, TIERH_HCAP, 64, 1, 2>;
 // Fourth tier: one sample per workgroup with a bitmap of n bits and a node list of n entries;
 // the few samples that outgrow the hash tier or meet an in-degree above 2^20 take sixteen waves
 // each; the HBM buffers of all slots are kept within TIERG_BUDGET bytes.
@@ -1633,7 +2235,6 @@ static void set_entries_per_sample_hint(int32_t n, int64_t m, double v)
 void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, uint64_t T, uint64_t seed,
                         const SampleConfig &cfg, Sketch &sk, hipStream_t s)
 {
-    (void)m;
     if (T >= (1ull << 31)) throw Error{SKIS_EINVAL, "num_samples must be below 2^31"};
     const uint32_t count = (uint32_t)T;
     const uint32_t seed_lo = (uint32_t)seed, seed_hi = (uint32_t)(seed >> 32);
@@ -1661,8 +2262,14 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     need(prep.row_ptr.ptr, "row_ptr");
     need(prep.q.ptr, "q");
     need(prep.P.ptr, "P");
-    need(prep.edges.ptr, "edges");
-    need(prep.wbits.ptr, "w bits");
+    if (!lt) {
+        need(prep.th.ptr, "coin thresholds");
+        need(prep.rows.ptr, "row records");
+    }
+    if (m > 0) {
+        need(prep.col, "col");
+        need(prep.w, "w");
+    }
 
     DevBuf<int4> rec;
     DevBuf<int32_t> u1;
@@ -1675,7 +2282,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     if (cfg.form != 2 && !lt) { // the captured form draws the roots inside its chain, chunk by chunk
         hipLaunchKernelGGL(k_roots, dim3(grid_cap(count, 256, 64)), dim3(256), 0, s, (uint64_t)cfg.first_id, count,
                            (const unsigned long long *)nullptr, seed_lo, seed_hi, n, prep.C, prep.alias.ptr,
-                           prep.row_ptr.ptr, prep.q.ptr, prep.P.ptr, prep.edges.ptr, prep.wbits.ptr, rec.ptr, u1.ptr, rerr.ptr,
+                           prep.row_ptr.ptr, prep.q.ptr, prep.P.ptr, prep.col, prep.w, rec.ptr, u1.ptr, rerr.ptr,
                            (int)cfg.ris);
         SKIS_HIP_TRY(hipGetLastError());
     }
@@ -1686,7 +2293,6 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     out_size.alloc(arena, count);
     out_off.alloc(arena, count);
     sk.probed.alloc(arena, count);
-    deferred.alloc(arena, count);
     medium.alloc(arena, count);
     DevBuf<Counters> ctr;
     ctr.alloc(arena, 1);
@@ -1696,6 +2302,17 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     const Variant &v0 =
         pick_variant(kTier0, sizeof(kTier0) / sizeof(kTier0[0]), cfg.threads, cfg.slots, cfg.visited, cfg.qpl);
     const Variant &vm = kTierMidV[cfg.threads == 64 ? 0 : 1];
+    // rows of one threshold each: the sweeps read no edge data (the default shapes only)
+    const bool uni = prep.uniform && cfg.threads == 64;
+    const SampleKernel tier0 =
+        uni && cfg.slots == 4 && cfg.visited == 192 && cfg.qpl == 1 ? kTier0Uniform : v0.fn;
+    // the front runs before the default first tier; not under a cap on device memory, which its
+    // handover records would count against
+    const bool front = !lt && cfg.form != 1 && cfg.threads == 64 && cfg.slots == 4 && cfg.visited == 192 &&
+                       cfg.qpl == 1 && !arena.cap;
+    const SampleKernel tier_front = prep.uniform ? k_sample_front<true> : k_sample_front<false>;
+    const SampleKernel tier1 = uni ? kTierMidUniform : vm.fn;
+    const SampleKernel tier2 = prep.uniform ? kTierHashUniform : kTierHash;
     // handover from tier 0 to tier 1 for the first ho_cap samples a launch hands on (the rest
     // start over in tier 1): an eighth of the ids one tier-0 launch takes (784 B a record at the
     // default shape; 8.2 % of the samples outgrow tier 0 on the 1.4B-edge WC graph)
@@ -1710,13 +2327,27 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     ho_state.alloc(arena, ho_cap);
     ho_nodes.alloc(arena, ho_cap * (uint64_t)ho_stride);
     const int cus = device_cu_count();
-    const int nb0 = occupancy_blocks(v0.fn, (int)v0.threads) * cus;
-    const int nbm = occupancy_blocks(vm.fn, (int)vm.threads) * cus;
+    const int nbf = occupancy_blocks(tier_front, 64) * cus;
+    const int nb0 = occupancy_blocks(tier0, (int)v0.threads) * cus;
+    const int nbm = occupancy_blocks(tier1, (int)vm.threads) * cus;
+    // handover from the front for a third of a launch's ids (192 B a record)
+    const uint64_t hof_cap = front ? std::min<uint64_t>(per_launch0, std::max<uint64_t>(1024, per_launch0 / 3)) : 0;
+    DevBuf<Handover> hof_state;
+    DevBuf<int32_t> hof_nodes;
+    DevBuf<uint32_t> front_ids; // the samples the front hands on
+    deferred.alloc(arena, count + (uint64_t)nb0 * HANDON_CHUNK); // with the chunks' unused places
+    if (front) {
+        hof_state.alloc(arena, hof_cap);
+        hof_nodes.alloc(arena, hof_cap * (uint64_t)FRONT_RCAP);
+        front_ids.alloc(arena, per_launch0 + (uint64_t)nbf * HANDON_CHUNK);
+    }
     // Staging: each LDS-tier workgroup reserves 8 * slots * visited entries at a time and
     // wastes less than one finished pass (slots * visited) per reservation plus its last
     // open chunk, so sum|R| * 8/7 + 2 chunks per workgroup bounds what a launch reserves.
     const uint64_t ch0 = 8ull * v0.slots * v0.visited, chm = 8ull * vm.slots * vm.visited;
-    const uint64_t slack = (uint64_t)std::min<uint64_t>(nb0, count) * 2 * ch0 +
+    const uint64_t chf = front ? 8ull * FRONT_SLOTS * FRONT_RCAP : 0;
+    const uint64_t slack = (uint64_t)std::min<uint64_t>(nbf, count) * 2 * chf +
+                           (uint64_t)std::min<uint64_t>(nb0, count) * 2 * ch0 +
                            (uint64_t)std::min<uint64_t>(nbm, count) * 2 * chm;
     auto staging_bound = [&](uint64_t entries, uint64_t launches) {
         return entries + entries / 7 + 1 + launches * slack + (1ull << 20);
@@ -1731,7 +2362,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     const int nbg = (int)std::min<uint64_t>((uint64_t)TIERG_PER_CU * cus, nbg_mem);
     // hash tier: as many one-wave workgroups as are resident at once, each with its own hash
     // and list
-    const int nbh = occupancy_blocks(kTierHash, 64) * cus;
+    const int nbh = occupancy_blocks(tier2, 64) * cus;
     DevBuf<uint32_t> deferred2;
     deferred2.alloc(arena, count);
     const int ho2_stride = (int)vm.visited; // tier 1 -> hash tier records
@@ -1820,17 +2451,18 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
         SKIS_HIP_TRY(hipStreamCreateWithFlags(&gg.cs, hipStreamNonBlocking));
         for (int attempt = 0; attempt < 2; ++attempt) {
             staging.alloc(arena, cap);
-            hipLaunchKernelGGL(k_fill<unsigned char>, dim3(1), dim3(64), 0, s, (uint64_t)sizeof(Counters),
-                               reinterpret_cast<unsigned char *>(ctr.ptr), (unsigned char)0);
+            hipLaunchKernelGGL(k_fill<unsigned long long>, dim3(4), dim3(256), 0, s, (uint64_t)sizeof(Counters) / 8,
+                               reinterpret_cast<unsigned long long *>(ctr.ptr), 0ull);
             hipLaunchKernelGGL(k_fill<unsigned char>, dim3(1), dim3(64), 0, s, (uint64_t)sizeof(ChainCtl),
                                reinterpret_cast<unsigned char *>(gc.ptr), (unsigned char)0);
             SKIS_HIP_TRY(hipGetLastError());
             SampleArgs A{};
             A.n = n;
-            A.row_ptr = prep.row_ptr.ptr;
-            A.pairs = reinterpret_cast<const uint4 *>(prep.edges.ptr);
-            A.nquads = (int64_t)(prep.edges.count / 4);
-            A.wbits = prep.wbits.ptr;
+            A.rows = prep.rows.ptr;
+            A.th = prep.th.ptr;
+            A.nquads = (int64_t)(prep.th.count / 4);
+            A.col = prep.col;
+            A.w = prep.w;
             A.rec = rec.ptr;
             A.u1 = u1.ptr;
             A.j0 = cfg.first_id;
@@ -1848,10 +2480,10 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A.words = words;
             need(A.staging, "staging");
             SampleArgs A0 = A, A1 = A, A2 = A, A3 = A;
-            A0.tier_stats = ctr.ptr->tier[0];
-            A1.tier_stats = ctr.ptr->tier[1];
-            A2.tier_stats = ctr.ptr->tier[2];
-            A3.tier_stats = ctr.ptr->tier[3];
+            A0.tier_stats = ctr.ptr->tier[0][0];
+            A1.tier_stats = ctr.ptr->tier[1][0];
+            A2.tier_stats = ctr.ptr->tier[2][0];
+            A3.tier_stats = ctr.ptr->tier[3][0];
             A0.next = &gc.ptr->next0;
             A0.id_list = nullptr;
             A0.id_count_dev = &gc.ptr->count;
@@ -1906,16 +2538,35 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A3.ho_cap_in = ho3_cap;
             A2.ho_stride_out = A3.ho_stride_in = ho3_stride;
 
+            SampleArgs AF = A0;
+            if (front) {
+                AF.next = &gc.ptr->nextf;
+                AF.tier_stats = ctr.ptr->tier[4][0];
+                AF.deferred = front_ids.ptr;
+                AF.n_deferred = &gc.ptr->ndf;
+                AF.ho_state_out = hof_state.ptr;
+                AF.ho_nodes_out = hof_nodes.ptr;
+                AF.ho_cap_out = hof_cap;
+                AF.ho_stride_out = FRONT_RCAP;
+                A0.id_list = front_ids.ptr;
+                A0.id_count_dev = &gc.ptr->ndf;
+                A0.id_base_dev = nullptr;
+                A0.ho_state_in = hof_state.ptr;
+                A0.ho_nodes_in = hof_nodes.ptr;
+                A0.ho_cap_in = hof_cap;
+                A0.ho_stride_in = FRONT_RCAP;
+            }
             SKIS_HIP_TRY(hipStreamBeginCapture(gg.cs, hipStreamCaptureModeThreadLocal));
             gg.capturing = true;
             hipLaunchKernelGGL(k_chain_begin, dim3(1), dim3(64), 0, gg.cs, gc.ptr, (uint64_t)count, chunk);
             hipLaunchKernelGGL(k_roots, dim3(grid_cap(chunk, 256, 64)), dim3(256), 0, gg.cs, (uint64_t)cfg.first_id, 0u,
                                (const unsigned long long *)&gc.ptr->base, seed_lo, seed_hi, n, prep.C,
-                               prep.alias.ptr, prep.row_ptr.ptr, prep.q.ptr, prep.P.ptr, prep.edges.ptr, prep.wbits.ptr, rec.ptr,
+                               prep.alias.ptr, prep.row_ptr.ptr, prep.q.ptr, prep.P.ptr, prep.col, prep.w, rec.ptr,
                                u1.ptr, rerr.ptr, (int)cfg.ris);
-            hipLaunchKernelGGL(v0.fn, dim3(nb0), dim3(v0.threads), 0, gg.cs, A0);
-            hipLaunchKernelGGL(vm.fn, dim3(nbm), dim3(vm.threads), 0, gg.cs, A1);
-            hipLaunchKernelGGL(kTierHash, dim3((unsigned)nbh), dim3(64), 0, gg.cs, A2);
+            if (front) hipLaunchKernelGGL(tier_front, dim3((unsigned)nbf), dim3(64), 0, gg.cs, AF);
+            hipLaunchKernelGGL(tier0, dim3(nb0), dim3(v0.threads), 0, gg.cs, A0);
+            hipLaunchKernelGGL(tier1, dim3(nbm), dim3(vm.threads), 0, gg.cs, A1);
+            hipLaunchKernelGGL(tier2, dim3((unsigned)nbh), dim3(64), 0, gg.cs, A2);
             hipLaunchKernelGGL(kTierGlobal, dim3((unsigned)nbg_g), dim3(TIERG_BLOCK), 0, gg.cs, A3);
             hipLaunchKernelGGL(k_chain_end, dim3(1), dim3(64), 0, gg.cs, gc.ptr);
             const hipError_t launch_err = hipGetLastError();
@@ -1938,9 +2589,9 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             if (hg.replays != replays || hg.cursor != count)
                 throw Error{SKIS_EHIP, "internal error: the captured chain covered " + std::to_string(hg.cursor) +
                                            " of " + std::to_string(count) + " samples"};
-            sk.deferred = hg.tot0;
-            sk.deferred_global = hg.tot1;
-            sk.deferred_bitmap = hg.tot2;
+            sk.deferred = hc.tier_sum(0, 5);
+            sk.deferred_global = hc.tier_sum(1, 5);
+            sk.deferred_bitmap = hc.tier_sum(2, 5);
             sk.graph_replays = (uint32_t)replays;
             (void)hipGraphExecDestroy(gg.x);
             (void)hipGraphDestroy(gg.g);
@@ -1948,7 +2599,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             gg.g = nullptr;
             if (!hc.overflow) return;
             // every size is known now: a bound that holds whatever order the chunks took
-            cap = staging_bound(hc.tier[0][1] + hc.tier[1][1] + hc.tier[2][1] + hc.tier[3][1], replays);
+            cap = staging_bound(hc.tier_sum(0, 1) + hc.tier_sum(1, 1) + hc.tier_sum(2, 1) + hc.tier_sum(3, 1), replays);
             staging.reset();
             if (attempt == 1) throw Error{SKIS_ENOMEM, "staging overflow after resize"};
         }
@@ -1958,8 +2609,8 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     if (lt) {
         // linear threshold model: the walk kernel and the long-walk kernel fill the same staging,
         // sizes, offsets and roots that the compaction below reads
-        hipLaunchKernelGGL(k_fill<unsigned char>, dim3(1), dim3(64), 0, s, (uint64_t)sizeof(Counters),
-                           reinterpret_cast<unsigned char *>(ctr.ptr), (unsigned char)0);
+        hipLaunchKernelGGL(k_fill<unsigned long long>, dim3(4), dim3(256), 0, s, (uint64_t)sizeof(Counters) / 8,
+                           reinterpret_cast<unsigned long long *>(ctr.ptr), 0ull);
         LtIo io;
         io.count = count;
         io.first_id = cfg.first_id;
@@ -1985,14 +2636,15 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     if (cfg.form == 1 && !lt) {
         // plain form: one launch per BFS level over all samples of a chunk
         staging.alloc(arena, cap);
-        hipLaunchKernelGGL(k_fill<unsigned char>, dim3(1), dim3(64), 0, s, (uint64_t)sizeof(Counters),
-                           reinterpret_cast<unsigned char *>(ctr.ptr), (unsigned char)0);
+        hipLaunchKernelGGL(k_fill<unsigned long long>, dim3(4), dim3(256), 0, s, (uint64_t)sizeof(Counters) / 8,
+                           reinterpret_cast<unsigned long long *>(ctr.ptr), 0ull);
         PlainInputs in{};
         in.count = count;
         in.row_ptr = prep.row_ptr.ptr;
-        in.pairs = reinterpret_cast<const uint4 *>(prep.edges.ptr);
-        in.nquads = (int64_t)(prep.edges.count / 4);
-        in.wbits = prep.wbits.ptr;
+        in.col = prep.col;
+        in.th = prep.th.ptr;
+        in.nquads = (int64_t)(prep.th.count / 4);
+        in.w = prep.w;
         in.rec = rec.ptr;
         in.u1 = u1.ptr;
         in.seed_lo = seed_lo;
@@ -2019,14 +2671,15 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     if (cfg.form == 2) sample_chain_graph();
     for (int attempt = 0; attempt < 2 && cfg.form == 0 && !lt; ++attempt) {
         staging.alloc(arena, cap);
-        hipLaunchKernelGGL(k_fill<unsigned char>, dim3(1), dim3(64), 0, s, (uint64_t)sizeof(Counters),
-                           reinterpret_cast<unsigned char *>(ctr.ptr), (unsigned char)0);
+        hipLaunchKernelGGL(k_fill<unsigned long long>, dim3(4), dim3(256), 0, s, (uint64_t)sizeof(Counters) / 8,
+                           reinterpret_cast<unsigned long long *>(ctr.ptr), 0ull);
         SampleArgs A{};
         A.n = n;
-        A.row_ptr = prep.row_ptr.ptr;
-        A.pairs = reinterpret_cast<const uint4 *>(prep.edges.ptr);
-        A.nquads = (int64_t)(prep.edges.count / 4);
-        A.wbits = prep.wbits.ptr;
+        A.rows = prep.rows.ptr;
+        A.th = prep.th.ptr;
+        A.nquads = (int64_t)(prep.th.count / 4);
+        A.col = prep.col;
+        A.w = prep.w;
         A.rec = rec.ptr;
         A.u1 = u1.ptr;
         A.j0 = cfg.first_id;
@@ -2048,12 +2701,12 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
         A.n_medium = &ctr.ptr->n_medium;
         A.overflow = &ctr.ptr->overflow;
         A.words = words;
-        A.tier_stats = ctr.ptr->tier[0];
+        A.tier_stats = ctr.ptr->tier[0][0];
         A.ho_state_out = ho_state.ptr;
         A.ho_nodes_out = ho_nodes.ptr;
         A.ho_cap_out = ho_cap;
         A.ho_stride_out = ho_stride;
-        for (const void *p : {(const void *)A.row_ptr, (const void *)A.pairs, (const void *)A.rec, (const void *)A.u1,
+        for (const void *p : {(const void *)A.rows, (const void *)A.th, (const void *)A.rec, (const void *)A.u1,
                               (const void *)A.next, (const void *)A.staging, (const void *)A.stage_used,
                               (const void *)A.out_size, (const void *)A.out_off, (const void *)A.out_probed,
                               (const void *)A.deferred, (const void *)A.n_deferred, (const void *)A.medium,
@@ -2061,11 +2714,30 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             need(p, "sampler argument");
         // tier 0: every sample, LDS visited sets of cfg.visited nodes
         SKIS_HIP_TRY(hipEventRecord(ev[4], s));
-        hipLaunchKernelGGL(v0.fn, dim3(nb0), dim3(v0.threads), 0, s, A);
+        if (front) {
+            SampleArgs AF = A;
+            AF.next = &ctr.ptr->next_front;
+            AF.tier_stats = ctr.ptr->tier[4][0];
+            AF.deferred = front_ids.ptr;
+            AF.n_deferred = &ctr.ptr->n_front;
+            AF.ho_state_out = hof_state.ptr;
+            AF.ho_nodes_out = hof_nodes.ptr;
+            AF.ho_cap_out = hof_cap;
+            AF.ho_stride_out = FRONT_RCAP;
+            hipLaunchKernelGGL(tier_front, dim3((unsigned)std::min<uint64_t>(nbf, count)), dim3(64), 0, s, AF);
+            SKIS_HIP_TRY(hipGetLastError());
+            A.id_list = front_ids.ptr; // the four-slot kernel takes the front's hand-ons
+            A.id_count_dev = &ctr.ptr->n_front;
+            A.ho_state_in = hof_state.ptr;
+            A.ho_nodes_in = hof_nodes.ptr;
+            A.ho_cap_in = hof_cap;
+            A.ho_stride_in = FRONT_RCAP;
+        }
+        hipLaunchKernelGGL(tier0, dim3(nb0), dim3(v0.threads), 0, s, A);
         SKIS_HIP_TRY(hipGetLastError());
         SKIS_HIP_TRY(hipEventRecord(ev[5], s));
         read_counters();
-        sk.deferred = hc.n_deferred;
+        sk.deferred = hc.tier_sum(0, 5);
         sk.deferred_global = 0;
         sk.deferred_bitmap = 0;
         ran_mid = ran_hash = ran_global = false;
@@ -2085,9 +2757,10 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             reset_ids();
             A.id_list = deferred.ptr;
             A.id_count = nd;
+            A.id_count_dev = nullptr;
             A.deferred = deferred2.ptr;
             A.big_row = std::max<uint32_t>(cfg.big_row, 1u << 20);
-            A.tier_stats = ctr.ptr->tier[1];
+            A.tier_stats = ctr.ptr->tier[1][0];
             A.ho_state_out = ho2_state.ptr;
             A.ho_nodes_out = ho2_nodes.ptr;
             A.ho_cap_out = ho2_cap;
@@ -2097,7 +2770,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A.ho_cap_in = ho_cap;
             A.ho_stride_in = ho_stride;
             SKIS_HIP_TRY(hipEventRecord(ev[6], s));
-            hipLaunchKernelGGL(vm.fn, dim3(nbm), dim3(vm.threads), 0, s, A);
+            hipLaunchKernelGGL(tier1, dim3(nbm), dim3(vm.threads), 0, s, A);
             SKIS_HIP_TRY(hipGetLastError());
             SKIS_HIP_TRY(hipEventRecord(ev[7], s));
             ran_mid = true;
@@ -2142,7 +2815,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A.ghash = ghash.ptr;
             A.glist2 = glist2.ptr;
             A.big_row = std::max<uint32_t>(cfg.big_row, TIERH_BIG_ROW);
-            A.tier_stats = ctr.ptr->tier[2];
+            A.tier_stats = ctr.ptr->tier[2][0];
             A.ho_state_out = ho3_state.ptr;
             A.ho_nodes_out = ho3_nodes.ptr;
             A.ho_cap_out = ho3_cap;
@@ -2153,7 +2826,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A.ho_cap_in = ho2_cap;
             A.ho_stride_in = ho2_stride;
             SKIS_HIP_TRY(hipEventRecord(ev[8], s));
-            hipLaunchKernelGGL(kTierHash, dim3((unsigned)nbh), dim3(64), 0, s, A);
+            hipLaunchKernelGGL(tier2, dim3((unsigned)nbh), dim3(64), 0, s, A);
             SKIS_HIP_TRY(hipGetLastError());
             SKIS_HIP_TRY(hipEventRecord(ev[9], s));
             ran_hash = true;
@@ -2177,7 +2850,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A.deferred = deferred2.ptr; // unused: the bitmap tier finishes every sample
             A.gbits = gbits.ptr;
             A.glist = glist.ptr;
-            A.tier_stats = ctr.ptr->tier[3];
+            A.tier_stats = ctr.ptr->tier[3][0];
             A.ho_state_out = nullptr;
             A.ho_nodes_out = nullptr;
             A.ho_cap_out = 0;
@@ -2203,13 +2876,13 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
                                        std::to_string(hc.overflow | herr) + ")"};
         if (!hc.overflow) break;
         // every size is known now: a bound that holds whatever order the chunks took
-        cap = staging_bound(hc.tier[0][1] + hc.tier[1][1] + hc.tier[2][1] + hc.tier[3][1], 1);
+        cap = staging_bound(hc.tier_sum(0, 1) + hc.tier_sum(1, 1) + hc.tier_sum(2, 1) + hc.tier_sum(3, 1), 1);
         staging.reset();
         if (attempt == 1) throw Error{SKIS_ENOMEM, "staging overflow after resize"};
     }
     SKIS_HIP_TRY(hipEventRecord(ev[2], s));
     for (int t = 0; t < 4; ++t)
-        for (int k = 0; k < 5; ++k) sk.tier_stats[t][k] = hc.tier[t][k];
+        for (int k = 0; k < 5; ++k) sk.tier_stats[t][k] = hc.tier_sum(t, k);
     if (lt) { // stage 0: the walk kernel, stage 1: the long walks; picks drawn in place of swept edges
         const uint64_t ts[2][5] = {{lts.walk_samples, lts.walk_entries, lts.walk_probed, lts.walk_picks, lts.walk_entries},
                                    {lts.long_samples, lts.long_entries, lts.long_probed, lts.long_picks, lts.long_entries}};

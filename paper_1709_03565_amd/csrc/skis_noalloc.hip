@@ -13,13 +13,15 @@
 
 namespace skis {
 
-// Layout in 32-bit words: [0, NA_LIST) the error word (word 0); [NA_LIST, NA_BITS) the large
-// sets of one host chunk as int64 set indexes; [NA_BITS, NA_WORDS) the bitmaps.
+// Layout in 32-bit words: word 0 the error word, words 4-7 the flags (EstFlags); [NA_LIST, NA_BITS)
+// the large sets of one host chunk as int64 set indexes, and before them, from word NA_LIST - 1,
+// the parked sets' list (its count in that word) and tickets; [NA_BITS, NA_WORDS) the bitmaps.
 constexpr uint64_t NA_WORDS = (32ull << 20) / 4; // 32 MiB
 constexpr int NA_CHUNK = 1024;                   // sets routed per host round
 constexpr uint64_t NA_LIST = 64;
 constexpr uint64_t NA_BITS = NA_LIST + 2 * NA_CHUNK;
 static_assert(NA_BITS % 64 == 0, "the bitmaps start 256-byte aligned");
+static_assert(NA_CHUNK <= EST_BLOCK, "one list of parked sets");
 
 static __device__ __align__(256) uint32_t scratch[NA_WORDS];
 
@@ -76,13 +78,13 @@ void estimate_noalloc(const Sketch &sk, int32_t Q, const int64_t *set_ptr, const
     int *err = reinterpret_cast<int *>(base);
     int64_t *qlist = reinterpret_cast<int64_t *>(base + NA_LIST);
     uint32_t *bits = base + NA_BITS;
-    // sets per launch: one bitmap of T bits each (small sets); a bitmap and a node bitmap of n
-    // bits each (large sets)
-    const uint64_t nb = std::min<uint64_t>(room / wordsT, (uint64_t)NA_CHUNK);
+    EstFlags *flags = reinterpret_cast<EstFlags *>(base + 4);
+    uint32_t *heavy = base + NA_LIST - 1, *ticket = base + NA_LIST + NA_CHUNK;
+    // large sets per launch: a bitmap of T bits and a node bitmap of n bits each
     const uint64_t ng = std::min<uint64_t>(room / (wordsT + wordsN), (uint64_t)NA_CHUNK);
     // the array keeps the last call's contents: clear what this call uses
     na_fill(base, NA_LIST, s);
-    na_fill(bits, std::max<uint64_t>(nb * wordsT, ng * (wordsT + wordsN)), s);
+    bool bits_clear = false;
     int64_t hp[NA_CHUNK + 1];
     int64_t lg[NA_CHUNK];
     for (int64_t c0 = 0; c0 < Q; c0 += NA_CHUNK) {
@@ -99,10 +101,16 @@ void estimate_noalloc(const Sketch &sk, int32_t Q, const int64_t *set_ptr, const
         if (nl > 0 && ng == 0)
             throw Error{SKIS_EINVAL, "a set above " + std::to_string(EST_MAX_SET) +
                                          " entries needs more than the no-alloc scratch holds on this sketch"};
-        for (int b0 = 0; b0 < ch; b0 += (int)nb)
-            estimate_launch_small(sk, c0 + b0, (int32_t)std::min<int64_t>((int64_t)nb, ch - b0), set_ptr, set_nodes,
-                                  bits, wordsT, reinterpret_cast<unsigned long long *>(cov), est, err, s);
+        unsigned long long *const cv = reinterpret_cast<unsigned long long *>(cov) + c0;
+        estimate_light(sk, ch, false, set_ptr + c0, set_nodes, cv, est + c0, ticket, flags, s);
+        EstFlags fl{};
+        SKIS_HIP_TRY(hipMemcpyAsync(&fl, flags, sizeof(fl), hipMemcpyDeviceToHost, s));
+        SKIS_HIP_TRY(hipStreamSynchronize(s));
+        if (fl.node) throw Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
+        if (fl.parked) estimate_split(sk, ch, set_ptr + c0, set_nodes, cv, est + c0, heavy, ticket, s);
         if (nl > 0) {
+            if (!bits_clear) na_fill(bits, ng * (wordsT + wordsN), s);
+            bits_clear = true; // the kernel leaves it so
             SKIS_HIP_TRY(hipMemcpyAsync(qlist, lg, sizeof(int64_t) * (size_t)nl, hipMemcpyHostToDevice, s));
             for (int g0 = 0; g0 < nl; g0 += (int)ng)
                 estimate_launch_large(sk, qlist, g0, (int32_t)std::min<int>((int)ng, nl - g0), set_ptr, set_nodes,

@@ -10,6 +10,18 @@ constexpr int EST_BLOCK = 1024;   // threads per query in k_estimate
 constexpr int EST_MAX_SET = 4096; // largest seed set one estimate workgroup holds in LDS
 constexpr int EST_WALK = 4;       // sample-list entries a thread walks per round, loads issued together
 
+constexpr int EST_HASH_SLOTS = 16384; // LDS hash of a light set's sample ids in k_est_light
+constexpr int EST_HASH_MAX = 10922;   // list entries a light set's members hold at most (1.5 slots each)
+constexpr unsigned long long EST_PARKED = ~0ull; // cov of a set that k_est_light left to the next kernel
+
+// What k_est_light reports (each word is only ever set to 1).
+struct EstFlags {
+    int ptr;    // set_ptr does not rise from 0
+    int node;   // a node id outside [0, n)
+    int large;  // a set above EST_MAX_SET entries was left out
+    int parked; // a set above EST_HASH_MAX list entries was parked
+};
+
 constexpr int GREEDY_HOT = 2048;  // hot nodes decremented in LDS
 
 struct GreedyState {
@@ -29,29 +41,37 @@ struct RecountItem {
     int32_t v;
 };
 
-// Per-sketch scratch for estimate: one bitmap of T bits per query in flight.
+// Per-sketch scratch for estimate.
 struct QueryScratch {
-    DevBuf<uint32_t> bitmaps;
+    DevBuf<uint32_t> bitmaps; // sets above EST_MAX_SET entries: one bitmap of T bits each in flight
     uint64_t bitmap_words = 0;
     DevBuf<int> err;
+    DevBuf<uint32_t> split;   // the parked sets' list and tickets
+    DevBuf<EstFlags> flags;   // used when no pinned place is free
 };
 
 void estimate_batch(const Sketch &sk, QueryScratch &qs, int32_t Q, const int64_t *set_ptr, const int32_t *set_nodes,
                     uint64_t *cov, double *est, hipStream_t s);
-// One launch pair for nq sets in CSR form on the device (set_ptr from 0): the sets of at
-// most EST_MAX_SET entries take a workgroup each; the nlarge sets listed in large[] (device
-// indexes into the CSR) take the chunked path with one node bitmap of n bits each in
-// nodebits.  bitmaps holds a zeroed bitmap of bitmap_words words for every workgroup
-// (max(nq, nlarge) of them) and is left zeroed.  Stream-ordered; no host synchronisation.
-void estimate_launch(const Sketch &sk, int32_t nq, const int64_t *set_ptr, const int32_t *set_nodes,
+// nq sets in CSR form on the device: sets of at most EST_MAX_SET entries whose members' lists hold
+// at most EST_HASH_MAX entries are answered, heavier ones parked (cov = EST_PARKED, est = their sum
+// of q, ticket 0 where ticket is not null), sets above EST_MAX_SET entries left out.  check:
+// set_ptr is checked first (at most EST_BLOCK sets); else it has been.
+void estimate_light(const Sketch &sk, int32_t nq, bool check, const int64_t *set_ptr, const int32_t *set_nodes,
+                    unsigned long long *cov, double *est, uint32_t *ticket, EstFlags *flags, hipStream_t s);
+// The sets that estimate_light parked, split over the device by windows of sample ids.  heavy
+// (nq + 1 words) and ticket (nq words) are scratch.
+void estimate_split(const Sketch &sk, int32_t nq, const int64_t *set_ptr, const int32_t *set_nodes,
+                    unsigned long long *cov, double *est, uint32_t *heavy, uint32_t *ticket, hipStream_t s);
+// A batch of the service, nq checked sets: by estimate_light when light_only (no set's lists hold
+// more than EST_HASH_MAX entries and none is large), else one workgroup a set with a bitmap of T
+// bits; and the nlarge sets listed in large[] (device indexes into the CSR) by the chunked path with
+// one node bitmap of n bits each in nodebits.  bitmaps holds a zeroed bitmap of bitmap_words words
+// for every workgroup (max(nq, nlarge) of them) and is left zeroed.  Stream-ordered; no host
+// synchronisation.
+void estimate_launch(const Sketch &sk, int32_t nq, bool light_only, const int64_t *set_ptr, const int32_t *set_nodes,
                      const int64_t *large, int32_t nlarge, uint32_t *bitmaps, uint64_t bitmap_words,
-                     uint32_t *nodebits, unsigned long long *cov, double *est, int *err, hipStream_t s);
-// The two launches of estimate_launch on their own: sets q0 .. q0+nq-1 of the CSR (those of
-// at most EST_MAX_SET entries; set q0+b uses bitmap b), and the ng large sets listed in
-// qlist[g0 .. g0+ng) (set qlist[g0+b] uses bitmap b and node bitmap b).  Stream-ordered.
-void estimate_launch_small(const Sketch &sk, int64_t q0, int32_t nq, const int64_t *set_ptr,
-                           const int32_t *set_nodes, uint32_t *bitmaps, uint64_t bitmap_words,
-                           unsigned long long *cov, double *est, int *err, hipStream_t s);
+                     uint32_t *nodebits, unsigned long long *cov, double *est, int *err, EstFlags *flags, hipStream_t s);
+// The ng large sets listed in qlist[g0 .. g0+ng) (set qlist[g0+b] uses bitmap b and node bitmap b).
 void estimate_launch_large(const Sketch &sk, const int64_t *qlist, int64_t g0, int32_t ng, const int64_t *set_ptr,
                            const int32_t *set_nodes, uint32_t *bitmaps, uint64_t bitmap_words, uint32_t *nodebits,
                            unsigned long long *cov, double *est, int *err, hipStream_t s);

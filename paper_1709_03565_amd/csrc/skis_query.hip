@@ -273,6 +273,345 @@ __global__ __launch_bounds__(EST_BLOCK) void k_estimate(const int64_t *__restric
 }
 
 // ---------------------------------------------------------------------------------------
+// Estimates of sets of at most EST_MAX_SET entries.
+//
+// k_est_light: one workgroup a set.  The distinct members' list lengths come first; when they add
+// up to at most EST_HASH_MAX entries, the sample ids go into an LDS hash (Cov = ids that were not
+// there), so a light set touches no bitmap in memory and has nothing to clear; a walk that flips
+// bits of a T-bit bitmap in memory took two passes over the lists and a returning global atomic an
+// entry (about 390M a second for a CU).  Heavier sets are parked: cov = EST_PARKED, est = the sum
+// of q.
+//
+// k_est_split: the parked sets.  The lists are sorted by sample id, so a window of ids is a range
+// of every list: a workgroup takes one (set, window), finds the ranges by binary search, sets the
+// window's bits in LDS and counts them; the windows of a set run on as many CUs as there are, with
+// no bitmap in memory.  Each adds its count to cov, and the set's last window forms the estimate
+// (no workgroup waits for another).  Whole calls, one workgroup and bitmap a set before -> now: 16
+// sets of up to 50 hubs on 2^25 samples of the 4M-node TRI graph 6.7 -> 0.13 ms, 100 sets of 1-50
+// uniform nodes on 2^24 samples of the 1M-node WC graph 0.30 -> 0.092 ms, one set of 3 nodes on
+// 200k samples 62 -> 32 us (the flags in host memory, one kernel).
+// ---------------------------------------------------------------------------------------
+__device__ __forceinline__ double first_term(unsigned long long cov, double Gamma, uint64_t T)
+{
+    return T > 0 ? __ddiv_rn(__dmul_rn((double)cov, Gamma), (double)T) : 0.0;
+}
+
+// check: 0, or the number of sets whose set_ptr this workgroup checks first (so that no set is
+// read by a set_ptr that does not rise from 0; at most EST_BLOCK of them).  flags: see EstFlags.
+__global__ __launch_bounds__(EST_BLOCK) void k_est_light(int32_t check, const int64_t *__restrict__ set_ptr,
+                                                         const int32_t *__restrict__ set_nodes, int32_t n, uint64_t T,
+                                                         double Gamma, const double *__restrict__ qv,
+                                                         const int64_t *__restrict__ node_ptr,
+                                                         const int32_t *__restrict__ node_samples,
+                                                         unsigned long long *__restrict__ cov_out,
+                                                         double *__restrict__ est_out, uint32_t *__restrict__ ticket,
+                                                         EstFlags *__restrict__ flags)
+{
+    __shared__ int32_t buf[EST_MAX_SET];
+    __shared__ int32_t pre[EST_MAX_SET + 1];  // first entry of each member's list in the walk
+    __shared__ int64_t lbase[EST_MAX_SET];    // list begin - pre
+    __shared__ uint32_t hash[EST_HASH_SLOTS];
+    __shared__ double ps[EST_BLOCK], pc[EST_BLOCK];
+    __shared__ int32_t s_scan[EST_BLOCK / 64 + 1];
+    __shared__ int64_t s_scan64[EST_BLOCK / 64 + 1];
+    __shared__ uint32_t s_cov, s_next;
+    __shared__ int s_bad_ptr, s_bad;
+
+    const int64_t qi = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid == 0) {
+        s_bad_ptr = s_bad = 0;
+        s_cov = 0u;
+        s_next = 0u;
+    }
+    __syncthreads();
+    if (tid < check) {
+        const int64_t x = set_ptr[tid], y = set_ptr[tid + 1];
+        if (x < 0 || y < x) s_bad_ptr = 1;
+    }
+    __syncthreads();
+    if (s_bad_ptr) {
+        if (tid == 0) flags->ptr = 1;
+        return;
+    }
+    const int64_t a = set_ptr[qi], b = set_ptr[qi + 1];
+    if (b - a > EST_MAX_SET) { // k_estimate<true>'s
+        if (tid == 0) {
+            flags->large = 1;
+            cov_out[qi] = 0ull; // not EST_PARKED by what the buffer held
+        }
+        return;
+    }
+    const int kc = (int)(b - a);
+    int P = 1;
+    while (P < kc) P <<= 1;
+    for (int t = tid; t < P; t += EST_BLOCK) {
+        int32_t v = INT32_MAX;
+        if (t < kc) {
+            v = set_nodes[a + t];
+            if (v < 0 || v >= n) {
+                s_bad = 1;
+                v = INT32_MAX;
+            }
+        }
+        buf[t] = v;
+    }
+    __syncthreads();
+    if (s_bad) {
+        if (tid == 0) flags->node = 1;
+        return;
+    }
+    if (P > 1) bitonic_sort_lds<EST_BLOCK>(buf, P);
+    // distinct members, compacted in order
+    constexpr int IPT = EST_MAX_SET / EST_BLOCK;
+    int nu = 0;
+    {
+        int32_t mine[IPT];
+        int keep = 0, cntu = 0;
+#pragma unroll
+        for (int r = 0; r < IPT; ++r) {
+            const int t = tid * IPT + r;
+            const int32_t v = t < kc ? buf[t] : INT32_MAX;
+            mine[r] = v;
+            const bool u = t < kc && (t == 0 || buf[t - 1] != v);
+            keep |= (u ? 1 : 0) << r;
+            cntu += u ? 1 : 0;
+        }
+        int pos = block_excl_scan<EST_BLOCK, int>(cntu, s_scan, &nu);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < IPT; ++r)
+            if (keep >> r & 1) buf[pos++] = mine[r];
+        __syncthreads();
+    }
+    // q of the members (summed below, in the same order as k_estimate) and the lists' bounds
+    double sq = 0.0, cq = 0.0;
+    if (qv)
+        for (int t = tid; t < nu; t += EST_BLOCK) neumaier_add(sq, cq, qv[buf[t]]);
+    int64_t np[IPT], dl[IPT];
+    int64_t acc = 0, E = 0;
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        const int t = tid * IPT + r;
+        int64_t d = 0;
+        np[r] = 0;
+        if (t < nu) {
+            const int32_t v = buf[t];
+            np[r] = node_ptr[v];
+            d = node_ptr[v + 1] - np[r];
+        }
+        dl[r] = acc;
+        acc += d;
+    }
+    const int64_t ex = block_excl_scan<EST_BLOCK, int64_t>(acc, s_scan64, &E);
+    ps[tid] = sq;
+    pc[tid] = cq;
+    const bool light = E <= (int64_t)EST_HASH_MAX;
+    uint32_t slots = 64; // a power of two of at least 1.5 slots an entry
+    if (light) {
+        while (2 * slots < 3 * (uint32_t)E) slots <<= 1;
+#pragma unroll
+        for (int r = 0; r < IPT; ++r) {
+            const int t = tid * IPT + r;
+            if (t < nu) {
+                pre[t] = (int32_t)(ex + dl[r]);
+                lbase[t] = np[r] - (ex + dl[r]);
+            }
+        }
+        if (tid == 0) pre[nu] = (int32_t)E;
+        for (uint32_t i = tid; i < slots; i += EST_BLOCK) hash[i] = 0xFFFFFFFFu;
+    }
+    __syncthreads();
+    double s = 0.0, cc = 0.0;
+    if (tid == 0) { // one chain of additions, beside the other waves' walk
+        const int tq = nu < EST_BLOCK ? nu : EST_BLOCK;
+        for (int t = 0; t < tq; ++t) {
+            neumaier_add(s, cc, ps[t]);
+            if (nu > EST_BLOCK) neumaier_add(s, cc, pc[t]); // a single member's compensation is +0
+        }
+    }
+    if (!light) {
+        if (tid == 0) {
+            cov_out[qi] = EST_PARKED;
+            est_out[qi] = __dadd_rn(s, cc);
+            if (ticket) ticket[qi] = 0u;
+            flags->parked = 1;
+        }
+        return;
+    }
+    const uint32_t sh = 32 - (31 - __clz((int)slots));
+    uint32_t found = 0;
+    for (;;) { // a wave takes 256 entries at a time
+        uint32_t c = 0;
+        if (lane == 0) c = atomicAdd(&s_next, 256u);
+        c = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
+        if (c >= (uint32_t)E) break;
+        int32_t jv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int idx = min((int)c + u * 64 + lane, (int)E - 1);
+            int lo = 0, hi = nu - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (pre[mid] <= idx) lo = mid; else hi = mid - 1;
+            }
+            jv[u] = node_samples[lbase[lo] + idx];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if ((int)c + u * 64 + lane >= (int)E) continue;
+            const uint32_t j = (uint32_t)jv[u];
+            uint32_t h = (j * 0x9E3779B1u) >> sh;
+            uint32_t old;
+#pragma unroll 1
+            for (;;) { // fewer entries than slots: an empty slot is always met
+                old = atomicCAS(&hash[h], 0xFFFFFFFFu, j);
+                if (old == 0xFFFFFFFFu || old == j) break;
+                h = (h + 1) & (slots - 1u);
+            }
+            found += old == 0xFFFFFFFFu ? 1u : 0u;
+        }
+    }
+    found = wave_sum(found);
+    if (lane == 0 && found) atomicAdd(&s_cov, found);
+    __syncthreads();
+    if (tid == 0) {
+        const unsigned long long c = s_cov;
+        cov_out[qi] = c;
+        est_out[qi] = __dadd_rn(first_term(c, Gamma, T), __dadd_rn(s, cc));
+    }
+}
+
+// First position of [lo, hi) with ns[pos] >= x, hi if there is none.
+__device__ __forceinline__ int64_t lower_bound_sample(const int32_t *__restrict__ ns, int64_t lo, int64_t hi, int64_t x)
+{
+    while (lo < hi) {
+        const int64_t mid = lo + ((hi - lo) >> 1);
+        if ((int64_t)ns[mid] >= x) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+}
+
+constexpr int SPLIT_BITS = 1 << 19;   // samples a window holds at most (64 KiB of LDS: two workgroups a CU)
+constexpr int SPLIT_MIN = 1 << 15;    // and at least, unless T is smaller
+constexpr int SPLIT_WINDOWS = 64;     // windows wanted: 16 sets then give every CU four of them
+static_assert(SPLIT_MIN % 32 == 0 && SPLIT_BITS % 32 == 0, "windows are whole words");
+
+__global__ __launch_bounds__(EST_BLOCK) void k_est_split(int32_t windows, int32_t wbits,
+                                                         const int64_t *__restrict__ set_ptr,
+                                                         const int32_t *__restrict__ set_nodes, uint64_t T,
+                                                         double Gamma, const int64_t *__restrict__ node_ptr,
+                                                         const int32_t *__restrict__ node_samples,
+                                                         const uint32_t *__restrict__ heavy,
+                                                         unsigned long long *__restrict__ cov_out,
+                                                         double *__restrict__ est_out, uint32_t *__restrict__ ticket)
+{
+    __shared__ uint32_t bits[SPLIT_BITS / 32];
+    __shared__ int64_t sbase[EST_BLOCK];   // range begin - pre
+    __shared__ int32_t pre[EST_BLOCK + 1]; // first entry of each member's range in the walk
+    __shared__ int32_t s_scan[EST_BLOCK / 64 + 1];
+    __shared__ uint32_t s_cnt;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int NW = EST_BLOCK / 64;
+    const uint32_t nheavy = heavy[0];
+    for (uint64_t item = blockIdx.x; item < (uint64_t)nheavy * (uint64_t)windows; item += gridDim.x) {
+        const int64_t qi = heavy[1 + item / (uint64_t)windows];
+        const int64_t w = (int64_t)(item % (uint64_t)windows);
+        const int64_t j0 = w * wbits, j1 = min(j0 + (int64_t)wbits, (int64_t)T);
+        const int words = (int)((j1 - j0 + 31) >> 5);
+        for (int i = tid; i < words; i += EST_BLOCK) bits[i] = 0u;
+        if (tid == 0) s_cnt = 0u;
+        const int64_t a = set_ptr[qi], b = set_ptr[qi + 1];
+        for (int64_t c0 = a; c0 < b; c0 += EST_BLOCK) { // repeated members set the same bits again
+            const int m = (int)min(b - c0, (int64_t)EST_BLOCK);
+            int64_t r0 = 0, r1 = 0;
+            if (tid < m) {
+                const int32_t v = set_nodes[c0 + tid];
+                const int64_t p0 = node_ptr[v], p1 = node_ptr[v + 1];
+                r0 = w == 0 ? p0 : lower_bound_sample(node_samples, p0, p1, j0);
+                r1 = w == windows - 1 ? p1 : lower_bound_sample(node_samples, r0, p1, j1);
+            }
+            int tot;
+            const int ex = block_excl_scan<EST_BLOCK, int>((int)(r1 - r0), s_scan, &tot);
+            pre[tid] = ex;
+            sbase[tid] = r0 - ex;
+            if (tid == 0) pre[EST_BLOCK] = tot;
+            __syncthreads();
+            // each wave walks an even share in chunks of 256; a chunk inside one range (a hub's)
+            // needs no search
+            const int share = ((tot + NW - 1) / NW + 255) & ~255;
+            const int f0 = wave * share, f1 = min(f0 + share, tot);
+            for (int f = f0; f < f1; f += 256) {
+                int lo = 0, hi = m - 1; // the range that holds entry f (uniform)
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (pre[mid] <= f) lo = mid; else hi = mid - 1;
+                }
+                const bool one = lo == m - 1 || pre[lo + 1] >= min(f + 256, f1);
+                int32_t jv[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int idx = min(f + u * 64 + lane, f1 - 1);
+                    int l = lo;
+                    if (!one) {
+                        int h = m - 1;
+                        while (l < h) {
+                            const int mid = (l + h + 1) >> 1;
+                            if (pre[mid] <= idx) l = mid; else h = mid - 1;
+                        }
+                    }
+                    jv[u] = node_samples[sbase[l] + idx];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) { // an entry past the share repeats the last one's bit
+                    const uint32_t j = (uint32_t)((int64_t)jv[u] - j0);
+                    if (j < (uint32_t)wbits) atomicOr(&bits[j >> 5], 1u << (j & 31));
+                }
+            }
+            __syncthreads();
+        }
+        if (b == a) __syncthreads();
+        uint32_t c = 0;
+        for (int i = tid; i < words; i += EST_BLOCK) c += (uint32_t)__popc(bits[i]);
+        c = wave_sum(c);
+        if (lane == 0 && c) atomicAdd(&s_cnt, c);
+        __syncthreads();
+        if (tid == 0) {
+            if (s_cnt) atomicAdd(&cov_out[qi], (unsigned long long)s_cnt);
+            __threadfence();
+            if (atomicAdd(&ticket[qi], 1u) == (uint32_t)windows - 1u) { // the set's last window
+                __threadfence();
+                const unsigned long long cov =
+                    __hip_atomic_load(&cov_out[qi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                est_out[qi] = __dadd_rn(first_term(cov, Gamma, T), est_out[qi]);
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Lists the parked sets, heavy = {count, set, set, ...}, and clears their cov (one workgroup).
+__global__ __launch_bounds__(EST_BLOCK) void k_est_list(int32_t Q, unsigned long long *__restrict__ cov_out,
+                                                        uint32_t *__restrict__ heavy)
+{
+    __shared__ int32_t s_scan[EST_BLOCK / 64 + 1];
+    uint32_t count = 0;
+    for (int32_t q0 = 0; q0 < Q; q0 += EST_BLOCK) {
+        const int32_t q = q0 + (int32_t)threadIdx.x;
+        const bool p = q < Q && cov_out[q] == EST_PARKED;
+        int tot;
+        const int ex = block_excl_scan<EST_BLOCK, int>(p ? 1 : 0, s_scan, &tot);
+        if (p) {
+            heavy[1 + count + (uint32_t)ex] = (uint32_t)q;
+            cov_out[q] = 0ull;
+        }
+        count += (uint32_t)tot;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) heavy[0] = count;
+}
+
+// ---------------------------------------------------------------------------------------
 // Greedy (Alg. 3) with exact marginal coverage.  delta[v] = #{ j in H(v) : j not covered }.
 // Each round: k_greedy_argmax picks the node of largest gain fl(fl(delta * Gamma) / T) + q_v
 // (Eq. margin; smallest id on ties); k_greedy_cover sets the covered bits of H(v*) and lowers
@@ -643,49 +982,162 @@ static unsigned gridq(uint64_t items, int block, int per_cu = 8)
     return (unsigned)(g > 0 ? g : 1);
 }
 
+// Sixteen bytes of flags in pinned host memory that a kernel writes and the host reads after a
+// synchronisation (a copy from the device and the fill before it had taken 20 us of a small
+// estimate): one page for the process, a call holds one of its places.  ptr is null when every
+// place is taken or the page could not be had; the caller then keeps its flags on the device.
+namespace {
+class HostFlags {
+    static constexpr int PLACES = 64;
+    struct Page {
+        std::mutex mu;
+        char *base = nullptr;
+        bool tried = false;
+        bool used[PLACES] = {};
+    };
+    static Page &page()
+    {
+        static Page p;
+        return p;
+    }
+    int at = -1;
+
+public:
+    EstFlags *host = nullptr, *dev = nullptr;
+    HostFlags()
+    {
+        Page &p = page();
+        std::lock_guard<std::mutex> g(p.mu);
+        if (!p.tried) {
+            p.tried = true;
+            void *m = nullptr;
+            if (hipHostMalloc(&m, 64 * PLACES, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+                p.base = static_cast<char *>(m);
+            (void)hipGetLastError();
+        }
+        if (!p.base) return;
+        for (int i = 0; i < PLACES && at < 0; ++i)
+            if (!p.used[i]) at = i;
+        if (at < 0) return;
+        host = reinterpret_cast<EstFlags *>(p.base + 64 * at);
+        void *d = nullptr;
+        if (hipHostGetDevicePointer(&d, host, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            host = nullptr;
+            at = -1;
+            return;
+        }
+        dev = static_cast<EstFlags *>(d);
+        p.used[at] = true;
+        *host = EstFlags{};
+    }
+    HostFlags(const HostFlags &) = delete;
+    HostFlags &operator=(const HostFlags &) = delete;
+    ~HostFlags()
+    {
+        if (at < 0) return;
+        Page &p = page();
+        std::lock_guard<std::mutex> g(p.mu);
+        p.used[at] = false;
+    }
+};
+} // namespace
+
+void estimate_light(const Sketch &sk, int32_t nq, bool check, const int64_t *set_ptr, const int32_t *set_nodes,
+                    unsigned long long *cov, double *est, uint32_t *ticket, EstFlags *flags, hipStream_t s)
+{
+    if (nq <= 0) return;
+    if (check && nq > EST_BLOCK) throw Error{SKIS_EHIP, "internal error: too many sets for a checked estimate"};
+    hipLaunchKernelGGL(k_est_light, dim3((unsigned)nq), dim3(EST_BLOCK), 0, s, check ? nq : 0, set_ptr, set_nodes, sk.n,
+                       sk.T, sk.est_scale(), sk.est_q(), sk.node_ptr.ptr, sk.node_samples.ptr, cov, est, ticket, flags);
+    SKIS_HIP_TRY(hipGetLastError());
+}
+
+void estimate_split(const Sketch &sk, int32_t nq, const int64_t *set_ptr, const int32_t *set_nodes,
+                    unsigned long long *cov, double *est, uint32_t *heavy, uint32_t *ticket, hipStream_t s)
+{
+    if (nq <= 0 || sk.T == 0) return;
+    hipLaunchKernelGGL(k_est_list, dim3(1), dim3(EST_BLOCK), 0, s, nq, cov, heavy);
+    // windows of whole words, the last one ragged
+    uint64_t wbits = (sk.T + SPLIT_WINDOWS - 1) / SPLIT_WINDOWS;
+    wbits = std::min<uint64_t>(std::max<uint64_t>((wbits + 31) / 32 * 32, SPLIT_MIN), SPLIT_BITS);
+    const uint64_t windows = (sk.T + wbits - 1) / wbits;
+    const uint64_t grid = std::min<uint64_t>((uint64_t)device_cu_count() * 2, (uint64_t)nq * windows);
+    hipLaunchKernelGGL(k_est_split, dim3((unsigned)grid), dim3(EST_BLOCK), 0, s, (int32_t)windows, (int32_t)wbits,
+                       set_ptr, set_nodes, sk.T, sk.est_scale(), sk.node_ptr.ptr, sk.node_samples.ptr, heavy, cov, est,
+                       ticket);
+    SKIS_HIP_TRY(hipGetLastError());
+}
+
 void estimate_batch(const Sketch &sk, QueryScratch &qs, int32_t Q, const int64_t *set_ptr, const int32_t *set_nodes,
-                    uint64_t *cov, double *est, hipStream_t s)
+                    uint64_t *cov_out, double *est, hipStream_t s)
 {
     Arena &arena = const_cast<Arena &>(sk.arena);
-    // set sizes on the host: argument checks and the list of sets above one LDS chunk
-    std::vector<int64_t> hptr((size_t)Q + 1);
-    SKIS_HIP_TRY(hipMemcpyAsync(hptr.data(), set_ptr, sizeof(int64_t) * ((size_t)Q + 1), hipMemcpyDeviceToHost, s));
-    SKIS_HIP_TRY(hipStreamSynchronize(s));
-    std::vector<int64_t> large;
-    for (int32_t i = 0; i < Q; ++i) {
-        const int64_t k = hptr[i + 1] - hptr[i];
-        if (k < 0 || hptr[i] < 0) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing from 0"};
-        if (k > EST_MAX_SET) large.push_back(i);
+    unsigned long long *const cov = reinterpret_cast<unsigned long long *>(cov_out);
+    // set sizes on the host: argument checks and the list of sets above one LDS chunk.  Up to
+    // EST_BLOCK sets are checked by the kernel instead, and read here only if one is that large
+    std::vector<int64_t> hptr, large;
+    auto read_sets = [&]() {
+        hptr.resize((size_t)Q + 1);
+        SKIS_HIP_TRY(hipMemcpyAsync(hptr.data(), set_ptr, sizeof(int64_t) * ((size_t)Q + 1), hipMemcpyDeviceToHost, s));
+        SKIS_HIP_TRY(hipStreamSynchronize(s));
+        for (int32_t i = 0; i < Q; ++i) {
+            const int64_t k = hptr[i + 1] - hptr[i];
+            if (k < 0 || hptr[i] < 0) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing from 0"};
+            if (k > EST_MAX_SET) large.push_back(i);
+        }
+        if (hptr[Q] > 0 && !set_nodes) throw Error{SKIS_EINVAL, "set_nodes must not be NULL"};
+    };
+    const bool device_check = Q <= EST_BLOCK && set_nodes;
+    if (!device_check) read_sets();
+    const size_t need = 2 * (size_t)Q + 1; // heavy = {count, sets}, tickets
+    if (qs.split.count < need) qs.split.alloc(arena, need);
+    uint32_t *const heavy = qs.split.ptr, *const ticket = qs.split.ptr + Q + 1;
+    EstFlags fl{};
+    {
+        HostFlags hf;
+        EstFlags *dev = hf.dev;
+        if (!dev) {
+            if (!qs.flags.ptr) qs.flags.alloc(arena, 1);
+            dev = qs.flags.ptr;
+            hipLaunchKernelGGL(k_fill_q<int>, dim3(1), dim3(64), 0, s, (uint64_t)(sizeof(EstFlags) / sizeof(int)),
+                               reinterpret_cast<int *>(dev), 0);
+        }
+        try {
+            estimate_light(sk, Q, device_check, set_ptr, set_nodes, cov, est, ticket, dev, s);
+            if (!hf.dev) SKIS_HIP_TRY(hipMemcpyAsync(&fl, dev, sizeof(fl), hipMemcpyDeviceToHost, s));
+            SKIS_HIP_TRY(hipStreamSynchronize(s));
+        } catch (...) {
+            (void)hipStreamSynchronize(s); // nothing may write the flags' place after it is given back
+            throw;
+        }
+        if (hf.dev) {
+            const volatile EstFlags *h = hf.host;
+            fl.ptr = h->ptr;
+            fl.node = h->node;
+            fl.large = h->large;
+            fl.parked = h->parked;
+        }
     }
-    if (hptr[Q] > 0 && !set_nodes) throw Error{SKIS_EINVAL, "set_nodes must not be NULL"};
-
-    const uint64_t wordsT = (sk.T + 31) / 32;
-    const uint64_t per = wordsT ? wordsT : 1;
-    // bitmaps for up to `batch` queries at a time, about 256 MiB
-    uint64_t batch = (256ull << 20) / (per * 4);
-    if (batch < 1) batch = 1;
-    if (batch > 4096) batch = 4096;
-    if (batch > (uint64_t)Q) batch = (uint64_t)Q;
-    if (qs.bitmap_words < batch * per) {
-        qs.bitmaps.alloc(arena, batch * per);
-        qs.bitmap_words = batch * per;
-        hipLaunchKernelGGL(k_fill_q<uint32_t>, dim3(gridq(batch * per, 256)), dim3(256), 0, s, batch * per,
-                           qs.bitmaps.ptr, 0u);
-        SKIS_HIP_TRY(hipGetLastError());
-    }
-    if (!qs.err.ptr) qs.err.alloc(arena, 1);
-    hipLaunchKernelGGL(k_fill_q<int>, dim3(1), dim3(64), 0, s, (uint64_t)1, qs.err.ptr, 0);
-    for (int64_t q0 = 0; q0 < Q; q0 += (int64_t)batch) {
-        const int64_t nq = (Q - q0) < (int64_t)batch ? (Q - q0) : (int64_t)batch;
-        hipLaunchKernelGGL(k_estimate<false>, dim3((unsigned)nq), dim3(EST_BLOCK), 0, s, (const int64_t *)nullptr, q0,
-                           set_ptr, set_nodes, sk.n, sk.T, sk.est_scale(), sk.est_q(), sk.node_ptr.ptr, sk.node_samples.ptr,
-                           qs.bitmaps.ptr, per, (uint32_t *)nullptr, (uint64_t)0,
-                           reinterpret_cast<unsigned long long *>(cov), est, qs.err.ptr);
-        SKIS_HIP_TRY(hipGetLastError());
-    }
-    if (!large.empty()) {
+    if (fl.ptr) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing from 0"};
+    if (fl.node) throw Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
+    if (fl.parked) estimate_split(sk, Q, set_ptr, set_nodes, cov, est, heavy, ticket, s);
+    if (fl.large) {
+        if (hptr.empty()) read_sets();
+        if (!qs.err.ptr) qs.err.alloc(arena, 1);
+        hipLaunchKernelGGL(k_fill_q<int>, dim3(1), dim3(64), 0, s, (uint64_t)1, qs.err.ptr, 0);
+        const uint64_t per = std::max<uint64_t>((sk.T + 31) / 32, 1);
         const uint64_t wordsN = ((uint64_t)sk.n + 31) / 32;
-        const uint64_t group = std::min<uint64_t>(std::min<uint64_t>(batch, 64), large.size());
+        // bitmaps for up to 64 sets at a time, about 256 MiB
+        uint64_t group = std::max<uint64_t>((256ull << 20) / (per * 4), 1);
+        group = std::min<uint64_t>(std::min<uint64_t>(group, 64), large.size());
+        if (qs.bitmap_words < group * per) {
+            qs.bitmaps.alloc(arena, group * per);
+            qs.bitmap_words = group * per;
+            hipLaunchKernelGGL(k_fill_q<uint32_t>, dim3(gridq(group * per, 256)), dim3(256), 0, s, group * per,
+                               qs.bitmaps.ptr, 0u);
+            SKIS_HIP_TRY(hipGetLastError());
+        }
         DevBuf<int64_t> qlist;
         DevBuf<uint32_t> nodebits;
         qlist.alloc(arena, large.size());
@@ -693,58 +1145,40 @@ void estimate_batch(const Sketch &sk, QueryScratch &qs, int32_t Q, const int64_t
         SKIS_HIP_TRY(hipMemcpyAsync(qlist.ptr, large.data(), sizeof(int64_t) * large.size(), hipMemcpyHostToDevice, s));
         hipLaunchKernelGGL(k_fill_q<uint32_t>, dim3(gridq(group * wordsN, 256)), dim3(256), 0, s, group * wordsN,
                            nodebits.ptr, 0u);
-        for (uint64_t g0 = 0; g0 < large.size(); g0 += group) {
-            const uint64_t ng = std::min<uint64_t>(group, large.size() - g0);
-            hipLaunchKernelGGL(k_estimate<true>, dim3((unsigned)ng), dim3(EST_BLOCK), 0, s,
-                               (const int64_t *)qlist.ptr, (int64_t)g0, set_ptr, set_nodes, sk.n, sk.T, sk.est_scale(),
-                               sk.est_q(), sk.node_ptr.ptr, sk.node_samples.ptr, qs.bitmaps.ptr, per, nodebits.ptr,
-                               wordsN, reinterpret_cast<unsigned long long *>(cov), est, qs.err.ptr);
-            SKIS_HIP_TRY(hipGetLastError());
+        for (uint64_t g0 = 0; g0 < large.size(); g0 += group)
+            estimate_launch_large(sk, qlist.ptr, (int64_t)g0, (int32_t)std::min<uint64_t>(group, large.size() - g0),
+                                  set_ptr, set_nodes, qs.bitmaps.ptr, per, nodebits.ptr, cov, est, qs.err.ptr, s);
+        int herr = 0;
+        SKIS_HIP_TRY(hipMemcpyAsync(&herr, qs.err.ptr, sizeof(int), hipMemcpyDeviceToHost, s));
+        SKIS_HIP_TRY(hipStreamSynchronize(s));
+        if (herr) {
+            // a workgroup that stopped early may have left bits set: clear all scratch
+            hipLaunchKernelGGL(k_fill_q<uint32_t>, dim3(gridq(qs.bitmap_words, 256)), dim3(256), 0, s, qs.bitmap_words,
+                               qs.bitmaps.ptr, 0u);
+            SKIS_HIP_TRY(hipStreamSynchronize(s));
         }
+        if (herr & 1) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing"};
+        if (herr & 4) throw Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
+    } else if (fl.parked) {
         SKIS_HIP_TRY(hipStreamSynchronize(s));
     }
-    int herr = 0;
-    SKIS_HIP_TRY(hipMemcpyAsync(&herr, qs.err.ptr, sizeof(int), hipMemcpyDeviceToHost, s));
-    SKIS_HIP_TRY(hipStreamSynchronize(s));
-    if (herr) {
-        // a workgroup that stopped early may have left bits set: clear all scratch
-        hipLaunchKernelGGL(k_fill_q<uint32_t>, dim3(gridq(qs.bitmap_words, 256)), dim3(256), 0, s, qs.bitmap_words,
-                           qs.bitmaps.ptr, 0u);
-        SKIS_HIP_TRY(hipStreamSynchronize(s));
-    }
-    if (herr & 1) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing"};
-    if (herr & 4) throw Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
 }
 
-void estimate_launch(const Sketch &sk, int32_t nq, const int64_t *set_ptr, const int32_t *set_nodes,
+void estimate_launch(const Sketch &sk, int32_t nq, bool light_only, const int64_t *set_ptr, const int32_t *set_nodes,
                      const int64_t *large, int32_t nlarge, uint32_t *bitmaps, uint64_t bitmap_words,
-                     uint32_t *nodebits, unsigned long long *cov, double *est, int *err, hipStream_t s)
+                     uint32_t *nodebits, unsigned long long *cov, double *est, int *err, EstFlags *flags, hipStream_t s)
 {
-    const uint64_t per = bitmap_words;
-    if (nq > 0) {
+    if (light_only) {
+        estimate_light(sk, nq, false, set_ptr, set_nodes, cov, est, nullptr, flags, s);
+    } else if (nq > 0) {
+        // one kernel for all: a second one for the parked sets would add its latency to the batch's
+        // (a burst of 1024 Zipf sets took 1.7 ms that way, 1.25 ms this way)
         hipLaunchKernelGGL(k_estimate<false>, dim3((unsigned)nq), dim3(EST_BLOCK), 0, s, (const int64_t *)nullptr,
                            (int64_t)0, set_ptr, set_nodes, sk.n, sk.T, sk.est_scale(), sk.est_q(), sk.node_ptr.ptr,
-                           sk.node_samples.ptr, bitmaps, per, (uint32_t *)nullptr, (uint64_t)0, cov, est, err);
+                           sk.node_samples.ptr, bitmaps, bitmap_words, (uint32_t *)nullptr, (uint64_t)0, cov, est, err);
         SKIS_HIP_TRY(hipGetLastError());
     }
-    if (nlarge > 0) {
-        const uint64_t wordsN = ((uint64_t)sk.n + 31) / 32;
-        hipLaunchKernelGGL(k_estimate<true>, dim3((unsigned)nlarge), dim3(EST_BLOCK), 0, s, large, (int64_t)0,
-                           set_ptr, set_nodes, sk.n, sk.T, sk.est_scale(), sk.est_q(), sk.node_ptr.ptr, sk.node_samples.ptr,
-                           bitmaps, per, nodebits, wordsN, cov, est, err);
-        SKIS_HIP_TRY(hipGetLastError());
-    }
-}
-
-void estimate_launch_small(const Sketch &sk, int64_t q0, int32_t nq, const int64_t *set_ptr,
-                           const int32_t *set_nodes, uint32_t *bitmaps, uint64_t bitmap_words,
-                           unsigned long long *cov, double *est, int *err, hipStream_t s)
-{
-    if (nq <= 0) return;
-    hipLaunchKernelGGL(k_estimate<false>, dim3((unsigned)nq), dim3(EST_BLOCK), 0, s, (const int64_t *)nullptr, q0,
-                       set_ptr, set_nodes, sk.n, sk.T, sk.est_scale(), sk.est_q(), sk.node_ptr.ptr, sk.node_samples.ptr,
-                       bitmaps, bitmap_words, (uint32_t *)nullptr, (uint64_t)0, cov, est, err);
-    SKIS_HIP_TRY(hipGetLastError());
+    estimate_launch_large(sk, large, 0, nlarge, set_ptr, set_nodes, bitmaps, bitmap_words, nodebits, cov, est, err, s);
 }
 
 void estimate_launch_large(const Sketch &sk, const int64_t *qlist, int64_t g0, int32_t ng, const int64_t *set_ptr,

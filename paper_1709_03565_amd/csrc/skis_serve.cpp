@@ -44,6 +44,9 @@ struct Pending {
 // sketch holds about 60 thousand, its top hub 3 million).
 constexpr uint64_t HEAVY_WORK = 1ull << 18;
 
+// a slot's error words: k_estimate's at 0, k_est_light's flags after it
+constexpr int ERR_FLAGS = 4, ERR_WORDS = ERR_FLAGS + (int)(sizeof(skis::EstFlags) / sizeof(int));
+
 struct Done {
     uint64_t cov;
     double est;
@@ -131,8 +134,11 @@ void skis_server::launch(Slot &sl)
     const int32_t nq = (int32_t)sl.batch.size();
     int64_t off = 0;
     int32_t nl = 0;
+    bool light = true; // no set's lists hold more than the LDS hash takes
     for (int32_t i = 0; i < nq; ++i) {
         const auto &v = sl.batch[i].nodes;
+        light = light && !node_ptr.empty() && sl.batch[i].work <= (uint64_t)skis::EST_HASH_MAX &&
+                (int64_t)v.size() <= skis::EST_MAX_SET;
         sl.h_ptr.ptr[i] = off;
         if (!v.empty()) std::memcpy(sl.h_nodes.ptr + off, v.data(), sizeof(int32_t) * v.size());
         off += (int64_t)v.size();
@@ -147,22 +153,24 @@ void skis_server::launch(Slot &sl)
     if (nl > 0)
         SKIS_HIP_TRY(hipMemcpyAsync(sl.d_large.ptr, sl.h_large.ptr, sizeof(int64_t) * (size_t)nl,
                                     hipMemcpyHostToDevice, s));
-    skis::estimate_launch(k, nq, sl.d_ptr.ptr, sl.d_nodes.ptr, sl.d_large.ptr, nl, sl.bitmaps.ptr, wordsT,
-                          sl.nodebits.ptr, sl.d_cov.ptr, sl.d_est.ptr, sl.d_err.ptr, s);
+    skis::estimate_launch(k, nq, light, sl.d_ptr.ptr, sl.d_nodes.ptr, sl.d_large.ptr, nl, sl.bitmaps.ptr, wordsT,
+                          sl.nodebits.ptr, sl.d_cov.ptr, sl.d_est.ptr, sl.d_err.ptr,
+                          reinterpret_cast<skis::EstFlags *>(sl.d_err.ptr + ERR_FLAGS), s);
     SKIS_HIP_TRY(hipMemcpyAsync(sl.h_cov.ptr, sl.d_cov.ptr, sizeof(unsigned long long) * (size_t)nq,
                                 hipMemcpyDeviceToHost, s));
     SKIS_HIP_TRY(hipMemcpyAsync(sl.h_est.ptr, sl.d_est.ptr, sizeof(double) * (size_t)nq, hipMemcpyDeviceToHost, s));
-    SKIS_HIP_TRY(hipMemcpyAsync(sl.h_err.ptr, sl.d_err.ptr, sizeof(int), hipMemcpyDeviceToHost, s));
+    SKIS_HIP_TRY(hipMemcpyAsync(sl.h_err.ptr, sl.d_err.ptr, sizeof(int) * ERR_WORDS, hipMemcpyDeviceToHost, s));
     SKIS_HIP_TRY(hipEventRecord(sl.done, s));
     sl.busy = true;
 }
 
 void skis_server::complete(Slot &sl)
 {
-    if (*sl.h_err.ptr) {
+    const skis::EstFlags &fl = *reinterpret_cast<const skis::EstFlags *>(sl.h_err.ptr + ERR_FLAGS);
+    if (sl.h_err.ptr[0] || fl.ptr || fl.node) {
         // ids were checked at submission, so this is an internal fault: scratch may hold bits
-        throw skis::Error{SKIS_EHIP, "internal error in the estimate kernel (flags " + std::to_string(*sl.h_err.ptr) +
-                                         ")"};
+        throw skis::Error{SKIS_EHIP, "internal error in the estimate kernel (flags " +
+                                         std::to_string(sl.h_err.ptr[0] | fl.ptr | 2 * fl.node) + ")"};
     }
     const auto now = Clock::now();
     const size_t nq = sl.batch.size();
@@ -373,19 +381,19 @@ int skis_server_create(const skis_sketch *sk, const skis_server_options *opt_in,
             s.h_large.alloc(opt.max_large_sets);
             s.h_cov.alloc(opt.max_batch_queries);
             s.h_est.alloc(opt.max_batch_queries);
-            s.h_err.alloc(1);
+            s.h_err.alloc(ERR_WORDS);
             s.d_ptr.alloc(sv->arena, opt.max_batch_queries + 1);
             s.d_nodes.alloc(sv->arena, opt.max_batch_entries);
             s.d_large.alloc(sv->arena, opt.max_large_sets);
             s.d_cov.alloc(sv->arena, opt.max_batch_queries);
             s.d_est.alloc(sv->arena, opt.max_batch_queries);
-            s.d_err.alloc(sv->arena, 1);
+            s.d_err.alloc(sv->arena, ERR_WORDS);
             s.bitmaps.alloc(sv->arena, nb * sv->wordsT);
             s.nodebits.alloc(sv->arena, (uint64_t)opt.max_large_sets * sv->wordsN);
             SKIS_HIP_TRY(hipDeviceSynchronize());
             skis::fill_u32(s.bitmaps.ptr, nb * sv->wordsT, s.stream);
             skis::fill_u32(s.nodebits.ptr, (uint64_t)opt.max_large_sets * sv->wordsN, s.stream);
-            skis::fill_u32(reinterpret_cast<uint32_t *>(s.d_err.ptr), 1, s.stream);
+            skis::fill_u32(reinterpret_cast<uint32_t *>(s.d_err.ptr), ERR_WORDS, s.stream);
             SKIS_HIP_TRY(hipStreamSynchronize(s.stream));
         }
         skis_server *raw = sv.get();

@@ -25,14 +25,30 @@ struct EstFlags {
 constexpr int GREEDY_HOT = 2048;  // hot nodes decremented in LDS
 
 struct GreedyState {
-    unsigned done;              // blocks of k_greedy_argmax that have finished
     int32_t vstar;              // this round's pick (-1: none left)
     unsigned shrunk;            // a heavy round has cut the lists down (they are in the work copy)
     int32_t cur;                // which of the two delta buffers holds the current counts
     unsigned long long dstar;   // delta of this round's pick: the samples it newly covers
     unsigned long long cov;     // coverage of the picks so far
     double est;
+    unsigned flipped;           // the round's argmax has switched buffers: the spare one is to be cleared
+    unsigned pad[2];
 };
+
+// A tile of GREEDY_TILE nodes keeps its best node as of its last scan and the second gain.  Delta
+// only falls, so g2 bounds the gains of all its other nodes from above ever after.
+constexpr int GREEDY_TILE = 2048;
+struct __align__(8) GreedyTile {
+    double g;   // its gain
+    double g2;  // the largest gain of the others, -1: none
+    int32_t v;  // the node, -1: every node of the tile is chosen
+    int32_t d;  // its delta
+};
+constexpr int GREEDY_BLOCK = 1024; // the pick is one workgroup's
+constexpr int GREEDY_BIG = 512;    // in the one-workgroup form, a sample above this is uncovered by all threads
+// Sketches whose greedy runs in one workgroup (no launches inside the k rounds).
+constexpr int GREEDY_SMALL_TILES = 2048;
+constexpr uint64_t GREEDY_SMALL_ENTRIES = 1ull << 19;
 
 // One recount work item: entries [p0, p0 + len) of node v's list.
 struct RecountItem {

@@ -665,126 +665,345 @@ __device__ __forceinline__ void wave_best(double &g, int32_t &v)
     }
 }
 
-// Workgroup-wide winner of 256 threads; every thread gets it.
-__device__ __forceinline__ void block_best(double &g, int32_t &v, double *sg, int32_t *sv)
+// Best of nodes [v0, v0 + 512) below n by one wave (every lane gets it), all loads issued first.
+// LIVE: delta is lowered by atomics of the same launch, so it is read past the L1 cache.
+constexpr int SCAN_PART = 512;
+constexpr GreedyTile NO_TILE = {-1.0, -1.0, -1, 0};
+static_assert(GREEDY_TILE % SCAN_PART == 0, "a tile is scanned in whole parts");
+
+template <bool LIVE>
+__device__ __forceinline__ GreedyTile scan_part(int64_t v0, int32_t n, uint64_t T, double Gamma,
+                                                const int32_t *__restrict__ delta, const double *__restrict__ qv,
+                                                const uint8_t *__restrict__ chosen)
 {
+    constexpr int U = SCAN_PART / 64;
+    const int lane = threadIdx.x & 63;
+    double bg = -1.0, b2 = -1.0; // the lane's best and second
+    int32_t bv = -1, bd = 0;
+    int32_t d[U];
+    double q[U];
+    uint8_t c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t v = v0 + u * 64 + lane;
+        const int64_t vc = v < n ? v : n - 1;
+        d[u] = LIVE ? __hip_atomic_load(&delta[vc], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : delta[vc];
+        q[u] = qv ? qv[vc] : 0.0;
+        c[u] = v < n ? chosen[vc] : (uint8_t)1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (c[u]) continue;
+        const int32_t v = (int32_t)(v0 + u * 64 + lane);
+        const double g = gain_of(d[u], T, Gamma, q[u]);
+        if (better(g, v, bg, bv)) {
+            b2 = bg;
+            bg = g;
+            bv = v;
+            bd = d[u];
+        } else {
+            b2 = g > b2 ? g : b2;
+        }
+    }
+    const int32_t mine = bv, md = bd;
+    const double mg = bg;
+    wave_best(bg, bv);
+    // the winner's delta from the lane that held it (the lanes' nodes differ)
+    const unsigned long long m = __ballot(bv >= 0 && mine == bv);
+    if (bv >= 0 && mine != bv) b2 = mg; // another lane's best is the part's: this lane's is a second
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) {
+        const double o = __shfl_xor(b2, s, 64);
+        b2 = o > b2 ? o : b2;
+    }
+    GreedyTile b;
+    b.g = bg;
+    b.g2 = b2;
+    b.v = bv;
+    b.d = m ? (int32_t)lane_value((uint32_t)md, __ffsll(m) - 1) : 0;
+    return b;
+}
+
+// e into the running best of a tile.
+__device__ __forceinline__ void merge_part(GreedyTile &best, const GreedyTile &e)
+{
+    if (e.v >= 0 && better(e.g, e.v, best.g, best.v)) {
+        const double s = best.v >= 0 ? best.g : -1.0;
+        const double g2 = e.g2 > s ? e.g2 : s;
+        best = e;
+        best.g2 = g2;
+    } else if (e.v >= 0) {
+        best.g2 = e.g > best.g2 ? e.g : best.g2;
+    }
+}
+
+// The pick of a round by one workgroup of GREEDY_BLOCK threads (every thread gets it; v = -1: no
+// node left).  The gains of the tiles' cached nodes, as of now, bound the pick from below; only a
+// tile whose node has changed and whose second gain, the bound of its other nodes from above,
+// reaches that is scanned again (a lazy greedy by tiles: delta only falls; by the first gain alone
+// some thirty tiles a round were scanned, the hubs' deltas falling in every round).  A scan of all n nodes a round had read 13
+// bytes a node: 33 us a round at 4M nodes and 2^25 samples, now 20 (15 without a tile to scan).
+constexpr int PICK_TILES = 4; // tiles a thread looks at together, their loads issued first
+
+struct PickShared {
+    double g[GREEDY_BLOCK / 64];
+    int32_t v[GREEDY_BLOCK / 64], d[GREEDY_BLOCK / 64];
+    int32_t dirty[GREEDY_BLOCK * PICK_TILES];
+    GreedyTile part[64 * (GREEDY_TILE / SCAN_PART)];
+    int ndirty;
+};
+
+// (g, v, d) of the workgroup's best, in every thread; two barriers.
+__device__ __forceinline__ void pick_reduce(double &g, int32_t &v, int32_t &d, PickShared &sh)
+{
+    const int32_t mine = v, md = d;
     wave_best(g, v);
+    const int wave = threadIdx.x >> 6;
+    if (v >= 0 && mine == v) sh.d[wave] = md; // one lane of the wave holds it
     if ((threadIdx.x & 63) == 0) {
-        sg[threadIdx.x >> 6] = g;
-        sv[threadIdx.x >> 6] = v;
+        sh.g[wave] = g;
+        sh.v[wave] = v;
     }
     __syncthreads();
-    g = sg[0];
-    v = sv[0];
-#pragma unroll
-    for (int w = 1; w < 4; ++w)
-        if (sv[w] >= 0 && better(sg[w], sv[w], g, v)) {
-            g = sg[w];
-            v = sv[w];
+    v = -1;
+    for (int w = 0; w < GREEDY_BLOCK / 64; ++w)
+        if (sh.v[w] >= 0 && better(sh.g[w], sh.v[w], g, v)) {
+            g = sh.g[w];
+            v = sh.v[w];
+            d = sh.d[w];
         }
     __syncthreads();
 }
 
-// Each thread scans ARGMAX_PER nodes of its workgroup's tile, all loads issued before the
-// gains are formed; the last workgroup to finish reduces the per-workgroup winners.
-constexpr int ARGMAX_PER = 16;
-
-// delta lives in two buffers: a round that recounts writes the spare one (kept zero), and
-// the next argmax switches to it and zeroes the one it leaves as it scans.
-__global__ __launch_bounds__(256) void k_greedy_argmax(int32_t n, int round, uint64_t T, double Gamma,
-                                                       int32_t *__restrict__ delta0, int32_t *__restrict__ delta1,
-                                                       const double *__restrict__ qv,
-                                                       uint8_t *__restrict__ chosen, double *__restrict__ part_g,
-                                                       int32_t *__restrict__ part_v, GreedyState *__restrict__ st,
-                                                       int32_t *__restrict__ seeds,
-                                                       unsigned long long *__restrict__ marg)
+template <bool LIVE>
+__device__ __forceinline__ GreedyTile pick_node(GreedyTile *tiles, int32_t ntiles, int32_t n, uint64_t T, double Gamma,
+                                                const int32_t *__restrict__ delta, const double *__restrict__ qv,
+                                                const uint8_t *chosen, PickShared &sh)
 {
-    __shared__ double sg[4];
-    __shared__ int32_t sv[4];
-    __shared__ bool last;
-    const bool recounted = heavy_round(st, T); // the previous round (st is rewritten by the last block)
-    const int cur = st->cur ^ (recounted ? 1 : 0);
-    const int32_t *delta = cur ? delta1 : delta0;
-    int32_t *spare = cur ? delta0 : delta1;
-    double bg = 0.0;
-    int32_t bv = -1;
-    for (int64_t v0 = (int64_t)blockIdx.x * 256 * ARGMAX_PER + threadIdx.x; v0 < n;
-         v0 += (int64_t)gridDim.x * 256 * ARGMAX_PER) {
-        int32_t d[ARGMAX_PER];
-        double q[ARGMAX_PER];
-        uint8_t c[ARGMAX_PER];
+    constexpr int PARTS = GREEDY_TILE / SCAN_PART;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int32_t BATCH = GREEDY_BLOCK * PICK_TILES;
+    GreedyTile c[PICK_TILES];
+    int32_t d[PICK_TILES];
+    bool gone[PICK_TILES];
+    double q[PICK_TILES];
+    auto look = [&](int32_t t0) { // tiles t0 + u * GREEDY_BLOCK + tid: the cached node, its delta now
 #pragma unroll
-        for (int u = 0; u < ARGMAX_PER; ++u) {
-            const int64_t v = v0 + (int64_t)u * 256;
-            const bool in = v < n;
-            c[u] = in ? chosen[v] : (uint8_t)1;
-            d[u] = in ? delta[v] : 0;
-            q[u] = in && qv ? qv[v] : 0.0;
-            if (recounted && in) spare[v] = 0;
+        for (int u = 0; u < PICK_TILES; ++u) c[u] = tiles[min(t0 + u * GREEDY_BLOCK + tid, ntiles - 1)];
+#pragma unroll
+        for (int u = 0; u < PICK_TILES; ++u) {
+            const int32_t v = max(c[u].v, 0);
+            gone[u] = c[u].v < 0 || chosen[v];
+            d[u] = LIVE ? __hip_atomic_load(&delta[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : delta[v];
+            q[u] = qv ? qv[v] : 0.0;
         }
+    };
+    // the lower bound: the cached nodes' gains now
+    double bg = 0.0;
+    int32_t bv = -1, bd = 0;
+    for (int32_t t0 = 0; t0 < ntiles; t0 += BATCH) {
+        look(t0);
 #pragma unroll
-        for (int u = 0; u < ARGMAX_PER; ++u) {
-            if (c[u]) continue;
-            const int32_t v = (int32_t)(v0 + (int64_t)u * 256);
-            const double g = gain_of(d[u], T, Gamma, q[u]);
-            if (better(g, v, bg, bv)) {
+        for (int u = 0; u < PICK_TILES; ++u) {
+            if (t0 + u * GREEDY_BLOCK + tid >= ntiles || gone[u]) continue;
+            const double g = d[u] == c[u].d ? c[u].g : gain_of(d[u], T, Gamma, q[u]);
+            if (better(g, c[u].v, bg, bv)) {
                 bg = g;
-                bv = v;
+                bv = c[u].v;
+                bd = d[u];
             }
         }
     }
-    block_best(bg, bv, sg, sv);
-    if (threadIdx.x == 0) {
-        part_g[blockIdx.x] = bg;
-        part_v[blockIdx.x] = bv;
-        __threadfence();
-        last = atomicAdd(&st->done, 1u) == gridDim.x - 1;
-    }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
-    bg = 0.0;
-    bv = -1;
-    for (unsigned b = threadIdx.x; b < gridDim.x; b += 256) {
-        const int32_t pv = __hip_atomic_load(&part_v[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const double pg = __longlong_as_double((long long)__hip_atomic_load(
-            reinterpret_cast<unsigned long long *>(&part_g[b]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        if (pv >= 0 && better(pg, pv, bg, bv)) {
-            bg = pg;
-            bv = pv;
+    pick_reduce(bg, bv, bd, sh);
+    const double low = bv >= 0 ? bg : 0.0; // gains are not negative
+    // scan the changed tiles that may hold a better one
+    for (int32_t t0 = 0; t0 < ntiles; t0 += BATCH) {
+        if (tid == 0) sh.ndirty = 0;
+        __syncthreads();
+        if (ntiles > BATCH) look(t0); // else the registers still hold them
+#pragma unroll
+        for (int u = 0; u < PICK_TILES; ++u) {
+            const int32_t t = t0 + u * GREEDY_BLOCK + tid;
+            if (t < ntiles && c[u].v >= 0 && (gone[u] || d[u] != c[u].d) && c[u].g2 >= low)
+                sh.dirty[atomicAdd(&sh.ndirty, 1)] = t;
+        }
+        __syncthreads();
+        const int nd = sh.ndirty;
+        for (int b0 = 0; b0 < nd; b0 += 64) {
+            const int nb = min(nd - b0, 64);
+            for (int i = wave; i < nb * PARTS; i += GREEDY_BLOCK / 64) {
+                const int64_t v0 = (int64_t)sh.dirty[b0 + i / PARTS] * GREEDY_TILE + (int64_t)(i % PARTS) * SCAN_PART;
+                GreedyTile e = NO_TILE;
+                if (v0 < n) e = scan_part<LIVE>(v0, n, T, Gamma, delta, qv, chosen);
+                if (lane == 0) sh.part[i] = e;
+            }
+            __syncthreads();
+            if (tid < nb) {
+                GreedyTile best = sh.part[tid * PARTS];
+                for (int k = 1; k < PARTS; ++k) merge_part(best, sh.part[tid * PARTS + k]);
+                tiles[sh.dirty[b0 + tid]] = best;
+                if (best.v >= 0 && better(best.g, best.v, bg, bv)) {
+                    bg = best.g;
+                    bv = best.v;
+                    bd = best.d;
+                }
+            }
+            __syncthreads();
         }
     }
-    block_best(bg, bv, sg, sv);
-    if (threadIdx.x == 0) {
-        st->done = 0u;
+    // every thread starts from the lower bound's node: the same node in several lanes is one node
+    pick_reduce(bg, bv, bd, sh);
+    GreedyTile r = NO_TILE;
+    r.g = bg;
+    r.v = bv;
+    r.d = bd;
+    return r;
+}
+
+// delta lives in two buffers: a round that recounts writes the spare one (kept zero), the next
+// argmax switches to it, and that round's cover clears the one it leaves.
+__global__ __launch_bounds__(GREEDY_BLOCK) void k_greedy_argmax(int32_t n, int round, uint64_t T, double Gamma,
+                                                                int32_t *__restrict__ delta0,
+                                                                int32_t *__restrict__ delta1,
+                                                                const double *__restrict__ qv,
+                                                                uint8_t *__restrict__ chosen,
+                                                                GreedyTile *__restrict__ tiles, int32_t ntiles,
+                                                                GreedyState *__restrict__ st,
+                                                                int32_t *__restrict__ seeds,
+                                                                unsigned long long *__restrict__ marg)
+{
+    __shared__ PickShared sh;
+    const bool recounted = heavy_round(st, T); // the previous round
+    const int cur = st->cur ^ (recounted ? 1 : 0);
+    const int32_t *delta = cur ? delta1 : delta0;
+    const GreedyTile b = pick_node<false>(tiles, ntiles, n, T, Gamma, delta, qv, chosen, sh);
+    if (threadIdx.x == 0) { // every thread has read st (the reductions' barriers)
+        st->flipped = recounted ? 1u : 0u;
         if (recounted) {
             st->shrunk = 1u; // the previous round rewrote the spans
             st->cur = cur;
         }
-        if (bv < 0) { // nothing left to pick (cannot happen for k <= n)
-            st->vstar = -1;
-            return;
-        }
-        st->vstar = bv;
-        const int32_t d = delta[bv];
-        st->dstar = (unsigned long long)d;
-        seeds[round] = bv;
-        marg[round] = (unsigned long long)d;
-        chosen[bv] = 1;
-        st->cov += (unsigned long long)d;
+        st->vstar = b.v;
+        if (b.v < 0) return; // nothing left to pick (cannot happen for k <= n)
+        st->dstar = (unsigned long long)b.d;
+        seeds[round] = b.v;
+        marg[round] = (unsigned long long)b.d;
+        chosen[b.v] = 1;
+        st->cov += (unsigned long long)b.d;
     }
 }
 
-// Covers H(v*).  H(v*) is in ascending sample order, so each lane takes a run of MARK_RUN
-// consecutive entries and sets the bits of one bitmap word with one atomicOr.  In a round that
-// does not recount, each wave queues the samples it newly covered in LDS and lowers delta of
+// All tiles scanned once (delta, no node chosen).
+__global__ __launch_bounds__(256) void k_greedy_tiles(int32_t n, uint64_t T, double Gamma,
+                                                      const int32_t *__restrict__ delta,
+                                                      const double *__restrict__ qv,
+                                                      const uint8_t *__restrict__ chosen,
+                                                      GreedyTile *__restrict__ tiles, int32_t ntiles)
+{
+    __shared__ GreedyTile part[4];
+    static_assert(GREEDY_TILE / SCAN_PART == 4, "a wave for each part of a tile");
+    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const int w = threadIdx.x >> 6;
+        const int64_t v0 = t * GREEDY_TILE + (int64_t)w * SCAN_PART;
+        GreedyTile c = NO_TILE;
+        if (v0 < n) c = scan_part<false>(v0, n, T, Gamma, delta, qv, chosen);
+        if ((threadIdx.x & 63) == 0) part[w] = c;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int k = 1; k < 4; ++k) merge_part(c, part[k]);
+            tiles[t] = c;
+        }
+        __syncthreads();
+    }
+}
+
+// The k rounds of a small sketch (D-SSA's) in one workgroup: three launches a round had cost more
+// than their work (D-SSA with k = 100 on the 4M-node TRI graph: 29.7 ms before, 18.6 now).  The tiles live in LDS; a round picks, covers H(v*) through LDS queues and
+// lowers delta by atomics.
+constexpr int SMALL_QUEUE = 4096;
+
+__global__ __launch_bounds__(GREEDY_BLOCK) void k_greedy_small(int32_t n, int32_t k, uint64_t T, double Gamma,
+                                                               int32_t *__restrict__ delta,
+                                                               const double *__restrict__ qv,
+                                                               uint8_t *__restrict__ chosen,
+                                                               const GreedyTile *__restrict__ tiles_in, int32_t ntiles,
+                                                               const int64_t *__restrict__ node_ptr,
+                                                               const int32_t *__restrict__ node_samples,
+                                                               uint32_t *__restrict__ covered,
+                                                               const int64_t *__restrict__ sptr,
+                                                               const int32_t *__restrict__ nodes,
+                                                               int32_t *__restrict__ seeds,
+                                                               unsigned long long *__restrict__ marg,
+                                                               GreedyState *__restrict__ st)
+{
+    __shared__ PickShared sh;
+    __shared__ GreedyTile tiles[GREEDY_SMALL_TILES];
+    // samples newly covered (first entry, entries): entries are below 2^31 here
+    __shared__ int2 queue[SMALL_QUEUE], bigq[SMALL_QUEUE];
+    __shared__ int s_q, s_big;
+    const int tid = threadIdx.x;
+    for (int t = tid; t < ntiles; t += GREEDY_BLOCK) tiles[t] = tiles_in[t];
+    __syncthreads();
+    unsigned long long cov = 0;
+    for (int32_t r = 0; r < k; ++r) {
+        const GreedyTile p = pick_node<true>(tiles, ntiles, n, T, Gamma, delta, qv, chosen, sh);
+        if (p.v < 0) { // nothing left to pick (cannot happen for k <= n)
+            if (tid == 0) st->vstar = -1;
+            return;
+        }
+        if (tid == 0) {
+            seeds[r] = p.v;
+            marg[r] = (unsigned long long)p.d;
+            chosen[p.v] = 1;
+            st->vstar = p.v;
+            s_q = 0;
+            s_big = 0;
+        }
+        cov += (unsigned long long)p.d;
+        const int64_t a = node_ptr[p.v], b = p.d > 0 ? node_ptr[p.v + 1] : a;
+        __syncthreads();
+        for (int64_t c0 = a; c0 < b; c0 += SMALL_QUEUE) {
+            for (int64_t e = c0 + tid; e < min(c0 + (int64_t)SMALL_QUEUE, b); e += GREEDY_BLOCK) {
+                const int32_t j = node_samples[e];
+                const uint32_t bit = 1u << (j & 31);
+                if (atomicOr(&covered[j >> 5], bit) & bit) continue;
+                const int e0 = (int)sptr[j], len = (int)sptr[j + 1] - e0;
+                if (len > GREEDY_BIG) bigq[atomicAdd(&s_big, 1)] = make_int2(e0, len);
+                else queue[atomicAdd(&s_q, 1)] = make_int2(e0, len);
+            }
+            __syncthreads();
+            const int nq = s_q, nb = s_big;
+            for (int i = tid >> 4; i < nq; i += GREEDY_BLOCK / 16) { // 16 lanes a sample
+                const int2 x = queue[i];
+                for (int t = tid & 15; t < x.y; t += 16) atomicSub(&delta[nodes[x.x + t]], 1);
+            }
+            for (int i = 0; i < nb; ++i) {
+                const int2 x = bigq[i];
+                for (int t = tid; t < x.y; t += GREEDY_BLOCK) atomicSub(&delta[nodes[x.x + t]], 1);
+            }
+            __syncthreads();
+            if (tid == 0) {
+                s_q = 0;
+                s_big = 0;
+            }
+            __syncthreads();
+        }
+        __threadfence(); // delta's atomics are performed before the next round reads it
+        __syncthreads();
+    }
+    if (tid == 0) st->cov = cov;
+}
+
+// Covers H(v*).  H(v*) is in ascending sample order; in a round that recounts, each lane takes a run
+// of MARK_RUN consecutive entries and sets the bits of one bitmap word with one atomicOr.  In a
+// round that does not, each wave queues the samples it newly covered in LDS and lowers delta of
 // every member of each (16 lanes per sample); the most frequent nodes (the transpose's hot
 // list) are decremented in LDS per workgroup and flushed once, so hubs do not serialise on
 // one counter.  Integer updates commute, so delta and the picks are exact.  The number of
 // samples a round newly covers is delta of its pick, known before the round starts.
 constexpr int MARK_RUN = 8;
 
-__global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restrict__ st, uint64_t T,
+__global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restrict__ st, uint64_t T, int32_t n,
                                                       const int64_t *__restrict__ node_ptr,
                                                       const int32_t *__restrict__ node_samples,
                                                       uint32_t *__restrict__ covered,
@@ -795,11 +1014,16 @@ __global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restr
                                                       int32_t *__restrict__ delta0, int32_t *__restrict__ delta1)
 {
     __shared__ int32_t hd[GREEDY_HOT];
-    __shared__ uint32_t queue[4][64 * MARK_RUN];
+    // (first entry, entries) of the newly covered samples: 33 bits of offset, 31 of length
+    __shared__ int2 queue[4][64 * MARK_RUN];
     const int32_t v = st->vstar;
     if (v < 0) return;
     const bool update = !heavy_round(st, T);
     int32_t *delta = st->cur ? delta1 : delta0;
+    if (st->flipped) { // the buffer that this round's argmax left
+        int32_t *spare = st->cur ? delta0 : delta1;
+        for (int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x; u < n; u += (int64_t)gridDim.x * 256) spare[u] = 0;
+    }
     if (update)
         for (int h = threadIdx.x; h < nhot; h += 256) hd[h] = 0;
     __syncthreads();
@@ -807,29 +1031,50 @@ __global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restr
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    uint32_t *q = queue[wid];
+    if (!update) {
+        for (int64_t c0 = a + wave * 64 * MARK_RUN; c0 < b; c0 += nwaves * 64 * MARK_RUN) {
+            const int64_t r0 = c0 + (int64_t)lane * MARK_RUN;
+            int32_t js[MARK_RUN];
+            int n = 0;
+#pragma unroll
+            for (int k = 0; k < MARK_RUN; ++k) {
+                js[k] = r0 + k < b ? node_samples[r0 + k] : -1;
+                n += js[k] >= 0 ? 1 : 0;
+            }
+            int k = 0;
+            while (k < n) { // one word at a time: a heavy pick's list is dense
+                const int32_t word = js[k] >> 5;
+                uint32_t bits = 0;
+                while (k < n && (js[k] >> 5) == word) bits |= 1u << (js[k++] & 31);
+                atomicOr(&covered[word], bits);
+            }
+        }
+        return;
+    }
+    // a light round: most of the list is covered already, so the words are read first, all at once,
+    // and only bits still clear are set by atomics, all at once again (one word after the other had
+    // cost a memory latency each: 91 us a round on average at 2^25 samples, now 70)
+    int2 *q = queue[wid];
     for (int64_t c0 = a + wave * 64 * MARK_RUN; c0 < b; c0 += nwaves * 64 * MARK_RUN) { // uniform per wave
-        const int64_t r0 = c0 + (int64_t)lane * MARK_RUN;
         int32_t js[MARK_RUN];
-        int n = 0;
+        uint32_t wd[MARK_RUN], old[MARK_RUN];
 #pragma unroll
         for (int k = 0; k < MARK_RUN; ++k) {
-            js[k] = r0 + k < b ? node_samples[r0 + k] : -1;
-            n += js[k] >= 0 ? 1 : 0;
+            const int64_t e = c0 + k * 64 + lane;
+            js[k] = node_samples[e < b ? e : b - 1];
+        }
+#pragma unroll
+        for (int k = 0; k < MARK_RUN; ++k)
+            wd[k] = c0 + k * 64 + lane < b ? covered[js[k] >> 5] : 0xFFFFFFFFu;
+#pragma unroll
+        for (int k = 0; k < MARK_RUN; ++k) {
+            const uint32_t bit = 1u << (js[k] & 31);
+            old[k] = 0xFFFFFFFFu;
+            if (!(wd[k] & bit)) old[k] = atomicOr(&covered[js[k] >> 5], bit);
         }
         uint32_t fresh = 0; // bit k: js[k] newly covered
-        int k = 0;
-        while (k < n) { // one word at a time
-            const int32_t word = js[k] >> 5;
-            uint32_t bits = 0;
-            int k1 = k;
-            while (k1 < n && (js[k1] >> 5) == word) bits |= 1u << (js[k1++] & 31);
-            const uint32_t newb = bits & ~atomicOr(&covered[word], bits);
-            for (int t = k; t < k1; ++t)
-                if (newb & (1u << (js[t] & 31))) fresh |= 1u << t;
-            k = k1;
-        }
-        if (!update) continue;
+#pragma unroll
+        for (int k = 0; k < MARK_RUN; ++k) fresh |= ((old[k] >> (js[k] & 31)) & 1u) ? 0u : 1u << k;
         const int cnt = __popc(fresh);
         const int incl = wave_incl_scan(cnt);
         const int tot = (int)lane_value((uint32_t)incl, 63);
@@ -837,7 +1082,10 @@ __global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restr
         int pos = incl - cnt;
 #pragma unroll
         for (int t = 0; t < MARK_RUN; ++t)
-            if (fresh & (1u << t)) q[pos++] = (uint32_t)js[t];
+            if (fresh & (1u << t)) {
+                const int64_t sa = sptr[js[t]], sb = sptr[js[t] + 1];
+                q[pos++] = make_int2((int32_t)(sa >> 1), (int32_t)(((sb - sa) << 1) | (sa & 1)));
+            }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -845,10 +1093,11 @@ __global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restr
         for (int i0 = 0; i0 < tot; i0 += 4) {
             const int i = i0 + g;
             if (i >= tot) continue;
-            const uint32_t j = q[i];
-            const int64_t sa = sptr[j], sb = sptr[j + 1];
-            for (int64_t t = sa + gl; t < sb; t += 16) {
-                const int32_t u = nodes[t];
+            const int2 x = q[i];
+            const int64_t sa = ((int64_t)(uint32_t)x.x << 1) | (x.y & 1);
+            const int len = (int)((uint32_t)x.y >> 1);
+            for (int t = gl; t < len; t += 16) {
+                const int32_t u = nodes[sa + t];
                 const int32_t h = hot_id ? hot_id[u] : -1;
                 if (h >= 0) atomicSub(&hd[h], 1);
                 else atomicSub(&delta[u], 1);
@@ -858,7 +1107,6 @@ __global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restr
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    if (!update) return;
     __syncthreads();
     for (int h = threadIdx.x; h < nhot; h += 256)
         if (hd[h]) atomicAdd(&delta[hot_node[h]], hd[h]);
@@ -1210,23 +1458,31 @@ void greedy(const Sketch &sk, QueryScratch &qs, int32_t k, int32_t *seeds, uint6
     DevBuf<uint8_t> chosen;
     DevBuf<uint32_t> covered;
     DevBuf<GreedyState> st;
-    const unsigned ga = gridq(((uint64_t)n + ARGMAX_PER - 1) / ARGMAX_PER, 256, 4);
-    DevBuf<double> pg;
-    DevBuf<int32_t> pv;
+    const int32_t ntiles = (int32_t)(((int64_t)n + GREEDY_TILE - 1) / GREEDY_TILE);
+    DevBuf<GreedyTile> tiles;
+    tiles.alloc(arena, (size_t)ntiles);
+    const bool small = sk.entries <= GREEDY_SMALL_ENTRIES && ntiles <= GREEDY_SMALL_TILES;
     delta.alloc(arena, n);
-    delta_spare.alloc(arena, n);
+    if (!small) delta_spare.alloc(arena, n);
     chosen.alloc(arena, n);
     covered.alloc(arena, wordsT ? wordsT : 1);
     st.alloc(arena, 1);
-    pg.alloc(arena, ga);
-    pv.alloc(arena, ga);
     hipLaunchKernelGGL(k_greedy_init, dim3(gridq(n, 256)), dim3(256), 0, s, n, sk.node_ptr.ptr, delta.ptr, chosen.ptr);
     hipLaunchKernelGGL(k_fill_q<uint32_t>, dim3(gridq(wordsT ? wordsT : 1, 256)), dim3(256), 0, s,
                        wordsT ? wordsT : 1, covered.ptr, 0u);
-    hipLaunchKernelGGL(k_fill_q<int32_t>, dim3(gridq(n, 256)), dim3(256), 0, s, (uint64_t)n, delta_spare.ptr, 0);
+    if (!small)
+        hipLaunchKernelGGL(k_fill_q<int32_t>, dim3(gridq(n, 256)), dim3(256), 0, s, (uint64_t)n, delta_spare.ptr, 0);
     hipLaunchKernelGGL(k_fill_q<unsigned char>, dim3(1), dim3(64), 0, s, (uint64_t)sizeof(GreedyState),
                        reinterpret_cast<unsigned char *>(st.ptr), (unsigned char)0);
     SKIS_HIP_TRY(hipGetLastError());
+    hipLaunchKernelGGL(k_greedy_tiles, dim3(gridq((uint64_t)ntiles * 256, 256, 8)), dim3(256), 0, s, n, sk.T,
+                       sk.est_scale(), delta.ptr, sk.est_q(), chosen.ptr, tiles.ptr, ntiles);
+    if (small) {
+        hipLaunchKernelGGL(k_greedy_small, dim3(1), dim3(GREEDY_BLOCK), 0, s, n, k, sk.T, sk.est_scale(), delta.ptr,
+                           sk.est_q(), chosen.ptr, tiles.ptr, ntiles, sk.node_ptr.ptr, sk.node_samples.ptr, covered.ptr,
+                           sk.sample_ptr.ptr, sk.nodes.ptr, seeds, reinterpret_cast<unsigned long long *>(marg), st.ptr);
+        SKIS_HIP_TRY(hipGetLastError());
+    }
     const unsigned gu = (unsigned)device_cu_count() * 4;
     const int nhot = std::min<int>(sk.nhot, GREEDY_HOT);
     const int32_t *hot_id = nhot > 0 ? sk.hot_id.ptr : nullptr;
@@ -1236,7 +1492,7 @@ void greedy(const Sketch &sk, QueryScratch &qs, int32_t k, int32_t *seeds, uint6
     DevBuf<RecountItem> items;
     DevBuf<int32_t> work; // the lists cut down by the heavy rounds
     uint64_t nit = 0;
-    if (sk.T) {
+    if (sk.T && !small) {
         nitems.alloc(arena, n);
         ioff.alloc(arena, (size_t)n + 1);
         hipLaunchKernelGGL(k_recount_items_count, dim3(gridq(n, 256)), dim3(256), 0, s, n, sk.node_ptr.ptr,
@@ -1253,13 +1509,13 @@ void greedy(const Sketch &sk, QueryScratch &qs, int32_t k, int32_t *seeds, uint6
         SKIS_HIP_TRY(hipGetLastError());
     }
     const unsigned gr = gridq(nit * RECOUNT_LANES, 256, 8);
-    for (int32_t r = 0; r < k; ++r) {
-        hipLaunchKernelGGL(k_greedy_argmax, dim3(ga), dim3(256), 0, s, n, (int)r, sk.T, sk.est_scale(), delta.ptr,
-                           delta_spare.ptr, sk.est_q(), chosen.ptr, pg.ptr, pv.ptr, st.ptr, seeds,
+    for (int32_t r = 0; r < k && !small; ++r) {
+        hipLaunchKernelGGL(k_greedy_argmax, dim3(1), dim3(GREEDY_BLOCK), 0, s, n, (int)r, sk.T, sk.est_scale(), delta.ptr,
+                           delta_spare.ptr, sk.est_q(), chosen.ptr, tiles.ptr, ntiles, st.ptr, seeds,
                            reinterpret_cast<unsigned long long *>(marg));
         if (sk.T) {
             // the cover lowers delta itself unless the round recounts, decided on the device
-            hipLaunchKernelGGL(k_greedy_cover, dim3(gu), dim3(256), 0, s, st.ptr, sk.T, sk.node_ptr.ptr,
+            hipLaunchKernelGGL(k_greedy_cover, dim3(gu), dim3(256), 0, s, st.ptr, sk.T, n, sk.node_ptr.ptr,
                                sk.node_samples.ptr, covered.ptr, sk.sample_ptr.ptr, sk.nodes.ptr, hot_id,
                                sk.hot_node.ptr, nhot, delta.ptr, delta_spare.ptr);
             hipLaunchKernelGGL(k_greedy_recount, dim3(gr), dim3(256), 0, s, st.ptr, sk.T, nit, items.ptr,

@@ -39,6 +39,7 @@ constexpr int SMALL_SORT = 1024;   // sizes up to this are sorted in registers b
 constexpr int SORT_LDS_MAX = 8192; // sizes up to this are sorted by k_gather_medium_regs and
                                    // k_gather_block, larger ones through a node bitmap by
                                    // k_gather_large
+constexpr int TIER_WIDE = 4;
 constexpr int VQ_CAP = 64;        // live edges a wave queues before visiting them
 // sample ids taken from the global counter at a time: at least the slots of a workgroup
 template <int S>
@@ -175,11 +176,10 @@ struct SampleArgs {
     int32_t *ho_nodes_out;
     uint64_t ho_cap_out;
     int32_t ho_stride_out;
-    // handover from the previous tier: the id at position p of id_list resumes from record
-    // ho_slot_in[p] (p itself when ho_slot_in is null) if that is below ho_cap_in
+    // handover from the previous tier: the id at position p of id_list resumes from record p if p
+    // is below ho_cap_in
     const Handover *ho_state_in;
     const int32_t *ho_nodes_in;
-    const uint32_t *ho_slot_in;
     uint64_t ho_cap_in;
     int32_t ho_stride_in;
 };
@@ -193,7 +193,8 @@ struct SampleArgs {
 // TIER: 0 the first LDS tier (hands its overflowing samples on with their state), 1 the
 // second LDS tier (resumes them and hands its own on), 2 the HBM hash tier (a hash of HCAP
 // slots and a list of RCAP nodes per sample in global memory; resumes and hands on), 3 the
-// HBM bitmap tier (a bitmap of n bits and a list of n nodes per sample; finishes every sample).
+// HBM bitmap tier (a bitmap of n bits and a list of n nodes per sample; finishes every sample);
+// TIER_WIDE: the hash tier with its visited set in LDS and a whole workgroup a sample.
 // Arguments used once per pass or less are read from the argument segment where they are used
 // (see karg_at); the ones the edge sweep uses every pass stay in scalar registers.  SampleArgs is
 // k_sample's only parameter, so it starts the segment and a field's offset is its offsetof.
@@ -207,7 +208,7 @@ static_assert(std::is_standard_layout<SampleArgs>::value, "argument offsets need
 // a half or a quarter of the workgroups in flight it took 98 and 148 ms).
 template <int S, int RCAP, int QPL, int TIER> constexpr int sample_min_waves()
 {
-    return TIER == 0 && S <= 4 && RCAP <= 192 && QPL == 1 ? 5 : TIER == 2 ? 6 : 1;
+    return TIER == 0 && S <= 4 && RCAP <= 192 && QPL == 1 ? 5 : TIER == 2 ? 6 : TIER == TIER_WIDE ? 4 : 1;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -488,8 +489,7 @@ __device__ __forceinline__ void sample_wave(const SampleArgs &a)
                     cursor = 1u;
                     flags = F_ACTIVE | (r.y + 1 < r.w ? F_ROOTPEND : 0);
                     if (SKIS_KARG(ho_state_in)) {
-                        const uint32_t *hs = SKIS_KARG(ho_slot_in);
-                        ho_rec = hs ? hs[nx_pos] : nx_pos;
+                        ho_rec = nx_pos;
                         if (ho_rec < SKIS_KARG(ho_cap_in)) {
                             const Handover h = SKIS_KARG(ho_state_in)[ho_rec];
                             const int cur = h.cursor_rp >> 1;
@@ -764,8 +764,8 @@ __device__ __forceinline__ void sample_block(const SampleArgs &a)
 {
     constexpr bool GLOBAL = TIER == 3; // bitmap visited sets: a sample never outgrows them
     constexpr bool GHASH = TIER == 2;  // hash visited sets in global memory
-    constexpr bool LDSV = TIER <= 1;   // hash visited sets in LDS
-    constexpr bool HO_OUT = TIER <= 2, HO_IN = TIER >= 1;
+    constexpr bool LDSV = !GLOBAL && !GHASH; // hash visited sets in LDS
+    constexpr bool HO_OUT = !GLOBAL, HO_IN = TIER >= 1;
     constexpr int IDBATCH = id_batch<S>();
     static_assert(GLOBAL || HCAP > RCAP, "the hash must be larger than the node list");
     static_assert(!LDSV || HCAP <= 65535, "list entries are 8- or 16-bit hash slot indexes");
@@ -893,6 +893,8 @@ __device__ __forceinline__ void sample_block(const SampleArgs &a)
                 list_ptr(s)[pos] = u;
             }
         } else {
+            // a sample already handed on resumes from its snapshot in the next tier
+            if (TIER == TIER_WIDE && (s_flags[s] & F_DEFER)) return;
             int32_t *H = sh_hash + s * HCAP;
             uint32_t h = hash_slot(u);
 #pragma unroll 1
@@ -929,7 +931,7 @@ __device__ __forceinline__ void sample_block(const SampleArgs &a)
     }
     // staging space is reserved STAGE_CHUNK entries at a time per workgroup (lane 0 of
     // wave 0 keeps the open chunk [st_base, st_end)); the HBM tiers reserve exactly
-    constexpr unsigned long long STAGE_CHUNK = LDSV ? 8ull * S * RCAP : 0ull;
+    constexpr unsigned long long STAGE_CHUNK = TIER <= 1 ? 8ull * S * RCAP : 0ull;
     unsigned long long st_base = 0, st_end = 0;
     bsync();
 
@@ -1141,8 +1143,7 @@ __device__ __forceinline__ void sample_block(const SampleArgs &a)
                     if (!GLOBAL && (uint32_t)(r.w - r.z) > a.big_row) nf |= F_DEFER;
                     bool resumed = false;
                     if constexpr (HO_IN) {
-                        const uint32_t *hs = SKIS_KARG(ho_slot_in);
-                        const unsigned long long rec_k = hs ? (unsigned long long)hs[myid] : list_pos(myid);
+                        const unsigned long long rec_k = list_pos(myid);
                         if (SKIS_KARG(ho_state_in) && rec_k < SKIS_KARG(ho_cap_in)) {
                             const Handover h = SKIS_KARG(ho_state_in)[rec_k];
                             const int cur = h.cursor_rp >> 1;
@@ -2175,6 +2176,10 @@ static SampleKernel const kTierMidUniform = k_sample_uniform<64, 1, 1024, 1200, 
 // took 67 ms at 1.4B edges, at 8192 62 ms, and at 4096 slots the samples sent on to the
 // bitmap tier cost more than the hash saved (71 ms); the samples that leave it mostly meet a
 // hub row rather than outgrow it.
+// A launch of few such samples ends with its largest one, and there eight waves a sample with its
+// hash in LDS (two workgroups a CU) do better: with 12 thousand samples (4M-node TRI graph, 2^24
+// samples) 2.7 ms against 12.0, with 183 thousand (40M-node WC graph) 48.9 against 15.5.  Up to
+// WIDE_MAX samples the host takes that kernel; a captured chain cannot know its count.
 constexpr int TIERH_RCAP = 6144;
 constexpr int TIERH_HCAP = 8192;
 // in-degree above which the hash tier hands a sample on: a hub row is swept faster by the
@@ -2182,6 +2187,10 @@ constexpr int TIERH_HCAP = 8192;
 constexpr uint32_t TIERH_BIG_ROW = 65536;
 static SampleKernel const kTierHash = k_sample<64, 1, TIERH_RCAP, TIERH_HCAP, 64, 1, 2>;
 static SampleKernel const kTierHashUniform = k_sample_uniform<64, 1, TIERH_RCAP, TIERH_HCAP, 64, 1, 2>;
+constexpr int WIDE_BLOCK = 512;
+constexpr uint64_t WIDE_MAX = 1ull << 15;
+static SampleKernel const kTierWide = k_sample<WIDE_BLOCK, 1, TIERH_RCAP, TIERH_HCAP, 1024, 2, TIER_WIDE>;
+static SampleKernel const kTierWideUniform = k_sample_uniform<WIDE_BLOCK, 1, TIERH_RCAP, TIERH_HCAP, 1024, 2, TIER_WIDE>;
 // Fourth tier: one sample per workgroup with a bitmap of n bits and a node list of n entries;
 // the few samples that outgrow the hash tier or meet an in-degree above 2^20 take sixteen waves
 // each; the HBM buffers of all slots are kept within TIERG_BUDGET bytes.
@@ -2500,7 +2509,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A2.next = &gc.ptr->next2;
             A2.id_list = deferred2.ptr;
             A2.id_count_dev = &gc.ptr->nd1;
-            A2.id_perm = 1; // the eager form shuffles on the host; here the order is scrambled in place
+            A2.id_perm = 1; // a fixed scramble: in the hand-on order the largest samples can bunch up
             A2.big_row = std::max<uint32_t>(cfg.big_row, TIERH_BIG_ROW);
             A2.deferred = deferred.ptr; // tier 1 has read tier 0's list by now
             A2.n_deferred = &gc.ptr->nd2;
@@ -2526,7 +2535,6 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A1.ho_cap_out = ho2_cap;
             A2.ho_state_in = ho2_state.ptr;
             A2.ho_nodes_in = ho2_nodes.ptr;
-            A2.ho_slot_in = nullptr;
             A2.ho_cap_in = ho2_cap;
             A1.ho_stride_out = A2.ho_stride_in = ho2_stride;
             A2.ho_state_out = ho3_state.ptr;
@@ -2534,7 +2542,6 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A2.ho_cap_out = ho3_cap;
             A3.ho_state_in = ho3_state.ptr;
             A3.ho_nodes_in = ho3_nodes.ptr;
-            A3.ho_slot_in = nullptr;
             A3.ho_cap_in = ho3_cap;
             A2.ho_stride_out = A3.ho_stride_in = ho3_stride;
 
@@ -2746,7 +2753,6 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
         // workloads, 15 % of tier 1's)
         DevBuf<Handover> ho2_state, ho3_state;
         DevBuf<int32_t> ho2_nodes, ho3_nodes;
-        DevBuf<uint32_t> ho2_slot;
         uint64_t ho2_cap = 0, ho3_cap = 0;
         if (hc.n_deferred > 0) {
             // tier 1: the samples that outgrew tier 0, LDS visited sets of 1024 nodes
@@ -2779,32 +2785,9 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
         if (ran_mid && hc.n_deferred > 0) {
             // tier 2: the samples that outgrew tier 1, hashes and lists sized to them in HBM
             const uint64_t nd = hc.n_deferred;
-            if (nd > 1) {
-                // a fixed pseudo-random order (Fisher-Yates, a 64-bit LCG): in tier 1's hand-on
-                // order the largest samples can bunch up and start last.  Each sample keeps its
-                // handover record: the record of new position q is the old position perm[q]
-                // (records exist below ho2_cap).
-                std::vector<uint32_t> ids(nd), perm(nd), moved(nd), slot(nd);
-                SKIS_HIP_TRY(hipMemcpyAsync(ids.data(), deferred2.ptr, sizeof(uint32_t) * nd, hipMemcpyDeviceToHost, s));
-                SKIS_HIP_TRY(hipStreamSynchronize(s));
-                for (uint64_t k = 0; k < nd; ++k) perm[k] = (uint32_t)k;
-                uint64_t x = 0x9E3779B97F4A7C15ull;
-                for (uint64_t k = nd - 1; k > 0; --k) {
-                    x = x * 6364136223846793005ull + 1442695040888963407ull;
-                    const uint64_t r = (uint64_t)(((unsigned __int128)(x >> 11) * (k + 1)) >> 53);
-                    std::swap(perm[k], perm[r]);
-                }
-                for (uint64_t q = 0; q < nd; ++q) {
-                    moved[q] = ids[perm[q]];
-                    slot[q] = perm[q] < ho2_cap ? perm[q] : 0xFFFFFFFFu;
-                }
-                ho2_slot.alloc(arena, nd);
-                SKIS_HIP_TRY(hipMemcpyAsync(deferred2.ptr, moved.data(), sizeof(uint32_t) * nd, hipMemcpyHostToDevice, s));
-                SKIS_HIP_TRY(hipMemcpyAsync(ho2_slot.ptr, slot.data(), sizeof(uint32_t) * nd, hipMemcpyHostToDevice, s));
-                SKIS_HIP_TRY(hipStreamSynchronize(s));
-            }
             sk.deferred_global = nd;
-            alloc_hash_tier();
+            const bool wide = nd <= WIDE_MAX;
+            if (!wide) alloc_hash_tier();
             ho3_cap = std::min<uint64_t>(nd, HO3_MAX);
             ho3_state.alloc(arena, ho3_cap);
             ho3_nodes.alloc(arena, ho3_cap * (uint64_t)ho3_stride);
@@ -2822,11 +2805,17 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A.ho_stride_out = ho3_stride;
             A.ho_state_in = ho2_state.ptr;
             A.ho_nodes_in = ho2_nodes.ptr;
-            A.ho_slot_in = ho2_slot.ptr; // null when there was nothing to shuffle
+            A.id_perm = 1; // a fixed scramble: in the hand-on order the largest samples can bunch up
             A.ho_cap_in = ho2_cap;
             A.ho_stride_in = ho2_stride;
             SKIS_HIP_TRY(hipEventRecord(ev[8], s));
-            hipLaunchKernelGGL(tier2, dim3((unsigned)nbh), dim3(64), 0, s, A);
+            if (wide) {
+                const SampleKernel fn = prep.uniform ? kTierWideUniform : kTierWide;
+                const uint64_t nbw = (uint64_t)occupancy_blocks(fn, WIDE_BLOCK) * (uint64_t)cus;
+                hipLaunchKernelGGL(fn, dim3((unsigned)std::min<uint64_t>(nbw, nd)), dim3(WIDE_BLOCK), 0, s, A);
+            } else {
+                hipLaunchKernelGGL(tier2, dim3((unsigned)nbh), dim3(64), 0, s, A);
+            }
             SKIS_HIP_TRY(hipGetLastError());
             SKIS_HIP_TRY(hipEventRecord(ev[9], s));
             ran_hash = true;
@@ -2846,7 +2835,6 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             reset_ids();
             A.id_list = deferred.ptr;
             A.id_count = nd;
-            A.id_perm = 1;              // a fixed scramble of the hand-on order
             A.deferred = deferred2.ptr; // unused: the bitmap tier finishes every sample
             A.gbits = gbits.ptr;
             A.glist = glist.ptr;
@@ -2856,7 +2844,6 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A.ho_cap_out = 0;
             A.ho_state_in = ho3_state.ptr; // records follow the list position
             A.ho_nodes_in = ho3_nodes.ptr;
-            A.ho_slot_in = nullptr;
             A.ho_cap_in = ho3_cap;
             A.ho_stride_in = ho3_stride;
             need(A.gbits, "gbits");

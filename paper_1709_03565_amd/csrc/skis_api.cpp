@@ -336,21 +336,12 @@ static int preprocess_model(int32_t n, int64_t m, const int32_t *row_ptr, const 
         skis::Arena arena;
         arena.stream = stream;
         skis::Prep prep;
-        skis::preprocess(arena, n, m, row_ptr, col, w, thr || alias, prep, stream, model, false);
-        if (P && m > 0)
+        skis::preprocess(arena, n, m, row_ptr, col, w, thr || alias, prep, stream, model, false, P);
+        if (P && m > 0 && prep.P.ptr)
             SKIS_HIP_TRY(hipMemcpyAsync(P, prep.P.ptr, sizeof(double) * (size_t)m, hipMemcpyDeviceToDevice, stream));
         if (q) SKIS_HIP_TRY(hipMemcpyAsync(q, prep.q.ptr, sizeof(double) * (size_t)n, hipMemcpyDeviceToDevice, stream));
         if (W) SKIS_HIP_TRY(hipMemcpyAsync(W, prep.W.ptr, sizeof(uint64_t) * (size_t)n, hipMemcpyDeviceToDevice, stream));
-        if (prep.C > 0) {
-            if (thr)
-                SKIS_HIP_TRY(hipMemcpy2DAsync(thr, sizeof(uint64_t), prep.alias.ptr, sizeof(skis::AliasEntry),
-                                              sizeof(uint64_t), (size_t)n, hipMemcpyDeviceToDevice, stream));
-            if (alias)
-                SKIS_HIP_TRY(hipMemcpy2DAsync(alias, sizeof(int32_t),
-                                              reinterpret_cast<const char *>(prep.alias.ptr) + sizeof(uint64_t),
-                                              sizeof(skis::AliasEntry), sizeof(int32_t), (size_t)n,
-                                              hipMemcpyDeviceToDevice, stream));
-        }
+        if (prep.C > 0) skis::alias_columns(n, prep.alias.ptr, thr, alias, stream);
         SKIS_HIP_TRY(hipStreamSynchronize(stream));
         arena.idle_on_destroy = true; // the synchronisation above ended every use of the blocks
         if (C_out) *C_out = prep.C;

@@ -156,9 +156,14 @@ struct Prep {
 };
 
 // Validates the graph, copies row_ptr, forms the coin thresholds (if coins, under IC), computes
-// P, q, W, C, Gamma and (if build_alias) the alias table.  Throws Error on failure.
+// P, q, W, C, Gamma and (if build_alias) the alias table.  P_out (device, [m]): P is formed there
+// and not in out.P if it is 16-byte aligned.  Throws Error on failure.
 void preprocess(Arena &arena, int32_t n, int64_t m, const int32_t *row_ptr, const int32_t *col,
-                const float *w, bool build_alias, Prep &out, hipStream_t s, int model = MODEL_IC, bool coins = true);
+                const float *w, bool build_alias, Prep &out, hipStream_t s, int model = MODEL_IC, bool coins = true,
+                double *P_out = nullptr);
+
+// The alias table's columns into device arrays [n] (either may be null).
+void alias_columns(int32_t n, const AliasEntry *table, uint64_t *thr, int32_t *alias, hipStream_t s);
 
 // ---------------------------------------------------------------------------------
 // Sampling (rows a4-a7, a11) and compaction.

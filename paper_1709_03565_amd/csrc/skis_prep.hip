@@ -3,6 +3,8 @@
 // weights W, the weight total C, Gamma (exactly rounded) and the alias table (Eq. probu).
 // Under the linear threshold model (Sec. 6) the same kernels form per-row running sums of w
 // in place of the products (gamma_v is the sum of v's in-weights).
+#include <algorithm>
+
 #include "skis_internal.h"
 
 namespace skis {
@@ -16,16 +18,21 @@ constexpr double LT_SUM_SLACK = 0x1p-20;
 // q of a row under the linear threshold model from its sum of weights
 __device__ __forceinline__ double lt_q(double sum) { return sum < 1.0 ? __dsub_rn(1.0, sum) : 0.0; }
 
-constexpr int32_t LONG_ROW = 256; // rows above this length are taken by a whole workgroup
-constexpr int ROW_BATCH = 8;      // edges a row thread loads at a time
+constexpr int32_t SHORT_ROW = 128; // rows up to this length are one lane's, up to LONG_ROW one wave's
+constexpr int32_t LONG_ROW = 1024; // rows above this length are taken by a whole workgroup
 
-__device__ __forceinline__ int check_edge(int32_t u, float wf, int64_t v, int32_t n)
+// An edge's faults but for the self-loop
+__device__ __forceinline__ int check_range(int32_t u, float wf, int32_t n)
 {
     int bad = 0;
     if (u < 0 || u >= n) bad |= ERR_COL;
-    if (u == (int32_t)v) bad |= ERR_SELFLOOP;
     if (!(wf >= 0.0f && wf <= 1.0f)) bad |= ERR_WEIGHT;
     return bad;
+}
+
+__device__ __forceinline__ int check_edge(int32_t u, float wf, int64_t v, int32_t n)
+{
+    return check_range(u, wf, n) | (u == (int32_t)v ? (int)ERR_SELFLOOP : 0);
 }
 
 // The products of a row (Eq. gamma_v / Eq. probn) are formed left to right:
@@ -94,95 +101,6 @@ __device__ __forceinline__ uint32_t edge_threshold(float w)
     return coin_threshold_hi(weight_bits(w));
 }
 
-// One thread per row: validates the row, writes its coin thresholds, P and q.  Rows longer than
-// LONG_ROW are k_prep_long's, but their row record is written here.  lt: running sums S in P
-// (S[e] = S[e-1] + w[e], 0 before the row's first edge) and q = 1 - the row's sum.  th is null
-// when no coin will be drawn (LT, the preprocessing alone).  *mixed: set when some row's edges
-// differ in their threshold.  The thresholds alone are kept (4 B an edge; the col values and the
-// w bits stay in the caller's arrays): a copy of (col, threshold) records and of the w bits had
-// cost 12 B an edge of writes, and every coin of the sampler 8 B of reads.
-__global__ __launch_bounds__(256) void k_prep_rows(int32_t n, int64_t m, const int32_t *__restrict__ row_ptr,
-                                                   const int32_t *__restrict__ col, const float *__restrict__ w,
-                                                   int32_t *__restrict__ rp_copy, uint2 *__restrict__ rows,
-                                                   uint32_t *__restrict__ th, double *__restrict__ P,
-                                                   double *__restrict__ q, int *err, int *mixed, int lt)
-{
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t a = row_ptr[v], b = row_ptr[v + 1];
-        rp_copy[v] = a;
-        if (v == n - 1) rp_copy[n] = b;
-        if (rows && v == n - 1) rows[n] = make_uint2((uint32_t)b, 0u);
-        int bad = 0;
-        if (v == 0 && a != 0) bad |= ERR_ROWPTR;
-        if (v == n - 1 && (int64_t)b != m) bad |= ERR_ROWPTR;
-        if (a < 0 || (int64_t)b > m || a > b) {
-            atomicOr(err, bad | ERR_ROWPTR);
-            q[v] = 1.0;
-            continue;
-        }
-        if (b - a > LONG_ROW) { // listed by k_find_long
-            if (bad) atomicOr(err, bad);
-            if (rows) rows[v] = make_uint2((uint32_t)a, edge_threshold(w[a]));
-            continue;
-        }
-        // ROW_BATCH edges at a time, the next batch's loads issued (clamped to the row's last
-        // edge, so unconditionally) before this batch is used: one memory latency per batch
-        double run = lt ? 0.0 : 1.0;
-        uint32_t th0 = 0u;
-        bool same = true;
-        if (b > a) {
-            int32_t uc[ROW_BATCH];
-            float wc[ROW_BATCH];
-#pragma unroll
-            for (int k = 0; k < ROW_BATCH; ++k) {
-                const int32_t e = min(a + k, b - 1);
-                uc[k] = col[e];
-                wc[k] = w[e];
-            }
-            th0 = edge_threshold(wc[0]);
-            for (int32_t e0 = a; e0 < b; e0 += ROW_BATCH) {
-                int32_t un[ROW_BATCH];
-                float wn[ROW_BATCH];
-#pragma unroll
-                for (int k = 0; k < ROW_BATCH; ++k) {
-                    const int32_t e = min(e0 + ROW_BATCH + k, b - 1);
-                    un[k] = col[e];
-                    wn[k] = w[e];
-                }
-#pragma unroll
-                for (int k = 0; k < ROW_BATCH; ++k) {
-                    const int32_t e = e0 + k;
-                    if (e >= b) break;
-                    const int32_t u = uc[k];
-                    const float wf = wc[k];
-                    bad |= check_edge(u, wf, v, n);
-                    if (th) {
-                        const uint32_t x = edge_threshold(wf);
-                        same = same && x == th0;
-                        th[e] = x;
-                    }
-                    run = lt ? __dadd_rn(run, (double)wf) : __dmul_rn(run, __dsub_rn(1.0, (double)wf));
-                    P[e] = run;
-                }
-#pragma unroll
-                for (int k = 0; k < ROW_BATCH; ++k) {
-                    uc[k] = un[k];
-                    wc[k] = wn[k];
-                }
-            }
-        }
-        if (lt) {
-            if (run > 1.0 + LT_SUM_SLACK) bad |= ERR_LTSUM;
-            q[v] = lt_q(run);
-        } else {
-            q[v] = run;
-        }
-        if (rows) rows[v] = make_uint2((uint32_t)a, th0);
-        if (!same && !*mixed) *mixed = 1; // every writer writes 1
-        if (bad) atomicOr(err, bad);
-    }
-}
-
 // One 256-thread workgroup per long row (the next row of the list taken with one atomic, so
 // that the workgroup holding the longest row takes no other; the rows above HUGE_ROW come
 // first), LONG_EDGES in-edges at a time.  A row's products are one dependent chain; on the
@@ -201,7 +119,7 @@ __global__ __launch_bounds__(256) void k_prep_rows(int32_t n, int64_t m, const i
 // stores had made the chain up to four times slower than its multiplies.  Three factor buffers
 // rotate (chained, fed, rebuilt).  LT: the terms are w (0 past the row's end) and the chain
 // adds.
-constexpr int LONG_EDGES = 4096;
+constexpr int LONG_EDGES = 3072;               // 77 KB of LDS: nine waves of k_prep_rows beside it
 constexpr int LONG_TRIP = 16;                  // factors per batch of the chain's LDS reads
 constexpr int LONG_PAD = 64;                   // read-ahead past a chunk
 constexpr int LONG_BLK = 64;                   // products per checkpoint
@@ -210,6 +128,8 @@ constexpr int LONG_PER = (LONG_EDGES + LONG_FEED - 1) / LONG_FEED; // edges a fe
 static_assert(LONG_EDGES % LONG_BLK == 0 && LONG_BLK == 4 * LONG_TRIP, "checkpoints fall on batch quads");
 static_assert(LONG_PAD >= LONG_TRIP, "the chain reads one batch past a block");
 static_assert(LONG_EDGES / LONG_BLK <= LONG_FEED, "one rebuilt block per feeding thread");
+
+static_assert(LONG_EDGES >= HUGE_ORDER_MAX, "the huge rows' order shares the factors' LDS");
 
 template <bool LT> __device__ __forceinline__ double chain_op(double x, double f)
 {
@@ -286,6 +206,69 @@ __device__ __forceinline__ void rebuild_block(const double *F, int blk, int cnt,
     }
 }
 
+// Tails.  Where coins are frequent the product underflows within some ten thousand edges and stays at
+// a denormal of a few units (fl(x f) = x for every later factor f) or at zero, while the row may
+// have millions more.  Once a whole chunk has left such a value as it was, k_prep_long gives the
+// rest of the row to k_prep_tails, pieces of which all CUs take: each edge's factor is checked to
+// leave the value as it is, and if one does not (a larger weight further on) the host has the long
+// rows done again without tails.  4M nodes and 70M edges of trivalency weights: the long rows took
+// 5.0 ms, the longest chain's time; now 0.33 ms and 0.06 ms for the tails.
+struct TailPiece {
+    int32_t e0, e1; // edges
+    int32_t v;      // row
+    int32_t units;  // the product in units of 2^-1074
+};
+// Values taken for a tail: weights of 2^-20 and more bring a long product below.
+constexpr int TAIL_UNITS = 1 << 20;
+constexpr int TAIL_PIECE = 16384;
+// A row with pieces has more than 2 LONG_EDGES edges, and the rows of a valid graph are disjoint.
+static inline int64_t tail_pieces_max(int64_t m) { return m / TAIL_PIECE + m / (2 * LONG_EDGES) + 1; }
+
+__global__ __launch_bounds__(256) void k_prep_tails(int32_t n, const int32_t *__restrict__ row_ptr,
+                                                    const int32_t *__restrict__ col, const float *__restrict__ w,
+                                                    uint32_t *__restrict__ th, double *__restrict__ P, int *err,
+                                                    int *mixed, const TailPiece *__restrict__ pieces,
+                                                    const unsigned int *__restrict__ n_pieces, unsigned int max_pieces,
+                                                    int64_t m, int *__restrict__ redo)
+{
+    const unsigned int np = *n_pieces;
+    if (np > max_pieces) return; // only where rows overlap, which k_prep_rows reports
+    int bad = 0;
+    bool same = true, moved = false;
+    for (unsigned int i = blockIdx.x; i < np; i += gridDim.x) {
+        const TailPiece p = pieces[i];
+        if (p.e0 < 0 || (int64_t)p.e1 > m || p.v < 0 || p.v >= n) continue; // likewise
+        const double x = __longlong_as_double((long long)p.units);
+        const uint32_t th0 = th ? edge_threshold(w[row_ptr[p.v]]) : 0u;
+        for (int32_t e0 = p.e0 + (int32_t)threadIdx.x; e0 < p.e1; e0 += 1024) { // below 2^31 - 1024: see the host
+            int32_t u[4];
+            float wf[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int32_t e = min(e0 + k * 256, p.e1 - 1);
+                u[k] = col[e];
+                wf[k] = w[e];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int32_t e = e0 + k * 256;
+                if (e >= p.e1) break;
+                bad |= check_edge(u[k], wf[k], p.v, n);
+                moved = moved || __dmul_rn(x, __dsub_rn(1.0, (double)wf[k])) != x;
+                if (th) {
+                    const uint32_t tx = edge_threshold(wf[k]);
+                    same = same && tx == th0;
+                    th[e] = tx;
+                }
+                P[e] = x;
+            }
+        }
+    }
+    if (bad) atomicOr(err, bad);
+    if (!same && !*mixed) *mixed = 1;
+    if (moved && !*redo) *redo = 1;
+}
+
 template <bool LT>
 __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__restrict__ row_ptr,
                                                    const int32_t *__restrict__ col, const float *__restrict__ w,
@@ -294,13 +277,15 @@ __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__r
                                                    int *mixed, const int32_t *__restrict__ long_rows,
                                                    const unsigned int *__restrict__ n_long,
                                                    const unsigned int *__restrict__ n_huge,
-                                                   unsigned int *__restrict__ next_row)
+                                                   unsigned int *__restrict__ next_row, TailPiece *__restrict__ pieces,
+                                                   unsigned int *__restrict__ n_pieces, unsigned int max_pieces)
 {
     __shared__ __align__(16) double s_f[3][LONG_EDGES + LONG_PAD]; // factors of three chunks (+ read-ahead pad)
     __shared__ double s_ck[2][LONG_EDGES / LONG_BLK];               // checkpoints of two chunks
-    __shared__ int32_t s_hrow[HUGE_ORDER_MAX], s_hlen[HUGE_ORDER_MAX];
-    __shared__ unsigned int s_r;
+    int32_t *const s_hrow = reinterpret_cast<int32_t *>(s_f[0]), *const s_hlen = s_hrow + HUGE_ORDER_MAX; // before the row
+    __shared__ unsigned int s_r, s_piece;
     __shared__ int32_t s_pick;
+    __shared__ double s_run[2]; // the chain after each of the last two chunks
     const int t = threadIdx.x;
     const unsigned int nh = *n_huge, cnt = nh + *n_long;
     const double ident = LT ? 0.0 : 1.0;
@@ -367,16 +352,19 @@ __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__r
             v = s_pick;
         }
         const int32_t a = row_ptr[v], b = row_ptr[v + 1];
-        const int nchunks = (b - a + LONG_EDGES - 1) / LONG_EDGES;
+        int nchunks = (b - a + LONG_EDGES - 1) / LONG_EDGES;
         int bad = 0;
         if (th) th0 = edge_threshold(w[a]);
         if (t >= 64) bad |= feed(v, a, b, 0);
         __syncthreads();
         double run = ident; // lane 0's chain
+        [[maybe_unused]] long long before = 0; // the product before the chunk just done
         for (int c = 0; c <= nchunks; ++c) {
             if (t == 0) {
-                if (c < nchunks)
+                if (c < nchunks) {
                     run = chain_chunk<LT>(s_f[c % 3], s_ck[c & 1], min(b - (a + c * LONG_EDGES), LONG_EDGES), run);
+                    if (!LT) s_run[c & 1] = run;
+                }
             } else if (t >= 64) {
                 if (c + 1 < nchunks) bad |= feed(v, a + (c + 1) * LONG_EDGES, b, (c + 1) % 3);
                 if (c >= 1) { // rebuild chunk c - 1 from its checkpoints, one block per thread
@@ -389,6 +377,26 @@ __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__r
                 }
             }
             __syncthreads();
+            if constexpr (!LT) {
+                // the same decision in every thread: lane 0 writes this place again after the next barrier
+                if (!pieces || c + 2 >= nchunks) continue;
+                const long long units = __double_as_longlong(s_run[c & 1]);
+                if (units < TAIL_UNITS && c > 0 && units == before) {
+                    const int32_t e0 = a + (c + 1) * LONG_EDGES;
+                    const int np = (b - e0 + TAIL_PIECE - 1) / TAIL_PIECE;
+                    if (t == 0) s_piece = atomicAdd(n_pieces, (unsigned int)np);
+                    __syncthreads();
+                    const unsigned int p0 = s_piece;
+                    if ((uint64_t)p0 + (unsigned int)np <= max_pieces) {
+                        for (int i = t; i < np; i += 256) {
+                            const int32_t x = e0 + i * TAIL_PIECE;
+                            pieces[p0 + i] = {x, b - x > TAIL_PIECE ? x + TAIL_PIECE : b, v, (int32_t)units};
+                        }
+                        nchunks = c + 1; // what is left here: this chunk's products
+                    }
+                }
+                before = units;
+            }
         }
         if (t == 0) {
             if (LT) {
@@ -403,6 +411,196 @@ __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__r
         same = true;
         __syncthreads();
     }
+}
+
+// The rows up to LONG_ROW edges: validation, coin thresholds, P and q; the row records of all rows,
+// the long ones too.  A wave takes 64 rows at a time (`per` such units an atomic).  The edges of the
+// rows up to SHORT_ROW go into LDS, as many rows as fit, coalesced; each lane forms its row's
+// products there in place, left to right, and they go out coalesced.  The rows between SHORT_ROW
+// and LONG_ROW follow one by one, by the whole wave as in k_prep_long.  A thread that read its own
+// row from memory had kept a wave's loads on 64 lines and waited a memory latency for every eight
+// edges, and a 256-thread workgroup a row left most of the device idle on rows of some hundred
+// edges: 4M nodes and 70M edges of trivalency weights took 1.36 ms (and the rows of 257 to 1024
+// edges another 0.5 ms in k_prep_long), now 0.56 ms; the bytes alone take 0.25 ms.
+// The units are taken as the waves get to them, since waves that find no room beside the long rows
+// start late.  LT: running sums S in P (S[e] = S[e-1] + w[e], 0 before the row's first edge) and
+// q = 1 - the row's sum.  th and rows are null when no coin will be drawn (LT, the preprocessing
+// alone).  *mixed: set when some row's edges differ in their threshold.
+constexpr int ROWS_CAP = LONG_ROW; // edges in LDS: 8.6 KB with the pad and the checkpoints
+constexpr int ROWS_FLIGHT = 6;     // edges a lane loads at a time
+
+template <bool LT>
+__global__ __launch_bounds__(64) void k_prep_rows(int32_t n, int64_t m, const int32_t *__restrict__ row_ptr,
+                                                  const int32_t *__restrict__ col, const float *__restrict__ w,
+                                                  int32_t *__restrict__ rp_copy, uint2 *__restrict__ rows,
+                                                  uint32_t *__restrict__ th, double *__restrict__ P,
+                                                  double *__restrict__ q, int *err, int *mixed,
+                                                  unsigned int *__restrict__ next_unit, unsigned int per)
+{
+    __shared__ __align__(16) double s_f[ROWS_CAP + LONG_PAD]; // a short edge's (col, w), then its product; factors
+    __shared__ double s_ck[ROWS_CAP / LONG_BLK];
+    const int lane = threadIdx.x;
+    const double ident = LT ? 0.0 : 1.0;
+    const unsigned int units = (unsigned int)(((int64_t)n + 63) / 64);
+    int bad = 0;
+    bool same = true;
+    for (unsigned int g1 = 0, g = 0;; ++g) {
+        if (g == g1) {
+            unsigned int x = 0;
+            if (lane == 0) x = atomicAdd(next_unit, per);
+            g = (unsigned int)__builtin_amdgcn_readfirstlane((int)x);
+            if (g >= units) break;
+            g1 = min(g + per, units);
+        }
+        const int64_t v = (int64_t)g * 64 + lane;
+        int32_t a = 0, b = 0;
+        bool ok = false;
+        uint32_t th0 = 0u;
+        if (v < n) {
+            a = row_ptr[v];
+            b = row_ptr[v + 1];
+            rp_copy[v] = a;
+            if (v == n - 1) {
+                rp_copy[n] = b;
+                if (rows) rows[n] = make_uint2((uint32_t)b, 0u);
+                if ((int64_t)b != m) bad |= ERR_ROWPTR;
+            }
+            if (v == 0 && a != 0) bad |= ERR_ROWPTR;
+            ok = a >= 0 && (int64_t)b <= m && a <= b;
+            if (!ok) {
+                bad |= ERR_ROWPTR;
+                q[v] = 1.0;
+            } else if (rows && b - a > SHORT_ROW) {
+                th0 = edge_threshold(w[a]);
+            }
+        }
+        const int32_t len = b - a;
+        const bool is_short = ok && len <= SHORT_ROW;
+        double run = ident;
+        // the short rows, by as many lanes as fit at a time
+        for (unsigned long long todo = __ballot(is_short && len > 0); todo;) {
+            const bool cand = (todo >> lane) & 1ull;
+            int32_t off = cand ? len : 0; // inclusive sums of the candidates' lengths
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int32_t y = __shfl_up(off, d, 64);
+                if (lane >= d) off += y;
+            }
+            const bool in = cand && off <= ROWS_CAP; // the first ones: the sums ascend
+            off -= cand ? len : 0;
+            const unsigned long long now = __ballot(in);
+            todo &= ~now;
+            // their edges, in runs of neighbouring rows (empty ones between them do not count)
+            const unsigned long long gap = __ballot(!(in || (is_short && len == 0)));
+            auto runs = [&](auto &&body) {
+                for (unsigned long long left = now; left;) {
+                    const int l0 = __ffsll(left) - 1;
+                    const unsigned long long after = gap & ~((1ull << l0) - 1ull);
+                    const unsigned long long mine = after ? left & ((1ull << (__ffsll(after) - 1)) - 1ull) : left;
+                    const int l1 = 63 - __clzll(mine);
+                    left &= ~mine;
+                    const int32_t e0 = __builtin_amdgcn_readlane(a, l0);
+                    body(e0, __builtin_amdgcn_readlane(b, l1) - e0, __builtin_amdgcn_readlane(off, l0));
+                }
+            };
+            runs([&](int32_t e0, int32_t cnt, int32_t o) {
+                for (int i0 = lane; i0 - lane < cnt; i0 += 64 * ROWS_FLIGHT) {
+                    int32_t u[ROWS_FLIGHT];
+                    float wf[ROWS_FLIGHT];
+#pragma unroll
+                    for (int k = 0; k < ROWS_FLIGHT; ++k) { // clamped, so unconditional
+                        const int i = min(i0 + k * 64, cnt - 1);
+                        u[k] = col[e0 + i];
+                        wf[k] = w[e0 + i];
+                    }
+#pragma unroll
+                    for (int k = 0; k < ROWS_FLIGHT; ++k) {
+                        const int i = min(i0 + k * 64, cnt - 1);
+                        s_f[o + i] = __longlong_as_double((long long)((uint64_t)(uint32_t)u[k] << 32 | __float_as_uint(wf[k])));
+                        if (th) th[e0 + i] = edge_threshold(wf[k]);
+                        bad |= check_range(u[k], wf[k], n); // the self-loops are seen below
+                    }
+                }
+            });
+            __syncthreads();
+            if (in) {
+                const uint32_t w0 = (uint32_t)__double_as_longlong(s_f[off]);
+                if (th) th0 = edge_threshold(__uint_as_float(w0));
+                for (int i0 = 0; i0 < len; i0 += 4) {
+                    uint64_t x[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) x[k] = (uint64_t)__double_as_longlong(s_f[off + min(i0 + k, len - 1)]);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        if (i0 + k >= len) break;
+                        const uint32_t wb = (uint32_t)x[k];
+                        const float wf = __uint_as_float(wb);
+                        if ((int32_t)(x[k] >> 32) == (int32_t)v) bad |= ERR_SELFLOOP;
+                        if (th && same && wb != w0) same = edge_threshold(wf) == th0;
+                        run = chain_op<LT>(run, LT ? (double)wf : __dsub_rn(1.0, (double)wf));
+                        s_f[off + i0 + k] = run;
+                    }
+                }
+            }
+            __syncthreads();
+            runs([&](int32_t e0, int32_t cnt, int32_t o) {
+                for (int i = lane; i < cnt; i += 64) P[e0 + i] = s_f[o + i];
+            });
+            __syncthreads();
+        }
+        // the rows of one wave
+        for (unsigned long long todo = __ballot(ok && !is_short && len <= LONG_ROW); todo; todo &= todo - 1ull) {
+            const int l = __ffsll(todo) - 1;
+            const int32_t e0 = __builtin_amdgcn_readlane(a, l), cnt = __builtin_amdgcn_readlane(len, l);
+            const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)th0, l);
+            const int32_t row = (int32_t)((int64_t)g * 64 + l);
+            const int end = (cnt + LONG_BLK - 1) / LONG_BLK * LONG_BLK + LONG_TRIP;
+            for (int i0 = lane; i0 - lane < end; i0 += 64 * ROWS_FLIGHT) {
+                int32_t u[ROWS_FLIGHT];
+                float wf[ROWS_FLIGHT];
+#pragma unroll
+                for (int k = 0; k < ROWS_FLIGHT; ++k) {
+                    const int i = min(i0 + k * 64, cnt - 1);
+                    u[k] = col[e0 + i];
+                    wf[k] = w[e0 + i];
+                }
+#pragma unroll
+                for (int k = 0; k < ROWS_FLIGHT; ++k) {
+                    const int i = i0 + k * 64, ic = min(i, cnt - 1);
+                    bad |= check_edge(u[k], wf[k], row, n);
+                    if (th) {
+                        const uint32_t x = edge_threshold(wf[k]);
+                        same = same && x == t0;
+                        th[e0 + ic] = x;
+                    }
+                    const double f = i < cnt ? (LT ? (double)wf[k] : __dsub_rn(1.0, (double)wf[k])) : ident;
+                    if (i < end) s_f[i] = f;
+                }
+            }
+            __syncthreads();
+            double r = ident;
+            if (lane == 0) r = chain_chunk<LT>(s_f, s_ck, cnt, r);
+            __syncthreads();
+            if (lane * LONG_BLK < cnt)
+                rebuild_block<LT>(s_f, lane, min(LONG_BLK, cnt - lane * LONG_BLK), s_ck[lane], P + e0 + lane * LONG_BLK);
+            r = __longlong_as_double((long long)readlane64((unsigned long long)__double_as_longlong(r), 0));
+            if (lane == l) run = r;
+            __syncthreads();
+        }
+        if (ok) {
+            if (len <= LONG_ROW) {
+                if (LT) {
+                    if (run > 1.0 + LT_SUM_SLACK) bad |= ERR_LTSUM;
+                    q[v] = lt_q(run);
+                } else {
+                    q[v] = run;
+                }
+            }
+            if (rows) rows[v] = make_uint2((uint32_t)a, th0);
+        }
+    }
+    if (bad) atomicOr(err, bad);
+    if (!same && !*mixed) *mixed = 1; // every writer writes 1
 }
 
 // Sum of hi:lo over the wave, two 64-bit halves with carry (every lane gets it).
@@ -581,26 +779,12 @@ static unsigned grid_for(int64_t items, int block = 256)
     return (unsigned)(g > 0 ? g : 1);
 }
 
-// k_prep_rows's grid: at most as many workgroups per CU as leave one k_prep_long wave room in
-// every SIMD's registers beside them (512 VGPRs a lane, allocated in steps of 8; at most 8 waves
-// a SIMD), so that the long rows' chains start with their kernel whichever of the two kernels
-// the device starts first (filling every CU, k_prep_rows had held the longest chain back by
-// about 19 ms at 40M rows).  A k_prep_rows workgroup puts one wave on each SIMD.
-static unsigned prep_rows_grid(int64_t n)
-{
-    auto vgprs = [](const void *fn) {
-        hipFuncAttributes a{};
-        if (hipFuncGetAttributes(&a, fn) != hipSuccess || a.numRegs <= 0) return 256;
-        return (a.numRegs + 7) / 8 * 8;
-    };
-    const int vr = vgprs(reinterpret_cast<const void *>(k_prep_rows));
-    const int vl = std::max(vgprs(reinterpret_cast<const void *>(k_prep_long<false>)),
-                            vgprs(reinterpret_cast<const void *>(k_prep_long<true>)));
-    const int per_simd = std::max(1, std::min(7, (512 - vl) / vr));
-    const int64_t cap = (int64_t)device_cu_count() * per_simd;
-    const int64_t g = std::min<int64_t>((n + 255) / 256, cap);
-    return (unsigned)(g > 0 ? g : 1);
-}
+// Workgroups a CU: one of the long rows' (77 KB of LDS) and at most this many of the other rows'
+// (9 KB), few enough that both find room whichever kernel the device starts first (filling every
+// CU, k_prep_rows had held the longest chain back by about 19 ms at 40M rows).  Measured against two
+// with chunks of 2048 edges beside ten, and one of 4096 beside seven: 4M rows alone 1.09, 1.06 and
+// 1.14 ms, 1M rows in a build 1.40-1.46, 1.47-1.64 and 1.41 ms, 40M rows 31.4, 32.6 and 32.5 ms.
+constexpr int LONG_PER_CU = 1, ROWS_PER_CU = 9;
 
 static int root_shift(int32_t n)
 {
@@ -609,8 +793,27 @@ static int root_shift(int32_t n)
     return 62 - L;
 }
 
+// The alias table's columns into the caller's arrays (either may be null): the strided copies had
+// taken 234 us for 4M nodes.
+__global__ __launch_bounds__(256) void k_alias_columns(int32_t n, const AliasEntry *__restrict__ table,
+                                                       uint64_t *__restrict__ thr, int32_t *__restrict__ alias)
+{
+    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (int64_t)gridDim.x * 256) {
+        const AliasEntry e = table[v];
+        if (thr) thr[v] = e.thr;
+        if (alias) alias[v] = e.alias;
+    }
+}
+
+void alias_columns(int32_t n, const AliasEntry *table, uint64_t *thr, int32_t *alias, hipStream_t s)
+{
+    if (!thr && !alias) return;
+    hipLaunchKernelGGL(k_alias_columns, dim3(grid_for(n)), dim3(256), 0, s, n, table, thr, alias);
+    SKIS_HIP_TRY(hipGetLastError());
+}
+
 void preprocess(Arena &arena, int32_t n, int64_t m, const int32_t *row_ptr, const int32_t *col, const float *w,
-                bool build_alias, Prep &out, hipStream_t s, int model, bool coins)
+                bool build_alias, Prep &out, hipStream_t s, int model, bool coins, double *P_out)
 {
     if (model != MODEL_IC && model != MODEL_LT) throw Error{SKIS_EINVAL, "model must be 0 (IC) or 1 (LT)"};
     out.model = model;
@@ -624,22 +827,34 @@ void preprocess(Arena &arena, int32_t n, int64_t m, const int32_t *row_ptr, cons
         out.th.alloc(arena, m_quad > 0 ? m_quad : 4);
         out.rows.alloc(arena, (size_t)n + 1);
     }
-    out.P.alloc(arena, (size_t)(m > 0 ? m : 1));
+    // the products go straight into the caller's buffer where the paired stores allow it
+    double *P = P_out && (reinterpret_cast<uintptr_t>(P_out) & 15) == 0 ? P_out : nullptr;
+    if (!P) {
+        out.P.alloc(arena, (size_t)(m > 0 ? m : 1));
+        P = out.P.ptr;
+    }
     out.q.alloc(arena, (size_t)n);
     out.W.alloc(arena, (size_t)n);
     // every threshold below m is written by the row kernels; the quad padding past m is clear
     if (out.th.count > (size_t)m)
         SKIS_HIP_TRY(hipMemsetAsync(out.th.ptr + m, 0, (out.th.count - (size_t)m) * sizeof(uint32_t), s));
     DevBuf<int> err;
-    err.alloc(arena, 5);
-    SKIS_HIP_TRY(hipMemsetAsync(err.ptr, 0, 5 * sizeof(int), s));
-    int *const mixed = err.ptr + 1; // read with the flags
+    constexpr int FLAGS = 8;
+    err.alloc(arena, FLAGS);
+    SKIS_HIP_TRY(hipMemsetAsync(err.ptr, 0, FLAGS * sizeof(int), s));
+    int *const mixed = err.ptr + 1, *const redo = err.ptr + 2; // read with the flags
     DevBuf<int32_t> long_rows;
     long_rows.alloc(arena, (size_t)n);
-    unsigned int *n_long = reinterpret_cast<unsigned int *>(err.ptr + 2);
-    unsigned int *next_long = reinterpret_cast<unsigned int *>(err.ptr + 3);
-    unsigned int *n_huge = reinterpret_cast<unsigned int *>(err.ptr + 4);
-    if (reinterpret_cast<uintptr_t>(out.P.ptr) & 15) throw Error{SKIS_EHIP, "internal error: P is not 16-byte aligned"};
+    unsigned int *n_long = reinterpret_cast<unsigned int *>(err.ptr + 3);
+    unsigned int *next_long = reinterpret_cast<unsigned int *>(err.ptr + 4);
+    unsigned int *n_huge = reinterpret_cast<unsigned int *>(err.ptr + 5);
+    unsigned int *n_pieces = reinterpret_cast<unsigned int *>(err.ptr + 6);
+    unsigned int *next_unit = reinterpret_cast<unsigned int *>(err.ptr + 7);
+    DevBuf<TailPiece> pieces;
+    // (a piece's last strides stay below 2^31; graphs within 2^14 edges of the limit go without tails)
+    if (!lt && m < (int64_t)INT32_MAX - TAIL_PIECE) pieces.alloc(arena, (size_t)tail_pieces_max(m));
+    const unsigned int max_pieces = (unsigned int)tail_pieces_max(m);
+    if (reinterpret_cast<uintptr_t>(P) & 15) throw Error{SKIS_EHIP, "internal error: P is not 16-byte aligned"};
     // The long rows' chains (bound by their length) run beside the short rows.  k_prep_long
     // follows k_find_long on the caller's stream and k_prep_rows goes to a second stream, which
     // first waits for the listing: the device then starts the chains first (when k_prep_rows
@@ -660,15 +875,25 @@ void preprocess(Arena &arena, int32_t n, int64_t m, const int32_t *row_ptr, cons
     } evg{&fork, &join};
     SKIS_HIP_TRY(hipEventCreateWithFlags(&join, hipEventDisableTiming));
     SKIS_HIP_TRY(hipEventRecord(fork, s));
-    hipLaunchKernelGGL(lt ? k_prep_long<true> : k_prep_long<false>, dim3((unsigned)device_cu_count()), dim3(256), 0, s,
-                       n, row_ptr, col, w, out.th.ptr, out.P.ptr, out.q.ptr, err.ptr, mixed, long_rows.ptr,
-                       n_long, n_huge, next_long);
+    auto launch_long = [&](TailPiece *tails) {
+        hipLaunchKernelGGL(lt ? k_prep_long<true> : k_prep_long<false>, dim3((unsigned)device_cu_count() * LONG_PER_CU),
+                           dim3(256), 0, s, n, row_ptr, col, w, out.th.ptr, P, out.q.ptr, err.ptr, mixed, long_rows.ptr,
+                           n_long, n_huge, next_long, tails, n_pieces, max_pieces);
+    };
+    launch_long(pieces.ptr);
+    if (pieces.ptr)
+        hipLaunchKernelGGL(k_prep_tails, dim3((unsigned)device_cu_count() * 4), dim3(256), 0, s, n, row_ptr, col, w,
+                           out.th.ptr, P, err.ptr, mixed, pieces.ptr, n_pieces, max_pieces, m, redo);
     const hipError_t long_err = hipGetLastError();
     // from here on, s waits for s2 before anything else, whatever fails
     hipError_t side_err = hipStreamWaitEvent(s2, fork, 0);
     if (side_err == hipSuccess) {
-        hipLaunchKernelGGL(k_prep_rows, dim3(prep_rows_grid(n)), dim3(256), 0, s2, n, m, row_ptr, col, w,
-                           out.row_ptr.ptr, out.rows.ptr, out.th.ptr, out.P.ptr, out.q.ptr, err.ptr, mixed, lt);
+        // some eight turns a wave; at most 8 units at a time, so that the last ones end together
+        const int64_t units = ((int64_t)n + 63) / 64, waves = (int64_t)device_cu_count() * ROWS_PER_CU;
+        const unsigned per = (unsigned)std::min<int64_t>(std::max<int64_t>(units / (waves * 8), 1), 8);
+        hipLaunchKernelGGL(lt ? k_prep_rows<true> : k_prep_rows<false>, dim3((unsigned)std::min(units, waves)), dim3(64), 0,
+                           s2, n, m, row_ptr, col, w, out.row_ptr.ptr, out.rows.ptr, out.th.ptr, P, out.q.ptr, err.ptr,
+                           mixed, next_unit, per);
         side_err = hipGetLastError();
     }
     const hipError_t rec_err = hipEventRecord(join, s2);
@@ -677,9 +902,16 @@ void preprocess(Arena &arena, int32_t n, int64_t m, const int32_t *row_ptr, cons
     SKIS_HIP_TRY(hipStreamWaitEvent(s, join, 0));
     SKIS_HIP_TRY(long_err);
     SKIS_HIP_TRY(side_err);
-    int hflags[2] = {0, 0};
+    int hflags[3] = {0, 0, 0};
     SKIS_HIP_TRY(hipMemcpyAsync(hflags, err.ptr, sizeof(hflags), hipMemcpyDeviceToHost, s));
     SKIS_HIP_TRY(hipStreamSynchronize(s));
+    if (hflags[2] && !hflags[0]) { // a factor moved a product that had been taken for constant
+        SKIS_HIP_TRY(hipMemsetAsync(next_long, 0, sizeof(int), s));
+        launch_long(nullptr);
+        SKIS_HIP_TRY(hipGetLastError());
+        SKIS_HIP_TRY(hipMemcpyAsync(hflags, err.ptr, sizeof(hflags), hipMemcpyDeviceToHost, s));
+        SKIS_HIP_TRY(hipStreamSynchronize(s));
+    }
     out.uniform = coins && !hflags[1];
     const int herr = hflags[0];
     if (herr) {

@@ -1,0 +1,117 @@
+"""Preprocessing at the edges of its split: rows at the lengths where a lane's, a wave's and a
+workgroup's part, units of rows that fill the LDS batch, runs of longer rows and empty ones, rows around
+the long chunk's size, products that stay at a denormal (or
+zero) for the rest of a long row, and ones that seem to and move once more.  Bit for bit with the
+oracle; a faulty edge deep inside a row is still refused."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+N = 3000
+
+
+@pytest.fixture(scope="module")
+def skis():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_1709_03565_amd import skis as s
+    return s
+
+
+def _graph(lens, weight, seed=1):
+    rng = np.random.default_rng(seed)
+    lens = np.concatenate([np.asarray(lens), np.zeros(N - len(lens), np.int64)])
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows = np.repeat(np.arange(N), lens)
+    col = rng.integers(0, N - 1, rp[-1])
+    col = (col + (col >= rows)).astype(np.int32)  # no self-loop
+    w = np.concatenate([weight(v, int(k), rng) for v, k in enumerate(lens)]).astype(np.float32)
+    return rp, col, w
+
+
+def _tri(v, k, rng):
+    return rng.choice([0.1, 0.01, 0.001], k)
+
+
+def _uniform(v, k, rng):
+    return np.full(k, 1.0 / max(k, 1))
+
+
+def _late(v, k, rng):  # stays at some units for several chunks, then is moved
+    w = np.full(k, (0.1, 0.01, 0.3)[v % 3])
+    w[20000 + 7 * v::9001] = (0.9, 1.0, 0.45)[v % 3]
+    return w
+
+
+def _ones(v, k, rng):
+    w = rng.random(k)
+    w[k // 3:k // 3 + 1] = 1.0
+    return w
+
+
+EDGE = [0, 1, 127, 128, 129, 0, 3, 1023, 1024, 1025, 191, 192, 193, 2047, 2048, 2049, 4095, 4096, 4097, 6143, 6145, 300, 301, 256, 256]
+FILL = [16] * 64 + [128] * 21 + [1] * 43 + [16] * 63 + [17] + [129] * 70 + [2] * 58 + [0, 128] * 9 + [1025, 3] * 90
+DEEP = [40000, 20000, 65535, 2 * 16384 + 3 * 2048, 50001, 30000, 7, 120000]
+
+
+@pytest.mark.parametrize("lens,weight", [(EDGE, _tri), (EDGE, _ones), (FILL, _uniform), (FILL, _tri), (DEEP, _tri),
+                                         (DEEP, _late), (DEEP, _ones), (DEEP, _uniform)],
+                         ids=["edge-tri", "edge-ones", "fill-uniform", "fill-tri", "deep-tri", "deep-late", "deep-ones",
+                              "deep-uniform"])
+def test_rows(skis, lens, weight):
+    rp, col, w = _graph(lens, weight)
+    out = skis.preprocess(rp, col, w)
+    P, q = oracle.row_prefix(rp, w)
+    W, C, _ = oracle.root_weights(q)
+    thr, alias = oracle.alias_build(W, C)
+    assert np.array_equal(out["P"].cpu().numpy()[:len(P)], P)
+    assert np.array_equal(out["q"].cpu().numpy(), q)
+    assert np.array_equal(out["W"].cpu().numpy().astype(np.uint64), W)
+    assert out["C"] == C and out["Gamma"] == oracle.gamma_total(q)
+    assert np.array_equal(out["thr"].cpu().numpy().astype(np.uint64), thr)
+    assert np.array_equal(out["alias"].cpu().numpy(), alias)
+    # the sampler's thresholds and row records come from the same kernels
+    T = 300
+    ora = oracle.build_sketch(rp, col, w, seed=5, j0=0, j1=T, nthreads=4)
+    sp, nodes, roots, probed = (x.cpu().numpy() for x in skis.build_sketch(rp, col, w, T, 5).export())
+    assert np.array_equal(sp, ora.sample_ptr) and np.array_equal(nodes, ora.nodes)
+    assert np.array_equal(roots, ora.roots) and np.array_equal(probed.astype(np.uint64), ora.probed)
+
+
+def test_products_at_an_odd_address(skis):
+    """A caller's P that is 8- but not 16-byte aligned."""
+    import torch
+    rp, col, w = _graph(EDGE + DEEP[:2], _tri)
+    P, q = oracle.row_prefix(rp, w)
+    d = [torch.from_numpy(x).cuda() for x in (rp, col, w)]
+    buf = torch.zeros(len(P) + 2, dtype=torch.float64, device="cuda")
+    qd = torch.zeros(N, dtype=torch.float64, device="cuda")
+    C, G = ctypes.c_uint64(), ctypes.c_double()
+    assert buf.data_ptr() % 16 == 0
+    ptr = lambda x, off=0: ctypes.c_void_p(x.data_ptr() + off)
+    st = skis.lib().skis_preprocess(ctypes.c_int32(N), ctypes.c_int64(len(P)), ptr(d[0]), ptr(d[1]), ptr(d[2]),
+                                    ptr(buf, 8), ptr(qd), None, None, None, ctypes.byref(C), ctypes.byref(G),
+                                    ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == 0
+    b = buf.cpu().numpy()
+    assert b[0] == 0 and b[-1] == 0 and np.array_equal(b[1:-1], P) and np.array_equal(qd.cpu().numpy(), q)
+
+
+@pytest.mark.parametrize("at", [100, 50000, 119999])
+@pytest.mark.parametrize("fault", ["col", "loop", "weight"])
+def test_faulty_edge_is_refused(skis, at, fault):
+    rp, col, w = _graph(DEEP, _tri)
+    v = len(DEEP) - 1
+    if fault == "col":
+        col[rp[v] + at] = N
+    elif fault == "loop":
+        col[rp[v] + at] = v
+    else:
+        w[rp[v] + at] = 1.5
+    with pytest.raises(skis.SkisError):
+        skis.preprocess(rp, col, w)

@@ -10,11 +10,12 @@ constexpr int EST_BLOCK = 1024;   // threads per query in k_estimate
 constexpr int EST_MAX_SET = 4096; // largest seed set one estimate workgroup holds in LDS
 constexpr int EST_WALK = 4;       // sample-list entries a thread walks per round, loads issued together
 
-constexpr int EST_HASH_SLOTS = 16384; // LDS hash of a light set's sample ids in k_est_light
+constexpr int EST_HASH_SLOTS = 16384; // LDS hash of a light set's sample ids in k_est_set
 constexpr int EST_HASH_MAX = 10922;   // list entries a light set's members hold at most (1.5 slots each)
-constexpr unsigned long long EST_PARKED = ~0ull; // cov of a set that k_est_light left to the next kernel
+constexpr uint64_t EST_WALK_MAX = 0xFFFF0000ull; // entries that k_est_set's walk counts in 32 bits
+constexpr unsigned long long EST_PARKED = ~0ull; // cov of a set that k_est_set left to the next kernel
 
-// What k_est_light reports (each word is only ever set to 1).
+// What k_est_set reports (each word is only ever set to 1).
 struct EstFlags {
     int ptr;    // set_ptr does not rise from 0
     int node;   // a node id outside [0, n)
@@ -78,13 +79,14 @@ void estimate_light(const Sketch &sk, int32_t nq, bool check, const int64_t *set
 // (nq + 1 words) and ticket (nq words) are scratch.
 void estimate_split(const Sketch &sk, int32_t nq, const int64_t *set_ptr, const int32_t *set_nodes,
                     unsigned long long *cov, double *est, uint32_t *heavy, uint32_t *ticket, hipStream_t s);
-// A batch of the service, nq checked sets: by estimate_light when light_only (no set's lists hold
-// more than EST_HASH_MAX entries and none is large), else one workgroup a set with a bitmap of T
-// bits; and the nlarge sets listed in large[] (device indexes into the CSR) by the chunked path with
+// A batch of the service, nq checked sets in one workgroup each, with a bitmap of T bits where the
+// set's lists hold more than EST_HASH_MAX entries; the nlarge sets listed in large[] (indexes into the
+// CSR: every set above EST_MAX_SET entries or EST_WALK_MAX list entries is) by the chunked path with
 // one node bitmap of n bits each in nodebits.  bitmaps holds a zeroed bitmap of bitmap_words words
-// for every workgroup (max(nq, nlarge) of them) and is left zeroed.  Stream-ordered; no host
+// for every workgroup (max(nq, nlarge) of them) and is left zeroed.  The CSR, large, cov and est may
+// be pinned host memory; cov of a set that met an error is not written.  Stream-ordered; no host
 // synchronisation.
-void estimate_launch(const Sketch &sk, int32_t nq, bool light_only, const int64_t *set_ptr, const int32_t *set_nodes,
+void estimate_launch(const Sketch &sk, int32_t nq, const int64_t *set_ptr, const int32_t *set_nodes,
                      const int64_t *large, int32_t nlarge, uint32_t *bitmaps, uint64_t bitmap_words,
                      uint32_t *nodebits, unsigned long long *cov, double *est, int *err, EstFlags *flags, hipStream_t s);
 // The ng large sets listed in qlist[g0 .. g0+ng) (set qlist[g0+b] uses bitmap b and node bitmap b).

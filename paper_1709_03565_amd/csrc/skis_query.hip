@@ -42,8 +42,9 @@ __device__ void bitonic_sort_lds(int32_t *buf, int P)
     }
 }
 
-// Flips the bit of sample j in bm for every lane of the wave with in = true and returns the
-// bits this lane flipped; every lane of the wave must call it.  A sample list is sorted by
+// flip_bits_wave flips the bit of sample j in bm for every lane of the wave with in = true and
+// returns the bits this lane flipped; every lane of the wave must call it (word_bits_wave is its
+// first half: the bits that a lane sets in its word if it is the one to do so).  A sample list is sorted by
 // sample id and a wave walks consecutive entries, so on a dense list (a hub's) neighbouring
 // lanes often share a bitmap word.  When any do, the bits of lanes with the same word are
 // OR-ed within aligned groups of 8 lanes by a segmented scan (a lane takes the running OR of
@@ -51,7 +52,7 @@ __device__ void bitonic_sort_lds(int32_t *buf, int P)
 // of another run with the same word only add bits of that word), and the last lane of each
 // run in a group sets them with one atomicOr.  Atomics on one word are serialised, so every
 // flip is counted once.  When no neighbours share a word, each lane flips its own bit.
-__device__ __forceinline__ unsigned long long flip_bits_wave(uint32_t *bm, int32_t j, bool in)
+__device__ __forceinline__ uint32_t word_bits_wave(int32_t j, bool in, bool *last)
 {
     const int lane = threadIdx.x & 63;
     const uint32_t w = (uint32_t)j >> 5;
@@ -59,27 +60,32 @@ __device__ __forceinline__ unsigned long long flip_bits_wave(uint32_t *bm, int32
     // the shuffle runs on every lane: under a mask it would read 0 from the masked lane 63
     const uint32_t nw = __shfl_down(w, 1, 64);
     const bool same_next = lane < 63 && nw == w;
-    bool last = true;
+    *last = true;
     if (__ballot(same_next) != 0ull) { // wave-uniform
 #pragma unroll
         for (int d = 1; d < 8; d <<= 1) {
             const uint32_t ow = __shfl_up(w, d, 64), oa = __shfl_up(acc, d, 64);
             if ((lane & 7) >= d && ow == w) acc |= oa;
         }
-        last = (lane & 7) == 7 || !same_next;
+        *last = (lane & 7) == 7 || !same_next;
     }
+    return acc;
+}
+
+__device__ __forceinline__ unsigned long long flip_bits_wave(uint32_t *bm, int32_t j, bool in)
+{
+    bool last;
+    const uint32_t acc = word_bits_wave(j, in, &last);
     if (!last || !acc) return 0ull;
-    const uint32_t old = atomicOr(&bm[w], acc);
+    const uint32_t old = atomicOr(&bm[(uint32_t)j >> 5], acc);
     return (unsigned long long)__popc(acc & ~old);
 }
 
-// One workgroup per query.  The set is taken in chunks of EST_MAX_SET entries; each chunk is
-// sorted and deduplicated in LDS.  LARGE workgroups (sets above one chunk) also keep a
-// bitmap of n bits that drops ids already met in an earlier chunk.  The distinct members'
-// q values are summed (compensated, in a fixed order) and their sample lists H(v) are
-// walked flat across the workgroup, flipping one bit per sample in a bitmap of T bits;
-// Cov(S) is the number of flips.
-template <bool LARGE>
+// Sets too large for k_est_set (members, or entries of their lists), one workgroup a set.  The set is
+// taken in chunks of EST_MAX_SET entries; each chunk is sorted and deduplicated in LDS, and a bitmap
+// of n bits drops ids already met in an earlier chunk.  The distinct members' q values are summed
+// (compensated, in a fixed order) and their sample lists H(v) are walked flat across the
+// workgroup, flipping one bit per sample in a bitmap of T bits; Cov(S) is the number of flips.
 __global__ __launch_bounds__(EST_BLOCK) void k_estimate(const int64_t *__restrict__ qlist, int64_t q0,
                                                         const int64_t *__restrict__ set_ptr,
                                                         const int32_t *__restrict__ set_nodes, int32_t n, uint64_t T,
@@ -99,7 +105,7 @@ __global__ __launch_bounds__(EST_BLOCK) void k_estimate(const int64_t *__restric
     __shared__ unsigned long long s_cov[EST_BLOCK / 64];
     __shared__ int s_bad;
 
-    const int64_t qi = LARGE ? qlist[q0 + blockIdx.x] : q0 + blockIdx.x;
+    const int64_t qi = qlist[q0 + blockIdx.x];
     const int tid = threadIdx.x;
     const int64_t a = set_ptr[qi], b = set_ptr[qi + 1];
     const int64_t k = b - a;
@@ -107,9 +113,8 @@ __global__ __launch_bounds__(EST_BLOCK) void k_estimate(const int64_t *__restric
         if (tid == 0) atomicOr(err, 1);
         return;
     }
-    if (!LARGE && k > EST_MAX_SET) return; // taken by the LARGE launch
     uint32_t *bm = bitmaps + (uint64_t)blockIdx.x * wordsT;
-    uint32_t *nb = LARGE ? nodebits + (uint64_t)blockIdx.x * wordsN : nullptr;
+    uint32_t *nb = nodebits + (uint64_t)blockIdx.x * wordsN;
     constexpr int IPT = EST_MAX_SET / EST_BLOCK;
 
     double sq = 0.0, cq = 0.0;
@@ -140,7 +145,7 @@ __global__ __launch_bounds__(EST_BLOCK) void k_estimate(const int64_t *__restric
         }
         if (P > 1) bitonic_sort_lds<EST_BLOCK>(buf, P);
 
-        // distinct members of the chunk (and, for LARGE, not met before), compacted in order
+        // distinct members of the chunk, not met before, compacted in order
         int32_t mine[IPT];
         int flags = 0, cntu = 0;
 #pragma unroll
@@ -149,7 +154,7 @@ __global__ __launch_bounds__(EST_BLOCK) void k_estimate(const int64_t *__restric
             const int32_t v = t < kc ? buf[t] : INT32_MAX;
             mine[r] = v;
             bool u = t < kc && (t == 0 || buf[t - 1] != v);
-            if (LARGE && u) {
+            if (u) {
                 const uint32_t bit = 1u << (v & 31);
                 u = !(atomicOr(&nb[v >> 5], bit) & bit);
             }
@@ -237,50 +242,26 @@ __global__ __launch_bounds__(EST_BLOCK) void k_estimate(const int64_t *__restric
         est_out[qi] = __dadd_rn(first, __dadd_rn(s, cc));
     }
     // leave the bitmaps clear for the next query
-    if (LARGE) {
-        for (uint64_t w = tid; w < wordsT; w += EST_BLOCK) bm[w] = 0u;
-        for (int64_t t = a + tid; t < b; t += EST_BLOCK) nb[set_nodes[t] >> 5] = 0u;
-    } else {
-        // one chunk: buf and dbase still hold it; the same rounds as the walk (a lane past E
-        // clears the word of entry E - 1 once more)
-        for (int64_t i0 = tid; i0 - (tid & 63) < E; i0 += (int64_t)EST_BLOCK * EST_WALK) { // wave-uniform
-            int64_t ix[EST_WALK];
-            int lv[EST_WALK];
-#pragma unroll
-            for (int u = 0; u < EST_WALK; ++u) {
-                const int64_t idx = i0 + (int64_t)u * EST_BLOCK;
-                ix[u] = idx < E ? idx : E - 1;
-                int lo = 0, hi = nu - 1;
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (dbase[mid] <= ix[u]) lo = mid; else hi = mid - 1;
-                }
-                lv[u] = lo;
-            }
-            int64_t np[EST_WALK];
-#pragma unroll
-            for (int u = 0; u < EST_WALK; ++u) np[u] = node_ptr[buf[lv[u]]];
-            int32_t jv[EST_WALK];
-#pragma unroll
-            for (int u = 0; u < EST_WALK; ++u) jv[u] = node_samples[np[u] + (ix[u] - dbase[lv[u]])];
-#pragma unroll
-            for (int u = 0; u < EST_WALK; ++u) { // the last lane of each run of equal words clears it
-                const uint32_t w = (uint32_t)jv[u] >> 5, nw = __shfl_down(w, 1, 64);
-                if ((threadIdx.x & 63) == 63 || nw != w) bm[w] = 0u;
-            }
-        }
-    }
+    for (uint64_t w = tid; w < wordsT; w += EST_BLOCK) bm[w] = 0u;
+    for (int64_t t = a + tid; t < b; t += EST_BLOCK) nb[set_nodes[t] >> 5] = 0u;
 }
 
 // ---------------------------------------------------------------------------------------
 // Estimates of sets of at most EST_MAX_SET entries.
 //
-// k_est_light: one workgroup a set.  The distinct members' list lengths come first; when they add
-// up to at most EST_HASH_MAX entries, the sample ids go into an LDS hash (Cov = ids that were not
-// there), so a light set touches no bitmap in memory and has nothing to clear; a walk that flips
-// bits of a T-bit bitmap in memory took two passes over the lists and a returning global atomic an
-// entry (about 390M a second for a CU).  Heavier sets are parked: cov = EST_PARKED, est = the sum
-// of q.
+// k_est_set: one workgroup a set.  The distinct members' list lengths come first; when they add up to
+// at most EST_HASH_MAX entries, the sample ids go into an LDS hash (Cov = ids that were not there), so
+// a light set touches no bitmap in memory and has nothing to clear; a walk that flips bits of a T-bit
+// bitmap in memory takes two passes over the lists and a returning global atomic an entry.  Heavier
+// sets are parked: cov = EST_PARKED, est = the sum of q.
+//
+// WALK (the service, where a second kernel for the parked sets would add its latency to every batch:
+// 1024 Zipf sets took 1.7 ms that way for 1.25): heavier sets are walked by the same workgroup with
+// a bitmap of T bits.  8 loads and then 8 atomics a lane are in flight (4 in turn before), the members
+// are searched between those of a wave's first and last entry, and their list begins wait in LDS:
+// batches of 256 Zipf(1.5) sets of 1-1000 members on 2^25 samples of the 4M-node TRI graph 350-520 ->
+// 200-330 us (by their heaviest set; 1000 members with 62k entries take 168 us, 16 in flight no less:
+// bound by the atomics, some 390M a second for a CU).
 //
 // k_est_split: the parked sets.  The lists are sorted by sample id, so a window of ids is a range
 // of every list: a workgroup takes one (set, window), finds the ranges by binary search, sets the
@@ -298,23 +279,25 @@ __device__ __forceinline__ double first_term(unsigned long long cov, double Gamm
 
 // check: 0, or the number of sets whose set_ptr this workgroup checks first (so that no set is
 // read by a set_ptr that does not rise from 0; at most EST_BLOCK of them).  flags: see EstFlags.
-__global__ __launch_bounds__(EST_BLOCK) void k_est_light(int32_t check, const int64_t *__restrict__ set_ptr,
+template <bool WALK>
+__global__ __launch_bounds__(EST_BLOCK) void k_est_set(int32_t check, const int64_t *__restrict__ set_ptr,
                                                          const int32_t *__restrict__ set_nodes, int32_t n, uint64_t T,
                                                          double Gamma, const double *__restrict__ qv,
                                                          const int64_t *__restrict__ node_ptr,
                                                          const int32_t *__restrict__ node_samples,
                                                          unsigned long long *__restrict__ cov_out,
                                                          double *__restrict__ est_out, uint32_t *__restrict__ ticket,
+                                                         uint32_t *__restrict__ bitmaps, uint64_t wordsT,
                                                          EstFlags *__restrict__ flags)
 {
     __shared__ int32_t buf[EST_MAX_SET];
-    __shared__ int32_t pre[EST_MAX_SET + 1];  // first entry of each member's list in the walk
+    __shared__ uint32_t pre[EST_MAX_SET + 1];  // first entry of each member's list in the walk
     __shared__ int64_t lbase[EST_MAX_SET];    // list begin - pre
     __shared__ uint32_t hash[EST_HASH_SLOTS];
     __shared__ double ps[EST_BLOCK], pc[EST_BLOCK];
     __shared__ int32_t s_scan[EST_BLOCK / 64 + 1];
     __shared__ int64_t s_scan64[EST_BLOCK / 64 + 1];
-    __shared__ uint32_t s_cov, s_next;
+    __shared__ uint32_t s_cov, s_next, s_clear;
     __shared__ int s_bad_ptr, s_bad;
 
     const int64_t qi = blockIdx.x;
@@ -322,7 +305,7 @@ __global__ __launch_bounds__(EST_BLOCK) void k_est_light(int32_t check, const in
     if (tid == 0) {
         s_bad_ptr = s_bad = 0;
         s_cov = 0u;
-        s_next = 0u;
+        s_next = s_clear = 0u;
     }
     __syncthreads();
     if (tid < check) {
@@ -335,8 +318,8 @@ __global__ __launch_bounds__(EST_BLOCK) void k_est_light(int32_t check, const in
         return;
     }
     const int64_t a = set_ptr[qi], b = set_ptr[qi + 1];
-    if (b - a > EST_MAX_SET) { // k_estimate<true>'s
-        if (tid == 0) {
+    if (b - a > EST_MAX_SET) { // k_estimate's
+        if (!WALK && tid == 0) {
             flags->large = 1;
             cov_out[qi] = 0ull; // not EST_PARKED by what the buffer held
         }
@@ -407,18 +390,21 @@ __global__ __launch_bounds__(EST_BLOCK) void k_est_light(int32_t check, const in
     ps[tid] = sq;
     pc[tid] = cq;
     const bool light = E <= (int64_t)EST_HASH_MAX;
+    if (WALK && (uint64_t)E > EST_WALK_MAX) return; // k_estimate's
     uint32_t slots = 64; // a power of two of at least 1.5 slots an entry
-    if (light) {
-        while (2 * slots < 3 * (uint32_t)E) slots <<= 1;
+    if (WALK || light) {
 #pragma unroll
         for (int r = 0; r < IPT; ++r) {
             const int t = tid * IPT + r;
             if (t < nu) {
-                pre[t] = (int32_t)(ex + dl[r]);
+                pre[t] = (uint32_t)(ex + dl[r]);
                 lbase[t] = np[r] - (ex + dl[r]);
             }
         }
-        if (tid == 0) pre[nu] = (int32_t)E;
+        if (tid == 0) pre[nu] = (uint32_t)E;
+    }
+    if (light) {
+        while (2 * slots < 3 * (uint32_t)E) slots <<= 1;
         for (uint32_t i = tid; i < slots; i += EST_BLOCK) hash[i] = 0xFFFFFFFFu;
     }
     __syncthreads();
@@ -430,7 +416,8 @@ __global__ __launch_bounds__(EST_BLOCK) void k_est_light(int32_t check, const in
             if (nu > EST_BLOCK) neumaier_add(s, cc, pc[t]); // a single member's compensation is +0
         }
     }
-    if (!light) {
+    uint32_t found = 0;
+    if (!light && !WALK) {
         if (tid == 0) {
             cov_out[qi] = EST_PARKED;
             est_out[qi] = __dadd_rn(s, cc);
@@ -439,9 +426,63 @@ __global__ __launch_bounds__(EST_BLOCK) void k_est_light(int32_t check, const in
         }
         return;
     }
+    if (!light) {
+        // a wave takes 64 U entries at a time, all its loads and then all its flips in flight; a lane
+        // past E repeats entry E - 1 (in bounds) and flips no bit
+        constexpr int U = 8;
+        uint32_t *const bm = bitmaps + (uint64_t)blockIdx.x * wordsT;
+        auto walk = [&](uint32_t *next, auto &&use) {
+            for (;;) {
+                uint32_t c = 0;
+                if (lane == 0) c = atomicAdd(next, 64u * U);
+                c = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
+                if (c >= (uint32_t)E) break;
+                // the member of an entry lies between those of the first and the last one
+                auto member = [&](uint32_t idx, int lo, int hi) {
+                    while (lo < hi) {
+                        const int mid = (lo + hi + 1) >> 1;
+                        if (pre[mid] <= idx) lo = mid; else hi = mid - 1;
+                    }
+                    return lo;
+                };
+                const int end = member(lane == 0 ? c : min(c + 64u * U, (uint32_t)E) - 1u, 0, nu - 1);
+                const int m0 = __builtin_amdgcn_readlane(end, 0), m1 = __builtin_amdgcn_readlane(end, 1);
+                int32_t jv[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t idx = min(c + (uint32_t)(u * 64 + lane), (uint32_t)E - 1u);
+                    jv[u] = node_samples[lbase[member(idx, m0, m1)] + idx];
+                }
+                use(c, jv);
+            }
+        };
+        walk(&s_next, [&](uint32_t c, const int32_t (&jv)[U]) {
+            uint32_t acc[U], old[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                bool last;
+                acc[u] = word_bits_wave(jv[u], c + (uint32_t)(u * 64 + lane) < (uint32_t)E, &last);
+                if (!last) acc[u] = 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                old[u] = 0u;
+                if (acc[u]) old[u] = atomicOr(&bm[(uint32_t)jv[u] >> 5], acc[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) found += (uint32_t)__popc(acc[u] & ~old[u]);
+        });
+        __syncthreads(); // every flip done
+        walk(&s_clear, [&](uint32_t, const int32_t (&jv)[U]) { // leave the bitmap clear for the next batch
+#pragma unroll
+            for (int u = 0; u < U; ++u) { // the last lane of each run of equal words clears it
+                const uint32_t w = (uint32_t)jv[u] >> 5, nw = __shfl_down(w, 1, 64);
+                if (lane == 63 || nw != w) bm[w] = 0u;
+            }
+        });
+    }
     const uint32_t sh = 32 - (31 - __clz((int)slots));
-    uint32_t found = 0;
-    for (;;) { // a wave takes 256 entries at a time
+    for (; light;) { // a wave takes 256 entries at a time
         uint32_t c = 0;
         if (lane == 0) c = atomicAdd(&s_next, 256u);
         c = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
@@ -449,7 +490,7 @@ __global__ __launch_bounds__(EST_BLOCK) void k_est_light(int32_t check, const in
         int32_t jv[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int idx = min((int)c + u * 64 + lane, (int)E - 1);
+            const uint32_t idx = min(c + (uint32_t)(u * 64 + lane), (uint32_t)E - 1u);
             int lo = 0, hi = nu - 1;
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
@@ -1296,8 +1337,9 @@ void estimate_light(const Sketch &sk, int32_t nq, bool check, const int64_t *set
 {
     if (nq <= 0) return;
     if (check && nq > EST_BLOCK) throw Error{SKIS_EHIP, "internal error: too many sets for a checked estimate"};
-    hipLaunchKernelGGL(k_est_light, dim3((unsigned)nq), dim3(EST_BLOCK), 0, s, check ? nq : 0, set_ptr, set_nodes, sk.n,
-                       sk.T, sk.est_scale(), sk.est_q(), sk.node_ptr.ptr, sk.node_samples.ptr, cov, est, ticket, flags);
+    hipLaunchKernelGGL(k_est_set<false>, dim3((unsigned)nq), dim3(EST_BLOCK), 0, s, check ? nq : 0, set_ptr, set_nodes, sk.n,
+                       sk.T, sk.est_scale(), sk.est_q(), sk.node_ptr.ptr, sk.node_samples.ptr, cov, est, ticket,
+                       (uint32_t *)nullptr, (uint64_t)0, flags);
     SKIS_HIP_TRY(hipGetLastError());
 }
 
@@ -1412,18 +1454,14 @@ void estimate_batch(const Sketch &sk, QueryScratch &qs, int32_t Q, const int64_t
     }
 }
 
-void estimate_launch(const Sketch &sk, int32_t nq, bool light_only, const int64_t *set_ptr, const int32_t *set_nodes,
+void estimate_launch(const Sketch &sk, int32_t nq, const int64_t *set_ptr, const int32_t *set_nodes,
                      const int64_t *large, int32_t nlarge, uint32_t *bitmaps, uint64_t bitmap_words,
                      uint32_t *nodebits, unsigned long long *cov, double *est, int *err, EstFlags *flags, hipStream_t s)
 {
-    if (light_only) {
-        estimate_light(sk, nq, false, set_ptr, set_nodes, cov, est, nullptr, flags, s);
-    } else if (nq > 0) {
-        // one kernel for all: a second one for the parked sets would add its latency to the batch's
-        // (a burst of 1024 Zipf sets took 1.7 ms that way, 1.25 ms this way)
-        hipLaunchKernelGGL(k_estimate<false>, dim3((unsigned)nq), dim3(EST_BLOCK), 0, s, (const int64_t *)nullptr,
-                           (int64_t)0, set_ptr, set_nodes, sk.n, sk.T, sk.est_scale(), sk.est_q(), sk.node_ptr.ptr,
-                           sk.node_samples.ptr, bitmaps, bitmap_words, (uint32_t *)nullptr, (uint64_t)0, cov, est, err);
+    if (nq > nlarge) {
+        hipLaunchKernelGGL(k_est_set<true>, dim3((unsigned)nq), dim3(EST_BLOCK), 0, s, 0, set_ptr, set_nodes, sk.n, sk.T,
+                           sk.est_scale(), sk.est_q(), sk.node_ptr.ptr, sk.node_samples.ptr, cov, est, (uint32_t *)nullptr,
+                           bitmaps, bitmap_words, flags);
         SKIS_HIP_TRY(hipGetLastError());
     }
     estimate_launch_large(sk, large, 0, nlarge, set_ptr, set_nodes, bitmaps, bitmap_words, nodebits, cov, est, err, s);
@@ -1435,7 +1473,7 @@ void estimate_launch_large(const Sketch &sk, const int64_t *qlist, int64_t g0, i
 {
     if (ng <= 0) return;
     const uint64_t wordsN = ((uint64_t)sk.n + 31) / 32;
-    hipLaunchKernelGGL(k_estimate<true>, dim3((unsigned)ng), dim3(EST_BLOCK), 0, s, qlist, g0, set_ptr, set_nodes,
+    hipLaunchKernelGGL(k_estimate, dim3((unsigned)ng), dim3(EST_BLOCK), 0, s, qlist, g0, set_ptr, set_nodes,
                        sk.n, sk.T, sk.est_scale(), sk.est_q(), sk.node_ptr.ptr, sk.node_samples.ptr, bitmaps, bitmap_words,
                        nodebits, wordsN, cov, est, err);
     SKIS_HIP_TRY(hipGetLastError());

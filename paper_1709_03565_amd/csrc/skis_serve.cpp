@@ -3,18 +3,19 @@
 // requests.
 //
 // Continuous batching: submitters append queries to a host queue; one worker thread owns
-// `depth` pipeline slots, each with its own HIP stream, pinned host staging, device CSR
-// buffers and zeroed bitmap scratch.  Whenever a slot is free and queries are waiting, the
+// `depth` pipeline slots, each with its own HIP stream, pinned host staging
+// and zeroed bitmap scratch.  Whenever a slot is free and queries are waiting, the
 // worker takes as many as the slot admits (by count, by total entries and by large sets),
 // except that a heavy set (one whose members' sample lists hold more than HEAVY_WORK entries,
 // a hub's set) runs in a batch of its own: a batch completes when its slowest set does, so a
 // hub set among light ones would hold them all for milliseconds, while alone it holds one
-// slot and the other slots keep serving.  It packs them into the slot's pinned CSR, and enqueues copy-in, the estimate kernels and
-// copy-out on the slot's stream without waiting.  It polls the slots' completion events,
+// slot and the other slots keep serving.  It packs them into the slot's pinned CSR and enqueues the estimate kernels, which read it
+// and write the answers to pinned memory, on the slot's stream without waiting.  It polls the slots' completion events,
 // and when a batch is done it stores each query's (Cov, I_hat) and completion time and
 // wakes the waiters.  A query's result does not depend on the batch it ran in: each set
 // takes its own workgroup and bitmap, and its sums run in a fixed order.
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <condition_variable>
 #include <cstring>
@@ -23,7 +24,6 @@
 #include <memory>
 #include <thread>
 #include <unordered_map>
-#include <unordered_set>
 
 #include "skis_internal.h"
 #include "skis_query.h"
@@ -44,18 +44,26 @@ struct Pending {
 // sketch holds about 60 thousand, its top hub 3 million).
 constexpr uint64_t HEAVY_WORK = 1ull << 18;
 
-// a slot's error words: k_estimate's at 0, k_est_light's flags after it
+constexpr uint16_t LONG_LIST = 0xFFFF;
+
+// Batches of light sets in flight before the next one waits for max_batch_queries queries or for one
+// of them to end: the streams share two hardware queues in most processes, where a third small batch
+// only waits (a burst of 1024 Zipf sets with four in flight 1.4-1.6 ms, with two 1.25-1.5).
+constexpr int LIGHT_IN_FLIGHT = 2;
+
+// a slot's error words: k_estimate's at 0, k_est_set's flags after it
 constexpr int ERR_FLAGS = 4, ERR_WORDS = ERR_FLAGS + (int)(sizeof(skis::EstFlags) / sizeof(int));
 
 struct Done {
     uint64_t cov;
     double est;
-    double latency_us;
+    double latency_us; // < 0: not answered yet
 };
 
 template <typename T>
 struct Pinned {
     T *ptr = nullptr;
+    T *dev = nullptr; // the same memory as the device addresses it
     size_t count = 0;
     Pinned() = default;
     Pinned(const Pinned &) = delete;
@@ -67,6 +75,7 @@ struct Pinned {
     void alloc(size_t n)
     {
         SKIS_HIP_TRY(hipHostMalloc((void **)&ptr, sizeof(T) * (n ? n : 1), hipHostMallocDefault));
+        SKIS_HIP_TRY(hipHostGetDevicePointer((void **)&dev, ptr, 0));
         count = n;
     }
 };
@@ -79,17 +88,12 @@ struct Slot {
     Pinned<int64_t> h_large;
     Pinned<unsigned long long> h_cov;
     Pinned<double> h_est;
-    Pinned<int> h_err;
-    skis::DevBuf<int64_t> d_ptr;
-    skis::DevBuf<int32_t> d_nodes;
-    skis::DevBuf<int64_t> d_large;
-    skis::DevBuf<unsigned long long> d_cov;
-    skis::DevBuf<double> d_est;
     skis::DevBuf<int> d_err;
     skis::DevBuf<uint32_t> bitmaps;  // max_batch_queries bitmaps of T bits
     skis::DevBuf<uint32_t> nodebits; // max_large node bitmaps of n bits
     std::vector<Pending> batch;
     bool busy = false;
+    bool heavy = false; // its batch is one heavy set
 };
 
 } // namespace
@@ -100,14 +104,19 @@ struct skis_server {
     int device = 0;
     uint64_t wordsT = 1, wordsN = 1;
     skis::Arena arena;
-    std::vector<int64_t> node_ptr; // host copy of the inverse index's offsets (n + 1), for the work of a set
+    std::vector<int64_t> node_ptr;     // host copy of the inverse index's offsets (n + 1), for the work of a set
+    std::vector<uint16_t> list_len;    // the lists' lengths, LONG_LIST where node_ptr tells (2 B of reads a member for
+                                       // 16 from a table four times the size: a member's read was most of a submission)
     std::vector<std::unique_ptr<Slot>> slots;
     std::thread worker;
     std::mutex mu;
     std::condition_variable cv_work, cv_done;
     std::deque<Pending> queue;
-    std::unordered_map<uint64_t, Done> results;
-    std::unordered_set<uint64_t> outstanding; // submitted, not yet collected by a wait
+    std::unordered_map<uint64_t, Done> results; // every ticket submitted and not yet collected by a wait
+    // of the queue, for the worker to see without the lock (written under mu): where it polled the slots
+    // under the lock, submitters met it there
+    std::atomic<size_t> queued{0};
+    std::atomic<bool> front_heavy{false};
     uint64_t next_ticket = 1;
     bool stop = false;
     std::string fault; // set when the worker stopped on an error
@@ -115,6 +124,11 @@ struct skis_server {
     uint64_t batches = 0, queries = 0, max_batch = 0;
     uint64_t hist[16] = {};
 
+    void queue_changed()
+    {
+        queued.store(queue.size(), std::memory_order_relaxed);
+        front_heavy.store(!queue.empty() && queue.front().work > HEAVY_WORK, std::memory_order_relaxed);
+    }
     void run();
     void launch(Slot &sl);
     void complete(Slot &sl);
@@ -134,51 +148,44 @@ void skis_server::launch(Slot &sl)
     const int32_t nq = (int32_t)sl.batch.size();
     int64_t off = 0;
     int32_t nl = 0;
-    bool light = true; // no set's lists hold more than the LDS hash takes
     for (int32_t i = 0; i < nq; ++i) {
         const auto &v = sl.batch[i].nodes;
-        light = light && !node_ptr.empty() && sl.batch[i].work <= (uint64_t)skis::EST_HASH_MAX &&
-                (int64_t)v.size() <= skis::EST_MAX_SET;
         sl.h_ptr.ptr[i] = off;
         if (!v.empty()) std::memcpy(sl.h_nodes.ptr + off, v.data(), sizeof(int32_t) * v.size());
         off += (int64_t)v.size();
-        if ((int64_t)v.size() > skis::EST_MAX_SET) sl.h_large.ptr[nl++] = i;
+        if ((int64_t)v.size() > skis::EST_MAX_SET || sl.batch[i].work > skis::EST_WALK_MAX) sl.h_large.ptr[nl++] = i;
+        sl.h_cov.ptr[i] = skis::EST_PARKED; // unanswered
     }
     sl.h_ptr.ptr[nq] = off;
+    // The kernels read the sets from the pinned staging and write the answers there: a set is read once,
+    // and six copies a batch had cost the worker and the queues more than the reads do (a burst of
+    // 1024 Zipf sets, with k_est_set's walk: 1.55 -> 1.45 ms).
     hipStream_t s = sl.stream;
-    SKIS_HIP_TRY(hipMemcpyAsync(sl.d_ptr.ptr, sl.h_ptr.ptr, sizeof(int64_t) * (size_t)(nq + 1), hipMemcpyHostToDevice, s));
-    if (off > 0)
-        SKIS_HIP_TRY(hipMemcpyAsync(sl.d_nodes.ptr, sl.h_nodes.ptr, sizeof(int32_t) * (size_t)off,
-                                    hipMemcpyHostToDevice, s));
-    if (nl > 0)
-        SKIS_HIP_TRY(hipMemcpyAsync(sl.d_large.ptr, sl.h_large.ptr, sizeof(int64_t) * (size_t)nl,
-                                    hipMemcpyHostToDevice, s));
-    skis::estimate_launch(k, nq, light, sl.d_ptr.ptr, sl.d_nodes.ptr, sl.d_large.ptr, nl, sl.bitmaps.ptr, wordsT,
-                          sl.nodebits.ptr, sl.d_cov.ptr, sl.d_est.ptr, sl.d_err.ptr,
+    skis::estimate_launch(k, nq, sl.h_ptr.dev, sl.h_nodes.dev, sl.h_large.dev, nl, sl.bitmaps.ptr, wordsT,
+                          sl.nodebits.ptr, sl.h_cov.dev, sl.h_est.dev, sl.d_err.ptr,
                           reinterpret_cast<skis::EstFlags *>(sl.d_err.ptr + ERR_FLAGS), s);
-    SKIS_HIP_TRY(hipMemcpyAsync(sl.h_cov.ptr, sl.d_cov.ptr, sizeof(unsigned long long) * (size_t)nq,
-                                hipMemcpyDeviceToHost, s));
-    SKIS_HIP_TRY(hipMemcpyAsync(sl.h_est.ptr, sl.d_est.ptr, sizeof(double) * (size_t)nq, hipMemcpyDeviceToHost, s));
-    SKIS_HIP_TRY(hipMemcpyAsync(sl.h_err.ptr, sl.d_err.ptr, sizeof(int) * ERR_WORDS, hipMemcpyDeviceToHost, s));
     SKIS_HIP_TRY(hipEventRecord(sl.done, s));
     sl.busy = true;
 }
 
 void skis_server::complete(Slot &sl)
 {
-    const skis::EstFlags &fl = *reinterpret_cast<const skis::EstFlags *>(sl.h_err.ptr + ERR_FLAGS);
-    if (sl.h_err.ptr[0] || fl.ptr || fl.node) {
-        // ids were checked at submission, so this is an internal fault: scratch may hold bits
-        throw skis::Error{SKIS_EHIP, "internal error in the estimate kernel (flags " +
-                                         std::to_string(sl.h_err.ptr[0] | fl.ptr | 2 * fl.node) + ")"};
-    }
+    for (size_t i = 0; i < sl.batch.size(); ++i)
+        if (sl.h_cov.ptr[i] == skis::EST_PARKED) {
+            // ids were checked at submission, so this is an internal fault: scratch may hold bits
+            int err[ERR_WORDS] = {};
+            SKIS_HIP_TRY(hipMemcpy(err, sl.d_err.ptr, sizeof(err), hipMemcpyDeviceToHost));
+            const skis::EstFlags &fl = *reinterpret_cast<const skis::EstFlags *>(err + ERR_FLAGS);
+            throw skis::Error{SKIS_EHIP, "internal error in the estimate kernel (flags " +
+                                             std::to_string(err[0] | fl.ptr | 2 * fl.node) + ")"};
+        }
     const auto now = Clock::now();
     const size_t nq = sl.batch.size();
     {
         std::lock_guard<std::mutex> g(mu);
         for (size_t i = 0; i < nq; ++i) {
             const double lat = std::chrono::duration<double, std::micro>(now - sl.batch[i].arrive).count();
-            results[sl.batch[i].ticket] = Done{(uint64_t)sl.h_cov.ptr[i], sl.h_est.ptr[i], lat};
+            results[sl.batch[i].ticket] = Done{(uint64_t)sl.h_cov.ptr[i], sl.h_est.ptr[i], lat > 0 ? lat : 0};
         }
         batches += 1;
         queries += nq;
@@ -197,23 +204,32 @@ void skis_server::run()
     try {
         SKIS_HIP_TRY(hipSetDevice(device));
         for (;;) {
+            // the slots are this thread's alone
             Slot *free_slot = nullptr;
             bool any_busy = false;
-            {
+            int in_flight = 0; // batches of light sets
+            for (auto &p : slots) {
+                if (!p->busy && !free_slot) free_slot = p.get();
+                any_busy |= p->busy;
+                in_flight += p->busy && !p->heavy ? 1 : 0;
+            }
+            if (!any_busy) {
                 std::unique_lock<std::mutex> g(mu);
-                for (auto &p : slots) any_busy |= p->busy;
-                if (!any_busy) cv_work.wait(g, [&] { return stop || !queue.empty(); });
-                if (stop && queue.empty() && !any_busy) return;
-                for (auto &p : slots)
-                    if (!p->busy) {
-                        free_slot = p.get();
-                        break;
-                    }
-                if (free_slot && !queue.empty()) {
+                cv_work.wait(g, [&] { return stop || !queue.empty(); });
+                if (stop && queue.empty()) return;
+            }
+            const size_t have = queued.load(std::memory_order_relaxed);
+            if (!have || (in_flight >= LIGHT_IN_FLIGHT && have < opt.max_batch_queries &&
+                          !front_heavy.load(std::memory_order_relaxed)))
+                free_slot = nullptr;
+            if (free_slot) {
+                std::lock_guard<std::mutex> g(mu);
+                if (!queue.empty()) {
                     // admission: by count, by entries (pinned staging) and by large sets
                     Slot &sl = *free_slot;
                     uint64_t entries = 0;
                     uint32_t large = 0;
+                    sl.heavy = queue.front().work > HEAVY_WORK;
                     while (!queue.empty() && sl.batch.size() < opt.max_batch_queries) {
                         const uint64_t e = queue.front().nodes.size();
                         const bool is_large = e > (uint64_t)skis::EST_MAX_SET;
@@ -227,8 +243,7 @@ void skis_server::run()
                         queue.pop_front();
                         if (heavy) break;
                     }
-                } else {
-                    free_slot = nullptr;
+                    queue_changed();
                 }
             }
             if (free_slot && !free_slot->batch.empty()) {
@@ -294,16 +309,29 @@ int submit_one(skis_server *sv, const int32_t *nodes, int32_t count, Clock::time
         if (nodes[i] < 0 || nodes[i] >= n) throw skis::Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
     Pending p;
     p.nodes.assign(nodes, nodes + count);
-    if (!sv->node_ptr.empty())
-        for (int32_t i = 0; i < count; ++i) p.work += (uint64_t)(sv->node_ptr[nodes[i] + 1] - sv->node_ptr[nodes[i]]);
+    if (!sv->node_ptr.empty()) {
+        uint64_t work = 0;
+        bool exact = true;
+        for (int32_t i = 0; i < count; ++i) {
+            const uint16_t len = sv->list_len[nodes[i]];
+            exact = exact && len != LONG_LIST;
+            work += len;
+        }
+        if (!exact)
+            for (int32_t i = 0; i < count; ++i)
+                if (sv->list_len[nodes[i]] == LONG_LIST)
+                    work += (uint64_t)(sv->node_ptr[nodes[i] + 1] - sv->node_ptr[nodes[i]]) - LONG_LIST;
+        p.work = work;
+    }
     p.arrive = arrive;
     {
         std::lock_guard<std::mutex> g(sv->mu);
         if (sv->stop) throw skis::Error{SKIS_EHIP, "server stopped: " + sv->fault};
         p.ticket = sv->next_ticket++;
-        sv->outstanding.insert(p.ticket);
+        sv->results.emplace(p.ticket, Done{0, 0.0, -1.0});
         if (ticket) *ticket = p.ticket;
         sv->queue.push_back(std::move(p));
+        sv->queue_changed();
     }
     sv->cv_work.notify_one();
     return SKIS_OK;
@@ -312,15 +340,19 @@ int submit_one(skis_server *sv, const int32_t *nodes, int32_t count, Clock::time
 int wait_one(skis_server *sv, uint64_t ticket, uint64_t *cov, double *est, double *latency_us)
 {
     std::unique_lock<std::mutex> g(sv->mu);
-    if (!sv->outstanding.count(ticket)) throw skis::Error{SKIS_EINVAL, "unknown or already collected ticket"};
-    sv->cv_done.wait(g, [&] { return sv->results.count(ticket) || sv->stop; });
     auto it = sv->results.find(ticket);
-    if (it == sv->results.end()) throw skis::Error{SKIS_EHIP, "server stopped: " + sv->fault};
+    if (it == sv->results.end()) throw skis::Error{SKIS_EINVAL, "unknown or already collected ticket"};
+    // (a second wait for the same ticket may collect it meanwhile, so it is looked up anew)
+    sv->cv_done.wait(g, [&] {
+        it = sv->results.find(ticket);
+        return it == sv->results.end() || it->second.latency_us >= 0 || sv->stop;
+    });
+    if (it == sv->results.end()) throw skis::Error{SKIS_EINVAL, "unknown or already collected ticket"};
+    if (it->second.latency_us < 0) throw skis::Error{SKIS_EHIP, "server stopped: " + sv->fault};
     if (cov) *cov = it->second.cov;
     if (est) *est = it->second.est;
     if (latency_us) *latency_us = it->second.latency_us;
     sv->results.erase(it);
-    sv->outstanding.erase(ticket);
     return SKIS_OK;
 }
 
@@ -368,6 +400,9 @@ int skis_server_create(const skis_sketch *sk, const skis_server_options *opt_in,
             sv->node_ptr.resize((size_t)sk->core.n + 1);
             SKIS_HIP_TRY(hipMemcpy(sv->node_ptr.data(), sk->core.node_ptr.ptr, sizeof(int64_t) * ((size_t)sk->core.n + 1),
                                    hipMemcpyDeviceToHost));
+            sv->list_len.resize((size_t)sk->core.n);
+            for (int32_t v = 0; v < sk->core.n; ++v)
+                sv->list_len[v] = (uint16_t)std::min<int64_t>(sv->node_ptr[v + 1] - sv->node_ptr[v], LONG_LIST);
         }
         const uint64_t nb = std::max<uint64_t>(opt.max_batch_queries, opt.max_large_sets);
         sv->arena.stream = nullptr; // allocations complete before any slot stream uses them (below)
@@ -381,12 +416,6 @@ int skis_server_create(const skis_sketch *sk, const skis_server_options *opt_in,
             s.h_large.alloc(opt.max_large_sets);
             s.h_cov.alloc(opt.max_batch_queries);
             s.h_est.alloc(opt.max_batch_queries);
-            s.h_err.alloc(ERR_WORDS);
-            s.d_ptr.alloc(sv->arena, opt.max_batch_queries + 1);
-            s.d_nodes.alloc(sv->arena, opt.max_batch_entries);
-            s.d_large.alloc(sv->arena, opt.max_large_sets);
-            s.d_cov.alloc(sv->arena, opt.max_batch_queries);
-            s.d_est.alloc(sv->arena, opt.max_batch_queries);
             s.d_err.alloc(sv->arena, ERR_WORDS);
             s.bitmaps.alloc(sv->arena, nb * sv->wordsT);
             s.nodebits.alloc(sv->arena, (uint64_t)opt.max_large_sets * sv->wordsN);
@@ -434,11 +463,11 @@ int skis_server_replay(skis_server *sv, int32_t num_queries, const int64_t *set_
         }
         std::vector<uint64_t> tickets((size_t)num_queries);
         const Clock::time_point t0 = Clock::now();
+        Clock::time_point now = t0;
         for (int32_t i = 0; i < num_queries; ++i) {
             const auto due = t0 + std::chrono::duration_cast<Clock::duration>(
                                       std::chrono::duration<double, std::micro>(arrival_us[i]));
-            while (Clock::now() < due) {
-            } // open loop: submit at the scheduled time, whatever is still in flight
+            while (now < due) now = Clock::now(); // open loop: submit at the scheduled time, whatever is still in flight
             submit_one(sv, set_nodes + set_ptr[i], (int32_t)(set_ptr[i + 1] - set_ptr[i]), due, &tickets[i]);
         }
         for (int32_t i = 0; i < num_queries; ++i) {

@@ -242,6 +242,51 @@ __device__ __forceinline__ uint32_t mask_rank(unsigned long long m, uint32_t bas
     return (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
 }
 
+// q of a row under the linear threshold model from its sum of weights
+__device__ __forceinline__ double lt_q(double sum) { return sum < 1.0 ? __dsub_rn(1.0, sum) : 0.0; }
+
+// The first e of [lo, hi) with above(e), hi if there is none (above never turns false again along
+// the range), looked for from the guess g in [lo, hi): both sides of it at once, then by doubling
+// steps.  A search of a row costs its random reads (some 85 G a second for the device), and rows of
+// equal or similar weights tell where the place is.
+template <typename Above>
+__device__ __forceinline__ int32_t first_above_from(int32_t lo, int32_t hi, int32_t g, Above &&above)
+{
+    const bool here = above(g), before = above(g > lo ? g - 1 : lo);
+    if (here && (g == lo || !before)) return g;
+    uint32_t step = 1; // (rows reach 2^31 - 1 edges)
+    if (here) { // in [lo, g - 1], and g - 1 is above
+        hi = g - 1;
+        while ((uint32_t)(hi - lo) > step) {
+            const int32_t x = hi - (int32_t)step;
+            if (!above(x)) {
+                lo = x + 1;
+                break;
+            }
+            hi = x;
+            step <<= 1;
+        }
+    } else { // in [g + 1, hi]
+        lo = g + 1;
+        while ((uint32_t)(hi - lo) > step) {
+            const int32_t x = lo + (int32_t)step - 1;
+            if (above(x)) {
+                hi = x;
+                break;
+            }
+            lo = x + 1;
+            step <<= 1;
+        }
+    }
+    while (lo < hi) {
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if (above(mid)) hi = mid;
+        else lo = mid + 1;
+    }
+    return lo;
+}
+
+
 // Value of lane s (uniform over the wave).
 __device__ __forceinline__ unsigned long long readlane64(unsigned long long v, int s)
 {

@@ -8,13 +8,17 @@
 // already in the sample.  A node's pick is keyed by (sample id, node) alone, so after the root
 // the walk is the orbit x_{k+1} = pick(x_k) of one fixed map: it ends, or it closes on itself.
 //
-// k_lt_walk: one lane per sample at a time; the walk's nodes sit in the lane's column of LDS
+// k_lt_walk (bound by random reads, some 85 G a second, and by their latencies in a row): one lane
+// per sample at a time; the walk's nodes sit in the lane's column of LDS
 // (at most LT_PATH of them, membership by a scan of the column).  The loop is flattened --
 // each iteration moves every lane's walk on by one node or starts the lane's next sample -- so
 // that a wave never idles while its longest walk finishes.  Samples that finish in an
 // iteration go to staging together: one wave-level prefix sum of their sizes places them in a
 // chunk of staging the wave reserved with one atomic.  Walks that outgrow LT_PATH are listed
-// for k_lt_long.
+// for k_lt_long.  A root's step runs the code of any other (a wave that held both had waited for
+// both chains of reads: 3.65 -> 3.0 ms for 16.8M samples of the 1M-node graph), its alias entry is
+// read when the lane starts the sample before, a row's bounds and sum are one record, and a wave
+// takes a range of sample ids, so that its results' lines fill up in L2 (3.0 -> 2.58 ms).
 //
 // k_lt_long: one thread per listed sample and no memory per sample: Brent's cycle finding
 // (R. P. Brent, BIT 20, 1980) on the orbit gives the number of distinct nodes before it ends or
@@ -41,16 +45,21 @@ struct LtCounters {
                                         // guard; 4: more samples listed for compaction than there are
 };
 
+// A row as a pick reads it: one access for its bounds and its sum of weights.
+struct alignas(16) LtRow {
+    int32_t b, e;
+    double sum;
+};
+
 struct LtArgs {
     int32_t n;
-    uint32_t count;
+    uint32_t count, per_wave; // samples, and a wave's share of them
     uint64_t j0;
     uint32_t seed_lo, seed_hi;
     uint64_t C;
     const AliasEntry *alias;
-    const int32_t *row_ptr;
+    const LtRow *rows;
     const double *S;       // running sums of w along each row
-    const double *q;       // 1 - gamma_v
     const int32_t *col;
     const float *w;
     int32_t *staging;
@@ -66,114 +75,138 @@ struct LtArgs {
     LtCounters *ctr;
 };
 
-// The first edge e of [lo, hi) with S[e] > theta, hi if there is none (S is nondecreasing
-// along a row: its terms w are not negative).
-__device__ __forceinline__ int32_t lt_first_above(const double *__restrict__ S, int32_t lo, int32_t hi, double theta)
+// The first edge e of [lo, hi) with S[e] > theta, hi if there is none (S is nondecreasing along a row:
+// its terms w are not negative).  sum: S of the last edge, or close to it: with all weights equal the
+// place is theta / sum of the row.  16.8M walks, 1M nodes: k_lt_walk 4.27 ->
+// 3.65 ms against halving the row.
+__device__ __forceinline__ int32_t lt_first_above(const double *__restrict__ S, int32_t lo, int32_t hi, double theta,
+                                                  double sum)
 {
-    while (lo < hi) {
-        const int32_t mid = lo + ((hi - lo) >> 1);
-        if (S[mid] > theta) hi = mid;
-        else lo = mid + 1;
-    }
-    return lo;
+    const double at = (double)(hi - lo) * (theta / sum);
+    const int32_t guess = lo + (at >= 0.0 && at < (double)(hi - lo) ? (int32_t)at : 0);
+    return first_above_from(lo, hi, guess, [&](int32_t e) { return S[e] > theta; });
 }
 
-// Root of the sample with id (jl, jh) and the in-neighbour it picks (exactly one); deg = the
-// root's in-degree.  False for a root outside [0, n) or without in-edges (impossible with a
-// valid table: a root has gamma > 0).
-__device__ __forceinline__ bool lt_root(const LtArgs &a, uint32_t jl, uint32_t jh, int32_t &root, int32_t &first,
-                                        uint32_t &deg)
+// The alias entry and the bucket that the root of sample (jl, jh) is drawn from, and the root.
+struct LtDraw {
+    AliasEntry ae;
+    int32_t b;
+    uint64_t r;
+};
+
+__device__ __forceinline__ LtDraw lt_draw(const LtArgs &a, uint32_t jl, uint32_t jh)
 {
     uint64_t X, Y;
     philox2x64(0u, jl, jh, TAG_ROOT, a.seed_lo, a.seed_hi, X, Y);
-    const uint64_t b = __umul64hi(X, (uint64_t)a.n);
-    const uint64_t r = __umul64hi(Y, a.C);
-    const AliasEntry ae = a.alias[b];
-    root = r < ae.thr ? (int32_t)b : ae.alias;
-    if (root < 0 || root >= a.n) return false;
-    const int32_t rb = a.row_ptr[root], re = a.row_ptr[root + 1];
-    if (re <= rb) return false;
-    deg = (uint32_t)(re - rb);
-    philox2x64(0u, jl, jh, TAG_FIRST, a.seed_lo, a.seed_hi, X, Y);
-    const double U = (double)(X >> 11) * 0x1p-53;
-    const double theta = __dmul_rn(U, __dsub_rn(1.0, a.q[root]));
-    int32_t e = lt_first_above(a.S, rb, re, theta);
-    if (e >= re) { // theta rounded up to the row's sum: the last in-edge of positive weight
-        e = re - 1;
-        while (e > rb && a.w[e] == 0.0f) --e;
-    }
-    first = a.col[e];
-    return true;
+    LtDraw d;
+    d.b = (int32_t)__umul64hi(X, (uint64_t)a.n);
+    d.r = __umul64hi(Y, a.C);
+    d.ae = a.alias[d.b];
+    return d;
 }
 
-// The in-neighbour node x picks in the sample with id (jl, jh), -1 for none; deg = x's in-degree.
-__device__ __forceinline__ int32_t lt_pick(const LtArgs &a, uint32_t jl, uint32_t jh, int32_t x, uint32_t &deg)
+// -1 for a root outside [0, n) (impossible with a valid table)
+__device__ __forceinline__ int32_t lt_drawn(const LtArgs &a, const LtDraw &d)
 {
-    const int32_t rb = a.row_ptr[x], re = a.row_ptr[x + 1];
+    const int32_t root = d.r < d.ae.thr ? d.b : d.ae.alias;
+    return root < 0 || root >= a.n ? -1 : root;
+}
+
+// The in-neighbour that node x picks in the sample with id (jl, jh); deg = x's in-degree.  The root
+// picks exactly one (-1 without in-edges, impossible with a valid table: a root has gamma > 0), the
+// others one or none (-1).
+__device__ __forceinline__ int32_t lt_pick(const LtArgs &a, uint32_t jl, uint32_t jh, int32_t x, bool is_root,
+                                           uint32_t &deg)
+{
+    const LtRow row = a.rows[x];
     uint64_t X, Y;
-    philox2x64((uint32_t)x, jl, jh, TAG_LT, a.seed_lo, a.seed_hi, X, Y);
-    const double V = (double)(X >> 11) * 0x1p-53;
-    deg = (uint32_t)(re - rb);
-    const int32_t f = lt_first_above(a.S, rb, re, V);
-    return f < re ? a.col[f] : -1;
+    philox2x64(is_root ? 0u : (uint32_t)x, jl, jh, is_root ? TAG_FIRST : TAG_LT, a.seed_lo, a.seed_hi, X, Y);
+    deg = (uint32_t)(row.e - row.b);
+    if (row.e <= row.b) return -1;
+    double theta = (double)(X >> 11) * 0x1p-53;
+    if (is_root) theta = __dmul_rn(theta, __dsub_rn(1.0, lt_q(row.sum))); // gamma of the row
+    else if (!(row.sum > theta)) return -1;
+    int32_t e = lt_first_above(a.S, row.b, row.e, theta, row.sum);
+    if (is_root && e >= row.e) { // theta rounded up to the row's sum: the last in-edge of positive weight
+        e = row.e - 1;
+        while (e > row.b && a.w[e] == 0.0f) --e;
+    }
+    return a.col[e];
+}
+
+__global__ __launch_bounds__(256) void k_lt_rows(int32_t n, const int32_t *__restrict__ row_ptr, const double *__restrict__ S,
+                                                 LtRow *__restrict__ rows)
+{
+    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (int64_t)gridDim.x * 256) {
+        const int32_t b = row_ptr[v], e = row_ptr[v + 1];
+        rows[v] = {b, e, e > b ? S[e - 1] : 0.0};
+    }
 }
 
 __global__ __launch_bounds__(LT_BLOCK) void k_lt_walk(LtArgs a)
 {
     __shared__ int32_t s_path[LT_PATH * LT_BLOCK];
     int32_t *const path = s_path + threadIdx.x; // node k of the lane's walk at path[k * LT_BLOCK]
-    const uint32_t stride = gridDim.x * LT_BLOCK;
-    uint32_t i = blockIdx.x * LT_BLOCK + threadIdx.x; // the lane's current sample
+    // the wave's samples [i0, i1) and the first one that no lane has taken: neighbouring lanes' results
+    // go out within a few iterations of each other, so the L2 puts their lines together (with the
+    // lanes a grid apart, each result was a write of its own: 60M write requests for 16.8M samples)
+    const uint32_t wave = blockIdx.x * (LT_BLOCK / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const uint32_t i0 = (uint32_t)min((uint64_t)a.count, (uint64_t)wave * a.per_wave);
+    const uint32_t i1 = (uint32_t)min((uint64_t)a.count, (uint64_t)i0 + a.per_wave);
+    uint32_t next = i0 + 64, i = i0 + lane, inext = i1; // the lane's current sample and its next one
     int len = 0;                                       // nodes of the walk so far (0: start sample i)
     int32_t cur = 0;                                   // the node picked last, not yet checked
     uint32_t jl = 0, jh = 0;
     unsigned long long probed = 0;
     unsigned long long n_fin = 0, n_ent = 0, n_prb = 0, n_picks = 0;
     unsigned long long wpos = 0, wend = 0; // the wave's staging chunk (the same in every lane)
-    while (__ballot(i < a.count) != 0ull) {
+    LtDraw draw{}; // of the lane's current sample until it starts, of its next one after
+    if (i < i1) draw = lt_draw(a, (uint32_t)(a.j0 + i), (uint32_t)((a.j0 + i) >> 32));
+    while (__ballot(i < i1) != 0ull) {
         bool fin = false;
-        if (i < a.count) {
-            if (len == 0) {
+        const bool start = i < i1 && len == 0;
+        const unsigned long long starting = __ballot(start);
+        if (i < i1) {
+            bool step = true;
+            if (start) {
                 const uint64_t j = a.j0 + i;
                 jl = (uint32_t)j;
                 jh = (uint32_t)(j >> 32);
-                int32_t root = 0, first = 0;
-                uint32_t deg = 0;
-                if (lt_root(a, jl, jh, root, first, deg)) {
-                    path[0] = root;
-                    len = 1;
-                    probed = deg;
-                    cur = first;
-                    a.rec[i] = make_int4(root, 0, 0, 0);
-                } else {
+                cur = lt_drawn(a, draw);
+                if (cur < 0) { // reported below, as a root without in-edges
                     atomicOr(&a.ctr->err, 1);
-                    path[0] = 0;
-                    len = 1;
-                    probed = 0;
-                    a.rec[i] = make_int4(0, 0, 0, 0);
-                    fin = true;
+                    cur = 0;
+                    step = false;
                 }
+                a.rec[i] = make_int4(cur, 0, 0, 0);
+                probed = 0;
+                inext = next + (uint32_t)__popcll(starting & ((1ull << lane) - 1ull));
+                if (inext < i1) draw = lt_draw(a, (uint32_t)(a.j0 + inext), (uint32_t)((a.j0 + inext) >> 32));
+                fin = !step;
             } else {
                 bool seen = false;
                 for (int k = 0; k < len; ++k) seen |= path[k * LT_BLOCK] == cur;
-                if (seen) {
-                    fin = true;
-                } else if (len == LT_PATH) {
+                fin = seen;
+                step = !seen;
+                if (!seen && len == LT_PATH) {
                     a.long_list[atomicAdd(&a.ctr->n_long, 1ull)] = i;
                     len = 0;
-                    i += stride;
-                } else {
-                    path[len * LT_BLOCK] = cur;
-                    ++len;
-                    uint32_t deg = 0;
-                    const int32_t nx = lt_pick(a, jl, jh, cur, deg);
-                    probed += deg;
-                    ++n_picks;
-                    if (nx < 0) fin = true;
-                    else cur = nx;
+                    i = inext;
+                    step = false;
                 }
             }
+            if (step || (start && fin)) path[len++ * LT_BLOCK] = cur;
+            if (step) {
+                uint32_t deg = 0;
+                const int32_t nx = lt_pick(a, jl, jh, cur, start, deg);
+                if (start && nx < 0) atomicOr(&a.ctr->err, 1);
+                probed += deg;
+                n_picks += start ? 0ull : 1ull;
+                if (nx < 0) fin = true;
+                else cur = nx;
+            }
         }
+        next += (uint32_t)__popcll(starting);
         // the samples finished in this iteration go to staging together
         const uint32_t need = fin ? (uint32_t)len : 0u;
         const uint32_t incl = wave_incl_scan(need);
@@ -200,7 +233,7 @@ __global__ __launch_bounds__(LT_BLOCK) void k_lt_walk(LtArgs a)
                 n_ent += (unsigned long long)len;
                 n_prb += probed;
                 len = 0;
-                i += stride;
+                i = inext;
             }
             wpos += total;
         }
@@ -229,7 +262,7 @@ __device__ int64_t lt_orbit_length(const LtArgs &a, uint32_t jl, uint32_t jh, in
     int32_t tort = first, hare = first;
     uint64_t idx = 0, power = 1, lam = 0;
     for (;;) {
-        const int32_t nx = lt_pick(a, jl, jh, hare, deg);
+        const int32_t nx = lt_pick(a, jl, jh, hare, false, deg);
         ++picks;
         if (nx < 0 || nx == root) return (int64_t)idx + 1; // the orbit ends after x_idx, all distinct
         hare = nx;
@@ -246,14 +279,14 @@ __device__ int64_t lt_orbit_length(const LtArgs &a, uint32_t jl, uint32_t jh, in
     // the first index mu with x_mu = x_{mu + lam}
     int32_t p = first, r = first;
     for (uint64_t k = 0; k < lam; ++k) {
-        r = lt_pick(a, jl, jh, r, deg);
+        r = lt_pick(a, jl, jh, r, false, deg);
         ++picks;
         if (r < 0) return -1;
     }
     uint64_t mu = 0;
     while (p != r) {
-        p = lt_pick(a, jl, jh, p, deg);
-        r = lt_pick(a, jl, jh, r, deg);
+        p = lt_pick(a, jl, jh, p, false, deg);
+        r = lt_pick(a, jl, jh, r, false, deg);
         picks += 2;
         ++mu;
         if (p < 0 || r < 0 || mu > guard) return -1;
@@ -270,10 +303,11 @@ __global__ __launch_bounds__(LT_LONG_BLOCK) void k_lt_long(LtArgs a)
         const uint32_t i = a.long_list[t];
         const uint64_t j = a.j0 + i;
         const uint32_t jl = (uint32_t)j, jh = (uint32_t)(j >> 32);
-        int32_t root = 0, first = 0;
         uint32_t deg = 0;
         int64_t len = -1;
-        if (lt_root(a, jl, jh, root, first, deg)) len = lt_orbit_length(a, jl, jh, root, first, n_picks);
+        const int32_t root = lt_drawn(a, lt_draw(a, jl, jh));
+        const int32_t first = root < 0 ? -1 : lt_pick(a, jl, jh, root, true, deg);
+        if (first >= 0) len = lt_orbit_length(a, jl, jh, root, first, n_picks);
         if (len < 0) {
             atomicOr(&a.ctr->err, 2);
             a.out_size[i] = 1;
@@ -291,7 +325,7 @@ __global__ __launch_bounds__(LT_LONG_BLOCK) void k_lt_long(LtArgs a)
             for (int64_t k = 0; k < len; ++k) {
                 a.staging[off + 1 + (unsigned long long)k] = x;
                 uint32_t dx = 0;
-                const int32_t nx = lt_pick(a, jl, jh, x, dx);
+                const int32_t nx = lt_pick(a, jl, jh, x, false, dx);
                 probed += dx;
                 ++n_picks;
                 x = nx < 0 ? 0 : nx; // the last pick (none, the root or a repeat) is not used
@@ -342,6 +376,11 @@ void sample_lt(Arena &arena, const Prep &prep, int32_t n, const LtIo &io, LtStat
     DevBuf<LtCounters> ctr;
     long_list.alloc(arena, count ? count : 1);
     ctr.alloc(arena, 1);
+    DevBuf<LtRow> rows;
+    rows.alloc(arena, (size_t)n);
+    hipLaunchKernelGGL(k_lt_rows, dim3((unsigned)std::min<int64_t>(((int64_t)n + 255) / 256, (int64_t)device_cu_count() * 8)),
+                       dim3(256), 0, s, n, prep.row_ptr.ptr, prep.P.ptr, rows.ptr);
+    SKIS_HIP_TRY(hipGetLastError());
     int blocks_per_cu = 0;
     SKIS_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks_per_cu, k_lt_walk, LT_BLOCK, 0));
     if (blocks_per_cu < 1) blocks_per_cu = 1;
@@ -369,14 +408,14 @@ void sample_lt(Arena &arena, const Prep &prep, int32_t n, const LtIo &io, LtStat
         LtArgs A{};
         A.n = n;
         A.count = count;
+        A.per_wave = (uint32_t)((((uint64_t)count + waves - 1) / waves + 63) / 64 * 64);
         A.j0 = io.first_id;
         A.seed_lo = io.seed_lo;
         A.seed_hi = io.seed_hi;
         A.C = prep.C;
         A.alias = prep.alias.ptr;
-        A.row_ptr = prep.row_ptr.ptr;
+        A.rows = rows.ptr;
         A.S = prep.P.ptr;
-        A.q = prep.q.ptr;
         A.col = prep.col;
         A.w = prep.w;
         A.staging = io.staging->ptr;

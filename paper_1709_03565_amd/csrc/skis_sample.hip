@@ -99,14 +99,15 @@ __global__ __launch_bounds__(256) void k_roots(uint64_t j0, uint32_t count, cons
         }
         philox2x64(0u, jl, jh, TAG_FIRST, seed_lo, seed_hi, X, Y);
         const double U = (double)(X >> 11) * 0x1p-53;
-        const double theta = __dmul_rn(U, __dsub_rn(1.0, q[root]));
-        // first e in the row with 1 - P[e] > theta (1 - P is nondecreasing along the row)
-        int32_t lo = rb, hi = re;
-        while (lo < hi) {
-            const int32_t mid = lo + ((hi - lo) >> 1);
-            if (__dsub_rn(1.0, P[mid]) > theta) hi = mid; else lo = mid + 1;
-        }
-        int32_t istar = lo;
+        const double qr = q[root];
+        const double theta = __dmul_rn(U, __dsub_rn(1.0, qr));
+        // first e in the row with 1 - P[e] > theta (1 - P is nondecreasing along the row); with all
+        // weights equal it is at log(1 - theta) / log(q) of the row.  16.8M roots: 1.83 ->
+        // 1.45 ms (1M nodes, weighted cascade), 2.13 -> 1.86 (4M, trivalency) against halving the row
+        // (bound by the random reads: alias entry, row bounds, q, P, col)
+        const float at = (float)(re - rb) * (__logf((float)__dsub_rn(1.0, theta)) / __logf((float)qr));
+        const int32_t guess = rb + (at >= 0.0f && at < (float)(re - rb) ? min((int32_t)at, re - rb - 1) : 0);
+        int32_t istar = first_above_from(rb, re, guess, [&](int32_t e) { return __dsub_rn(1.0, P[e]) > theta; });
         if (istar >= re) { // theta rounded up to gamma: last in-edge of positive probability
             istar = re - 1;
             while (istar > rb && w[istar] == 0.0f) --istar;

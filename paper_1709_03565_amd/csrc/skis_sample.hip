@@ -1596,6 +1596,11 @@ __global__ __launch_bounds__(BLOCK, (sample_min_waves<S, RCAP, QPL, TIER>())) vo
 // most of its lanes although a small sample offers about three a pass.  Samples that outgrow a
 // slot go on to the four-slot kernel with their state.
 constexpr int FRONT_SLOTS = 16, FRONT_RCAP = 44, FRONT_HCAP = 64;
+// Samples from which the front runs: below, its 82 thousand slots are taken a few times at most and
+// the launch is its longest samples, which the four-slot kernel ends sooner by itself: 200 thousand
+// samples (15k nodes) 0.56 ms with it and 0.43 without, 1M 1.12 and 1.05, 4M 1.9 and 3.1; 1M-node WC
+// graph 1M 2.53 and 2.51, 4M 5.9 and 7.1.
+constexpr uint32_t FRONT_MIN = 1u << 20;
 
 template <bool UNIFORM>
 __global__ __launch_bounds__(64) void k_sample_front(SampleArgs a)
@@ -2318,7 +2323,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
         uni && cfg.slots == 4 && cfg.visited == 192 && cfg.qpl == 1 ? kTier0Uniform : v0.fn;
     // the front runs before the default first tier; not under a cap on device memory, which its
     // handover records would count against
-    const bool front = !lt && cfg.form != 1 && cfg.threads == 64 && cfg.slots == 4 && cfg.visited == 192 &&
+    const bool front = !lt && count >= FRONT_MIN && cfg.form != 1 && cfg.threads == 64 && cfg.slots == 4 && cfg.visited == 192 &&
                        cfg.qpl == 1 && !arena.cap;
     const SampleKernel tier_front = prep.uniform ? k_sample_front<true> : k_sample_front<false>;
     const SampleKernel tier1 = uni ? kTierMidUniform : vm.fn;

@@ -24,6 +24,7 @@
 #include <memory>
 #include <thread>
 #include <unordered_map>
+#include <unordered_set>
 
 #include "skis_internal.h"
 #include "skis_query.h"
@@ -46,9 +47,11 @@ constexpr uint64_t HEAVY_WORK = 1ull << 18;
 
 constexpr uint16_t LONG_LIST = 0xFFFF;
 
-// Batches of light sets in flight before the next one waits for max_batch_queries queries or for one
-// of them to end: the streams share two hardware queues in most processes, where a third small batch
-// only waits (a burst of 1024 Zipf sets with four in flight 1.4-1.6 ms, with two 1.25-1.5).
+// Batches of light sets in flight before the next one waits for max_batch_queries queries, for one of
+// them to end or for QUIET without a new query: the streams share two hardware queues in most
+// processes, where a third small batch only waits (a burst of 1024 Zipf sets with four in flight
+// 1.4-1.6 ms, with two 1.25-1.5; a burst of few queries has nothing to wait for).
+constexpr auto QUIET = std::chrono::microseconds(3);
 constexpr int LIGHT_IN_FLIGHT = 2;
 
 // a slot's error words: k_estimate's at 0, k_est_set's flags after it
@@ -57,7 +60,7 @@ constexpr int ERR_FLAGS = 4, ERR_WORDS = ERR_FLAGS + (int)(sizeof(skis::EstFlags
 struct Done {
     uint64_t cov;
     double est;
-    double latency_us; // < 0: not answered yet
+    double latency_us;
 };
 
 template <typename T>
@@ -110,17 +113,22 @@ struct skis_server {
     std::vector<std::unique_ptr<Slot>> slots;
     std::thread worker;
     std::mutex mu;
-    std::condition_variable cv_work, cv_done;
+    std::condition_variable cv_work; // of mu
+    std::condition_variable cv_done; // of done_mu
     std::deque<Pending> queue;
-    std::unordered_map<uint64_t, Done> results; // every ticket submitted and not yet collected by a wait
+    std::unordered_set<uint64_t> outstanding; // submitted, not yet collected by a wait
     // of the queue, for the worker to see without the lock (written under mu): where it polled the slots
     // under the lock, submitters met it there
-    std::atomic<size_t> queued{0};
+    alignas(64) std::atomic<size_t> queued{0};
     std::atomic<bool> front_heavy{false};
     uint64_t next_ticket = 1;
-    bool stop = false;
+    std::atomic<bool> stop{false}; // written under mu and done_mu
     std::string fault; // set when the worker stopped on an error
-    // statistics (under mu)
+    // the answers, under a lock of their own: a batch's end holds it for its queries' entries, and under
+    // mu submitters had waited there
+    alignas(64) std::mutex done_mu;
+    std::unordered_map<uint64_t, Done> results;
+    // statistics (under done_mu)
     uint64_t batches = 0, queries = 0, max_batch = 0;
     uint64_t hist[16] = {};
 
@@ -182,10 +190,10 @@ void skis_server::complete(Slot &sl)
     const auto now = Clock::now();
     const size_t nq = sl.batch.size();
     {
-        std::lock_guard<std::mutex> g(mu);
+        std::lock_guard<std::mutex> g(done_mu);
         for (size_t i = 0; i < nq; ++i) {
             const double lat = std::chrono::duration<double, std::micro>(now - sl.batch[i].arrive).count();
-            results[sl.batch[i].ticket] = Done{(uint64_t)sl.h_cov.ptr[i], sl.h_est.ptr[i], lat > 0 ? lat : 0};
+            results[sl.batch[i].ticket] = Done{(uint64_t)sl.h_cov.ptr[i], sl.h_est.ptr[i], lat};
         }
         batches += 1;
         queries += nq;
@@ -203,6 +211,8 @@ void skis_server::run()
 {
     try {
         SKIS_HIP_TRY(hipSetDevice(device));
+        size_t had = 0; // queries waiting at the last look, and since when as many
+        Clock::time_point since{};
         for (;;) {
             // the slots are this thread's alone
             Slot *free_slot = nullptr;
@@ -219,9 +229,15 @@ void skis_server::run()
                 if (stop && queue.empty()) return;
             }
             const size_t have = queued.load(std::memory_order_relaxed);
-            if (!have || (in_flight >= LIGHT_IN_FLIGHT && have < opt.max_batch_queries &&
-                          !front_heavy.load(std::memory_order_relaxed)))
-                free_slot = nullptr;
+            bool hold = false;
+            if (free_slot && have && in_flight >= LIGHT_IN_FLIGHT && have < opt.max_batch_queries &&
+                !front_heavy.load(std::memory_order_relaxed)) {
+                const auto now = Clock::now();
+                if (have != had) since = now;
+                hold = have != had || now - since < QUIET;
+            }
+            had = have;
+            if (!have || hold) free_slot = nullptr;
             if (free_slot) {
                 std::lock_guard<std::mutex> g(mu);
                 if (!queue.empty()) {
@@ -266,12 +282,12 @@ void skis_server::run()
             if (!progressed) std::this_thread::yield();
         }
     } catch (const skis::Error &e) {
-        std::lock_guard<std::mutex> g(mu);
+        std::scoped_lock g(mu, done_mu);
         fault = e.msg;
         stop = true;
         cv_done.notify_all();
     } catch (const std::exception &e) {
-        std::lock_guard<std::mutex> g(mu);
+        std::scoped_lock g(mu, done_mu);
         fault = e.what();
         stop = true;
         cv_done.notify_all();
@@ -328,7 +344,7 @@ int submit_one(skis_server *sv, const int32_t *nodes, int32_t count, Clock::time
         std::lock_guard<std::mutex> g(sv->mu);
         if (sv->stop) throw skis::Error{SKIS_EHIP, "server stopped: " + sv->fault};
         p.ticket = sv->next_ticket++;
-        sv->results.emplace(p.ticket, Done{0, 0.0, -1.0});
+        sv->outstanding.insert(p.ticket);
         if (ticket) *ticket = p.ticket;
         sv->queue.push_back(std::move(p));
         sv->queue_changed();
@@ -339,21 +355,27 @@ int submit_one(skis_server *sv, const int32_t *nodes, int32_t count, Clock::time
 
 int wait_one(skis_server *sv, uint64_t ticket, uint64_t *cov, double *est, double *latency_us)
 {
-    std::unique_lock<std::mutex> g(sv->mu);
-    auto it = sv->results.find(ticket);
-    if (it == sv->results.end()) throw skis::Error{SKIS_EINVAL, "unknown or already collected ticket"};
-    // (a second wait for the same ticket may collect it meanwhile, so it is looked up anew)
-    sv->cv_done.wait(g, [&] {
-        it = sv->results.find(ticket);
-        return it == sv->results.end() || it->second.latency_us >= 0 || sv->stop;
-    });
-    if (it == sv->results.end()) throw skis::Error{SKIS_EINVAL, "unknown or already collected ticket"};
-    if (it->second.latency_us < 0) throw skis::Error{SKIS_EHIP, "server stopped: " + sv->fault};
-    if (cov) *cov = it->second.cov;
-    if (est) *est = it->second.est;
-    if (latency_us) *latency_us = it->second.latency_us;
-    sv->results.erase(it);
-    return SKIS_OK;
+    {
+        std::lock_guard<std::mutex> g(sv->mu);
+        if (!sv->outstanding.count(ticket)) throw skis::Error{SKIS_EINVAL, "unknown or already collected ticket"};
+    }
+    {
+        std::unique_lock<std::mutex> g(sv->done_mu);
+        sv->cv_done.wait(g, [&] { return sv->results.count(ticket) || sv->stop; });
+        auto it = sv->results.find(ticket);
+        if (it != sv->results.end()) {
+            if (cov) *cov = it->second.cov;
+            if (est) *est = it->second.est;
+            if (latency_us) *latency_us = it->second.latency_us;
+            sv->results.erase(it);
+            g.unlock();
+            std::lock_guard<std::mutex> gq(sv->mu);
+            sv->outstanding.erase(ticket);
+            return SKIS_OK;
+        }
+    }
+    std::lock_guard<std::mutex> g(sv->mu);
+    throw skis::Error{SKIS_EHIP, "server stopped: " + sv->fault};
 }
 
 } // namespace
@@ -486,7 +508,7 @@ int skis_server_get_stats(skis_server *sv, skis_server_stats *st)
 {
     return serve_guarded([&]() -> int {
         if (!sv || !st) throw skis::Error{SKIS_EINVAL, "NULL argument"};
-        std::lock_guard<std::mutex> g(sv->mu);
+        std::lock_guard<std::mutex> g(sv->done_mu);
         std::memset(st, 0, sizeof(*st));
         st->batches = sv->batches;
         st->queries = sv->queries;
@@ -501,7 +523,7 @@ void skis_server_destroy(skis_server *sv)
 {
     if (!sv) return;
     {
-        std::lock_guard<std::mutex> g(sv->mu);
+        std::scoped_lock g(sv->mu, sv->done_mu);
         sv->stop = true;
     }
     sv->cv_work.notify_all();

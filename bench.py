@@ -35,25 +35,28 @@ def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
 
 
-def sample_bytes(T: int, entries: int, probed: int) -> int:
+def sample_bytes(T: int, entries: int, probed: int, thresholds: bool = True) -> int:
     """Bytes the sampler must move for whole samples: per sample the root record (20 B) and
-    its result meta (size 4 + offset 8 + probed 8 B); per node of R_j its row bounds (8 B) and
-    its staged id (4 B); per probed in-edge its (col, coin threshold) record (8 B)."""
-    return 40 * T + 12 * entries + 8 * probed
+    its result meta (size 4 + offset 8 + probed 8 B); per node of R_j its row record (8 B), its
+    head (4 B) and its staged id (4 B); per probed in-edge its coin threshold (4 B; none where
+    every row has one threshold: thresholds false)."""
+    return 40 * T + 16 * entries + (4 * probed if thresholds else 0)
 
 
-def launch_bytes(inf, t: int, lt: bool = False) -> int:
+def launch_bytes(inf, t: int, lt: bool = False, thresholds: bool = True) -> int:
     """Bytes one sampler tier's launch must move for the work it did: the root record and
-    result meta of every sample it finished (40 B) and their staged ids (4 B a node), the row
-    bounds of every node it expanded (8 B) and the record of every in-edge it swept (8 B).
+    result meta of every sample it finished (40 B), their heads and staged ids (8 B a node), the
+    row record of every node it expanded (8 B) and the threshold of every in-edge it swept (4 B;
+    none where every row has one threshold, which its record holds: thresholds false).
     A sample resumed from an earlier tier is charged only for what this launch expanded.
-    Linear threshold kernels (lt): per sample the alias entry (16 B), the root's row bounds
-    (8 B), q (8 B), one running sum (8 B), the picked id (4 B) and the result meta (36 B); per
-    further node of R_j its row bounds, one running sum and the picked id (20 B); per node its
-    staged id (4 B): 60 B a sample + 24 B a node."""
+    Linear threshold kernels (lt): per sample the alias entry (16 B), the root's row record
+    (16 B), one running sum (8 B), the picked id (4 B) and the result meta (36 B); per further
+    node of R_j its row record, one running sum and the picked id (28 B); per node its staged id
+    (4 B): 52 B a sample + 32 B a node."""
     if lt:
-        return 60 * inf.tier_samples[t] + 24 * inf.tier_entries[t]
-    return 40 * inf.tier_samples[t] + 4 * inf.tier_entries[t] + 8 * inf.tier_items[t] + 8 * inf.tier_swept[t]
+        return 52 * inf.tier_samples[t] + 32 * inf.tier_entries[t]
+    return (40 * inf.tier_samples[t] + 8 * inf.tier_entries[t] + 8 * inf.tier_items[t]
+            + (4 * inf.tier_swept[t] if thresholds else 0))
 
 
 # (threads, slots, visited, quads per lane) -> (hash size, items per pass) of the first-tier
@@ -74,6 +77,18 @@ def tier_kernel_names(opts):
     hcap, icap = _TIER0[key]
     t0 = "k_sample<%d, %d, %d, %d, %d, %d, 0>" % (key[0], key[1], key[2], hcap, icap, key[3])
     return [t0, TIER1_KERNEL, TIER2_KERNEL, TIER3_KERNEL]
+
+
+def launched_names(opts, workload):
+    """The tiers' kernels on a workload: on weighted-cascade graphs, whose rows have one threshold
+    each, the first three run as k_sample_uniform in the default shape."""
+    names = tier_kernel_names(opts)
+    shape = (opts.get("threads_per_block", 64), opts.get("slots_per_block", 4), opts.get("visited_threshold", 192),
+             opts.get("quads_per_lane", 1))
+    if workload.endswith("_wc"):
+        names = [x.replace("k_sample<", "k_sample_uniform<") if t in (1, 2) or (t == 0 and shape == (64, 4, 192, 1)) else x
+                 for t, x in enumerate(names)]
+    return names
 
 
 def cpu_model() -> str:
@@ -164,7 +179,7 @@ def tier_lines(infos, names, workload, lt=False):
     for t in range(2 if lt else 4):
         ms = sum(getattr(x, "ms_tier%d" % t) for x in infos) / len(infos)
         inf = infos[-1]
-        b = launch_bytes(inf, t, lt)
+        b = launch_bytes(inf, t, lt, thresholds=not workload.endswith("_wc"))
         gbs = b / (ms * 1e-3) / 1e9 if ms > 0 else 0.0
         out.append({"tier": t, "kernel": names[t], "launch_ms": ms, "alg_bytes_per_launch": b,
                     "achieved_gbs": gbs, "frac_of_hbm_peak": gbs / HBM_PEAK_GBS,
@@ -420,7 +435,7 @@ def full_step_workload(name, dev, steps, warmup, k, queries, plain_compare, serv
            "ms_per_step": elapsed * 1000.0 / steps, "samples_per_s": T * steps / elapsed,
            "sampling_samples_per_s": T / (samp_ms * 1e-3), "edges_probed_per_s": inf.probed_total * steps / elapsed,
            "entries": inf.entries, "probed_total": inf.probed_total, "stages_ms": stage_means(infos),
-           "tiers": tier_lines(infos, LT_KERNELS if lt else tier_kernel_names({}), name, lt)}
+           "tiers": tier_lines(infos, LT_KERNELS if lt else launched_names({}, name), name, lt)}
     if plain_compare:
         sk = skis.build_sketch(rp, col, w, T, inputs.SAMPLE_SEED, form=1, build_inverse_index=0)
         pinf = sk.info()
@@ -557,12 +572,13 @@ def main():
     inf = infos[-1]
     ms_step = elapsed * 1000.0 / args.steps
     value = T * args.steps / elapsed
-    names = LT_KERNELS if lt else tier_kernel_names(opts)
+    names = LT_KERNELS if lt else launched_names(opts, name)
     tiers = tier_lines(infos, names, name, lt)
     dom = max(tiers, key=lambda x: x["launch_ms"])
     samp_ms = sum(x.ms_roots + x.ms_sample + x.ms_compact for x in infos) / len(infos)
     sampler_ms = sum(x.ms_tier0 + x.ms_tier1 + x.ms_tier2 + x.ms_tier3 for x in infos) / len(infos)
-    b_chain = 60 * T + 24 * inf.entries if lt else sample_bytes(T, inf.entries, inf.probed_total)
+    b_chain = (52 * T + 32 * inf.entries if lt else
+               sample_bytes(T, inf.entries, inf.probed_total, thresholds=not name.endswith("_wc")))
     line = {
         "metric": "SKIS samples/s",
         "value": value,
@@ -604,9 +620,10 @@ def main():
             "traffic": dom["traffic"],
             "alg_bytes_per_launch": dom["alg_bytes_per_launch"],
             "launch_ms": dom["launch_ms"],
-            "note": ("the LT walk kernel with the longest launch; bytes = 60 per sample + 24 per node" if lt else
-                     "the sampler tier with the longest launch; bytes = 40 per finished sample + 4 per staged "
-                     "node + 8 per expanded node + 8 per swept in-edge of that launch"),
+            "note": ("the LT walk kernel with the longest launch; bytes = 52 per sample + 32 per node" if lt else
+                     "the sampler tier with the longest launch; bytes = 40 per finished sample + 8 per staged "
+                     "node + 8 per expanded node + 4 per swept in-edge of that launch (0 where every row has one "
+                     "threshold: the launch is then bound by the instructions of its coins)"),
             "sampler_alg_bytes": b_chain,
             "sampler_ms": sampler_ms,
             "sampler_gbs": b_chain / (sampler_ms * 1e-3) / 1e9,

@@ -179,7 +179,7 @@ def tier_lines(infos, names, workload, lt=False):
     for t in range(2 if lt else 4):
         ms = sum(getattr(x, "ms_tier%d" % t) for x in infos) / len(infos)
         inf = infos[-1]
-        b = launch_bytes(inf, t, lt, thresholds=not workload.endswith("_wc"))
+        b = launch_bytes(inf, t, lt, thresholds=t == 3 or not workload.endswith("_wc"))
         gbs = b / (ms * 1e-3) / 1e9 if ms > 0 else 0.0
         out.append({"tier": t, "kernel": names[t], "launch_ms": ms, "alg_bytes_per_launch": b,
                     "achieved_gbs": gbs, "frac_of_hbm_peak": gbs / HBM_PEAK_GBS,

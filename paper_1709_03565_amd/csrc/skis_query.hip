@@ -1,7 +1,9 @@
 // skis_query.hip -- queries on the device-resident sketch:
-//   k_estimate   Eq. (eq21): Cov(S) by marking the samples of every v in S in a bitmap over
-//                the T samples (a sample counts once, when its bit first flips), and
+//   k_est_*      Eq. (eq21): Cov(S) by collecting the samples of every v in S in an LDS hash (few
+//                list entries) or by windows of sample ids over the device (many), and
 //                I_hat(S) = fl(fl(Cov * Gamma) / T) + sum_{v in S} q_v (compensated sum).
+//   k_estimate   the same for sets of more members than a workgroup holds: marks the samples in
+//                a bitmap over the T samples (a sample counts once, when its bit first flips).
 //   k_greedy_*   Alg. 3: the node of largest gain fl(fl(Delta * Gamma) / T) + q (Eq. margin),
 //                smallest id on ties; Delta kept exact by decrementing the members of every
 //                newly covered sample.

@@ -1,16 +1,18 @@
 // skis_sample.hip -- IIS sampling (Alg. 1) and compaction into the CSR sketch (Alg. 2).
 //
 //   k_roots        one thread per sample: root by the alias table (Eq. probu) and first
-//                  live in-edge i* by Eq. (probn) (binary search over the prefix products)
+//                  live in-edge i* by Eq. (probn) (a search of the prefix products from a guess)
 //   k_sample<...>  persistent sampler: every workgroup keeps S samples in flight, each
 //                  with its visited set and node list; the unexpanded nodes of all slots
 //                  form one flat list of (slot, edge range) items, and the lanes sweep the
-//                  edges of all items four at a time (two 16-byte loads and one Philox call
-//                  per aligned edge quad).  Tiers 0 and 1 keep the visited set in LDS (an
+//                  edges of all items four at a time (one 16-byte load of thresholds, none where
+//                  every row has one, and one Philox call per aligned edge quad; a head is
+//                  read when its edge is live).  A front of sixteen small slots a wave goes
+//                  before tier 0 where there are samples enough.  Tiers 0 and 1 keep the visited set in LDS (an
 //                  open-addressing hash) and hand a sample to the next tier when it outgrows
 //                  the hash or meets an in-degree above big_row; tier 2 keeps a hash and a
 //                  node list sized to the sample in HBM (one sample per one-wave workgroup,
-//                  thousands in flight); tier 3 keeps a bitmap of n bits and a node list of
+//                  thousands in flight) or, for few samples, in LDS (eight waves a sample); tier 3 keeps a bitmap of n bits and a node list of
 //                  n entries per sample in HBM (one sample per 1024-thread workgroup).
 //   k_gather_*     sorts each sample's nodes and writes the CSR in sample order.
 //

@@ -116,7 +116,7 @@ struct skis_server {
     std::condition_variable cv_work; // of mu
     std::condition_variable cv_done; // of done_mu
     std::deque<Pending> queue;
-    std::unordered_set<uint64_t> outstanding; // submitted, not yet collected by a wait
+    std::unordered_set<uint64_t> outstanding; // submitted, not yet taken by a wait
     // of the queue, for the worker to see without the lock (written under mu): where it polled the slots
     // under the lock, submitters met it there
     alignas(64) std::atomic<size_t> queued{0};
@@ -357,7 +357,7 @@ int wait_one(skis_server *sv, uint64_t ticket, uint64_t *cov, double *est, doubl
 {
     {
         std::lock_guard<std::mutex> g(sv->mu);
-        if (!sv->outstanding.count(ticket)) throw skis::Error{SKIS_EINVAL, "unknown or already collected ticket"};
+        if (!sv->outstanding.erase(ticket)) throw skis::Error{SKIS_EINVAL, "unknown or already collected ticket"};
     }
     {
         std::unique_lock<std::mutex> g(sv->done_mu);
@@ -368,13 +368,11 @@ int wait_one(skis_server *sv, uint64_t ticket, uint64_t *cov, double *est, doubl
             if (est) *est = it->second.est;
             if (latency_us) *latency_us = it->second.latency_us;
             sv->results.erase(it);
-            g.unlock();
-            std::lock_guard<std::mutex> gq(sv->mu);
-            sv->outstanding.erase(ticket);
             return SKIS_OK;
         }
     }
     std::lock_guard<std::mutex> g(sv->mu);
+    sv->outstanding.insert(ticket); // not collected
     throw skis::Error{SKIS_EHIP, "server stopped: " + sv->fault};
 }
 

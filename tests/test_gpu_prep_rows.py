@@ -1,8 +1,8 @@
 """Preprocessing at the edges of its split: rows at the lengths where a lane's, a wave's and a
-workgroup's part, units of rows that fill the LDS batch, runs of longer rows and empty ones, rows around
-the long chunk's size, products that stay at a denormal (or
-zero) for the rest of a long row, and ones that seem to and move once more.  Bit for bit with the
-oracle; a faulty edge deep inside a row is still refused."""
+workgroup's part, units of rows that fill the LDS batch, runs of longer rows and empty ones, rows
+around the long chunk's size, products that stay at a denormal (or zero) for the rest of a long
+row, and ones that seem to and move once more.  Bit for bit with the oracle; a faulty edge deep
+inside a row is still refused."""
 import ctypes
 
 import numpy as np

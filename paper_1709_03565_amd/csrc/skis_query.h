@@ -51,6 +51,21 @@ constexpr int GREEDY_BIG = 512;    // in the one-workgroup form, a sample above 
 constexpr int GREEDY_SMALL_TILES = 2048;
 constexpr uint64_t GREEDY_SMALL_ENTRIES = 1ull << 19;
 
+// A newly covered sample in a queue of k_greedy_cover: its first entry (a sketch may hold 2^33 entries
+// and more) and its entries; 12 bytes.
+struct CoverItem {
+    uint32_t lo, hi;
+    int32_t size;
+    __host__ __device__ void set(int64_t a, int64_t b)
+    {
+        lo = (uint32_t)a;
+        hi = (uint32_t)(a >> 32);
+        size = (int32_t)(b - a);
+    }
+    __host__ __device__ int64_t first() const { return (int64_t)((uint64_t)hi << 32 | lo); }
+    __host__ __device__ int32_t len() const { return size; }
+};
+
 // One recount work item: entries [p0, p0 + len) of node v's list.
 struct RecountItem {
     int64_t p0;

@@ -1057,8 +1057,7 @@ __global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restr
                                                       int32_t *__restrict__ delta0, int32_t *__restrict__ delta1)
 {
     __shared__ int32_t hd[GREEDY_HOT];
-    // (first entry, entries) of the newly covered samples: 33 bits of offset, 31 of length
-    __shared__ int2 queue[4][64 * MARK_RUN];
+    __shared__ CoverItem queue[4][64 * MARK_RUN]; // the newly covered samples
     const int32_t v = st->vstar;
     if (v < 0) return;
     const bool update = !heavy_round(st, T);
@@ -1097,7 +1096,7 @@ __global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restr
     // a light round: most of the list is covered already, so the words are read first, all at once,
     // and only bits still clear are set by atomics, all at once again (one word after the other had
     // cost a memory latency each: 91 us a round on average at 2^25 samples, now 70)
-    int2 *q = queue[wid];
+    CoverItem *q = queue[wid];
     for (int64_t c0 = a + wave * 64 * MARK_RUN; c0 < b; c0 += nwaves * 64 * MARK_RUN) { // uniform per wave
         int32_t js[MARK_RUN];
         uint32_t wd[MARK_RUN], old[MARK_RUN];
@@ -1125,10 +1124,7 @@ __global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restr
         int pos = incl - cnt;
 #pragma unroll
         for (int t = 0; t < MARK_RUN; ++t)
-            if (fresh & (1u << t)) {
-                const int64_t sa = sptr[js[t]], sb = sptr[js[t] + 1];
-                q[pos++] = make_int2((int32_t)(sa >> 1), (int32_t)(((sb - sa) << 1) | (sa & 1)));
-            }
+            if (fresh & (1u << t)) q[pos++].set(sptr[js[t]], sptr[js[t] + 1]);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1136,9 +1132,8 @@ __global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restr
         for (int i0 = 0; i0 < tot; i0 += 4) {
             const int i = i0 + g;
             if (i >= tot) continue;
-            const int2 x = q[i];
-            const int64_t sa = ((int64_t)(uint32_t)x.x << 1) | (x.y & 1);
-            const int len = (int)((uint32_t)x.y >> 1);
+            const int64_t sa = q[i].first();
+            const int len = q[i].len();
             for (int t = gl; t < len; t += 16) {
                 const int32_t u = nodes[sa + t];
                 const int32_t h = hot_id ? hot_id[u] : -1;

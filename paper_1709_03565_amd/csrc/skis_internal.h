@@ -67,8 +67,8 @@ struct DevBuf {
     {
         reset();
         arena = &a;
-        count = n;
         ptr = (T *)a.alloc(sizeof(T) * (n ? n : 1));
+        count = n; // after the allocation: a refused one leaves an empty buffer
     }
     void reset()
     {

@@ -76,7 +76,6 @@ struct RecountItem {
 // Per-sketch scratch for estimate.
 struct QueryScratch {
     DevBuf<uint32_t> bitmaps; // sets above EST_MAX_SET entries: one bitmap of T bits each in flight
-    uint64_t bitmap_words = 0;
     DevBuf<int> err;
     DevBuf<uint32_t> split;   // the parked sets' list and tickets
     DevBuf<EstFlags> flags;   // used when no pinned place is free

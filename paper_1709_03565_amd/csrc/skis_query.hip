@@ -1418,9 +1418,8 @@ void estimate_batch(const Sketch &sk, QueryScratch &qs, int32_t Q, const int64_t
         // bitmaps for up to 64 sets at a time, about 256 MiB
         uint64_t group = std::max<uint64_t>((256ull << 20) / (per * 4), 1);
         group = std::min<uint64_t>(std::min<uint64_t>(group, 64), large.size());
-        if (qs.bitmap_words < group * per) {
+        if (qs.bitmaps.count < group * per) {
             qs.bitmaps.alloc(arena, group * per);
-            qs.bitmap_words = group * per;
             hipLaunchKernelGGL(k_fill_q<uint32_t>, dim3(gridq(group * per, 256)), dim3(256), 0, s, group * per,
                                qs.bitmaps.ptr, 0u);
             SKIS_HIP_TRY(hipGetLastError());
@@ -1440,7 +1439,7 @@ void estimate_batch(const Sketch &sk, QueryScratch &qs, int32_t Q, const int64_t
         SKIS_HIP_TRY(hipStreamSynchronize(s));
         if (herr) {
             // a workgroup that stopped early may have left bits set: clear all scratch
-            hipLaunchKernelGGL(k_fill_q<uint32_t>, dim3(gridq(qs.bitmap_words, 256)), dim3(256), 0, s, qs.bitmap_words,
+            hipLaunchKernelGGL(k_fill_q<uint32_t>, dim3(gridq(qs.bitmaps.count, 256)), dim3(256), 0, s, (uint64_t)qs.bitmaps.count,
                                qs.bitmaps.ptr, 0u);
             SKIS_HIP_TRY(hipStreamSynchronize(s));
         }

@@ -56,7 +56,8 @@ typedef struct skis_options {
     uint32_t slots_per_block;     /* samples in flight per workgroup of the first sampler tier */
     uint32_t visited_threshold;   /* nodes per sample kept in LDS by the first tier before the sample
                                      moves to the next tier */
-    uint32_t big_row;             /* in-degree above which the first tier hands a sample on */
+    uint32_t big_row;             /* in-degree above which the first tier hands a sample on (at most
+                                     2^22 is used: larger rows are the last tier's) */
     uint32_t build_inverse_index; /* 1 (default): build node->samples for estimate / greedy; 0: build only */
     uint32_t threads_per_block;   /* 64 (default: one wave per workgroup) or 256.  Supported
                                      (threads, slots, visited, quads_per_lane):

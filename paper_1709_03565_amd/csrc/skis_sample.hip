@@ -236,6 +236,13 @@ template <int S, int RCAP, int QPL, int TIER> constexpr int sample_min_waves()
 // one in 17 to 34 swept edges on the weighted-cascade workloads).  Otherwise a sweep reads the
 // quad's four thresholds (16 bytes).
 // ---------------------------------------------------------------------------------------
+// Rows above this leave every tier but the bitmap tier, whatever the caller's big_row: a pass's quads
+// (1024 items at most; 64 in a one-wave workgroup, whose sweep marks then grow by 2^26 + 64 at most
+// and stay ordered) fit 31 bits.
+constexpr uint32_t BIG_ROW_MAX = 1u << 22;
+static_assert(1024ull * (BIG_ROW_MAX / 4 + 1) < 1ull << 31, "quads of a pass");
+constexpr uint32_t QTAG_RESET = 0xF0000000u; // marks above this start over when the pass ends
+static_assert(QTAG_RESET + 64ull * (BIG_ROW_MAX / 4 + 1) + 128 < 1ull << 32, "marks do not wrap within a pass");
 constexpr int WQ_CAP = 192;                   // queued live edges: below 64 before a sweep, then 128 of it at most
 constexpr uint32_t CNT_BIG_ROW = 0x40000000u; // set in a slot's node count: hand it on
 
@@ -740,7 +747,7 @@ __device__ __forceinline__ void sample_wave(const SampleArgs &a)
             load(min(wq_n, 64u));
             insert();
         }
-        if (qtag > 0xF0000000u) { // marks must grow: start over from clear ones
+        if (qtag > QTAG_RESET) { // marks must grow: start over from clear ones
             s_qmap[lane] = 0u;
             qtag = 64;
         }
@@ -2271,6 +2278,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     auto need = [](const void *p, const char *what) {
         if (!p) throw Error{SKIS_EHIP, std::string("internal error: null device buffer ") + what};
     };
+    const uint32_t big_row = std::min<uint32_t>(cfg.big_row, BIG_ROW_MAX);
     const bool lt = cfg.model == MODEL_LT;
     if (lt && (cfg.ris || cfg.form != 0))
         throw Error{SKIS_EINVAL, "the linear threshold sampler has the persistent form only and no RIS mode"};
@@ -2505,20 +2513,20 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A0.id_list = nullptr;
             A0.id_count_dev = &gc.ptr->count;
             A0.id_base_dev = &gc.ptr->base;
-            A0.big_row = cfg.big_row;
+            A0.big_row = big_row;
             A0.deferred = deferred.ptr;
             A0.n_deferred = &gc.ptr->nd0;
             A1.next = &gc.ptr->next1;
             A1.id_list = deferred.ptr;
             A1.id_count_dev = &gc.ptr->nd0;
-            A1.big_row = std::max<uint32_t>(cfg.big_row, 1u << 20);
+            A1.big_row = std::max<uint32_t>(big_row, 1u << 20);
             A1.deferred = deferred2.ptr;
             A1.n_deferred = &gc.ptr->nd1;
             A2.next = &gc.ptr->next2;
             A2.id_list = deferred2.ptr;
             A2.id_count_dev = &gc.ptr->nd1;
             A2.id_perm = 1; // a fixed scramble: in the hand-on order the largest samples can bunch up
-            A2.big_row = std::max<uint32_t>(cfg.big_row, TIERH_BIG_ROW);
+            A2.big_row = std::max<uint32_t>(big_row, TIERH_BIG_ROW);
             A2.deferred = deferred.ptr; // tier 1 has read tier 0's list by now
             A2.n_deferred = &gc.ptr->nd2;
             A2.ghash = ghash.ptr;
@@ -2703,7 +2711,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
         A.next = &ctr.ptr->next;
         A.id_list = nullptr;
         A.id_count = count;
-        A.big_row = cfg.big_row;
+        A.big_row = big_row;
         A.staging = staging.ptr;
         A.stage_cap = cap;
         A.stage_used = &ctr.ptr->stage_used;
@@ -2773,7 +2781,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A.id_count = nd;
             A.id_count_dev = nullptr;
             A.deferred = deferred2.ptr;
-            A.big_row = std::max<uint32_t>(cfg.big_row, 1u << 20);
+            A.big_row = std::max<uint32_t>(big_row, 1u << 20);
             A.tier_stats = ctr.ptr->tier[1][0];
             A.ho_state_out = ho2_state.ptr;
             A.ho_nodes_out = ho2_nodes.ptr;
@@ -2805,7 +2813,7 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             A.deferred = deferred.ptr; // tier 1 has read tier 0's list by now
             A.ghash = ghash.ptr;
             A.glist2 = glist2.ptr;
-            A.big_row = std::max<uint32_t>(cfg.big_row, TIERH_BIG_ROW);
+            A.big_row = std::max<uint32_t>(big_row, TIERH_BIG_ROW);
             A.tier_stats = ctr.ptr->tier[2][0];
             A.ho_state_out = ho3_state.ptr;
             A.ho_nodes_out = ho3_nodes.ptr;

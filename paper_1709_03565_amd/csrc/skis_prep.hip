@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void k_find_long(int32_t n, int64_t m, const i
     auto kind = [&](int64_t v) -> int {
         if (v >= v1) return 0;
         const int32_t a = row_ptr[v], b = row_ptr[v + 1];
-        if (!(a >= 0 && (int64_t)b <= m && b - a > LONG_ROW)) return 0;
+        if (!(a >= 0 && b >= a && (int64_t)b <= m && b - a > LONG_ROW)) return 0; // (b - a may wrap for b < 0)
         return b - a > HUGE_ROW ? 2 : 1;
     };
     if (t == 0) {

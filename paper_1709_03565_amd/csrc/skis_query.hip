@@ -179,7 +179,7 @@ __global__ __launch_bounds__(EST_BLOCK) void k_estimate(const int64_t *__restric
         for (int r = 0; r < IPT; ++r) {
             const int t = tid * IPT + r;
             int64_t d = 0;
-            if (t < nu) {
+            if (t < nu && T) { // without samples there may be no index
                 const int32_t v = buf[t];
                 d = node_ptr[v + 1] - node_ptr[v];
             }
@@ -380,7 +380,7 @@ __global__ __launch_bounds__(EST_BLOCK) void k_est_set(int32_t check, const int6
         const int t = tid * IPT + r;
         int64_t d = 0;
         np[r] = 0;
-        if (t < nu) {
+        if (t < nu && T) { // without samples there may be no index
             const int32_t v = buf[t];
             np[r] = node_ptr[v];
             d = node_ptr[v + 1] - np[r];

@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "skis_internal.h"
+#include "skis_query.h"
 
 namespace skis {
 
@@ -67,6 +68,7 @@ void build_inverse(Sketch &sk, hipStream_t s)
     Arena &arena = sk.arena;
     const int32_t n = sk.n;
     const uint64_t T = sk.T;
+    make_flags_page(); // for the estimates on the index
     sk.node_ptr.alloc(arena, (size_t)n + 1);
     sk.node_samples.alloc(arena, (size_t)sk.entries);
     DevBuf<uint32_t> cnt;

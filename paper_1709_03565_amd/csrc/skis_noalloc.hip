@@ -13,7 +13,8 @@
 
 namespace skis {
 
-// Layout in 32-bit words: word 0 the error word, words 4-7 the flags (EstFlags); [NA_LIST, NA_BITS)
+// Layout in 32-bit words: word 0 the error word of the large sets, words 4-7 the flags (EstFlags) where
+// no place in host memory is free; [NA_LIST, NA_BITS)
 // the large sets of one host chunk as int64 set indexes, and before them, from word NA_LIST - 1,
 // the parked sets' list (its count in that word) and tickets; [NA_BITS, NA_WORDS) the bitmaps.
 constexpr uint64_t NA_WORDS = (32ull << 20) / 4; // 32 MiB
@@ -82,49 +83,63 @@ void estimate_noalloc(const Sketch &sk, int32_t Q, const int64_t *set_ptr, const
     uint32_t *heavy = base + NA_LIST - 1, *ticket = base + NA_LIST + NA_CHUNK;
     // large sets per launch: a bitmap of T bits and a node bitmap of n bits each
     const uint64_t ng = std::min<uint64_t>(room / (wordsT + wordsN), (uint64_t)NA_CHUNK);
-    // the array keeps the last call's contents: clear what this call uses
-    na_fill(base, NA_LIST, s);
-    bool bits_clear = false;
+    // A call of light sets is one kernel and one wait: the kernel checks set_ptr, which is read to the
+    // host only where a large set is met.  With set_ptr and an error word read each time as well, one set
+    // of 3 nodes on 4000 samples of the 15k-node graph took 80 us; now 29 (66 by
+    // one workgroup and T-bit bitmap a set, before light sets had a kernel of their own).
+    bool any_large = false, waiting = false;
     int64_t hp[NA_CHUNK + 1];
     int64_t lg[NA_CHUNK];
     for (int64_t c0 = 0; c0 < Q; c0 += NA_CHUNK) {
         const int ch = (int)std::min<int64_t>(NA_CHUNK, Q - c0);
-        SKIS_HIP_TRY(hipMemcpyAsync(hp, set_ptr + c0, sizeof(int64_t) * (size_t)(ch + 1), hipMemcpyDeviceToHost, s));
-        SKIS_HIP_TRY(hipStreamSynchronize(s));
         int nl = 0;
-        for (int i = 0; i < ch; ++i) {
-            const int64_t k = hp[i + 1] - hp[i];
-            if (k < 0 || hp[i] < 0) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing from 0"};
-            if (k > EST_MAX_SET) lg[nl++] = c0 + i;
-        }
-        if (hp[ch] > hp[0] && !set_nodes) throw Error{SKIS_EINVAL, "set_nodes must not be NULL"};
-        if (nl > 0 && ng == 0)
+        auto read_sets = [&]() {
+            SKIS_HIP_TRY(hipMemcpyAsync(hp, set_ptr + c0, sizeof(int64_t) * (size_t)(ch + 1), hipMemcpyDeviceToHost, s));
+            SKIS_HIP_TRY(hipStreamSynchronize(s));
+            for (int i = 0; i < ch; ++i) {
+                const int64_t k = hp[i + 1] - hp[i];
+                if (k < 0 || hp[i] < 0) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing from 0"};
+                if (k > EST_MAX_SET) lg[nl++] = c0 + i;
+            }
+            if (hp[ch] > hp[0] && !set_nodes) throw Error{SKIS_EINVAL, "set_nodes must not be NULL"};
+        };
+        if (!set_nodes) read_sets(); // every set must be empty
+        unsigned long long *const cv = reinterpret_cast<unsigned long long *>(cov) + c0;
+        const EstFlags fl = estimate_light(sk, ch, set_nodes != nullptr, set_ptr + c0, set_nodes, cv, est + c0, ticket, flags, s);
+        if (fl.ptr) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing from 0"};
+        if (fl.node) throw Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
+        if (fl.large && ng == 0)
             throw Error{SKIS_EINVAL, "a set above " + std::to_string(EST_MAX_SET) +
                                          " entries needs more than the no-alloc scratch holds on this sketch"};
-        unsigned long long *const cv = reinterpret_cast<unsigned long long *>(cov) + c0;
-        estimate_light(sk, ch, false, set_ptr + c0, set_nodes, cv, est + c0, ticket, flags, s);
-        EstFlags fl{};
-        SKIS_HIP_TRY(hipMemcpyAsync(&fl, flags, sizeof(fl), hipMemcpyDeviceToHost, s));
-        SKIS_HIP_TRY(hipStreamSynchronize(s));
-        if (fl.node) throw Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
-        if (fl.parked) estimate_split(sk, ch, set_ptr + c0, set_nodes, cv, est + c0, heavy, ticket, s);
-        if (nl > 0) {
-            if (!bits_clear) na_fill(bits, ng * (wordsT + wordsN), s);
-            bits_clear = true; // the kernel leaves it so
+        if (fl.parked) {
+            estimate_split(sk, ch, set_ptr + c0, set_nodes, cv, est + c0, heavy, ticket, s);
+            waiting = true;
+        }
+        if (fl.large) {
+            read_sets();
+            if (!any_large) { // the array keeps the last call's contents; the kernel leaves the bitmaps clear
+                na_fill(base, 1, s);
+                na_fill(bits, ng * (wordsT + wordsN), s);
+            }
+            any_large = true;
             SKIS_HIP_TRY(hipMemcpyAsync(qlist, lg, sizeof(int64_t) * (size_t)nl, hipMemcpyHostToDevice, s));
             for (int g0 = 0; g0 < nl; g0 += (int)ng)
                 estimate_launch_large(sk, qlist, g0, (int32_t)std::min<int>((int)ng, nl - g0), set_ptr, set_nodes,
                                       bits, wordsT, bits + ng * wordsT, reinterpret_cast<unsigned long long *>(cov),
                                       est, err, s);
-            SKIS_HIP_TRY(hipStreamSynchronize(s)); // lg is rewritten by the next chunk
+            if (c0 + NA_CHUNK < Q) SKIS_HIP_TRY(hipStreamSynchronize(s)); // lg is rewritten by the next chunk
         }
     }
-    int herr = 0;
-    SKIS_HIP_TRY(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, s));
-    SKIS_HIP_TRY(hipStreamSynchronize(s));
-    if (herr & 1) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing"};
-    if (herr & 4) throw Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
-    if (herr) throw Error{SKIS_EHIP, "internal error in the estimate kernel (flags " + std::to_string(herr) + ")"};
+    if (any_large) {
+        int herr = 0;
+        SKIS_HIP_TRY(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, s));
+        SKIS_HIP_TRY(hipStreamSynchronize(s));
+        if (herr & 1) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing"};
+        if (herr & 4) throw Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
+        if (herr) throw Error{SKIS_EHIP, "internal error in the estimate kernel (flags " + std::to_string(herr) + ")"};
+    } else if (waiting) {
+        SKIS_HIP_TRY(hipStreamSynchronize(s));
+    }
 }
 
 } // namespace skis

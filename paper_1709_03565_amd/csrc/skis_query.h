@@ -77,8 +77,7 @@ struct RecountItem {
 struct QueryScratch {
     DevBuf<uint32_t> bitmaps; // sets above EST_MAX_SET entries: one bitmap of T bits each in flight
     DevBuf<int> err;
-    DevBuf<uint32_t> split;   // the parked sets' list and tickets
-    DevBuf<EstFlags> flags;   // used when no pinned place is free
+    DevBuf<uint32_t> split;   // the parked sets' list and tickets, flags
 };
 
 void estimate_batch(const Sketch &sk, QueryScratch &qs, int32_t Q, const int64_t *set_ptr, const int32_t *set_nodes,
@@ -86,9 +85,12 @@ void estimate_batch(const Sketch &sk, QueryScratch &qs, int32_t Q, const int64_t
 // nq sets in CSR form on the device: sets of at most EST_MAX_SET entries whose members' lists hold
 // at most EST_HASH_MAX entries are answered, heavier ones parked (cov = EST_PARKED, est = their sum
 // of q, ticket 0 where ticket is not null), sets above EST_MAX_SET entries left out.  check:
-// set_ptr is checked first (at most EST_BLOCK sets); else it has been.
-void estimate_light(const Sketch &sk, int32_t nq, bool check, const int64_t *set_ptr, const int32_t *set_nodes,
-                    unsigned long long *cov, double *est, uint32_t *ticket, EstFlags *flags, hipStream_t s);
+// set_ptr is checked first (at most EST_BLOCK sets); else it has been.  Waits, and returns what was
+// met; spare (device) takes the flags when no place in host memory is free.
+EstFlags estimate_light(const Sketch &sk, int32_t nq, bool check, const int64_t *set_ptr, const int32_t *set_nodes,
+                        unsigned long long *cov, double *est, uint32_t *ticket, EstFlags *spare, hipStream_t s);
+// Makes the page of host memory that the flags go to, once a process (estimates themselves allocate none).
+void make_flags_page();
 // The sets that estimate_light parked, split over the device by windows of sample ids.  heavy
 // (nq + 1 words) and ticket (nq words) are scratch.
 void estimate_split(const Sketch &sk, int32_t nq, const int64_t *set_ptr, const int32_t *set_nodes,

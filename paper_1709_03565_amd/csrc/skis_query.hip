@@ -1270,8 +1270,9 @@ static unsigned gridq(uint64_t items, int block, int per_cu = 8)
 
 // Sixteen bytes of flags in pinned host memory that a kernel writes and the host reads after a
 // synchronisation (a copy from the device and the fill before it had taken 20 us of a small
-// estimate): one page for the process, a call holds one of its places.  ptr is null when every
-// place is taken or the page could not be had; the caller then keeps its flags on the device.
+// estimate): one page for the process, made with the first inverse index, a call holds one of its
+// places.  host is null when every place is taken or there is no page; the caller then keeps its
+// flags on the device.
 namespace {
 class HostFlags {
     static constexpr int PLACES = 64;
@@ -1290,17 +1291,21 @@ class HostFlags {
 
 public:
     EstFlags *host = nullptr, *dev = nullptr;
+    static void make_page()
+    {
+        Page &p = page();
+        std::lock_guard<std::mutex> g(p.mu);
+        if (p.tried) return;
+        p.tried = true;
+        void *m = nullptr;
+        if (hipHostMalloc(&m, 64 * PLACES, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+            p.base = static_cast<char *>(m);
+        (void)hipGetLastError();
+    }
     HostFlags()
     {
         Page &p = page();
         std::lock_guard<std::mutex> g(p.mu);
-        if (!p.tried) {
-            p.tried = true;
-            void *m = nullptr;
-            if (hipHostMalloc(&m, 64 * PLACES, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
-                p.base = static_cast<char *>(m);
-            (void)hipGetLastError();
-        }
         if (!p.base) return;
         for (int i = 0; i < PLACES && at < 0; ++i)
             if (!p.used[i]) at = i;
@@ -1329,15 +1334,38 @@ public:
 };
 } // namespace
 
-void estimate_light(const Sketch &sk, int32_t nq, bool check, const int64_t *set_ptr, const int32_t *set_nodes,
-                    unsigned long long *cov, double *est, uint32_t *ticket, EstFlags *flags, hipStream_t s)
+void make_flags_page() { HostFlags::make_page(); }
+
+EstFlags estimate_light(const Sketch &sk, int32_t nq, bool check, const int64_t *set_ptr, const int32_t *set_nodes,
+                        unsigned long long *cov, double *est, uint32_t *ticket, EstFlags *spare, hipStream_t s)
 {
-    if (nq <= 0) return;
+    EstFlags fl{};
+    if (nq <= 0) return fl;
     if (check && nq > EST_BLOCK) throw Error{SKIS_EHIP, "internal error: too many sets for a checked estimate"};
-    hipLaunchKernelGGL(k_est_set<false>, dim3((unsigned)nq), dim3(EST_BLOCK), 0, s, check ? nq : 0, set_ptr, set_nodes, sk.n,
-                       sk.T, sk.est_scale(), sk.est_q(), sk.node_ptr.ptr, sk.node_samples.ptr, cov, est, ticket,
-                       (uint32_t *)nullptr, (uint64_t)0, flags);
-    SKIS_HIP_TRY(hipGetLastError());
+    HostFlags hf;
+    EstFlags *const dev = hf.dev ? hf.dev : spare;
+    if (!hf.dev)
+        hipLaunchKernelGGL(k_fill_q<int>, dim3(1), dim3(64), 0, s, (uint64_t)(sizeof(EstFlags) / sizeof(int)),
+                           reinterpret_cast<int *>(dev), 0);
+    try {
+        hipLaunchKernelGGL(k_est_set<false>, dim3((unsigned)nq), dim3(EST_BLOCK), 0, s, check ? nq : 0, set_ptr, set_nodes,
+                           sk.n, sk.T, sk.est_scale(), sk.est_q(), sk.node_ptr.ptr, sk.node_samples.ptr, cov, est, ticket,
+                           (uint32_t *)nullptr, (uint64_t)0, dev);
+        SKIS_HIP_TRY(hipGetLastError());
+        if (!hf.dev) SKIS_HIP_TRY(hipMemcpyAsync(&fl, dev, sizeof(fl), hipMemcpyDeviceToHost, s));
+        SKIS_HIP_TRY(hipStreamSynchronize(s));
+    } catch (...) {
+        (void)hipStreamSynchronize(s); // nothing may write the flags' place after it is given back
+        throw;
+    }
+    if (hf.dev) {
+        const volatile EstFlags *h = hf.host;
+        fl.ptr = h->ptr;
+        fl.node = h->node;
+        fl.large = h->large;
+        fl.parked = h->parked;
+    }
+    return fl;
 }
 
 void estimate_split(const Sketch &sk, int32_t nq, const int64_t *set_ptr, const int32_t *set_nodes,
@@ -1377,35 +1405,12 @@ void estimate_batch(const Sketch &sk, QueryScratch &qs, int32_t Q, const int64_t
     };
     const bool device_check = Q <= EST_BLOCK && set_nodes;
     if (!device_check) read_sets();
-    const size_t need = 2 * (size_t)Q + 1; // heavy = {count, sets}, tickets
+    constexpr size_t FLAGS = sizeof(EstFlags) / sizeof(uint32_t);
+    const size_t need = 2 * (size_t)Q + 1 + FLAGS; // heavy = {count, sets}, tickets, flags
     if (qs.split.count < need) qs.split.alloc(arena, need);
     uint32_t *const heavy = qs.split.ptr, *const ticket = qs.split.ptr + Q + 1;
-    EstFlags fl{};
-    {
-        HostFlags hf;
-        EstFlags *dev = hf.dev;
-        if (!dev) {
-            if (!qs.flags.ptr) qs.flags.alloc(arena, 1);
-            dev = qs.flags.ptr;
-            hipLaunchKernelGGL(k_fill_q<int>, dim3(1), dim3(64), 0, s, (uint64_t)(sizeof(EstFlags) / sizeof(int)),
-                               reinterpret_cast<int *>(dev), 0);
-        }
-        try {
-            estimate_light(sk, Q, device_check, set_ptr, set_nodes, cov, est, ticket, dev, s);
-            if (!hf.dev) SKIS_HIP_TRY(hipMemcpyAsync(&fl, dev, sizeof(fl), hipMemcpyDeviceToHost, s));
-            SKIS_HIP_TRY(hipStreamSynchronize(s));
-        } catch (...) {
-            (void)hipStreamSynchronize(s); // nothing may write the flags' place after it is given back
-            throw;
-        }
-        if (hf.dev) {
-            const volatile EstFlags *h = hf.host;
-            fl.ptr = h->ptr;
-            fl.node = h->node;
-            fl.large = h->large;
-            fl.parked = h->parked;
-        }
-    }
+    const EstFlags fl = estimate_light(sk, Q, device_check, set_ptr, set_nodes, cov, est, ticket,
+                                       reinterpret_cast<EstFlags *>(qs.split.ptr + 2 * (size_t)Q + 1), s);
     if (fl.ptr) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing from 0"};
     if (fl.node) throw Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
     if (fl.parked) estimate_split(sk, Q, set_ptr, set_nodes, cov, est, heavy, ticket, s);

@@ -33,7 +33,9 @@ struct GreedyState {
     unsigned long long cov;     // coverage of the picks so far
     double est;
     unsigned flipped;           // the round's argmax has switched buffers: the spare one is to be cleared
-    unsigned pad[2];
+    int32_t rounds;             // rounds whose pick k_greedy_argmax has taken
+    unsigned light;             // the others are k_greedy_small's
+    unsigned before;            // small sketches: entries left before the last round
 };
 
 // A tile of GREEDY_TILE nodes keeps its best node as of its last scan and the second gain.  Delta
@@ -47,9 +49,15 @@ struct __align__(8) GreedyTile {
 };
 constexpr int GREEDY_BLOCK = 1024; // the pick is one workgroup's
 constexpr int GREEDY_BIG = 512;    // in the one-workgroup form, a sample above this is uncovered by all threads
-// Sketches whose greedy runs in one workgroup (no launches inside the k rounds).
+// Sketches whose greedy runs in one workgroup, with no launches inside its rounds, but for the first ones.
 constexpr int GREEDY_SMALL_TILES = 2048;
 constexpr uint64_t GREEDY_SMALL_ENTRIES = 1ull << 19;
+constexpr uint64_t GREEDY_SMALL_ROUND = 1ull << 15;
+// entries left, and lowered by the last round, up to which one workgroup does the rest (over graphs of
+// 2000 to 4M nodes and 8 to 500 thousand entries 32768 to 98304 and 8192 to 49152 are within 4 %)
+constexpr uint32_t GREEDY_FEW_LEFT = 65536, GREEDY_FEW_LOWERED = 8192;
+// the entries left after a round, in parts a line apart (one counter for 2048 workgroups takes 19 us)
+constexpr int GREEDY_LEFT_PARTS = 32, GREEDY_LEFT_STEP = 16;
 
 // A newly covered sample in a queue of k_greedy_cover: its first entry (a sketch may hold 2^33 entries
 // and more) and its entries; 12 bytes.

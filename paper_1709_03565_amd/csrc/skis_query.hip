@@ -669,9 +669,26 @@ constexpr int RECOUNT_SPAN = 1024; // list entries per recount work item
 constexpr int RECOUNT_LANES = 16;  // lanes per work item
 constexpr int RECOUNT_UNROLL = 8;  // loads in flight per lane
 
-__device__ __forceinline__ bool heavy_round(const GreedyState *st, uint64_t T)
+// recount: the samples from which on a round recounts (0 before the first round: st->rounds is 0)
+__device__ __forceinline__ bool heavy_round(const GreedyState *st, uint64_t recount)
 {
-    return st->vstar >= 0 && st->dstar > T / RECOUNT_DIV;
+    return st->vstar >= 0 && st->rounds > 0 && st->dstar >= recount;
+}
+
+// Whether `todo` rounds are worth the 60 us that going over to k_greedy_small takes: a round by launches
+// is longer by some 10 us and 40 us a million nodes (WC and TRI graphs of 15 thousand to 4M nodes), by
+// hardly anything where all nodes are one tile (2000 nodes: a round of either some 25 us).
+__host__ __device__ __forceinline__ bool worth_going_over(int32_t todo, int32_t n)
+{
+    return (int64_t)todo * (n <= GREEDY_TILE ? 2 : 10 + n / 25000) > 60;
+}
+
+// A small sketch's last round, of the whole device, has lowered few entries, or few are left, and the
+// rounds to come are worth it.
+__device__ __forceinline__ bool greedy_few(const GreedyState *st, uint32_t left, int32_t todo, int32_t n)
+{
+    return st->rounds > 0 && (left <= GREEDY_FEW_LEFT || st->before - left <= GREEDY_FEW_LOWERED) &&
+           worth_going_over(todo, n);
 }
 
 __device__ __forceinline__ double gain_of(int64_t d, uint64_t T, double Gamma, double q)
@@ -904,23 +921,40 @@ __device__ __forceinline__ GreedyTile pick_node(GreedyTile *tiles, int32_t ntile
 }
 
 // delta lives in two buffers: a round that recounts writes the spare one (kept zero), the next
-// argmax switches to it, and that round's cover clears the one it leaves.
-__global__ __launch_bounds__(GREEDY_BLOCK) void k_greedy_argmax(int32_t n, int round, uint64_t T, double Gamma,
+// argmax switches to it, and that round's cover clears the one it leaves.  few: the entries of a small
+// sketch (else 0), whose rounds go over to k_greedy_small once the last one has lowered few entries or
+// few are left.
+__global__ __launch_bounds__(GREEDY_BLOCK) void k_greedy_argmax(int32_t n, int round, int32_t k, uint64_t recount, uint32_t few, uint64_t T,
+                                                                double Gamma,
                                                                 int32_t *__restrict__ delta0,
                                                                 int32_t *__restrict__ delta1,
                                                                 const double *__restrict__ qv,
                                                                 uint8_t *__restrict__ chosen,
                                                                 GreedyTile *__restrict__ tiles, int32_t ntiles,
                                                                 GreedyState *__restrict__ st,
+                                                                uint32_t *__restrict__ left_parts,
                                                                 int32_t *__restrict__ seeds,
                                                                 unsigned long long *__restrict__ marg)
 {
     __shared__ PickShared sh;
-    const bool recounted = heavy_round(st, T); // the previous round
+    uint32_t left = 0;
+    if (few) {
+        const int lane = threadIdx.x & 63;
+        left = wave_sum(lane < GREEDY_LEFT_PARTS ? left_parts[lane * GREEDY_LEFT_STEP] : 0u);
+        if (st->light || greedy_few(st, left, k - round, n)) { // (light is the only word written: a late reader agrees)
+            if (threadIdx.x == 0) st->light = 1u;
+            return;
+        }
+    }
+    const bool recounted = heavy_round(st, recount); // the previous round
     const int cur = st->cur ^ (recounted ? 1 : 0);
     const int32_t *delta = cur ? delta1 : delta0;
     const GreedyTile b = pick_node<false>(tiles, ntiles, n, T, Gamma, delta, qv, chosen, sh);
-    if (threadIdx.x == 0) { // every thread has read st (the reductions' barriers)
+    // every thread has read st and the parts (the reductions' barriers)
+    if (few && threadIdx.x < GREEDY_LEFT_PARTS) left_parts[threadIdx.x * GREEDY_LEFT_STEP] = 0u;
+    if (threadIdx.x == 0) {
+        st->rounds += 1;
+        st->before = round ? left : few;
         st->flipped = recounted ? 1u : 0u;
         if (recounted) {
             st->shrunk = 1u; // the previous round rewrote the spans
@@ -960,13 +994,19 @@ __global__ __launch_bounds__(256) void k_greedy_tiles(int32_t n, uint64_t T, dou
     }
 }
 
-// The k rounds of a small sketch (D-SSA's) in one workgroup: three launches a round had cost more
-// than their work (D-SSA with k = 100 on the 4M-node TRI graph: 29.7 ms before, 18.6 now).  The tiles live in LDS; a round picks, covers H(v*) through LDS queues and
-// lowers delta by atomics.
+// The light rounds of a small sketch (D-SSA's) in one workgroup: three launches a round had cost more
+// than their work (D-SSA with k = 100 on the 4M-node TRI graph: 29.7 ms before, 18.6 now).  The tiles
+// live in LDS; a round picks, covers H(v*) through LDS queues and lowers delta by atomics.  A hub's round
+// is some 1.5 ns an entry lowered for one workgroup, which the first picks mostly are, so those are the
+// whole device's (see greedy_few).  k = 1, 5, 20 and 100 on 500 thousand entries, 100 thousand nodes (WC):
+// 0.15, 0.31, 0.98 and 3.5 ms by launches alone, 0.90, 1.27, 1.70 and 2.9 by the one workgroup alone, 0.14,
+// 0.27, 0.78 and 2.0 so; on 460 thousand, 4M nodes (TRI): 0.21, 0.72, 2.6, 8.4; 0.67, 0.91, 1.29, 2.85; 0.20,
+// 0.40, 0.80, 2.4.
 constexpr int SMALL_QUEUE = 4096;
 
 __global__ __launch_bounds__(GREEDY_BLOCK) void k_greedy_small(int32_t n, int32_t k, uint64_t T, double Gamma,
-                                                               int32_t *__restrict__ delta,
+                                                               int32_t *__restrict__ delta0,
+                                                               int32_t *__restrict__ delta1,
                                                                const double *__restrict__ qv,
                                                                uint8_t *__restrict__ chosen,
                                                                const GreedyTile *__restrict__ tiles_in, int32_t ntiles,
@@ -985,10 +1025,13 @@ __global__ __launch_bounds__(GREEDY_BLOCK) void k_greedy_small(int32_t n, int32_
     __shared__ int2 queue[SMALL_QUEUE], bigq[SMALL_QUEUE];
     __shared__ int s_q, s_big;
     const int tid = threadIdx.x;
+    const int32_t r0 = st->rounds; // taken by the launches before, which all recounted
+    if (r0 >= k) return;
+    int32_t *const delta = (st->cur ^ (r0 > 0 ? 1 : 0)) ? delta1 : delta0; // as k_greedy_argmax
+    unsigned long long cov = st->cov;
     for (int t = tid; t < ntiles; t += GREEDY_BLOCK) tiles[t] = tiles_in[t];
     __syncthreads();
-    unsigned long long cov = 0;
-    for (int32_t r = 0; r < k; ++r) {
+    for (int32_t r = r0; r < k; ++r) {
         const GreedyTile p = pick_node<true>(tiles, ntiles, n, T, Gamma, delta, qv, chosen, sh);
         if (p.v < 0) { // nothing left to pick (cannot happen for k <= n)
             if (tid == 0) st->vstar = -1;
@@ -1003,6 +1046,11 @@ __global__ __launch_bounds__(GREEDY_BLOCK) void k_greedy_small(int32_t n, int32_
             s_big = 0;
         }
         cov += (unsigned long long)p.d;
+        // the pick's own delta is not read any more, and every sample would lower it (atomics on one
+        // address take 9.4 ns each)
+        auto lower = [&](int32_t u) {
+            if (u != p.v) atomicSub(&delta[u], 1);
+        };
         const int64_t a = node_ptr[p.v], b = p.d > 0 ? node_ptr[p.v + 1] : a;
         __syncthreads();
         for (int64_t c0 = a; c0 < b; c0 += SMALL_QUEUE) {
@@ -1018,11 +1066,11 @@ __global__ __launch_bounds__(GREEDY_BLOCK) void k_greedy_small(int32_t n, int32_
             const int nq = s_q, nb = s_big;
             for (int i = tid >> 4; i < nq; i += GREEDY_BLOCK / 16) { // 16 lanes a sample
                 const int2 x = queue[i];
-                for (int t = tid & 15; t < x.y; t += 16) atomicSub(&delta[nodes[x.x + t]], 1);
+                for (int t = tid & 15; t < x.y; t += 16) lower(nodes[x.x + t]);
             }
             for (int i = 0; i < nb; ++i) {
                 const int2 x = bigq[i];
-                for (int t = tid; t < x.y; t += GREEDY_BLOCK) atomicSub(&delta[nodes[x.x + t]], 1);
+                for (int t = tid; t < x.y; t += GREEDY_BLOCK) lower(nodes[x.x + t]);
             }
             __syncthreads();
             if (tid == 0) {
@@ -1046,7 +1094,7 @@ __global__ __launch_bounds__(GREEDY_BLOCK) void k_greedy_small(int32_t n, int32_
 // samples a round newly covers is delta of its pick, known before the round starts.
 constexpr int MARK_RUN = 8;
 
-__global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restrict__ st, uint64_t T, int32_t n,
+__global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restrict__ st, uint64_t recount, int32_t n,
                                                       const int64_t *__restrict__ node_ptr,
                                                       const int32_t *__restrict__ node_samples,
                                                       uint32_t *__restrict__ covered,
@@ -1059,8 +1107,8 @@ __global__ __launch_bounds__(256) void k_greedy_cover(const GreedyState *__restr
     __shared__ int32_t hd[GREEDY_HOT];
     __shared__ CoverItem queue[4][64 * MARK_RUN]; // the newly covered samples
     const int32_t v = st->vstar;
-    if (v < 0) return;
-    const bool update = !heavy_round(st, T);
+    if (v < 0 || st->light) return;
+    const bool update = !heavy_round(st, recount);
     int32_t *delta = st->cur ? delta1 : delta0;
     if (st->flipped) { // the buffer that this round's argmax left
         int32_t *spare = st->cur ? delta0 : delta1;
@@ -1183,13 +1231,15 @@ __global__ __launch_bounds__(256) void k_recount_items_fill(int32_t n, const int
 // entry only moves to a lower position, after every load of its batch).  The order within
 // a span stays ascending.  RECOUNT_LANES lanes per span, RECOUNT_UNROLL list loads and then
 // as many bitmap loads in flight per lane.
-__global__ __launch_bounds__(256) void k_greedy_recount(const GreedyState *__restrict__ st, uint64_t T,
+__global__ __launch_bounds__(256) void k_greedy_recount(const GreedyState *__restrict__ st, uint64_t recount, uint32_t *__restrict__ left_parts,
                                                         uint64_t nitems, RecountItem *__restrict__ items,
                                                         const int32_t *node_samples, int32_t *work,
                                                         const uint32_t *__restrict__ covered,
                                                         int32_t *__restrict__ delta0, int32_t *__restrict__ delta1)
 {
-    if (!heavy_round(st, T)) return;
+    __shared__ uint32_t s_left[4];
+    uint32_t left = 0; // entries kept
+    if (st->light || !heavy_round(st, recount)) return;
     int32_t *delta = st->cur ? delta0 : delta1; // the spare buffer, all zero; the next argmax switches
     const int32_t *src = st->shrunk ? work : node_samples;
     constexpr int G = 64 / RECOUNT_LANES;
@@ -1226,7 +1276,15 @@ __global__ __launch_bounds__(256) void k_greedy_recount(const GreedyState *__res
         if (t == 0 && it < nitems) {
             items[it].len = kept;
             if (kept) atomicAdd(&delta[w.v], kept);
+            left += (uint32_t)kept;
         }
+    }
+    if (left_parts) {
+        left = wave_sum(left);
+        if (lane == 0) s_left[threadIdx.x >> 6] = left;
+        __syncthreads();
+        if (threadIdx.x == 0 && (left = s_left[0] + s_left[1] + s_left[2] + s_left[3]))
+            atomicAdd(&left_parts[blockIdx.x % GREEDY_LEFT_PARTS * GREEDY_LEFT_STEP], left);
     }
 }
 
@@ -1501,27 +1559,35 @@ void greedy(const Sketch &sk, QueryScratch &qs, int32_t k, int32_t *seeds, uint6
     DevBuf<GreedyTile> tiles;
     tiles.alloc(arena, (size_t)ntiles);
     const bool small = sk.entries <= GREEDY_SMALL_ENTRIES && ntiles <= GREEDY_SMALL_TILES;
+    // of a small sketch the whole device takes the first rounds, as many as may be worth it: all of 8,
+    // else one for every GREEDY_SMALL_ROUND entries
+    int32_t rounds = k;
+    if (small && sk.entries <= (k > 1 ? GREEDY_FEW_LEFT : GREEDY_FEW_LEFT / 2)) rounds = 0;
+    else if (small && k > 8) rounds = (int32_t)std::min<uint64_t>((uint64_t)k, sk.entries / GREEDY_SMALL_ROUND + 1);
+    const uint64_t recount = small ? 0 : sk.T / RECOUNT_DIV + 1;
+    const bool go_over = small && (rounds < k || worth_going_over(k - 1, n));
+    const uint32_t few = go_over ? (uint32_t)sk.entries : 0u;
     delta.alloc(arena, n);
-    if (!small) delta_spare.alloc(arena, n);
+    if (rounds) delta_spare.alloc(arena, n);
+    DevBuf<uint32_t> left;
+    constexpr uint64_t LEFT_WORDS = GREEDY_LEFT_PARTS * GREEDY_LEFT_STEP;
+    if (go_over && rounds) {
+        left.alloc(arena, LEFT_WORDS);
+        hipLaunchKernelGGL(k_fill_q<uint32_t>, dim3(1), dim3(256), 0, s, LEFT_WORDS, left.ptr, 0u);
+    }
     chosen.alloc(arena, n);
     covered.alloc(arena, wordsT ? wordsT : 1);
     st.alloc(arena, 1);
     hipLaunchKernelGGL(k_greedy_init, dim3(gridq(n, 256)), dim3(256), 0, s, n, sk.node_ptr.ptr, delta.ptr, chosen.ptr);
     hipLaunchKernelGGL(k_fill_q<uint32_t>, dim3(gridq(wordsT ? wordsT : 1, 256)), dim3(256), 0, s,
                        wordsT ? wordsT : 1, covered.ptr, 0u);
-    if (!small)
+    if (rounds)
         hipLaunchKernelGGL(k_fill_q<int32_t>, dim3(gridq(n, 256)), dim3(256), 0, s, (uint64_t)n, delta_spare.ptr, 0);
     hipLaunchKernelGGL(k_fill_q<unsigned char>, dim3(1), dim3(64), 0, s, (uint64_t)sizeof(GreedyState),
                        reinterpret_cast<unsigned char *>(st.ptr), (unsigned char)0);
     SKIS_HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_greedy_tiles, dim3(gridq((uint64_t)ntiles * 256, 256, 8)), dim3(256), 0, s, n, sk.T,
                        sk.est_scale(), delta.ptr, sk.est_q(), chosen.ptr, tiles.ptr, ntiles);
-    if (small) {
-        hipLaunchKernelGGL(k_greedy_small, dim3(1), dim3(GREEDY_BLOCK), 0, s, n, k, sk.T, sk.est_scale(), delta.ptr,
-                           sk.est_q(), chosen.ptr, tiles.ptr, ntiles, sk.node_ptr.ptr, sk.node_samples.ptr, covered.ptr,
-                           sk.sample_ptr.ptr, sk.nodes.ptr, seeds, reinterpret_cast<unsigned long long *>(marg), st.ptr);
-        SKIS_HIP_TRY(hipGetLastError());
-    }
     const unsigned gu = (unsigned)device_cu_count() * 4;
     const int nhot = std::min<int>(sk.nhot, GREEDY_HOT);
     const int32_t *hot_id = nhot > 0 ? sk.hot_id.ptr : nullptr;
@@ -1531,7 +1597,7 @@ void greedy(const Sketch &sk, QueryScratch &qs, int32_t k, int32_t *seeds, uint6
     DevBuf<RecountItem> items;
     DevBuf<int32_t> work; // the lists cut down by the heavy rounds
     uint64_t nit = 0;
-    if (sk.T && !small) {
+    if (sk.T && rounds) {
         nitems.alloc(arena, n);
         ioff.alloc(arena, (size_t)n + 1);
         hipLaunchKernelGGL(k_recount_items_count, dim3(gridq(n, 256)), dim3(256), 0, s, n, sk.node_ptr.ptr,
@@ -1548,19 +1614,24 @@ void greedy(const Sketch &sk, QueryScratch &qs, int32_t k, int32_t *seeds, uint6
         SKIS_HIP_TRY(hipGetLastError());
     }
     const unsigned gr = gridq(nit * RECOUNT_LANES, 256, 8);
-    for (int32_t r = 0; r < k && !small; ++r) {
-        hipLaunchKernelGGL(k_greedy_argmax, dim3(1), dim3(GREEDY_BLOCK), 0, s, n, (int)r, sk.T, sk.est_scale(), delta.ptr,
-                           delta_spare.ptr, sk.est_q(), chosen.ptr, tiles.ptr, ntiles, st.ptr, seeds,
+    for (int32_t r = 0; r < rounds; ++r) {
+        hipLaunchKernelGGL(k_greedy_argmax, dim3(1), dim3(GREEDY_BLOCK), 0, s, n, (int)r, k, recount, few, sk.T, sk.est_scale(),
+                           delta.ptr, delta_spare.ptr, sk.est_q(), chosen.ptr, tiles.ptr, ntiles, st.ptr, left.ptr, seeds,
                            reinterpret_cast<unsigned long long *>(marg));
         if (sk.T) {
             // the cover lowers delta itself unless the round recounts, decided on the device
-            hipLaunchKernelGGL(k_greedy_cover, dim3(gu), dim3(256), 0, s, st.ptr, sk.T, n, sk.node_ptr.ptr,
+            hipLaunchKernelGGL(k_greedy_cover, dim3(gu), dim3(256), 0, s, st.ptr, recount, n, sk.node_ptr.ptr,
                                sk.node_samples.ptr, covered.ptr, sk.sample_ptr.ptr, sk.nodes.ptr, hot_id,
                                sk.hot_node.ptr, nhot, delta.ptr, delta_spare.ptr);
-            hipLaunchKernelGGL(k_greedy_recount, dim3(gr), dim3(256), 0, s, st.ptr, sk.T, nit, items.ptr,
+            hipLaunchKernelGGL(k_greedy_recount, dim3(gr), dim3(256), 0, s, st.ptr, recount, left.ptr, nit, items.ptr,
                                sk.node_samples.ptr, work.ptr, covered.ptr, delta.ptr, delta_spare.ptr);
         }
     }
+    if (go_over)
+        hipLaunchKernelGGL(k_greedy_small, dim3(1), dim3(GREEDY_BLOCK), 0, s, n, k, sk.T, sk.est_scale(), delta.ptr,
+                           delta_spare.ptr, sk.est_q(), chosen.ptr, tiles.ptr, ntiles, sk.node_ptr.ptr, sk.node_samples.ptr,
+                           covered.ptr, sk.sample_ptr.ptr, sk.nodes.ptr, seeds, reinterpret_cast<unsigned long long *>(marg),
+                           st.ptr);
     SKIS_HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_greedy_final, dim3(1), dim3(256), 0, s, k, sk.T, sk.est_scale(), seeds, sk.est_q(), st.ptr);
     SKIS_HIP_TRY(hipGetLastError());

@@ -416,6 +416,7 @@ int skis_build_sketch(int32_t n, int64_t m, const int32_t *row_ptr, const int32_
                 float ms = 0;
                 SKIS_HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
                 sk.ms_preprocess = ms;
+                prep.W.reset(); // the alias table holds it
                 sk.Gamma = prep.Gamma;
                 sk.C = prep.C;
                 sk.ris = opt.ris_mode != 0;

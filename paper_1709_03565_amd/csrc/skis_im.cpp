@@ -96,6 +96,7 @@ extern "C" int skis_im_dssa(int32_t n, int64_t m, const int32_t *row_ptr, const 
         arena.stream = stream;
         skis::Prep prep;
         skis::preprocess(arena, n, m, row_ptr, col, w, true, prep, stream, (int)opt.model);
+        prep.W.reset(); // the alias table holds it
         info->Gamma = prep.Gamma;
         if (prep.C == 0) {
             // Gamma = 0: no edge can be live, I(S) = |S| for every S; the greedy's tie rule picks 0..k-1

@@ -981,12 +981,6 @@ void preprocess(Arena &arena, int32_t n, int64_t m, const int32_t *row_ptr, cons
     light.alloc(arena, n);
     lrank.alloc(arena, n);
     Ltot.alloc(arena, 1);
-    lid.alloc(arena, n);
-    hid.alloc(arena, n);
-    dval.alloc(arena, n);
-    sval.alloc(arena, n);
-    Dinc.alloc(arena, n);
-    Sinc.alloc(arena, n);
     hipLaunchKernelGGL(k_alias_flags, dim3(grid_for(n)), dim3(256), 0, s, n, out.W.ptr, out.C, light.ptr);
     SKIS_HIP_TRY(hipGetLastError());
     excl_scan<uint32_t>(arena, light.ptr, lrank.ptr, n, Ltot.ptr, s);
@@ -994,6 +988,12 @@ void preprocess(Arena &arena, int32_t n, int64_t m, const int32_t *row_ptr, cons
     SKIS_HIP_TRY(hipMemcpyAsync(&hL, Ltot.ptr, sizeof(hL), hipMemcpyDeviceToHost, s));
     SKIS_HIP_TRY(hipStreamSynchronize(s));
     const int64_t L = hL, H = (int64_t)n - hL;
+    lid.alloc(arena, L);
+    hid.alloc(arena, H);
+    dval.alloc(arena, L);
+    sval.alloc(arena, H);
+    Dinc.alloc(arena, L);
+    Sinc.alloc(arena, H);
     hipLaunchKernelGGL(k_alias_split, dim3(grid_for(n)), dim3(256), 0, s, n, out.W.ptr, out.C, light.ptr, lrank.ptr,
                        lid.ptr, hid.ptr, dval.ptr, sval.ptr);
     SKIS_HIP_TRY(hipGetLastError());

@@ -2360,20 +2360,20 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     DevBuf<Handover> hof_state;
     DevBuf<int32_t> hof_nodes;
     DevBuf<uint32_t> front_ids; // the samples the front hands on
-    deferred.alloc(arena, count + (uint64_t)nb0 * HANDON_CHUNK); // with the chunks' unused places
+    // (with the chunks' unused places: a workgroup without a sample reserves none)
+    deferred.alloc(arena, count + std::min<uint64_t>(nb0, count) * HANDON_CHUNK);
     if (front) {
         hof_state.alloc(arena, hof_cap);
         hof_nodes.alloc(arena, hof_cap * (uint64_t)FRONT_RCAP);
-        front_ids.alloc(arena, per_launch0 + (uint64_t)nbf * HANDON_CHUNK);
+        front_ids.alloc(arena, per_launch0 + std::min<uint64_t>(nbf, count) * HANDON_CHUNK);
     }
-    // Staging: each LDS-tier workgroup reserves 8 * slots * visited entries at a time and
-    // wastes less than one finished pass (slots * visited) per reservation plus its last
-    // open chunk, so sum|R| * 8/7 + 2 chunks per workgroup bounds what a launch reserves.
+    // Staging: each LDS-tier workgroup reserves 8 * slots * visited entries at a time and wastes less
+    // than one finished pass (slots * visited) of every such chunk but its last, so sum|R| * 8/7 + one
+    // chunk per workgroup bounds what a launch reserves.
     const uint64_t ch0 = 8ull * v0.slots * v0.visited, chm = 8ull * vm.slots * vm.visited;
     const uint64_t chf = front ? 8ull * FRONT_SLOTS * FRONT_RCAP : 0;
-    const uint64_t slack = (uint64_t)std::min<uint64_t>(nbf, count) * 2 * chf +
-                           (uint64_t)std::min<uint64_t>(nb0, count) * 2 * ch0 +
-                           (uint64_t)std::min<uint64_t>(nbm, count) * 2 * chm;
+    const uint64_t slack = (uint64_t)std::min<uint64_t>(nbf, count) * chf + (uint64_t)std::min<uint64_t>(nb0, count) * ch0 +
+                           (uint64_t)std::min<uint64_t>(nbm, count) * chm;
     auto staging_bound = [&](uint64_t entries, uint64_t launches) {
         return entries + entries / 7 + 1 + launches * slack + (1ull << 20);
     };

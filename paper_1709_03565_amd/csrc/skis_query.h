@@ -12,6 +12,7 @@ constexpr int EST_WALK = 4;       // sample-list entries a thread walks per roun
 
 constexpr int EST_HASH_SLOTS = 16384; // LDS hash of a light set's sample ids in k_est_set
 constexpr int EST_HASH_MAX = 10922;   // list entries a light set's members hold at most (1.5 slots each)
+constexpr int32_t EST_ROUND = 1 << 16; // sets of one round of skis_estimate
 constexpr uint64_t EST_WALK_MAX = 0xFFFF0000ull; // entries that k_est_set's walk counts in 32 bits
 constexpr unsigned long long EST_PARKED = ~0ull; // cov of a set that k_est_set left to the next kernel
 

@@ -1463,16 +1463,24 @@ void estimate_batch(const Sketch &sk, QueryScratch &qs, int32_t Q, const int64_t
     };
     const bool device_check = Q <= EST_BLOCK && set_nodes;
     if (!device_check) read_sets();
+    // EST_ROUND sets at a time, so that a call of any number of sets needs half a megabyte of scratch
     constexpr size_t FLAGS = sizeof(EstFlags) / sizeof(uint32_t);
-    const size_t need = 2 * (size_t)Q + 1 + FLAGS; // heavy = {count, sets}, tickets, flags
+    const int32_t most = std::min<int32_t>(Q, EST_ROUND);
+    const size_t need = 2 * (size_t)most + 1 + FLAGS; // heavy = {count, sets}, tickets, flags
     if (qs.split.count < need) qs.split.alloc(arena, need);
-    uint32_t *const heavy = qs.split.ptr, *const ticket = qs.split.ptr + Q + 1;
-    const EstFlags fl = estimate_light(sk, Q, device_check, set_ptr, set_nodes, cov, est, ticket,
-                                       reinterpret_cast<EstFlags *>(qs.split.ptr + 2 * (size_t)Q + 1), s);
-    if (fl.ptr) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing from 0"};
-    if (fl.node) throw Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
-    if (fl.parked) estimate_split(sk, Q, set_ptr, set_nodes, cov, est, heavy, ticket, s);
-    if (fl.large) {
+    uint32_t *const heavy = qs.split.ptr, *const ticket = heavy + most + 1;
+    EstFlags *const spare = reinterpret_cast<EstFlags *>(ticket + most);
+    bool any_large = false, any_parked = false;
+    for (int64_t c0 = 0; c0 < Q; c0 += EST_ROUND) {
+        const int32_t ch = (int32_t)std::min<int64_t>(EST_ROUND, Q - c0);
+        const EstFlags fl = estimate_light(sk, ch, device_check, set_ptr + c0, set_nodes, cov + c0, est + c0, ticket, spare, s);
+        if (fl.ptr) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing from 0"};
+        if (fl.node) throw Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
+        if (fl.parked) estimate_split(sk, ch, set_ptr + c0, set_nodes, cov + c0, est + c0, heavy, ticket, s);
+        any_large = any_large || fl.large;
+        any_parked = any_parked || fl.parked;
+    }
+    if (any_large) {
         if (hptr.empty()) read_sets();
         if (!qs.err.ptr) qs.err.alloc(arena, 1);
         hipLaunchKernelGGL(k_fill_q<int>, dim3(1), dim3(64), 0, s, (uint64_t)1, qs.err.ptr, 0);
@@ -1508,7 +1516,7 @@ void estimate_batch(const Sketch &sk, QueryScratch &qs, int32_t Q, const int64_t
         }
         if (herr & 1) throw Error{SKIS_EINVAL, "set_ptr must be nondecreasing"};
         if (herr & 4) throw Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
-    } else if (fl.parked) {
+    } else if (any_parked) {
         SKIS_HIP_TRY(hipStreamSynchronize(s));
     }
 }

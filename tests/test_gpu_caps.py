@@ -37,3 +37,27 @@ def test_limits(skis, n, m, weights, T, limit, options):
     b = skis.build_sketch(*g, T, 5, model=model, **options)
     for x, y in zip(a.export(), b.export()):
         assert np.array_equal(x.cpu().numpy(), y.cpu().numpy())
+
+
+def test_many_sets_under_a_limit(skis):
+    # 8 bytes of scratch a set would be more than the limit leaves
+    import torch
+    g = inputs.workload_graph("cl15k_wc")
+    sk = skis.build_sketch(g.row_ptr, g.col, g.w, 1000, 1, staging_entries=1 << 16, max_device_bytes=122_000_000)
+    sets = inputs.random_sets(g.n, 20, 10, seed=3)
+    hubs = np.argsort(-np.diff(sk.inverse()[0].cpu().numpy()), kind="stable")[:40].astype(np.int32)
+    sets[11] = hubs
+    p, x = inputs.sets_to_csr(sets)
+    cov, est = (t.cpu().numpy() for t in sk.estimate(p, x))
+    Q = (1 << 24) + 3 # the sets at the ends of rounds, the others empty
+    at = [0, 1, 65534, 65535, 65536, 65537, 131071, 131072, 5_000_000, 1 << 23, (1 << 24) - 1, 1 << 24, Q - 2, Q - 1]
+    size = torch.zeros(Q + 1, dtype=torch.int64)
+    order = [i % 20 for i in range(len(at))]
+    for pos, i in zip(at, order):
+        size[pos + 1] = len(sets[i])
+    nodes = np.concatenate([sets[i] for i in order]).astype(np.int32)
+    c, e = sk.estimate(torch.cumsum(size, 0).cuda(), torch.as_tensor(nodes))
+    assert np.array_equal(c[at].cpu().numpy(), cov[order]) and np.array_equal(e[at].cpu().numpy(), est[order])
+    c[at] = 0
+    e[at] = 0
+    assert not c.any() and not e.any()

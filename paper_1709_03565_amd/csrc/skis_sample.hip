@@ -1610,6 +1610,7 @@ constexpr int FRONT_SLOTS = 16, FRONT_RCAP = 44, FRONT_HCAP = 64;
 // samples (15k nodes) 0.56 ms with it and 0.43 without, 1M 1.12 and 1.05, 4M 1.9 and 3.1; 1M-node WC
 // graph 1M 2.53 and 2.51, 4M 5.9 and 7.1.
 constexpr uint32_t FRONT_MIN = 1u << 20;
+constexpr uint64_t HOF_MAX = 1ull << 24; // handover records of the front: 3.2 GB
 
 template <bool UNIFORM>
 __global__ __launch_bounds__(64) void k_sample_front(SampleArgs a)
@@ -2331,10 +2332,6 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     const bool uni = prep.uniform && cfg.threads == 64;
     const SampleKernel tier0 =
         uni && cfg.slots == 4 && cfg.visited == 192 && cfg.qpl == 1 ? kTier0Uniform : v0.fn;
-    // the front runs before the default first tier; not under a cap on device memory, which its
-    // handover records would count against
-    const bool front = !lt && count >= FRONT_MIN && cfg.form != 1 && cfg.threads == 64 && cfg.slots == 4 && cfg.visited == 192 &&
-                       cfg.qpl == 1 && !arena.cap;
     const SampleKernel tier_front = prep.uniform ? k_sample_front<true> : k_sample_front<false>;
     const SampleKernel tier1 = uni ? kTierMidUniform : vm.fn;
     const SampleKernel tier2 = prep.uniform ? kTierHashUniform : kTierHash;
@@ -2344,6 +2341,10 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     const uint64_t per_launch0 =
         cfg.form == 2 ? std::min<uint64_t>(count, cfg.chunk ? cfg.chunk : CHAIN_CHUNK_DEFAULT) : count;
     const bool tiered = !lt && cfg.form != 1;
+    // the front runs before the default first tier where a launch has ids enough; not under a cap on
+    // device memory, which its handover records would count against
+    bool front = tiered && per_launch0 >= FRONT_MIN && cfg.threads == 64 && cfg.slots == 4 && cfg.visited == 192 &&
+                 cfg.qpl == 1 && !arena.cap;
     const uint64_t ho_cap = tiered ? std::min<uint64_t>(per_launch0, std::max<uint64_t>(1024, per_launch0 / 8)) : 0;
     const int ho_stride = (int)v0.visited;
     if (v0.visited > vm.visited) throw Error{SKIS_EHIP, "internal error: tier 1 smaller than tier 0"};
@@ -2355,18 +2356,41 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     const int nbf = occupancy_blocks(tier_front, 64) * cus;
     const int nb0 = occupancy_blocks(tier0, (int)v0.threads) * cus;
     const int nbm = occupancy_blocks(tier1, (int)vm.threads) * cus;
-    // handover from the front for a third of a launch's ids (192 B a record)
-    const uint64_t hof_cap = front ? std::min<uint64_t>(per_launch0, std::max<uint64_t>(1024, per_launch0 / 3)) : 0;
+    // handover from the front for a third of a launch's ids (192 B a record), HOF_MAX at most; the
+    // samples past them start over in the next tier
+    const uint64_t hof_cap = front ? std::min<uint64_t>(HOF_MAX, per_launch0 / 3) : 0;
     DevBuf<Handover> hof_state;
     DevBuf<int32_t> hof_nodes;
     DevBuf<uint32_t> front_ids; // the samples the front hands on
     // (with the chunks' unused places: a workgroup without a sample reserves none)
     deferred.alloc(arena, count + std::min<uint64_t>(nb0, count) * HANDON_CHUNK);
-    if (front) {
-        hof_state.alloc(arena, hof_cap);
-        hof_nodes.alloc(arena, hof_cap * (uint64_t)FRONT_RCAP);
-        front_ids.alloc(arena, per_launch0 + std::min<uint64_t>(nbf, count) * HANDON_CHUNK);
-    }
+    // the front's buffers, which a build does without where they do not fit beside the others
+    auto drop_front = [&]() {
+        front = false;
+        hof_state.reset();
+        hof_nodes.reset();
+        front_ids.reset();
+    };
+    auto alloc_front = [&]() {
+        if (!front) return;
+        try {
+            hof_state.alloc(arena, hof_cap);
+            hof_nodes.alloc(arena, hof_cap * (uint64_t)FRONT_RCAP);
+            front_ids.alloc(arena, per_launch0 + std::min<uint64_t>(nbf, count) * HANDON_CHUNK);
+        } catch (const Error &e) {
+            if (e.code != SKIS_ENOMEM) throw;
+            drop_front();
+        }
+    };
+    auto alloc_staging = [&](uint64_t entries) {
+        try {
+            staging.alloc(arena, entries);
+        } catch (const Error &e) {
+            if (e.code != SKIS_ENOMEM || !front) throw;
+            drop_front();
+            staging.alloc(arena, entries);
+        }
+    };
     // Staging: each LDS-tier workgroup reserves 8 * slots * visited entries at a time and wastes less
     // than one finished pass (slots * visited) of every such chunk but its last, so sum|R| * 8/7 + one
     // chunk per workgroup bounds what a launch reserves.
@@ -2474,8 +2498,9 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
             }
         } gg;
         SKIS_HIP_TRY(hipStreamCreateWithFlags(&gg.cs, hipStreamNonBlocking));
+        alloc_front();
         for (int attempt = 0; attempt < 2; ++attempt) {
-            staging.alloc(arena, cap);
+            alloc_staging(cap);
             hipLaunchKernelGGL(k_fill<unsigned long long>, dim3(4), dim3(256), 0, s, (uint64_t)sizeof(Counters) / 8,
                                reinterpret_cast<unsigned long long *>(ctr.ptr), 0ull);
             hipLaunchKernelGGL(k_fill<unsigned char>, dim3(1), dim3(64), 0, s, (uint64_t)sizeof(ChainCtl),
@@ -2693,7 +2718,8 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
     }
     if (cfg.form == 2) sample_chain_graph();
     for (int attempt = 0; attempt < 2 && cfg.form == 0 && !lt; ++attempt) {
-        staging.alloc(arena, cap);
+        alloc_front();
+        alloc_staging(cap);
         hipLaunchKernelGGL(k_fill<unsigned long long>, dim3(4), dim3(256), 0, s, (uint64_t)sizeof(Counters) / 8,
                            reinterpret_cast<unsigned long long *>(ctr.ptr), 0ull);
         SampleArgs A{};
@@ -2760,6 +2786,9 @@ void sample_and_compact(Arena &arena, const Prep &prep, int32_t n, int64_t m, ui
         SKIS_HIP_TRY(hipGetLastError());
         SKIS_HIP_TRY(hipEventRecord(ev[5], s));
         read_counters();
+        hof_state.reset(); // the first tier has taken the front's hand-ons
+        hof_nodes.reset();
+        front_ids.reset();
         sk.deferred = hc.tier_sum(0, 5);
         sk.deferred_global = 0;
         sk.deferred_bitmap = 0;

@@ -38,3 +38,15 @@ def test_sizes(skis, size, mixed, T):
     assert np.array_equal(sp, ora.sample_ptr) and np.array_equal(nodes, ora.nodes)
     assert np.array_equal(roots, ora.roots) and np.array_equal(probed.astype(np.uint64), ora.probed)
     assert sum(sk.info().tier_samples) == T
+
+
+@pytest.mark.parametrize("T,chunk", [(FRONT_MIN + 17, FRONT_MIN), (FRONT_MIN + 17, FRONT_MIN - 1), (2 * FRONT_MIN + 5, 1 << 18)])
+def test_captured_chunks(skis, T, chunk):
+    """The captured form takes the front by the ids of a chunk, not of the build."""
+    print("front chunks", T, chunk, flush=True)
+    g = inputs.chung_lu_graph(3000, 24000, 2.1, 31, "wc", cache=False)
+    a = skis.build_sketch(g.row_ptr, g.col, g.w, T, 3, build_inverse_index=0)
+    b = skis.build_sketch(g.row_ptr, g.col, g.w, T, 3, build_inverse_index=0, form=2, chunk_samples=chunk)
+    for x, y in zip(a.export(), b.export()):
+        assert np.array_equal(x.cpu().numpy(), y.cpu().numpy())
+    assert a.info().deferred == b.info().deferred and sum(b.info().tier_samples) == T

@@ -43,9 +43,13 @@ constexpr int SORT_LDS_MAX = 8192; // sizes up to this are sorted by k_gather_me
                                    // k_gather_large
 constexpr int TIER_WIDE = 4;
 constexpr int VQ_CAP = 64;        // live edges a wave queues before visiting them
-// sample ids taken from the global counter at a time: at least the slots of a workgroup
-template <int S>
-constexpr int id_batch() { return S <= 16 ? 16 : 32; }
+// Sample ids taken from the global counter at a time: at least the slots of a workgroup.  The tiers of
+// one long sample a workgroup take one (one wave: four, an atomic of 9.4 ns being some of its time):
+// ids that wait behind a long sample leave other workgroups idle.  With 16, 2^24 samples of the 4M-node
+// TRI graph took 6.8 ms in the bitmap tier (1293 samples), now 2.9, and 2.28 in the wide one (16975), now
+// 1.85; 2^22 of the 40M-node WC graph 4.7 (347), now 1.5, and 6.8 in the hash tier (45973), now 5.0.
+template <int S, int TIER>
+constexpr int id_batch() { return S == 1 ? (TIER == 2 ? 4 : 1) : S <= 16 ? 16 : 32; }
 
 // F_RESUME: admitted this pass from a handover (its nodes are put back in phase B1r)
 enum : int { F_ACTIVE = 1, F_ROOTPEND = 2, F_DEFER = 4, F_CLEAR = 8, F_RESUME = 16 };
@@ -776,7 +780,7 @@ __device__ __forceinline__ void sample_block(const SampleArgs &a)
     constexpr bool GHASH = TIER == 2;  // hash visited sets in global memory
     constexpr bool LDSV = !GLOBAL && !GHASH; // hash visited sets in LDS
     constexpr bool HO_OUT = !GLOBAL, HO_IN = TIER >= 1;
-    constexpr int IDBATCH = id_batch<S>();
+    constexpr int IDBATCH = id_batch<S, TIER>();
     static_assert(GLOBAL || HCAP > RCAP, "the hash must be larger than the node list");
     static_assert(!LDSV || HCAP <= 65535, "list entries are 8- or 16-bit hash slot indexes");
     static_assert(!GHASH || BLOCK == 64, "the hash tier's workgroups are one wave");
@@ -2193,9 +2197,11 @@ static SampleKernel const kTierMidUniform = k_sample_uniform<64, 1, 1024, 1200, 
 // bitmap tier cost more than the hash saved (71 ms); the samples that leave it mostly meet a
 // hub row rather than outgrow it.
 // A launch of few such samples ends with its largest one, and there eight waves a sample with its
-// hash in LDS (two workgroups a CU) do better: with 12 thousand samples (4M-node TRI graph, 2^24
-// samples) 2.7 ms against 12.0, with 183 thousand (40M-node WC graph) 48.9 against 15.5.  Up to
-// WIDE_MAX samples the host takes that kernel; a captured chain cannot know its count.
+// hash in LDS (two workgroups a CU) do better: 4M-node TRI graph, 17, 34 and 69 thousand samples 1.9, 3.6
+// and 7.0 ms against 5.3, 7.4 and 12.4 by one wave; 40M-node WC graph, whose samples differ less, 12, 23,
+// 46 and 183 thousand 3.3, 6.2, 12.1 and 47.7 against 2.3, 3.1, 5.0 and 15.9.  Up to WIDE_MAX samples the host
+// takes that kernel, where the one graph's loss (some 4 ms of a build of 60) is less than the other's gain
+// (4 of 25); a captured chain cannot know its count.
 constexpr int TIERH_RCAP = 6144;
 constexpr int TIERH_HCAP = 8192;
 // in-degree above which the hash tier hands a sample on: a hub row is swept faster by the

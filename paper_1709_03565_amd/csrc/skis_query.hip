@@ -123,23 +123,33 @@ __global__ __launch_bounds__(EST_BLOCK) void k_estimate(const int64_t *__restric
     unsigned long long local = 0;
     int nu = 0, maxnu = 0; // maxnu: threads at or past it never took a member (their sums are +0)
     int64_t E = 0;
+    // a chunk's members are read while the one before is sorted, all at once: the service's sets lie in
+    // host memory (one read after the other, 300 thousand members on 2^18 samples took 8.9 ms, 7.9 with
+    // the set copied to the device first; now 8.0)
+    int32_t ahead[IPT];
+    auto fetch = [&](int64_t c0) {
+        if (c0 >= b) return;
+#pragma unroll
+        for (int r = 0; r < IPT; ++r) ahead[r] = set_nodes[min(c0 + tid + r * EST_BLOCK, b - 1)];
+    };
+    fetch(a);
     for (int64_t c0 = a; c0 < b; c0 += EST_MAX_SET) {
         const int kc = (int)((b - c0) < EST_MAX_SET ? (b - c0) : EST_MAX_SET);
         if (tid == 0) s_bad = 0;
         __syncthreads();
         int P = 1;
         while (P < kc) P <<= 1;
-        for (int t = tid; t < P; t += EST_BLOCK) {
-            int32_t v = INT32_MAX;
-            if (t < kc) {
-                v = set_nodes[c0 + t];
-                if (v < 0 || v >= n) {
-                    s_bad = 1;
-                    v = INT32_MAX;
-                }
+#pragma unroll
+        for (int r = 0; r < IPT; ++r) {
+            const int t = tid + r * EST_BLOCK;
+            int32_t v = t < kc ? ahead[r] : INT32_MAX;
+            if (t < kc && (v < 0 || v >= n)) {
+                s_bad = 1;
+                v = INT32_MAX;
             }
-            buf[t] = v;
+            if (t < P) buf[t] = v;
         }
+        fetch(c0 + EST_MAX_SET);
         __syncthreads();
         if (s_bad) {
             if (tid == 0) atomicOr(err, 4);
@@ -245,7 +255,14 @@ __global__ __launch_bounds__(EST_BLOCK) void k_estimate(const int64_t *__restric
     }
     // leave the bitmaps clear for the next query
     for (uint64_t w = tid; w < wordsT; w += EST_BLOCK) bm[w] = 0u;
-    for (int64_t t = a + tid; t < b; t += EST_BLOCK) nb[set_nodes[t] >> 5] = 0u;
+    constexpr int CLEAR = 8; // members a thread reads together
+    for (int64_t t0 = a + tid; t0 < b; t0 += (int64_t)EST_BLOCK * CLEAR) {
+        int32_t v[CLEAR];
+#pragma unroll
+        for (int u = 0; u < CLEAR; ++u) v[u] = set_nodes[min(t0 + (int64_t)u * EST_BLOCK, b - 1)];
+#pragma unroll
+        for (int u = 0; u < CLEAR; ++u) nb[v[u] >> 5] = 0u; // past the last one: that one again
+    }
 }
 
 // ---------------------------------------------------------------------------------------

@@ -47,11 +47,15 @@ constexpr uint64_t HEAVY_WORK = 1ull << 18;
 
 constexpr uint16_t LONG_LIST = 0xFFFF;
 
-// Batches of light sets in flight before the next one waits for max_batch_queries queries, for one of
-// them to end or for QUIET without a new query: the streams share two hardware queues in most
-// processes, where a third small batch only waits (a burst of 1024 Zipf sets with four in flight
-// 1.4-1.6 ms, with two 1.25-1.5; a burst of few queries has nothing to wait for).
+// Batches of light sets in flight before the next one is held back, for as many queries as a batch
+// admits, for one of them to end, for QUIET without a new query or one on its way in, HOLD_MAX at most:
+// the streams share two hardware queues in most processes, where a third small batch only waits (a
+// burst of 1024 Zipf sets with four in flight 1.4-1.6 ms, with two 1.25-1.5; a burst of few queries has
+// nothing to wait for).  Behind a set above EST_MAX_SET members, which takes hundreds of microseconds, one
+// in flight is enough (8 sets of 5000 members on 2^18 samples of a 300 thousand-node TRI graph in five
+// batches 0.61 ms, in three 0.41).
 constexpr auto QUIET = std::chrono::microseconds(3);
+constexpr auto HOLD_MAX = std::chrono::microseconds(200);
 constexpr int LIGHT_IN_FLIGHT = 2;
 
 // a slot's error words: k_estimate's at 0, k_est_set's flags after it
@@ -120,7 +124,10 @@ struct skis_server {
     // of the queue, for the worker to see without the lock (written under mu): where it polled the slots
     // under the lock, submitters met it there
     alignas(64) std::atomic<size_t> queued{0};
-    std::atomic<bool> front_heavy{false};
+    std::atomic<bool> front_heavy{false}, front_large{false}, batch_full{false}; // full: large sets or entries
+                                                                                 // for a whole batch wait
+    std::atomic<int> coming{0};                              // submissions that have begun
+    uint64_t queued_large = 0, queued_entries = 0;           // under mu
     uint64_t next_ticket = 1;
     std::atomic<bool> stop{false}; // written under mu and done_mu
     std::string fault; // set when the worker stopped on an error
@@ -132,10 +139,20 @@ struct skis_server {
     uint64_t batches = 0, queries = 0, max_batch = 0;
     uint64_t hist[16] = {};
 
+    // a set of `entries` members has joined or left the queue
+    void count(uint64_t entries, bool joined)
+    {
+        const uint64_t large = entries > (uint64_t)skis::EST_MAX_SET ? 1 : 0;
+        queued_large = joined ? queued_large + large : queued_large - large;
+        queued_entries = joined ? queued_entries + entries : queued_entries - entries;
+    }
     void queue_changed()
     {
+        batch_full.store(queued_large >= opt.max_large_sets || queued_entries >= opt.max_batch_entries,
+                         std::memory_order_relaxed);
         queued.store(queue.size(), std::memory_order_relaxed);
         front_heavy.store(!queue.empty() && queue.front().work > HEAVY_WORK, std::memory_order_relaxed);
+        front_large.store(!queue.empty() && queue.front().nodes.size() > (size_t)skis::EST_MAX_SET, std::memory_order_relaxed);
     }
     void run();
     void launch(Slot &sl);
@@ -211,8 +228,9 @@ void skis_server::run()
 {
     try {
         SKIS_HIP_TRY(hipSetDevice(device));
-        size_t had = 0; // queries waiting at the last look, and since when as many
-        Clock::time_point since{};
+        size_t had = 0;       // queries waiting at the last look
+        bool holding = false; // they were held back
+        Clock::time_point since{}, held{}; // since when no other has come, since when held
         for (;;) {
             // the slots are this thread's alone
             Slot *free_slot = nullptr;
@@ -230,12 +248,14 @@ void skis_server::run()
             }
             const size_t have = queued.load(std::memory_order_relaxed);
             bool hold = false;
-            if (free_slot && have && in_flight >= LIGHT_IN_FLIGHT && have < opt.max_batch_queries &&
-                !front_heavy.load(std::memory_order_relaxed)) {
+            if (free_slot && have && in_flight >= (front_large.load(std::memory_order_relaxed) ? 1 : LIGHT_IN_FLIGHT) &&
+                have < opt.max_batch_queries && !front_heavy.load(std::memory_order_relaxed) && !batch_full.load(std::memory_order_relaxed)) {
                 const auto now = Clock::now();
-                if (have != had) since = now;
-                hold = have != had || now - since < QUIET;
+                if (!holding) held = now;
+                if (!holding || have != had || coming.load(std::memory_order_relaxed) > 0) since = now;
+                hold = now - since < QUIET && now - held < HOLD_MAX;
             }
+            holding = hold;
             had = have;
             if (!have || hold) free_slot = nullptr;
             if (free_slot) {
@@ -257,6 +277,7 @@ void skis_server::run()
                         large += is_large ? 1u : 0u;
                         sl.batch.push_back(std::move(queue.front()));
                         queue.pop_front();
+                        count(e, false);
                         if (heavy) break;
                     }
                     queue_changed();
@@ -316,6 +337,11 @@ int serve_guarded(F &&f)
 
 int submit_one(skis_server *sv, const int32_t *nodes, int32_t count, Clock::time_point arrive, uint64_t *ticket)
 {
+    struct Coming {
+        std::atomic<int> &n;
+        explicit Coming(std::atomic<int> &x) : n(x) { n.fetch_add(1, std::memory_order_relaxed); }
+        ~Coming() { n.fetch_sub(1, std::memory_order_relaxed); }
+    } on_its_way(sv->coming);
     if (count < 0) throw skis::Error{SKIS_EINVAL, "count must be >= 0"};
     if (count > 0 && !nodes) throw skis::Error{SKIS_EINVAL, "nodes must not be NULL"};
     if ((uint64_t)count > sv->opt.max_batch_entries)
@@ -347,6 +373,7 @@ int submit_one(skis_server *sv, const int32_t *nodes, int32_t count, Clock::time
         sv->outstanding.insert(p.ticket);
         if (ticket) *ticket = p.ticket;
         sv->queue.push_back(std::move(p));
+        sv->count((uint64_t)count, true);
         sv->queue_changed();
     }
     sv->cv_work.notify_one();

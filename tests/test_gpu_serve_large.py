@@ -40,3 +40,22 @@ def test_large_sets(skis):
         c, e, _ = srv.replay(set_ptr, set_nodes, np.zeros(len(sets)))
         assert np.array_equal(c, cov.astype(np.uint64)) and np.array_equal(e, est)
     srv.close()
+
+
+@pytest.mark.parametrize("options", [dict(max_batch_entries=9000, max_large_sets=1), dict(max_batch_queries=4096),
+                                     dict(pipeline_depth=1), dict(max_batch_entries=1 << 20, max_large_sets=64)])
+def test_held_batches_go(skis, options):
+    """Bursts in which large sets, entries or nothing fill a batch that is held back."""
+    print("held", options, flush=True)
+    g = inputs.chung_lu_graph(30000, 60000, 2.3, 5, "wc", cache=False)
+    sk = skis.build_sketch(g.row_ptr, g.col, g.w, 3000, 1)
+    rng = np.random.default_rng(3)
+    sets = [rng.choice(g.n, 5000 if i % 7 in (2, 3) else 900 if i % 5 == 1 else 3, replace=False).astype(np.int32) for i in range(80)]
+    set_ptr, set_nodes = inputs.sets_to_csr(sets)
+    cov, est = (x.cpu().numpy() for x in sk.estimate(set_ptr, set_nodes))
+    srv = skis.Server(sk, **options)
+    for at in (np.zeros(80), np.arange(80) * 2.0, np.arange(80) * 40.0):
+        c, e, _ = srv.replay(set_ptr, set_nodes, at)
+        assert np.array_equal(c, cov.astype(np.uint64)) and np.array_equal(e, est)
+    assert srv.stats()["queries"] == 240
+    srv.close()

@@ -89,6 +89,26 @@ struct QueryScratch {
     DevBuf<uint32_t> split;   // the parked sets' list and tickets, flags
 };
 
+// The service's host copy of the lists' lengths: two bytes a node, LONG_LIST where node_ptr tells.
+constexpr uint16_t LONG_LIST = 0xFFFF;
+
+// Entries of the lists of nodes[0 .. count), repeated nodes counted again.
+inline uint64_t list_entries(const uint16_t *list_len, const int64_t *node_ptr, const int32_t *nodes, int32_t count)
+{
+    uint64_t entries = 0;
+    bool exact = true;
+    for (int32_t i = 0; i < count; ++i) {
+        const uint16_t len = list_len[nodes[i]];
+        exact = exact && len != LONG_LIST;
+        entries += len;
+    }
+    if (!exact)
+        for (int32_t i = 0; i < count; ++i)
+            if (list_len[nodes[i]] == LONG_LIST)
+                entries += (uint64_t)(node_ptr[nodes[i] + 1] - node_ptr[nodes[i]]) - LONG_LIST;
+    return entries;
+}
+
 void estimate_batch(const Sketch &sk, QueryScratch &qs, int32_t Q, const int64_t *set_ptr, const int32_t *set_nodes,
                     uint64_t *cov, double *est, hipStream_t s);
 // nq sets in CSR form on the device: sets of at most EST_MAX_SET entries whose members' lists hold

@@ -45,8 +45,6 @@ struct Pending {
 // sketch holds about 60 thousand, its top hub 3 million).
 constexpr uint64_t HEAVY_WORK = 1ull << 18;
 
-constexpr uint16_t LONG_LIST = 0xFFFF;
-
 // Batches of light sets in flight before the next one is held back, for as many queries as a batch
 // admits, for one of them to end, for QUIET without a new query or one on its way in, HOLD_MAX at most:
 // the streams share two hardware queues in most processes, where a third small batch only waits (a
@@ -351,20 +349,7 @@ int submit_one(skis_server *sv, const int32_t *nodes, int32_t count, Clock::time
         if (nodes[i] < 0 || nodes[i] >= n) throw skis::Error{SKIS_EINVAL, "a seed set holds a node id outside [0, n)"};
     Pending p;
     p.nodes.assign(nodes, nodes + count);
-    if (!sv->node_ptr.empty()) {
-        uint64_t work = 0;
-        bool exact = true;
-        for (int32_t i = 0; i < count; ++i) {
-            const uint16_t len = sv->list_len[nodes[i]];
-            exact = exact && len != LONG_LIST;
-            work += len;
-        }
-        if (!exact)
-            for (int32_t i = 0; i < count; ++i)
-                if (sv->list_len[nodes[i]] == LONG_LIST)
-                    work += (uint64_t)(sv->node_ptr[nodes[i] + 1] - sv->node_ptr[nodes[i]]) - LONG_LIST;
-        p.work = work;
-    }
+    if (!sv->node_ptr.empty()) p.work = skis::list_entries(sv->list_len.data(), sv->node_ptr.data(), nodes, count);
     p.arrive = arrive;
     {
         std::lock_guard<std::mutex> g(sv->mu);
@@ -449,7 +434,7 @@ int skis_server_create(const skis_sketch *sk, const skis_server_options *opt_in,
                                    hipMemcpyDeviceToHost));
             sv->list_len.resize((size_t)sk->core.n);
             for (int32_t v = 0; v < sk->core.n; ++v)
-                sv->list_len[v] = (uint16_t)std::min<int64_t>(sv->node_ptr[v + 1] - sv->node_ptr[v], LONG_LIST);
+                sv->list_len[v] = (uint16_t)std::min<int64_t>(sv->node_ptr[v + 1] - sv->node_ptr[v], skis::LONG_LIST);
         }
         const uint64_t nb = std::max<uint64_t>(opt.max_batch_queries, opt.max_large_sets);
         sv->arena.stream = nullptr; // allocations complete before any slot stream uses them (below)

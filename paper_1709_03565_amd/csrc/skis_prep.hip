@@ -325,7 +325,7 @@ __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__r
         float wf[LONG_PER];
 #pragma unroll
         for (int k = 0; k < LONG_PER; ++k) {
-            const int32_t ec = min(c0 + t - 64 + k * LONG_FEED, b - 1);
+            const uint32_t ec = min((uint32_t)(c0 + t - 64) + k * LONG_FEED, (uint32_t)b - 1u); // may pass 2^31
             u[k] = col[ec];
             wf[k] = w[ec];
         }
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__r
 #pragma unroll
         for (int k = 0; k < LONG_PER; ++k) {
             const int i = t - 64 + k * LONG_FEED;
-            const int32_t e = c0 + i, ec = min(e, b - 1);
+            const uint32_t e = (uint32_t)c0 + (uint32_t)i, ec = min(e, (uint32_t)b - 1u);
             const float x = wf[k];
             bad |= check_edge(u[k], x, v, n);
             if (LT) diff = diff || x != w0; // a clamped one repeats the row's last
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__r
                 same = same && tx == th0;
                 th[ec] = tx;
             }
-            const double f = e < b ? (LT ? (double)x : __dsub_rn(1.0, (double)x)) : ident;
+            const double f = e < (uint32_t)b ? (LT ? (double)x : __dsub_rn(1.0, (double)x)) : ident;
             if (k + 1 < LONG_PER || i < LONG_EDGES) s_f[buf][i] = f;
         }
         if (LT && diff) s_diff[buf] = num;
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__r
             v = s_pick;
         }
         const int32_t a = row_ptr[v], b = row_ptr[v + 1];
-        int nchunks = (b - a + LONG_EDGES - 1) / LONG_EDGES;
+        int nchunks = (int)(((uint32_t)(b - a) + LONG_EDGES - 1) / LONG_EDGES);
         int bad = 0;
         if (th) th0 = edge_threshold(w[a]);
         if (LT) w0 = w[a];

@@ -205,15 +205,16 @@ int skis_estimate(const skis_sketch *sk, int32_t num_sets, const int64_t *set_pt
                   uint64_t *cov, double *est, hipStream_t stream);
 
 /*
- * skis_estimate without device allocation, for callers that cannot allocate (code under HIP
- * graph capture, tight serving loops, harnesses that forbid hipMalloc): the same sets, the
- * same results bit for bit, the same errors as skis_estimate.  Its scratch (an error word,
- * the list of large sets and the per-set bitmaps) is one file-scope device array of 32 MiB
- * that every GPU the library runs on holds until the process ends; the call clears the part
- * it uses and allocates nothing.  Every call on a GPU shares that GPU's array: calls that
- * overlap on one GPU (from several threads or streams) race and must be serialised by the
- * caller.  Sets are taken in rounds of 1024 (set_ptr read to the host, stack staging); each
- * launch holds as many T-bit bitmaps as fit in the array, so T may be at most about 2^28.
+ * skis_estimate without device allocation, for callers that cannot allocate (tight serving
+ * loops, harnesses that forbid hipMalloc; it waits for its stream, so it cannot be captured): the
+ * same sets, the same results bit for bit, the same errors as skis_estimate.  Its scratch (an error word,
+ * the lists of large and of heavy sets and the bitmaps of large ones) is one file-scope device
+ * array of 32 MiB that every GPU the library runs on holds until the process ends; the call
+ * clears the part it uses and allocates nothing.  Every call on a GPU shares that GPU's array:
+ * calls that overlap on one GPU (from several threads or streams) race and must be serialised
+ * by the caller.  Sets are taken in rounds of 1024, with one wait a round; set_ptr is read to
+ * the host (staged on the stack) only where a set above 4096 entries is met.  T-bit bitmaps
+ * have to fit in the array, so T may be at most about 2^28.
  * Sets above 4096 entries also need a node bitmap of n bits beside their T-bit bitmap;
  * SKIS_EINVAL when one of those does not fit, or when T-bit bitmaps alone do not.  Blocking.
  */
@@ -320,15 +321,17 @@ int skis_probe_random_read(const void *table, uint64_t rows, uint32_t row_bytes,
  * sketch (Eq. eq21), so a stream of influence queries is served without touching the
  * graph.  One worker thread per server batches waiting queries continuously: whenever one
  * of pipeline_depth batch slots is free, every waiting query it admits (by count, by total
- * entries, and by sets above 4096 entries) is packed into pinned host memory and sent
- * through copy-in, the estimate kernels and copy-out on the slot's own HIP stream, while
- * the next batch is being formed.  A set whose members' sample lists hold more than 2^18
+ * entries, and by sets above 4096 entries) is packed into pinned host memory, which the
+ * estimate kernels on the slot's own HIP stream read and write their answers to, while the
+ * next batch is being formed.  With two batches in flight (one, if the next query's set is
+ * above 4096 entries) a batch that is not full waits for more, until one of them ends or no
+ * query has come for 3 us, 200 us at most.  A set whose members' sample lists hold more than 2^18
  * entries in all (a set with a hub) goes in a batch of its own, so that it does not hold
  * the light sets it would have been batched with.  Results are identical to skis_estimate's
  * for the same set, alone or in any mix: every set has its own workgroup, bitmap and
  * summation order.  The sketch must outlive the server; the server does not lock it, and
  * other calls on the sketch (estimate, greedy, export) may run at the same time.  Memory:
- * each slot holds max_batch_queries bitmaps of T bits and max_large_sets bitmaps of n bits
+ * each slot holds max_batch_queries (or max_large_sets, if more) bitmaps of T bits and max_large_sets bitmaps of n bits
  * on the device; the host keeps a copy of the inverse index's n + 1 offsets.
  */
 typedef struct skis_server skis_server;

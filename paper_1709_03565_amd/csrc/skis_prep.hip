@@ -289,7 +289,7 @@ __global__ __launch_bounds__(256) void k_prep_tails(int32_t n, const int32_t *__
 }
 
 // Edge: uint32_t where the last chunk of a row may end past 2^31 (see the host), else int32_t, with which
-// the longest chains are some 3 % faster (8.5M edges, 436 thousand nodes: 780 and 815 us).
+// the longest chains are some 3 % faster (8.5M edges, 436 thousand nodes: 785 us for 818).
 template <bool LT, typename Edge>
 __global__ __launch_bounds__(256) void k_prep_long(int32_t n, const int32_t *__restrict__ row_ptr,
                                                    const int32_t *__restrict__ col, const float *__restrict__ w,

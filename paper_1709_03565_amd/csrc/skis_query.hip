@@ -287,9 +287,9 @@ __global__ __launch_bounds__(EST_BLOCK) void k_estimate(const int64_t *__restric
 // window's bits in LDS and counts them; the windows of a set run on as many CUs as there are, with
 // no bitmap in memory.  Each adds its count to cov, and the set's last window forms the estimate
 // (no workgroup waits for another).  Whole calls, one workgroup and bitmap a set before -> now: 16
-// sets of up to 50 hubs on 2^25 samples of the 4M-node TRI graph 6.7 -> 0.13 ms, 100 sets of 1-50
-// uniform nodes on 2^24 samples of the 1M-node WC graph 0.30 -> 0.092 ms, one set of 3 nodes on
-// 200k samples 62 -> 32 us (the flags in host memory, one kernel).
+// sets of up to 50 hubs on 2^25 samples of the 4M-node TRI graph 6.6 -> 0.14 ms, 100 sets of 1-50
+// uniform nodes on 2^24 samples of the 1M-node WC graph 0.21 -> 0.090 ms, one set of 3 nodes on
+// 200k samples 61 -> 27 us (the flags in host memory, one kernel).
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ double first_term(unsigned long long cov, double Gamma, uint64_t T)
 {
